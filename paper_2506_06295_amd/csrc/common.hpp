@@ -213,6 +213,17 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
                 hipStream_t st);
 
+// float32 models (kernels_gemm_f32.hip): operands in whole aligned 16-byte pieces; tile shape and
+// slices for a launch (at most s_cap slices; force_s > 0: that many); C gets p.S slices
+struct F32Plan { int shape, S, kps, nt, mt; double t; };
+bool gemm_f32_ok(const void* A, int lda, const void* W0, const void* W1, int K);
+F32Plan plan_f32(int M, int N, int K, int s_cap, int force_s);
+void launch_gemm_f32(const F32Plan& p, const float* A, int lda, const int* rows, int M, const float* W0,
+                     const float* W1, int N0, int N, int K, float* C, hipStream_t st);
+// (false: nothing launched, slices and launch_swiglu are quicker)
+bool launch_gemm_f32_swiglu(const float* A, int lda, const int* rows, int M, const float* w_gate,
+                            const float* w_up, int m, int K, float* u, hipStream_t st);
+
 // Fused gate/up projection with the SwiGLU product: u[i][j] = T(silu(a_i . w_gate_j) *
 // (a_i . w_up_j)), no slices, nothing but u written.  Returns false (and launches nothing)
 // when the shape or type is not handled; the caller then uses launch_gemm + launch_swiglu.

@@ -1,9 +1,9 @@
 // Gathered linear maps  C[i, :] = A[rows[i], :] * W^T  (W row-major [N, K], K contiguous).
 //
 // Kernels:
-//  * k_gemm_simple  -- plain LDS-tiled FMA kernel for any storage type and shape (used for
-//                      float32 models and as the fallback for shapes the MFMA kernel
-//                      does not take).
+//  * k_gemm_simple  -- plain LDS-tiled FMA kernel for any storage type and shape: the fallback
+//                      for shapes and alignments that the MFMA kernels do not take (float32
+//                      models: kernels_gemm_f32.hip).
 //  * k_gemm_stream  -- bf16 MFMA kernel built for the cached step's regime: few activation
 //                      rows (64 or 128 per workgroup tile) against a weight matrix that is read
 //                      exactly once from HBM.  The activation tile is staged in LDS, the
@@ -1065,8 +1065,8 @@ void gemm_set_tuning(int nw, int nw_dual, int force_s, int target_wg) {
 // Which kernel, how many slices of the contraction index and how long a slice: pure host logic.
 struct GemmPlan {
   int kind;  // 0 nothing fits, 1 plain, 2 streaming, 3 256x256 LDS-direct, 4 128x128 LDS-direct,
-             // 5 / 6 streaming with 256 / 128 rows per workgroup
-  int S, kps, KC, nt, mt;
+             // 5 / 6 streaming with 256 / 128 rows per workgroup, 7 float32 on the matrix cores
+  int S, kps, KC, nt, mt;  // KC: phase length of the streaming kernel, tile shape of kind 7
 };
 
 GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int N0, int K,
@@ -1079,6 +1079,11 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
                                          ? c_capacity / MN : static_cast<size_t>(kMaxSlices));
   const int NW = g_tune.nw;
   const int BN = 16 * NW;
+  if (dtype == 0 && operands_aligned && K % 4 == 0 && lda % 4 == 0) {
+    const F32Plan f = plan_f32(M, N, K, s_cap, g_tune.force_s);
+    p.kind = 7; p.S = f.S; p.kps = f.kps; p.nt = f.nt; p.mt = f.mt; p.KC = f.shape;
+    return p;
+  }
   const bool mfma_ok = dtype == 1 && operands_aligned && (K % 128 == 0) && (lda % 8 == 0);
   if (!(mfma_ok && N % BN == 0 && N0 % BN == 0)) {
     p.kind = 1; p.S = 1; p.kps = K; p.nt = (N + 63) / 64; p.mt = (M + 63) / 64;
@@ -1184,6 +1189,10 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                            static_cast<const float*>(W0), static_cast<const float*>(W1), N0, N, K,
                            c_part);
       break;
+    case 7:
+      launch_gemm_f32(F32Plan{p.KC, p.S, p.kps, p.nt, p.mt, 0.0}, static_cast<const float*>(A), lda, rows, M,
+                      static_cast<const float*>(W0), static_cast<const float*>(W1), N0, N, K, c_part, st);
+      break;
     case 3:
       hipLaunchKernelGGL(k_gemm_fat, grid, dim3(512), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps,
                          c_part);
@@ -1222,6 +1231,13 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
                         const void* w_gate, const void* w_up, int m, int K, void* u,
                         hipStream_t st) {
   if (M <= 0 || m <= 0) return true;
+  if (dtype == 0) {
+    if (!gemm_f32_ok(A, lda, w_gate, w_up, K)) return false;
+    t_last_stream = false;
+    return launch_gemm_f32_swiglu(static_cast<const float*>(A), lda, rows, M,
+                                  static_cast<const float*>(w_gate), static_cast<const float*>(w_up), m, K,
+                                  static_cast<float*>(u), st);
+  }
   // (phases of 128: the two register sets of gate and up pieces of a 256-wide phase do not fit
   // beside the activation chunks)
   const int KC = 128;
