@@ -5,7 +5,9 @@
 // Queries arrive compact: sequence b owns rows [b*Mq, (b+1)*Mq) of q and out.
 //
 //  * k_attn_simple -- any storage type / head width: one wavefront per (query, head), scores
-//                     kept in LDS, two passes.  Used for float32 models.
+//                     kept in LDS, two passes.  Head widths other than 64 and 128.
+//  * k_attn_f32    -- float32 models with head width 64 or 128, bf16 with head width 64: float32
+//                     products on the matrix cores.
 //  * k_attn_mfma / k_attn_walk -- bf16, head width 128.  Flash-style online softmax on
 //                     v_mfma_f32_16x16x32_bf16.  The score tile is computed transposed
 //                     (S^T = K * Q^T) so that each lane ends up holding, for one query, eight
@@ -72,7 +74,183 @@ __global__ __launch_bounds__(64) void k_attn_simple(const T* __restrict__ q, int
   }
 }
 
-constexpr int kDH = 128;       // head width of the MFMA kernel
+// ---- float32 arithmetic on the matrix cores ----------------------------------------------
+// k_attn_f32: float32 models with head width 64 or 128, and bf16 ones with head width 64 (converted as
+// they are multiplied): products, probabilities and sums in float32, v_mfma_f32_16x16x4_f32.
+// A workgroup is 16 queries of one head; its four wavefronts take a quarter of the keys each, 16 at a
+// time, and their (O, m, l) meet in LDS.  As in the bf16 kernels the scores are computed transposed
+// (S^T = K Q^T), so that a lane holds four keys of one query, 4 * lg .. + 3, and the product O^T = V^T
+// P^T takes them as they are: instruction j multiplies the keys {4 * lg + j}.  The rows of V^T are dealt to the
+// instructions' 16 rows in runs (row r of block db is dim r * D/16 + db), so that a lane's share of a
+// key, and of the result, is one contiguous piece.  No LDS on the way in: an instruction takes 32 cycles
+// and feeds on 4 bytes a lane.
+// Bound by those instructions (2048 cycles per 16 keys and 16 queries at width 128) once there are ~256
+// workgroups, by trips to memory below.  Against k_attn_simple (one wavefront per query and head, keys as
+// lanes: every lane walks its own row), us: 8 queries, 96 keys, 4 heads of 64: 12.5 -> 4.6; 2 x 176
+// queries, 176 keys, 8 heads of 128: 73.6 -> 9.4.
+template <typename T> struct Quad;  // four neighbouring elements as loaded, and as float32
+template <> struct Quad<float> {
+  typedef f32x4 raw;
+  static __device__ __forceinline__ f32x4 f32(const raw& r) { return r; }
+};
+template <> struct Quad<bf16_t> {
+  typedef uint2 raw;
+  static __device__ __forceinline__ f32x4 f32(const raw& r) {
+    return f32x4{__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
+                 __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u)};
+  }
+};
+
+constexpr int kFW = 4;  // wavefronts of a workgroup: parts of the key range
+
+template <typename T, int D, bool PAGED>
+__global__ __launch_bounds__(64 * kFW, 2) void k_attn_f32(const T* __restrict__ q, int Mq,
+                                                          const T* __restrict__ kc,
+                                                          const T* __restrict__ vc, int n, int H_q,
+                                                          int H_kv, T* __restrict__ out,
+                                                          const int* __restrict__ rmap) {
+  constexpr int C = D / 16;  // 16-dim blocks
+  typedef typename Quad<T>::raw raw_t;
+  __shared__ __attribute__((aligned(16))) float o_part[kFW][16][D + 4];
+  __shared__ float m_part[kFW][16], l_part[kFW][16];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int ln = lane % 16, lg = lane / 16;
+  const int i0 = blockIdx.x * 16, a = blockIdx.y, b = blockIdx.z;
+  const int d_q = H_q * D, d_kv = H_kv * D;
+  const int kv = a / (H_q / H_kv);
+  const T* K = kc + kv * D + lg * 4;
+  const T* V = vc + kv * D + ln * C;
+  const int seq0 = b * n;
+
+  // Q fragments: query ln, dims 16c + 4lg .. + 3 (queries past the end repeat the last one, never stored)
+  f32x4 qf[C];
+  {
+    const T* qr = q + (static_cast<size_t>(b) * Mq + min(i0 + ln, Mq - 1)) * d_q + a * D + lg * 4;
+#pragma unroll
+    for (int c = 0; c < C; ++c) qf[c] = Quad<T>::f32(*reinterpret_cast<const raw_t*>(qr + c * 16));
+  }
+  const float scale = 1.0f / sqrtf(static_cast<float>(D));
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4 o_acc[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) o_acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int nblk = (n + 15) / 16;
+  const int per = (nblk + kFW - 1) / kFW;
+  const int blk0 = min(wave * per, nblk), blk1 = min(nblk, blk0 + per);
+
+  struct Block { raw_t k[C], v[4][C / 4]; };
+  // keys past the end repeat the last one and are masked; blocks past the range repeat its last one
+  auto fetch = [&](int blk, Block& t) {
+    const int key0 = min(blk, blk1 - 1) * 16;
+    auto row = [&](int key) {
+      const int r = seq0 + min(key, n - 1);
+      return static_cast<size_t>(PAGED ? rmap[r] : r) * d_kv;
+    };
+    const T* kr = K + row(key0 + ln);
+#pragma unroll
+    for (int c = 0; c < C; ++c) t.k[c] = *reinterpret_cast<const raw_t*>(kr + c * 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const T* vr = V + row(key0 + 4 * lg + j);
+#pragma unroll
+      for (int c = 0; c < C / 4; ++c) t.v[j][c] = *reinterpret_cast<const raw_t*>(vr + c * 4);
+    }
+  };
+  auto use = [&](int blk, const Block& t) {
+    f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0;  // (two chains: an instruction may not wait for its predecessor)
+#pragma unroll
+    for (int c = 0; c < C; c += 2) {
+      const f32x4 k0 = Quad<T>::f32(t.k[c]), k1 = Quad<T>::f32(t.k[c + 1]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(k0[e], qf[c][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(k1[e], qf[c + 1][e], s1, 0, 0, 0);
+      }
+    }
+    float p[4];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[e] = blk * 16 + 4 * lg + e < n ? (s0[e] + s1[e]) * scale : -INFINITY;
+      mx = fmaxf(mx, p[e]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+      const float alpha = expf(m_run - m_use);  // 0 while nothing has been seen yet
+      l_run *= alpha;
+      m_run = m_new;
+#pragma unroll
+      for (int c = 0; c < C; ++c) o_acc[c] *= alpha;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[e] = expf(p[e] - m_use);
+      l_run += p[e];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int c = 0; c < C / 4; ++c) {
+        const f32x4 v = Quad<T>::f32(t.v[j][c]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          o_acc[4 * c + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], p[j], o_acc[4 * c + e], 0, 0, 0);
+      }
+  };
+  if (blk0 < blk1) {
+    Block b0, b1;  // two register sets that swap roles: the next block is in flight under this one
+    fetch(blk0, b0);
+    int blk = blk0;
+    for (; blk + 1 < blk1; blk += 2) {
+      fetch(blk + 1, b1);
+      use(blk, b0);
+      fetch(blk + 2, b0);
+      use(blk + 1, b1);
+    }
+    if (blk < blk1) use(blk, b0);
+  }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+
+  // lane: query ln, dims (4lg + i) * C + 0 .. C - 1
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int c = 0; c < C; c += 4)
+      *reinterpret_cast<float4*>(&o_part[wave][ln][(4 * lg + i) * C + c]) =
+          make_float4(o_acc[c][i], o_acc[c + 1][i], o_acc[c + 2][i], o_acc[c + 3][i]);
+  if (lg == 0) {
+    m_part[wave][ln] = m_run;
+    l_part[wave][ln] = l_run;
+  }
+  __syncthreads();
+  // 16 threads per query, D / 16 dims each; the parts in key order
+  const int qi = threadIdx.x / 16, t = threadIdx.x % 16;
+  if (i0 + qi >= Mq) return;
+  float M = m_part[0][qi];
+#pragma unroll
+  for (int w = 1; w < kFW; ++w) M = fmaxf(M, m_part[w][qi]);
+  float L = 0.f, o[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) o[c] = 0.f;
+#pragma unroll
+  for (int w = 0; w < kFW; ++w) {
+    const float mw = m_part[w][qi];
+    const float f = mw == -INFINITY ? 0.f : expf(mw - M);
+    L += l_part[w][qi] * f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) o[c] += o_part[w][qi][c * 16 + t] * f;
+  }
+  T* dst = out + (static_cast<size_t>(b) * Mq + i0 + qi) * d_q + a * D;
+#pragma unroll
+  for (int c = 0; c < C; ++c) stf(dst + c * 16 + t, o[c] / L);
+}
+
+constexpr int kDH = 128;       // head width of the bf16 MFMA kernels
 constexpr int kVtStride = 40;  // 32 keys + 8 pad (bf16 elements) per transposed V row
 constexpr int kQT = 64;        // queries per workgroup: four wavefronts x 16
 constexpr int kPreload = 3;    // key ranges of up to this many 32-key blocks are fetched whole
@@ -922,6 +1100,24 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
                          oo);
     else if (KS > 1)
       hipLaunchKernelGGL(k_attn_merge<8>, dim3(B * Mq * H_q), dim3(64), 0, st, scratch, KS, oo);
+    return;
+  }
+  // float32 arithmetic on the matrix cores: operands in whole aligned 16-byte (bf16: 8-byte) pieces
+  const uintptr_t low = reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k_cache) |
+                        reinterpret_cast<uintptr_t>(v_cache);
+  if ((d_h == 64 || (d_h == kDH && dtype == 0)) && low % (dtype == 1 ? 8 : 16) == 0) {
+    const dim3 grid((Mq + 15) / 16, H_q, B);
+#define DLLMC_ATTN(T, D, PG)                                                                           \
+  hipLaunchKernelGGL((k_attn_f32<T, D, PG>), grid, dim3(64 * kFW), 0, st, static_cast<const T*>(q), Mq, \
+                     static_cast<const T*>(k_cache), static_cast<const T*>(v_cache), n, H_q, H_kv,      \
+                     static_cast<T*>(out), rmap)
+    if (dtype == 1 && rmap) DLLMC_ATTN(bf16_t, 64, true);
+    else if (dtype == 1) DLLMC_ATTN(bf16_t, 64, false);
+    else if (d_h == 64 && rmap) DLLMC_ATTN(float, 64, true);
+    else if (d_h == 64) DLLMC_ATTN(float, 64, false);
+    else if (rmap) DLLMC_ATTN(float, 128, true);
+    else DLLMC_ATTN(float, 128, false);
+#undef DLLMC_ATTN
     return;
   }
   const size_t lds = static_cast<size_t>(d_h + n) * sizeof(float);

@@ -6,7 +6,8 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2506_06295_amd import binding, inputs as I
+from oracle import dllm_cache_oracle as O
+from paper_2506_06295_amd import binding
 from tests import parity_util as PU
 from tests.parity_util import rel_err
 from tests.test_gpu_step import MINI_DREAM, MINI_LLADA, run_schedule
@@ -66,6 +67,30 @@ def test_linear_non_finite_values_stay_in_their_rows_and_columns():
     want[3], want[:, 65] = np.inf, -np.inf
     want[3, 65], want[5] = np.nan, np.nan
     assert np.array_equal(out, want.astype(np.float32), equal_nan=True)
+
+
+@pytest.mark.parametrize("dtype,B,Mq,n,H_q,H_kv,d_h", [
+    ("f32", 1, 1, 1, 1, 1, 64),        # one query, one key: three wavefronts have no keys
+    ("f32", 1, 17, 16, 2, 1, 128),     # second query tile of one row, one whole block of keys
+    ("f32", 2, 33, 65, 4, 2, 64),      # ragged, two blocks for some wavefronts and one for others
+    ("f32", 1, 16, 300, 7, 1, 128),    # grouped KV heads, five blocks each, the last range shorter
+    ("f32", 2, 100, 1000, 2, 2, 128),
+    ("bf16", 2, 37, 130, 4, 2, 64),    # converted as it is multiplied
+    ("bf16", 1, 16, 64, 1, 1, 64),
+])
+def test_attention(dtype, B, Mq, n, H_q, H_kv, d_h):
+    """Scores of a few units: their float32 error 2^-24 sqrt(d_h) passes through exp unchanged, the sums over
+    n add 2^-24 sqrt(n); bf16 results are rounded once (2^-9 at most per element, 2^-9 / sqrt(3) in the norm)."""
+    r = np.random.default_rng(Mq * 7 + n)
+    q, k, v = (r.standard_normal((B, rows, h * d_h)).astype(np.float32) * s
+               for rows, h, s in ((Mq, H_q, 1.5), (n, H_kv, 1.0), (n, H_kv, 1.0)))
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    dq, dk, dv = (torch.from_numpy(x).cuda().to(t) for x in (q, k, v))
+    got = binding.op_attention(dtype, dq, dk, dv, H_q, H_kv, d_h).float().cpu().numpy()
+    bar = 2.0 ** -24 * (8 * np.sqrt(d_h) + np.sqrt(n)) + (2.0 ** -9 if dtype == "bf16" else 0.0)
+    for b in range(B):
+        want = O.attention(*(x[b].double().cpu().numpy() for x in (dq, dk, dv)), H_q, H_kv, d_h)
+        assert rel_err(got[b], want) < bar
 
 
 @pytest.mark.parametrize("cfg", [MINI_LLADA.replace(dtype="f32"), MINI_DREAM.replace(dtype="f32", m=2436),
