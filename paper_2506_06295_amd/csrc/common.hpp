@@ -231,6 +231,16 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
                         const void* w_gate, const void* w_up, int m, int K, void* u,
                         hipStream_t st);
 
+// Vocabulary projection that leaves, instead of the logits, their reduction per row and 128-column
+// tile: part[i * tiles + t] for i < M.  Returns the number of tiles, 0 (nothing launched) when the shape is not
+// handled; part: M * tiles entries, 16-byte aligned.
+struct HeadPart {  // of a run of logits: their maximum, sum of exp(l - maximum), first index of it
+  float m, s;
+  int a, unused;
+};
+int launch_gemm_head(int dtype, const void* A, int lda, int M, const void* W, int N, int K, HeadPart* part,
+                     size_t part_capacity, hipStream_t st);
+
 // out[i][:] = sum_s c_part[s][i][:]
 void launch_reduce_slices(const float* c_part, int S, int M, int N, float* out, hipStream_t st);
 
@@ -380,9 +390,13 @@ void launch_final_norm(int dtype, const void* hidden, const int* rows, int M, in
                        const void* gain, void* z, hipStream_t st);
 // for i < M: token = first argmax of logits[i][0..vocab), p = softmax(logits[i])[token]; with
 // rows (rows[i] = b*n + L_p + j): x0[b][j] = token, conf[b][j] = sign * p; rows == nullptr:
-// x0[i], conf[i]
-void launch_head_finalize(const float* logits, int M, int vocab, const int* rows, int n, int L_p,
-                          float sign, int* x0, float* conf, hipStream_t st);
+// x0[i], conf[i].  part: scratch of part_floats floats (16-byte aligned) for partial results of a row.
+void launch_head_finalize(const float* logits, int M, int vocab, float* part, size_t part_floats,
+                          const int* rows, int n, int L_p, float sign, int* x0, float* conf,
+                          hipStream_t st);
+// the same from n_part partial results per row (see launch_gemm_head)
+void launch_head_merge(const HeadPart* part, int n_part, int M, const int* rows, int n, int L_p,
+                       float sign, int* x0, float* conf, hipStream_t st);
 void launch_negate_f32(float* p, size_t count, hipStream_t st);
 // tokens[b][L_p + chosen[b*chosen_stride + t]] = x0[b][...] for t < n_unmask
 void launch_apply_tokens(int* tokens, int B, int n, int L_p, const int* chosen, int chosen_stride,

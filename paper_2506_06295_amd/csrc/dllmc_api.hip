@@ -945,17 +945,26 @@ int dllmc_gen_step(dllmc_gen* g, int32_t* tokens, int32_t step_idx, int32_t* sel
       launch_select(elig, B, L_r, masked, nullptr, 0, rows, masked, 0, nullptr, n, L_p, st);
       launch_final_norm(dt, hout, rows, M, d, c->m.rms_eps, g->g.final_norm_g, z, st);
     }
+    int tiles;
     {
-      // capacity of exactly one slice: the whole contraction in one pass, logits complete
+      // reduced per row and column tile by the projection itself, or logits in one slice (capacity of exactly
+      // one: the whole contraction in one pass)
       Timed tm(c, DLLMC_KC_HEAD_GEMM, (V * d + static_cast<double>(M) * d) * esz + M * V * 4.0,
                2.0 * M * V * d);
-      const int S = launch_gemm(dt, z, d, nullptr, M, g->g.lm_head, nullptr, g->g.vocab, g->g.vocab,
-                                d, logits, static_cast<size_t>(M) * g->g.vocab, st);
-      if (S != 1) return DLLMC_ENOMEM;
+      tiles = launch_gemm_head(dt, z, d, M, g->g.lm_head, g->g.vocab, d, reinterpret_cast<HeadPart*>(logits),
+                               static_cast<size_t>(M) * g->g.vocab / 4, st);
+      if (tiles > 0) tm.bytes = (V * d + static_cast<double>(M) * d) * esz + M * tiles * 16.0;
+      else if (launch_gemm(dt, z, d, nullptr, M, g->g.lm_head, nullptr, g->g.vocab, g->g.vocab, d, logits,
+                           static_cast<size_t>(M) * g->g.vocab, st) != 1)
+        return DLLMC_ENOMEM;
     }
     {
-      Timed tm(c, DLLMC_KC_GEN_OTHER, M * V * 4.0 + B * L_r * 8.0, 0);
-      launch_head_finalize(logits, M, g->g.vocab, rows, n, L_p, -1.0f, x0, negc, st);
+      Timed tm(c, DLLMC_KC_GEN_OTHER, (tiles > 0 ? M * tiles * 16.0 : M * V * 4.0) + B * L_r * 8.0, 0);
+      if (tiles > 0)
+        launch_head_merge(reinterpret_cast<HeadPart*>(logits), tiles, M, rows, n, L_p, -1.0f, x0, negc, st);
+      else  // (the normed rows are done with: room for partial results)
+        launch_head_finalize(logits, M, g->g.vocab, static_cast<float*>(z),
+                             static_cast<size_t>(M) * d * c->lay.esz / 4, rows, n, L_p, -1.0f, x0, negc, st);
       // the n_rev most confident (lowest negated confidence, ties to the lower position)
       launch_select(negc, B, L_r, n_rev, chosen, L_r, nullptr, 0, 0, nullptr, n, L_p, st);
       launch_apply_tokens(tokens, B, n, L_p, chosen, L_r, n_rev, x0, st);
@@ -1016,10 +1025,17 @@ int dllmc_op_head(int32_t dtype, const void* hidden, const int32_t* rows, int32_
   float* logits = reinterpret_cast<float*>(static_cast<char*>(scratch) +
                                            align_up(static_cast<size_t>(M) * d * esz, 256));
   launch_final_norm(dtype, hidden, rows, M, d, eps, final_norm_g, z, st);
-  const int S = launch_gemm(dtype, z, d, nullptr, M, lm_head, nullptr, vocab, vocab, d, logits,
-                            static_cast<size_t>(M) * vocab, st);
-  if (S != 1) return DLLMC_ENOMEM;
-  launch_head_finalize(logits, M, vocab, nullptr, 0, 0, 1.0f, x0, conf, st);
+  HeadPart* part = reinterpret_cast<HeadPart*>(logits);
+  const int tiles = launch_gemm_head(dtype, z, d, M, lm_head, vocab, d, part, static_cast<size_t>(M) * vocab / 4, st);
+  if (tiles > 0) {
+    launch_head_merge(part, tiles, M, nullptr, 0, 0, 1.0f, x0, conf, st);
+  } else {
+    const int S = launch_gemm(dtype, z, d, nullptr, M, lm_head, nullptr, vocab, vocab, d, logits,
+                              static_cast<size_t>(M) * vocab, st);
+    if (S != 1) return DLLMC_ENOMEM;
+    launch_head_finalize(logits, M, vocab, static_cast<float*>(z), static_cast<size_t>(M) * d * esz / 4, nullptr, 0, 0,
+                         1.0f, x0, conf, st);
+  }
   HIP_TRY(hipGetLastError());
   return DLLMC_OK;
 }

@@ -121,7 +121,12 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, in
 //             wavefront keeps the accumulators of 128 / 256 rows, so the weights of a launch
 //             with that many rows are streamed once instead of once per 64-row tile (phases of
 //             128 then, to fit the activation tiles in LDS).
-template <int NW, int KC, int DUAL, int KH, int RB = 4>
+//   HEAD = 1: the vocabulary projection of the mask predictor's head (one slice): the tile's results are
+//             reduced per row to (maximum, sum of exp, first index of the maximum) and only that is
+//             stored, to entry row * gridDim.x + column tile of C.  The results cross the tile through LDS
+//             (a thread takes 16 or 32 neighbouring columns of a row; reducing them in the accumulator
+//             layout, 16 lanes to a row, takes four times the vector instructions).
+template <int NW, int KC, int DUAL, int KH, int RB = 4, int HEAD = 0>
 __global__ __launch_bounds__(NW * 64) void k_gemm_stream(
     const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
     const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0, int N, int K,
@@ -335,6 +340,60 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_stream(
             acc[b][mb][i] += red[((((g - 1) * NWC + wcol) * NB + b) * (4 * RB) + mb * 4 + i) * 64 + lane];
   }
 
+  if (HEAD) {
+    // (every LDS read of the activation tiles is behind the barrier that ended the last phase)
+    static_assert(!HEAD || (NW == 8 && KH == 1 && !DUAL && sizeof(As) >= R * 128 * sizeof(float)),
+                  "a 128-column tile of results fits the activation tiles");
+    float* tile = reinterpret_cast<float*>(&As[0][0][0]);
+    // row r, column c at c ^ 16 * (r / 4 % 4): the four rows that a wavefront stores at once hit
+    // different banks
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        tile[(mb * 16 + lg * 4 + i) * 128 + ((wave * 16 + ln) ^ (lg << 4))] = acc[0][mb][i];
+    __syncthreads();
+    constexpr int TPR = NW * 64 / R, CPT = 128 / TPR;  // threads per row, columns per thread
+    const int r = threadIdx.x / TPR, c0 = (threadIdx.x % TPR) * CPT;
+    const int swz = ((r >> 2) & 3) << 4;
+    float v[CPT];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < CPT / 4; ++t) {
+      // (neighbouring rows start at different pieces of their columns: other banks)
+      const int c = c0 + 4 * ((t + r) % (CPT / 4));
+      const float4 f = *reinterpret_cast<const float4*>(&tile[r * 128 + (c ^ swz)]);
+      v[4 * t] = f.x; v[4 * t + 1] = f.y; v[4 * t + 2] = f.z; v[4 * t + 3] = f.w;
+      mx = fmaxf(mx, fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w)));
+    }
+    const float mu = mx == -INFINITY ? 0.f : mx;
+    float sum = 0.f;
+    int first = 0x7fffffff;
+#pragma unroll
+    for (int t = 0; t < CPT / 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sum += __builtin_amdgcn_exp2f((v[4 * t + e] - mu) * 1.4426950408889634f);
+        if (v[4 * t + e] == mx) first = min(first, c0 + 4 * ((t + r) % (CPT / 4)) + e);
+      }
+    if (first == 0x7fffffff) first = c0;  // nothing but NaN
+    // the row's threads are neighbouring lanes
+#pragma unroll
+    for (int o = 1; o < TPR; o <<= 1) {
+      const float om = __shfl_xor(mx, o, 64), os = __shfl_xor(sum, o, 64);
+      const int oa = __shfl_xor(first, o, 64);
+      const float nm = fmaxf(mx, om), nu = nm == -INFINITY ? 0.f : nm;
+      const float fs = mx == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mx - nu) * 1.4426950408889634f);
+      const float fo = om == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((om - nu) * 1.4426950408889634f);
+      first = mx > om ? first : (om > mx ? oa : min(first, oa));
+      sum = sum * fs + os * fo;
+      mx = nm;
+    }
+    if (threadIdx.x % TPR == 0 && m0 + r < M)
+      reinterpret_cast<HeadPart*>(C)[static_cast<size_t>(m0 + r) * gridDim.x + col_tile] =
+          HeadPart{mx, sum, col_tile * 128 + first, 0};
+    return;
+  }
   if (!active) return;
   if (DUAL) {
 #pragma unroll
@@ -1225,6 +1284,28 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
     }
   }
   return p.S;
+}
+
+int launch_gemm_head(int dtype, const void* A, int lda, int M, const void* W, int N, int K, HeadPart* part,
+                     size_t part_capacity, hipStream_t st) {
+  // The shapes that run the streaming kernel, whose workgroups own whole 128-column tiles of up to 128
+  // rows.
+  const bool al = aligned16(A) && aligned16(W) && aligned16(part);
+  const GemmPlan p = plan_gemm(dtype, al, lda, M, N, N, K, static_cast<size_t>(M) * N);
+  if (g_tune.nw != 8 || (p.kind != 2 && p.kind != 6) || static_cast<size_t>(M) * p.nt > part_capacity) return 0;
+  t_last_stream = true;
+  const dim3 grid(p.nt, p.mt, 1);
+  const bf16_t* a = static_cast<const bf16_t*>(A);
+  const bf16_t* w = static_cast<const bf16_t*>(W);
+#define DLLMC_GH(KCv, RBv)                                                                                   \
+  hipLaunchKernelGGL((k_gemm_stream<8, KCv, 0, 1, RBv, 1>), grid, dim3(512), 0, st, a, lda, nullptr, M, w, \
+                     static_cast<const bf16_t*>(nullptr), N, N, K, K, reinterpret_cast<float*>(part), nullptr, p.nt)
+  if (p.kind == 6 && p.KC == 256) DLLMC_GH(256, 8);
+  else if (p.kind == 6) DLLMC_GH(128, 8);
+  else if (p.KC == 256) DLLMC_GH(256, 4);
+  else DLLMC_GH(128, 4);
+#undef DLLMC_GH
+  return p.nt;
 }
 
 bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int M,

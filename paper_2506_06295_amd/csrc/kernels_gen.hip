@@ -3,8 +3,10 @@
 //   k_embed_gather    token ids -> embedded rows
 //   k_elig_scores     which response positions are still masked inside the current block
 //   k_final_norm      RMSNorm with the final gain of the listed rows, compact output
-//   k_head_finalize   per row of logits: greedy token (lowest id among equal logits) and its
-//                     softmax probability, in one pass (running maximum and rescaled sum)
+//   k_head_partial    per row and run of logits: maximum, sum of exponentials, first index of the
+//                     maximum; k_head_merge: the row's greedy token (lowest id among equal logits) and its
+//                     softmax probability from those, or from the ones that the vocabulary projection of
+//                     up to 191 rows leaves instead of logits (k_gemm_stream)
 //   k_apply_tokens    the chosen positions take their greedy token
 // The vocabulary projection itself is a gathered linear map (kernels_gemm.hip); the choice of
 // the positions is the integer-exact bottom-k selection (kernels_select.hip) on the negated
@@ -56,86 +58,210 @@ __global__ __launch_bounds__(kThreads) void k_elig_scores(const int* __restrict_
   x0[i] = -1;
 }
 
-template <typename T>
+// eight (bf16) or four (float32) neighbouring elements of a row, as one 16-byte access
+template <typename T> struct Piece {
+  static constexpr int N = 16 / sizeof(T);
+  float v[N];
+  __device__ __forceinline__ void load(const T* p) {
+    const uint4 u = *reinterpret_cast<const uint4*>(p);
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      v[i] = sizeof(T) == 4 ? __uint_as_float(w[i % 4])
+                            : __uint_as_float(i % 2 ? w[i / 2 % 4] & 0xffff0000u : w[i / 2 % 4] << 16);
+  }
+  __device__ __forceinline__ void store(T* p) const {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      w[i] = sizeof(T) == 4 ? __float_as_uint(v[i % N])
+                            : static_cast<uint32_t>(f32_to_bf16(v[2 * i % N])) |
+                                  (static_cast<uint32_t>(f32_to_bf16(v[(2 * i + 1) % N])) << 16);
+    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+};
+
+// VEC: rows in whole aligned 16-byte pieces.  A row of up to two pieces per thread (bf16: 4096 wide) stays in
+// registers, with the gain's pieces requested under the reduction: one trip to memory (with 2-byte accesses
+// and the row read twice 10 us for 100 rows of 4096, now 5).
+template <typename T, bool VEC>
 __global__ __launch_bounds__(kThreads) void k_final_norm(const T* __restrict__ hidden,
                                                          const int* __restrict__ rows, int d,
                                                          float eps, const T* __restrict__ gain,
                                                          T* __restrict__ z) {
   __shared__ float red[kNW];
+  constexpr int N = Piece<T>::N, KEEP = 2;
   const int i = blockIdx.x;
   const int row = rows ? rows[i] : i;
   const T* src = hidden + static_cast<size_t>(row) * d;
+  T* dst = z + static_cast<size_t>(i) * d;
   float ss = 0.f;
+  if (VEC) {
+    Piece<T> x[KEEP], g[KEEP];
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+      const int c = min((k * kThreads + static_cast<int>(threadIdx.x)) * N, d - N);
+      x[k].load(src + c);
+      g[k].load(gain + c);
+    }
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k)
+      if ((k * kThreads + static_cast<int>(threadIdx.x)) * N < d) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) ss += x[k].v[e] * x[k].v[e];
+      }
+    for (int c = (KEEP * kThreads + static_cast<int>(threadIdx.x)) * N; c < d; c += kThreads * N) {
+      Piece<T> y;
+      y.load(src + c);
+#pragma unroll
+      for (int e = 0; e < N; ++e) ss += y.v[e] * y.v[e];
+    }
+    ss = block_sum<kNW>(ss, red);
+    const float rstd = 1.0f / sqrtf(ss / static_cast<float>(d) + eps);
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+      const int c = (k * kThreads + static_cast<int>(threadIdx.x)) * N;
+      if (c < d) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) x[k].v[e] = x[k].v[e] * rstd * g[k].v[e];
+        x[k].store(dst + c);
+      }
+    }
+    for (int c = (KEEP * kThreads + static_cast<int>(threadIdx.x)) * N; c < d; c += kThreads * N) {
+      Piece<T> y, gy;
+      y.load(src + c);
+      gy.load(gain + c);
+#pragma unroll
+      for (int e = 0; e < N; ++e) y.v[e] = y.v[e] * rstd * gy.v[e];
+      y.store(dst + c);
+    }
+    return;
+  }
   for (int c = threadIdx.x; c < d; c += kThreads) {
     const float v = ldf(src + c);
     ss += v * v;
   }
   ss = block_sum<kNW>(ss, red);
   const float rstd = 1.0f / sqrtf(ss / static_cast<float>(d) + eps);
-  T* dst = z + static_cast<size_t>(i) * d;
   for (int c = threadIdx.x; c < d; c += kThreads) stf(dst + c, ldf(src + c) * rstd * ldf(gain + c));
 }
 
 // running (maximum, sum of exp(l - maximum), index of the first maximum)
-struct Soft {
-  float m, s;
-  int a;
-};
-__device__ __forceinline__ Soft soft_merge(const Soft& p, const Soft& q) {
-  Soft r;
+__device__ __forceinline__ HeadPart soft_merge(const HeadPart& p, const HeadPart& q) {
+  HeadPart r;
   r.m = fmaxf(p.m, q.m);
-  r.s = (p.m == -INFINITY ? 0.f : p.s * expf(p.m - r.m)) +
-        (q.m == -INFINITY ? 0.f : q.s * expf(q.m - r.m));
+  // (nothing but -inf so far: the sum is 0, or NaN)
+  r.s = (p.m == -INFINITY ? p.s : p.s * expf(p.m - r.m)) + (q.m == -INFINITY ? q.s : q.s * expf(q.m - r.m));
   r.a = p.m > q.m ? p.a : (q.m > p.m ? q.a : min(p.a, q.a));
+  r.unused = 0;
   return r;
 }
 
-// One workgroup per row i of logits: greedy token and confidence from logits[i][0..vocab).
-// With rows (rows[i] = b*n + L_p + j) the results go to x0[b][j] and conf[b][j], otherwise to
-// x0[i] and conf[i]; conf = sign * probability.
-__global__ __launch_bounds__(kThreads) void k_head_finalize(const float* __restrict__ logits,
-                                                            int vocab,
-                                                            const int* __restrict__ rows, int n,
-                                                            int L_p, float sign,
-                                                            int* __restrict__ x0,
-                                                            float* __restrict__ neg_conf) {
-  __shared__ Soft part[kNW];
-  const int i = blockIdx.x;
-  const float* l = logits + static_cast<size_t>(i) * vocab;
-  Soft t{-INFINITY, 0.f, 0x7fffffff};
-  if (vocab % 4 == 0) {
-    for (int c = threadIdx.x * 4; c < vocab; c += kThreads * 4) {
-      const float4 v = *reinterpret_cast<const float4*>(l + c);
-      const float e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) t = soft_merge(t, Soft{e[k], 1.f, c + k});
-    }
-  } else {
-    for (int c = threadIdx.x; c < vocab; c += kThreads) t = soft_merge(t, Soft{l[c], 1.f, c});
-  }
-  // lanes, then wavefronts, in a fixed order
+// the workgroup's partial results, lanes and then wavefronts in a fixed order; the total in thread 0
+__device__ __forceinline__ HeadPart soft_reduce(HeadPart t, HeadPart* lds) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) {
-    Soft q;
+    HeadPart q;
     q.m = __shfl_xor(t.m, o, kWave);
     q.s = __shfl_xor(t.s, o, kWave);
     q.a = __shfl_xor(t.a, o, kWave);
     t = soft_merge(t, q);
   }
-  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = t;
+  if ((threadIdx.x & (kWave - 1)) == 0) lds[threadIdx.x / kWave] = t;
   __syncthreads();
   if (threadIdx.x == 0) {
-    Soft r = part[0];
+    t = lds[0];
 #pragma unroll
-    for (int w = 1; w < kNW; ++w) r = soft_merge(r, part[w]);
-    int o = i;
-    if (rows) {
-      const int row = rows[i];
-      o = (row / n) * (n - L_p) + (row % n - L_p);
-    }
-    x0[o] = r.a;
-    neg_conf[o] = sign / r.s;
+    for (int w = 1; w < kNW; ++w) t = soft_merge(t, lds[w]);
   }
+  return t;
+}
+
+// Greedy token and confidence of row i: to x0[b][j] and conf[b][j] with rows (rows[i] = b*n + L_p + j),
+// otherwise to x0[i] and conf[i]; conf = sign * probability.
+__device__ __forceinline__ void head_store(const HeadPart& r, int i, const int* __restrict__ rows, int n,
+                                           int L_p, float sign, int* __restrict__ x0,
+                                           float* __restrict__ conf) {
+  int o = i;
+  if (rows) {
+    const int row = rows[i];
+    o = (row / n) * (n - L_p) + (row % n - L_p);
+  }
+  x0[o] = r.a;
+  conf[o] = sign / r.s;
+}
+
+// Row blockIdx.x of the logits, columns of run blockIdx.y: one partial result per run, or (a single run) the
+// row's token and confidence.  A thread takes 16 logits at a time: their maximum, then their
+// exponentials against it (one per logit; merging them one by one into the running result took two and a
+// chain of dependent instructions per logit: 92 us for 100 rows of 126464, one workgroup each).
+template <bool VEC>
+__global__ __launch_bounds__(kThreads) void k_head_partial(const float* __restrict__ logits, int vocab,
+                                                           int run, HeadPart* __restrict__ part,
+                                                           const int* __restrict__ rows, int n, int L_p,
+                                                           float sign, int* __restrict__ x0,
+                                                           float* __restrict__ conf) {
+  __shared__ HeadPart lds[kNW];
+  const int i = blockIdx.x;
+  const float* l = logits + static_cast<size_t>(i) * vocab;
+  const int c0 = blockIdx.y * run, c1 = min(vocab, c0 + run);
+  HeadPart t{-INFINITY, 0.f, 0x7fffffff, 0};
+  constexpr int W = VEC ? 4 : 1, U = 16 / W;  // U loads of W neighbouring logits
+  for (int base = c0; base < c1; base += kThreads * 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = base + (u * kThreads + static_cast<int>(threadIdx.x)) * W;
+      if (VEC) {
+        const float4 f = *reinterpret_cast<const float4*>(l + min(c, vocab - 4));
+        v[u * W] = f.x; v[u * W + 1 % W] = f.y; v[u * W + 2 % W] = f.z; v[u * W + 3 % W] = f.w;
+      } else {
+        v[u] = l[min(c, vocab - 1)];
+      }
+    }
+    HeadPart q{-INFINITY, 0.f, 0x7fffffff, 0};
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int c = base + ((u / W) * kThreads + static_cast<int>(threadIdx.x)) * W + u % W;
+      if (c < c1) q.m = fmaxf(q.m, v[u]);
+    }
+    const float mu = q.m == -INFINITY ? 0.f : q.m;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int c = base + ((u / W) * kThreads + static_cast<int>(threadIdx.x)) * W + u % W;
+      if (c < c1) {
+        q.s += expf(v[u] - mu);
+        if (!(v[u] < q.m)) q.a = min(q.a, c);  // (a NaN, the only one past the maximum, counts as found)
+      }
+    }
+    t = soft_merge(t, q);
+  }
+  t = soft_reduce(t, lds);
+  if (threadIdx.x == 0) {
+    if (part) part[static_cast<size_t>(i) * gridDim.y + blockIdx.y] = t;
+    else head_store(t, i, rows, n, L_p, sign, x0, conf);
+  }
+}
+
+// row blockIdx.x's n_part partial results -> token and confidence
+__global__ __launch_bounds__(kThreads) void k_head_merge(const HeadPart* __restrict__ part, int n_part,
+                                                         const int* __restrict__ rows, int n, int L_p,
+                                                         float sign, int* __restrict__ x0,
+                                                         float* __restrict__ conf) {
+  __shared__ HeadPart lds[kNW];
+  const int i = blockIdx.x;
+  const HeadPart* p = part + static_cast<size_t>(i) * n_part;
+  HeadPart t{-INFINITY, 0.f, 0x7fffffff, 0};
+  for (int c0 = threadIdx.x; c0 < n_part; c0 += 4 * kThreads) {
+    HeadPart q[4];  // four in flight
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = p[min(c0 + u * kThreads, n_part - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (c0 + u * kThreads < n_part) t = soft_merge(t, q[u]);
+  }
+  t = soft_reduce(t, lds);
+  if (threadIdx.x == 0) head_store(t, i, rows, n, L_p, sign, x0, conf);
 }
 
 // tokens[b][L_p + chosen[b][t]] = x0[b][chosen[b][t]] for t < n_unmask
@@ -188,21 +314,46 @@ void launch_elig_scores(const int* tokens, int B, int n, int L_p, int lo, int hi
 void launch_final_norm(int dtype, const void* hidden, const int* rows, int M, int d, float eps,
                        const void* gain, void* z, hipStream_t st) {
   if (M <= 0) return;
-  if (dtype == 1)
-    hipLaunchKernelGGL(k_final_norm<bf16_t>, dim3(M), dim3(kThreads), 0, st,
-                       static_cast<const bf16_t*>(hidden), rows, d, eps,
-                       static_cast<const bf16_t*>(gain), static_cast<bf16_t*>(z));
-  else
-    hipLaunchKernelGGL(k_final_norm<float>, dim3(M), dim3(kThreads), 0, st,
-                       static_cast<const float*>(hidden), rows, d, eps,
-                       static_cast<const float*>(gain), static_cast<float*>(z));
+  const uintptr_t low = reinterpret_cast<uintptr_t>(hidden) | reinterpret_cast<uintptr_t>(gain) |
+                        reinterpret_cast<uintptr_t>(z);
+  const bool vec = low % 16 == 0 && d % (dtype == 1 ? 8 : 4) == 0;
+#define DLLMC_FN(T, VEC)                                                                              \
+  hipLaunchKernelGGL((k_final_norm<T, VEC>), dim3(M), dim3(kThreads), 0, st, static_cast<const T*>(hidden), \
+                     rows, d, eps, static_cast<const T*>(gain), static_cast<T*>(z))
+  if (dtype == 1 && vec) DLLMC_FN(bf16_t, true);
+  else if (dtype == 1) DLLMC_FN(bf16_t, false);
+  else if (vec) DLLMC_FN(float, true);
+  else DLLMC_FN(float, false);
+#undef DLLMC_FN
 }
 
-void launch_head_finalize(const float* logits, int M, int vocab, const int* rows, int n, int L_p,
-                          float sign, int* x0, float* conf, hipStream_t st) {
+void launch_head_finalize(const float* logits, int M, int vocab, float* part, size_t part_floats,
+                          const int* rows, int n, int L_p, float sign, int* x0, float* conf,
+                          hipStream_t st) {
   if (M <= 0) return;
-  hipLaunchKernelGGL(k_head_finalize, dim3(M), dim3(kThreads), 0, st, logits, vocab, rows, n, L_p,
-                     sign, x0, conf);
+  // Runs of 4096 logits (one round of a workgroup), fewer and longer ones where the scratch is short of
+  // room for their results, one if there is none.
+  int runs = (vocab + 4095) / 4096;
+  const size_t room = part_floats / (static_cast<size_t>(M) * 4);
+  if (part == nullptr || room < 2) runs = 1;
+  else if (static_cast<size_t>(runs) > room) runs = static_cast<int>(room);
+  const int run = ((vocab + runs - 1) / runs + 3) / 4 * 4;
+  runs = (vocab + run - 1) / run;
+  HeadPart* hp = runs > 1 ? reinterpret_cast<HeadPart*>(part) : nullptr;
+  const bool vec = vocab % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0;
+  if (vec)
+    hipLaunchKernelGGL(k_head_partial<true>, dim3(M, runs), dim3(kThreads), 0, st, logits, vocab, run, hp, rows,
+                       n, L_p, sign, x0, conf);
+  else
+    hipLaunchKernelGGL(k_head_partial<false>, dim3(M, runs), dim3(kThreads), 0, st, logits, vocab, run, hp, rows,
+                       n, L_p, sign, x0, conf);
+  if (hp) launch_head_merge(hp, runs, M, rows, n, L_p, sign, x0, conf, st);
+}
+
+void launch_head_merge(const HeadPart* part, int n_part, int M, const int* rows, int n, int L_p, float sign,
+                       int* x0, float* conf, hipStream_t st) {
+  if (M <= 0) return;
+  hipLaunchKernelGGL(k_head_merge, dim3(M), dim3(kThreads), 0, st, part, n_part, rows, n, L_p, sign, x0, conf);
 }
 
 void launch_apply_tokens(int* tokens, int B, int n, int L_p, const int* chosen, int chosen_stride,
