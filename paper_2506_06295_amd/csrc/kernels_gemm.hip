@@ -17,7 +17,8 @@
 //                      operands both go through LDS by direct global->LDS loads, for
 //                      launches with hundreds of activation rows; the same body with paired
 //                      gate/up column blocks and SwiGLU in the epilogue (k_gemm_*_swiglu,
-//                      k_gemm_tall_swiglu: 256 x 96 for up to 256 rows).
+//                      k_gemm_tall_swiglu: 256 x 96 for up to 256 rows), and with the head's reduction
+//                      (k_gemm_mid_head).
 #include <mutex>
 #include <type_traits>
 
@@ -121,12 +122,7 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, in
 //             wavefront keeps the accumulators of 128 / 256 rows, so the weights of a launch
 //             with that many rows are streamed once instead of once per 64-row tile (phases of
 //             128 then, to fit the activation tiles in LDS).
-//   HEAD = 1: the vocabulary projection of the mask predictor's head (one slice): the tile's results are
-//             reduced per row to (maximum, sum of exp, first index of the maximum) and only that is
-//             stored, to entry row * gridDim.x + column tile of C.  The results cross the tile through LDS
-//             (a thread takes 16 or 32 neighbouring columns of a row; reducing them in the accumulator
-//             layout, 16 lanes to a row, takes four times the vector instructions).
-template <int NW, int KC, int DUAL, int KH, int RB = 4, int HEAD = 0>
+template <int NW, int KC, int DUAL, int KH, int RB = 4>
 __global__ __launch_bounds__(NW * 64) void k_gemm_stream(
     const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
     const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0, int N, int K,
@@ -340,60 +336,6 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_stream(
             acc[b][mb][i] += red[((((g - 1) * NWC + wcol) * NB + b) * (4 * RB) + mb * 4 + i) * 64 + lane];
   }
 
-  if (HEAD) {
-    // (every LDS read of the activation tiles is behind the barrier that ended the last phase)
-    static_assert(!HEAD || (NW == 8 && KH == 1 && !DUAL && sizeof(As) >= R * 128 * sizeof(float)),
-                  "a 128-column tile of results fits the activation tiles");
-    float* tile = reinterpret_cast<float*>(&As[0][0][0]);
-    // row r, column c at c ^ 16 * (r / 4 % 4): the four rows that a wavefront stores at once hit
-    // different banks
-#pragma unroll
-    for (int mb = 0; mb < RB; ++mb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        tile[(mb * 16 + lg * 4 + i) * 128 + ((wave * 16 + ln) ^ (lg << 4))] = acc[0][mb][i];
-    __syncthreads();
-    constexpr int TPR = NW * 64 / R, CPT = 128 / TPR;  // threads per row, columns per thread
-    const int r = threadIdx.x / TPR, c0 = (threadIdx.x % TPR) * CPT;
-    const int swz = ((r >> 2) & 3) << 4;
-    float v[CPT];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < CPT / 4; ++t) {
-      // (neighbouring rows start at different pieces of their columns: other banks)
-      const int c = c0 + 4 * ((t + r) % (CPT / 4));
-      const float4 f = *reinterpret_cast<const float4*>(&tile[r * 128 + (c ^ swz)]);
-      v[4 * t] = f.x; v[4 * t + 1] = f.y; v[4 * t + 2] = f.z; v[4 * t + 3] = f.w;
-      mx = fmaxf(mx, fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w)));
-    }
-    const float mu = mx == -INFINITY ? 0.f : mx;
-    float sum = 0.f;
-    int first = 0x7fffffff;
-#pragma unroll
-    for (int t = 0; t < CPT / 4; ++t)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sum += __builtin_amdgcn_exp2f((v[4 * t + e] - mu) * 1.4426950408889634f);
-        if (v[4 * t + e] == mx) first = min(first, c0 + 4 * ((t + r) % (CPT / 4)) + e);
-      }
-    if (first == 0x7fffffff) first = c0;  // nothing but NaN
-    // the row's threads are neighbouring lanes
-#pragma unroll
-    for (int o = 1; o < TPR; o <<= 1) {
-      const float om = __shfl_xor(mx, o, 64), os = __shfl_xor(sum, o, 64);
-      const int oa = __shfl_xor(first, o, 64);
-      const float nm = fmaxf(mx, om), nu = nm == -INFINITY ? 0.f : nm;
-      const float fs = mx == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mx - nu) * 1.4426950408889634f);
-      const float fo = om == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((om - nu) * 1.4426950408889634f);
-      first = mx > om ? first : (om > mx ? oa : min(first, oa));
-      sum = sum * fs + os * fo;
-      mx = nm;
-    }
-    if (threadIdx.x % TPR == 0 && m0 + r < M)
-      reinterpret_cast<HeadPart*>(C)[static_cast<size_t>(m0 + r) * gridDim.x + col_tile] =
-          HeadPart{mx, sum, col_tile * 128 + first, 0};
-    return;
-  }
   if (!active) return;
   if (DUAL) {
 #pragma unroll
@@ -451,6 +393,8 @@ constexpr int kMidM = 128, kMidN = 128;
 //           weight rows are dealt so that a lane's accumulators j and j + 2 hold the rotation pair
 //           (t, t + 64): rotated in registers, query heads go to the compact q_out[i] and the
 //           other heads to cache row rows[i].
+//        3: vocabulary projection of the head: the tile's logits are reduced per row
+//           (head_tile_reduce), to the entries at C.
 struct TileEpilogue {
   // EPI = 1
   int first, per_seq, n, L_p;
@@ -463,6 +407,54 @@ struct TileEpilogue {
   bf16_t* q_out;         // [M, N0]
   int d_kv, rope_second;
 };
+
+// Head: a tile of logits in LDS (128 columns per row, column c of row r at c ^ 16 * (r / 4 % 4): the four
+// rows that a wavefront stores at once hit different banks) is reduced per row to (maximum, sum of
+// exp, first index of the maximum) by TPR neighbouring threads and stored to part[row * tiles + tile].
+// The results cross through LDS for this: reducing them in the accumulator layout, 16 lanes to a row,
+// takes four times the vector instructions.
+template <int TPR>
+__device__ __forceinline__ void head_tile_reduce(const float* tile, int m0, int M, int col_tile, int tiles,
+                                                 HeadPart* __restrict__ part) {
+  constexpr int CPT = 128 / TPR;  // columns per thread
+  constexpr float kLog2e = 1.4426950408889634f;
+  const int r = threadIdx.x / TPR, c0 = (threadIdx.x % TPR) * CPT;
+  const int swz = ((r >> 2) & 3) << 4;
+  float v[CPT];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < CPT / 4; ++t) {
+    // (neighbouring rows start at different pieces of their columns: other banks)
+    const int c = c0 + 4 * ((t + r) % (CPT / 4));
+    const float4 f = *reinterpret_cast<const float4*>(&tile[r * 128 + (c ^ swz)]);
+    v[4 * t] = f.x; v[4 * t + 1] = f.y; v[4 * t + 2] = f.z; v[4 * t + 3] = f.w;
+    mx = fmaxf(mx, fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w)));
+  }
+  const float mu = mx == -INFINITY ? 0.f : mx;
+  float sum = 0.f;
+  int first = 0x7fffffff;
+#pragma unroll
+  for (int t = 0; t < CPT / 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sum += __builtin_amdgcn_exp2f((v[4 * t + e] - mu) * kLog2e);
+      if (v[4 * t + e] == mx) first = min(first, c0 + 4 * ((t + r) % (CPT / 4)) + e);
+    }
+  if (first == 0x7fffffff) first = c0;  // nothing but NaN
+#pragma unroll
+  for (int o = 1; o < TPR; o <<= 1) {
+    const float om = __shfl_xor(mx, o, 64), os = __shfl_xor(sum, o, 64);
+    const int oa = __shfl_xor(first, o, 64);
+    const float nm = fmaxf(mx, om), nu = nm == -INFINITY ? 0.f : nm;
+    const float fs = mx == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mx - nu) * kLog2e);
+    const float fo = om == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((om - nu) * kLog2e);
+    first = mx > om ? first : (om > mx ? oa : min(first, oa));
+    sum = sum * fs + os * fo;
+    mx = nm;
+  }
+  if (threadIdx.x % TPR == 0 && m0 + r < M)
+    part[static_cast<size_t>(m0 + r) * tiles + col_tile] = HeadPart{mx, sum, col_tile * 128 + first, 0};
+}
 
 template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0>
 __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int lda,
@@ -489,7 +481,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // loop.
   constexpr bool ONE_BARRIER = BM == 256;
   constexpr int kSlot = (BM > BN ? BM : BN) * 8;
-  constexpr int kLdsTotal = ONE_BARRIER ? 5 * kSlot : 2 * kStage + (EPI ? 2 * BM / 4 : 0);
+  constexpr int kLdsTotal = ONE_BARRIER ? 5 * kSlot : 2 * kStage + (EPI == 1 || EPI == 2 ? 2 * BM / 4 : 0);
   static_assert(kLdsTotal * sizeof(uint4) <= 160 * 1024, "LDS of one CU");
   __shared__ __attribute__((aligned(1024))) uint4 lds_all[kLdsTotal];
   uint4 (*lds)[kStage] = reinterpret_cast<uint4 (*)[kStage]>(lds_all);
@@ -546,7 +538,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // (with five slots there is no room for the table during the main loop: the thread keeps its
   // row's two entries in registers and writes them to the last slot afterwards)
   int meta_r0 = 0, meta_r1 = 0;
-  if (EPI != 0 && threadIdx.x < BM) {
+  if ((EPI == 1 || EPI == 2) && threadIdx.x < BM) {
     const int r = threadIdx.x;
     const int m = min(m0 + r, M - 1);
     if (EPI == 1) {
@@ -584,7 +576,9 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // apart, so unrotated every load in flight on the chip has the same address bits below the row
   // pitch and the memory channels are loaded unevenly (4096 x 4096 x 16384: 959 -> 1097 TFLOP/s).
   // The workgroups of one XCD keep a common start, they share operand blocks through its L2.
-  const int rot = (((blockIdx.x + gridDim.x * blockIdx.y) & 7) * nkt) >> 3;
+  // (EPI 3: no such start -- equal rows of the vocabulary projection have to give equal logits whatever tile
+  // they are in, so that the lowest token wins, and a sum's bits depend on where its walk begins)
+  const int rot = EPI == 3 ? 0 : (((blockIdx.x + gridDim.x * blockIdx.y) & 7) * nkt) >> 3;
   auto kof = [&](int kt) { const int k = kt + rot; return (k < nkt ? k : k - nkt) * kFatK; };
   if (ONE_BARRIER) {
     // Five slots of one operand block (256 rows x 64 contraction values) each.  Blocks are
@@ -780,12 +774,28 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   }
 #undef DLLMC_LDS_ISSUE
 
-  if (EPI != 0) {
+  if (EPI == 3) {
+    static_assert(EPI != 3 || (BN == 128 && BM * 128 * sizeof(float) <= sizeof(lds_all)), "the tile fits");
+    __syncthreads();  // everybody has finished the fragment reads of the last step
+    float* tile = reinterpret_cast<float*>(lds_all);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          tile[(wm * (MI * 16) + i * 16 + lg * 4 + e) * 128 + ((wn * (NJ * 16) + j * 16 + ln) ^ (lg << 4))] =
+              acc[i][j][e];
+    __syncthreads();
+    head_tile_reduce<NWV * 64 / BM>(tile, m0, M, col_tile, gridDim.x, reinterpret_cast<HeadPart*>(C));
+    return;
+  }
+  if (EPI == 1 || EPI == 2) {
     // Epilogues that finish the step's work on the tile.  A wavefront's 16-row x 64-column block of
     // results (rounded to bf16) is staged through a private piece of LDS so that it leaves, and
     // the cached rows it is compared with arrive, as 16-byte pieces of contiguous row segments:
     // lane l then holds columns 8*(l%8) .. +8 of block rows l/8 and l/8 + 8.
-    static_assert(EPI == 0 || NJ == 4, "a wavefront's block is 64 columns wide");
+    static_assert((EPI != 1 && EPI != 2) || NJ == 4, "a wavefront's block is 64 columns wide");
     static_assert(EPI != 2 || WN % 2 == 0, "a head is two column wavefronts");
     constexpr int kStg = 72;  // staging row stride in elements: 64 columns + 16 bytes
     static_assert(NWV * 16 * kStg * sizeof(bf16_t) <= kStage * sizeof(uint4), "staging fits a stage");
@@ -1003,6 +1013,12 @@ __global__ __launch_bounds__(256) void k_gemm_mid_qk(const bf16_t* __restrict__ 
                                                      const bf16_t* __restrict__ W1, int N0, int N, int K,
                                                      TileEpilogue ep) {
   gemm_lds_body<2, 2, 4, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
+}
+
+__global__ __launch_bounds__(256) void k_gemm_mid_head(const bf16_t* __restrict__ A, int lda, int M,
+                                                       const bf16_t* __restrict__ W, int N, int K,
+                                                       float* __restrict__ C) {
+  gemm_lds_body<2, 2, 4, 4, 0, 3>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C);
 }
 
 // fused gate/up + SwiGLU for many rows: N is the FFN width, grid.x = N / 128 (fat) or N / 64 (mid)
@@ -1288,24 +1304,19 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
 
 int launch_gemm_head(int dtype, const void* A, int lda, int M, const void* W, int N, int K, HeadPart* part,
                      size_t part_capacity, hipStream_t st) {
-  // The shapes that run the streaming kernel, whose workgroups own whole 128-column tiles of up to 128
-  // rows.
-  const bool al = aligned16(A) && aligned16(W) && aligned16(part);
-  const GemmPlan p = plan_gemm(dtype, al, lda, M, N, N, K, static_cast<size_t>(M) * N);
-  if (g_tune.nw != 8 || (p.kind != 2 && p.kind != 6) || static_cast<size_t>(M) * p.nt > part_capacity) return 0;
-  t_last_stream = true;
-  const dim3 grid(p.nt, p.mt, 1);
-  const bf16_t* a = static_cast<const bf16_t*>(A);
-  const bf16_t* w = static_cast<const bf16_t*>(W);
-#define DLLMC_GH(KCv, RBv)                                                                                   \
-  hipLaunchKernelGGL((k_gemm_stream<8, KCv, 0, 1, RBv, 1>), grid, dim3(512), 0, st, a, lda, nullptr, M, w, \
-                     static_cast<const bf16_t*>(nullptr), N, N, K, K, reinterpret_cast<float*>(part), nullptr, p.nt)
-  if (p.kind == 6 && p.KC == 256) DLLMC_GH(256, 8);
-  else if (p.kind == 6) DLLMC_GH(128, 8);
-  else if (p.KC == 256) DLLMC_GH(256, 4);
-  else DLLMC_GH(128, 4);
-#undef DLLMC_GH
-  return p.nt;
+  // The 128 x 128 tile kernel whatever the number of rows: with a single row it streams the weights at 5.9
+  // TB/s (op_head of 1 / 64 / 100 / 128 rows x 126464 x 4096: 184 / 190 / 196 / 203 us; the streaming kernel
+  // with the same reduction 213 / 227 / 247 / 250), two workgroups per CU and loads of whole lines.
+  // From 641 rows the 256 x 256 tiles are ahead in spite of the logits' trip through memory (513 rows 645
+  // against 690 us, 700 rows 779 against 750).
+  if (dtype != 1 || K % kFatK || N % kMidN || lda % 8 || M > 640) return 0;
+  if (!aligned16(A) || !aligned16(W) || !aligned16(part)) return 0;
+  if (static_cast<size_t>(M) * (N / kMidN) > part_capacity) return 0;
+  t_last_stream = false;
+  hipLaunchKernelGGL(k_gemm_mid_head, dim3(N / kMidN, (M + kMidM - 1) / kMidM), dim3(256), 0, st,
+                     static_cast<const bf16_t*>(A), lda, M, static_cast<const bf16_t*>(W), N, K,
+                     reinterpret_cast<float*>(part));
+  return N / kMidN;
 }
 
 bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int M,

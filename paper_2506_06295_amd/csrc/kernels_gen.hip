@@ -6,7 +6,7 @@
 //   k_head_partial    per row and run of logits: maximum, sum of exponentials, first index of the
 //                     maximum; k_head_merge: the row's greedy token (lowest id among equal logits) and its
 //                     softmax probability from those, or from the ones that the vocabulary projection of
-//                     up to 191 rows leaves instead of logits (k_gemm_stream)
+//                     up to 640 rows leaves instead of logits (k_gemm_mid_head)
 //   k_apply_tokens    the chosen positions take their greedy token
 // The vocabulary projection itself is a gathered linear map (kernels_gemm.hip); the choice of
 // the positions is the integer-exact bottom-k selection (kernels_select.hip) on the negated
