@@ -304,7 +304,7 @@ def main():
         achieved = ks["alg_bytes"] / (k_ms * 1e-3) / 1e9 if k_ms > 0 else 0.0
         traffic = TRAFFIC_BYTES_PER_LAUNCH.get(cfg.name)
         result["roofline"] = {
-            "kernel": "k_gemm_stream (every launch: fused gate/up, Q|K, output and down projections "
+            "kernel": "k_gemm_ring (every launch: fused gate/up, Q|K, output and down projections "
                       "of the recomputed rows)",
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,

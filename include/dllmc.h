@@ -203,7 +203,7 @@ enum {
   DLLMC_KC_GEMM_DOWN, DLLMC_KC_ATTENTION, DLLMC_KC_SELECT, DLLMC_KC_ROW, DLLMC_KC_LISTS,
   DLLMC_KC_EVENT_OVERHEAD, /* an empty span per step: what one event record adds to a span */
   DLLMC_KC_STREAM_KERNEL,  /* the launches of the five gemm classes that ran the weight-streaming
-                              kernel (k_gemm_stream), counted here a second time: one kernel's
+                              kernel (k_gemm_ring), counted here a second time: one kernel's
                               figures, comparable with a profiler's per-kernel average */
   DLLMC_KC_HEAD_GEMM,      /* closed loop: vocabulary projection of the masked rows */
   DLLMC_KC_GEN_OTHER,      /* closed loop: final norm, greedy token + confidence, eligibility,
@@ -288,17 +288,11 @@ int dllmc_op_head(int32_t dtype, const void* hidden, const int32_t* rows, int32_
  * process default (thread-safe); a context copies the default when it is created and keeps its
  * copy for life, so live contexts are not affected; the single operations (dllmc_op_*) and the
  * closed loop's head use the default in force when they are called.  An argument outside its
- * range leaves that knob unchanged: nw wavefronts per workgroup (4|8) of the single-matrix kernel; nw_dual
- * shape of the fused gate/up kernel: 4|8 wavefronts in one group, or 100 + (4|6|8): the
- * wavefronts form two groups that each walk one half of the contraction range (default 106:
- * 48 columns of each matrix per workgroup); force_s number of contraction slices
- * (0 = automatic), target_wg
- * workgroups the automatic choice aims for, tile_min_m / fat_min_m number of activation rows
- * (defaults 192 / 512) from which the 128 x 128 / the 256 x 256 LDS-direct tile kernel replaces
- * the weight-streaming kernel; tall_max_m (default 128; 0 = off): from 128 on, launches of 65..128
- * rows run the weight-streaming kernel with 128 rows per workgroup (weights streamed once
- * instead of once per 64-row tile); from 256 on, launches of tile_min_m .. tall_max_m rows use
- * it with 256 rows per workgroup instead of the 128 x 128 tiles.
+ * range leaves that knob unchanged: force_s number of contraction slices (0 = automatic), target_wg
+ * workgroups the slice count of the 128 x 128 tile kernel aims for, tile_min_m / fat_min_m number of
+ * activation rows (defaults 192 / 512) from which the 128 x 128 / the 256 x 256 LDS-direct tile kernel
+ * replaces the weight-streaming kernel.  nw, nw_dual and tall_max_m chose shapes of a kernel that is no
+ * longer there: any value is accepted and has no effect.
  * Results are
  * bit-reproducible for fixed settings; different settings change the float32 summation order
  * only. */

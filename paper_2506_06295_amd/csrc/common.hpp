@@ -176,21 +176,10 @@ int gemm_max_slices();
 // from the process default when it is created); the launchers use the copy of the context whose
 // call is running on this thread (TuningScope), the process default otherwise.
 struct GemmTuning {
-  int nw = 8;          // wavefronts per workgroup (4 or 8) of the single-matrix kernel
-  int nw_dual = 106;   // fused gate/up kernel: 6 wavefronts in two groups over the contraction
-                       // range (+100), i.e. 48 columns of each matrix per workgroup: the
-                       // narrowest tile that still amortises the activation tile measured
-                       // fastest at both FFN widths (12288: one workgroup per CU)
-  int force_s = 0;     // > 0: number of slices of the contraction index
-  int target_wg = 256; // workgroups the automatic slice count aims for
+  int force_s = 0;          // > 0: number of slices of the contraction index
+  int target_wg = 256;      // workgroups the slice count of the 128 x 128 tile kernel aims for
   int fat_min_m = 512;      // activation rows from which the 256 x 256 LDS-direct kernel is used
-  int tall_max_m = 128;     // most rows the streaming kernel covers with one workgroup tile:
-                            // 65..128 rows run with 128 rows per workgroup when it is >= 128
-                            // (weights streamed once instead of once per 64-row tile); from
-                            // 256 on, launches of tile_min_m..tall_max_m rows use 256 rows per
-                            // workgroup instead of the 128 x 128 tiles (slower where measured)
   int tile_min_m = 192;     // activation rows from which the 128 x 128 LDS-direct kernel is used
-                            // (off by default: the streaming kernel is faster at the sizes measured)
 };
 GemmTuning gemm_default_tuning();
 struct TuningScope {
@@ -202,11 +191,11 @@ struct TuningScope {
 };
 // slices launch_gemm would use for 16-byte aligned operands (0: capacity too small); host only
 int gemm_plan_slices(int dtype, int M, int N, int N0, int K, size_t c_capacity);
-void gemm_set_tuning(int nw, int nw_dual, int force_s, int target_wg);
+void gemm_set_tuning(int force_s, int target_wg);
 void gemm_set_tile_min_m(int m);
 void gemm_set_fat_min_m(int m);
-void gemm_set_tall_max_m(int m);
-// True when the most recent launch_gemm / launch_gemm_swiglu of this thread ran k_gemm_stream.
+// True when the most recent launch_gemm / launch_gemm_swiglu of this thread ran the
+// weight-streaming kernel (k_gemm_ring).
 bool gemm_last_was_stream();
 void gemm_clear_last_stream();  // a matrix product launched by another launcher follows
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
@@ -230,6 +219,15 @@ bool launch_gemm_f32_swiglu(const float* A, int lda, const int* rows, int M, con
 bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int M,
                         const void* w_gate, const void* w_up, int m, int K, void* u,
                         hipStream_t st);
+
+// bf16 maps of few rows and of any column count (kernels_gemm_ring.hip): row and column blocks of a tile, slices
+struct RingPlan { int rb, nb, S, kps, nt, mt; };
+bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K);
+RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s);
+void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
+                      const bf16_t* W1, int N0, int N, int K, float* C, hipStream_t st);
+void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,
+                             const bf16_t* w_up, int m, int K, bf16_t* u, hipStream_t st);
 
 // Vocabulary projection that leaves, instead of the logits, their reduction per row and 128-column
 // tile: part[i * tiles + t] for i < M.  Returns the number of tiles, 0 (nothing launched) when the shape is not

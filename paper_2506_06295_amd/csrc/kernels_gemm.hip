@@ -4,15 +4,8 @@
 //  * k_gemm_simple  -- plain LDS-tiled FMA kernel for any storage type and shape: the fallback
 //                      for shapes and alignments that the MFMA kernels do not take (float32
 //                      models: kernels_gemm_f32.hip).
-//  * k_gemm_stream  -- bf16 MFMA kernel built for the cached step's regime: few activation
-//                      rows (64 or 128 per workgroup tile) against a weight matrix that is read
-//                      exactly once from HBM.  The activation tile is staged in LDS, the
-//                      weight rows go straight from global memory into the MFMA B operand
-//                      (each lane reads 64 contiguous bytes of one weight row, so a
-//                      wavefront consumes whole 256-byte row segments), and the contraction
-//                      index is split over workgroups so that every CU gets one.
-//                      Partial sums go to float32 slices that the row kernels add up in a
-//                      fixed order (no float atomics: results are bit-reproducible).
+//  * k_gemm_ring    -- bf16 MFMA kernel for few activation rows against a weight matrix that is read
+//                      exactly once from HBM, and for any column count: kernels_gemm_ring.hip.
 //  * k_gemm_fat / k_gemm_mid -- bf16 MFMA kernels with 256 x 256 / 128 x 128 tiles whose
 //                      operands both go through LDS by direct global->LDS loads, for
 //                      launches with hundreds of activation rows; the same body with paired
@@ -90,273 +83,6 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, in
       const int nn = n0 + tx * 4 + j;
       if (nn < N) C[static_cast<size_t>(m) * N + nn] = acc[i][j];
     }
-  }
-}
-
-// ------------------------------------------------------------------------------------
-// k_gemm_stream<NW, KC, DUAL, KH>
-// Workgroup = NW wavefronts; tile = 64 activation rows x (16*NW) output columns; wavefront w
-// owns 16 columns and all 64 rows (four 16x16 accumulators of v_mfma_f32_16x16x32_bf16 per
-// weight matrix).  The workgroup's slice of the contraction index is walked in phases of KC:
-// the activation tile of phase p+1 is fetched into registers while phase p is multiplied and
-// is written to the other LDS buffer at the end of the phase (one barrier per phase).  The
-// weight stream is prefetched one whole phase ahead and runs across phase boundaries.
-// Lane (n = lane%16, g = lane/16) holds, for MFMA step c of a 128-wide step, the eight
-// weights W[col n][k0 + 32c + 8g ..+8]; the A operand is read from LDS at the same offsets
-// (the 16-byte chunks of an LDS row are XOR-permuted in groups of 16 by row % 16, which keeps
-// the fragment reads free of bank conflicts; with a padded row stride, or a permutation by
-// row % 8, half of the LDS cycles of the reads were conflicts).
-//   DUAL = 0: columns [0,N0) come from W0, [N0,N) from W1; float32 partial sums are stored
-//             to slice blockIdx.z of C.
-//   DUAL = 1: every lane streams row n of W0 (gate) and row n of W1 (up) and the epilogue
-//             stores bf16(silu(gate) * up) to U[M, N] (SwiGLU, complexity appendix of the
-//             paper); needs a single slice.
-//   KH = 2:   the wavefronts form two groups that walk the two halves of the workgroup's
-//             contraction range side by side (tile = 16*NW/2 columns); the second group hands
-//             its accumulators over through LDS at the end and the first adds them (its own
-//             sum first).  Doubles the wavefronts, and with them the loads in flight, of a
-//             launch that cannot split the contraction over workgroups (DUAL).
-// N only has to be a multiple of 16: a ragged last tile is allowed, and with it any number of
-// column wavefronts.
-//   RB:       16-row blocks per workgroup (4: the 64 rows described above).  With RB = 8 / 16 a
-//             wavefront keeps the accumulators of 128 / 256 rows, so the weights of a launch
-//             with that many rows are streamed once instead of once per 64-row tile (phases of
-//             128 then, to fit the activation tiles in LDS).
-template <int NW, int KC, int DUAL, int KH, int RB = 4>
-__global__ __launch_bounds__(NW * 64) void k_gemm_stream(
-    const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
-    const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0, int N, int K,
-    int k_per_slice, float* __restrict__ C, bf16_t* __restrict__ U, int n_full) {
-  constexpr int LS = KC;                          // LDS row stride; chunk q of row r sits in slot
-                                                  // q ^ (r % 16) of its group of 16 (no padding)
-  constexpr int CPR = KC / 8;                     // 16-byte chunks per activation row and phase
-  constexpr int R = 16 * RB;                      // activation rows per workgroup
-  constexpr int TOT = KH * R * CPR;               // chunks of the workgroup's activation tiles
-  constexpr int NCH = (TOT + NW * 64 - 1) / (NW * 64);  // chunks staged per thread and phase
-  constexpr bool EVEN = TOT % (NW * 64) == 0;     // otherwise the last chunk of some threads is void
-  constexpr int NB = DUAL ? 2 : 1;
-  constexpr int NWC = NW / KH;                    // wavefronts side by side over the columns
-  static_assert(NW % KH == 0, "wavefront groups must be equal");
-  __shared__ __attribute__((aligned(16))) bf16_t As[2][KH][R * LS];
-  // (the wavefront index as a scalar: the column block and whether the wavefront has one are
-  // then scalar too)
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int ln = lane % 16, lg = lane / 16;
-  const int wcol = wave % NWC, kh = wave / NWC;
-  int col_tile, row_tile;
-  xcd_tile_map(col_tile, row_tile);
-  const int m0 = row_tile * R;
-  const int kbeg = blockIdx.z * k_per_slice;
-  const int klen = min(K, kbeg + k_per_slice) - kbeg;  // multiple of KH * KC
-  const int hlen = klen / KH;                          // contraction range of one group
-  const int nph = hlen / KC;
-  // DUAL: the walk starts at a phase that depends on the column tile and wraps around.  The
-  // workgroups of such a launch (one per CU, a single slice) run nearly in step, and rows of W
-  // are a multiple of 4 KB apart at these widths: unrotated, every load in flight on the chip
-  // has the same address bits below the row pitch and the memory channels are loaded unevenly
-  // (the launch took 48 to 61 us depending on where the two matrices happened to lie; rotated,
-  // 49 to 52 us everywhere).  The split launches already walk different ranges side by side
-  // and gain nothing; a single-slice launch with several workgroups per CU (the vocabulary
-  // projection) lost 10-35 %, so they keep the plain order.
-  const int rot = (DUAL && nph > 1) ? col_tile % nph : 0;
-  // This wavefront's block of 16 columns.  The first n_full column tiles own NWC blocks each, the
-  // others NWC - 1 (the host evens out the blocks per CU that way when a launch needs more than
-  // one round of workgroups); a wavefront without a block, also in a ragged last tile, only
-  // helps to stage the activations and keeps the barriers.
-  const int cb = col_tile < n_full ? col_tile * NWC + wcol
-                                   : n_full * NWC + (col_tile - n_full) * (NWC - 1) + wcol;
-  const bool active = (col_tile < n_full || wcol < NWC - 1) && cb * 16 < N;
-  const int ncol = (active ? cb : 0) * 16 + ln;
-  // A wavefront without a block runs the same phases as the others (no branch in the loop: see
-  // below), on the first 256 contraction values of block 0 over and over: cache hits.
-  const int kmul = active ? 1 : 0;
-  const bf16_t* wp[NB];
-  if (DUAL) {
-    wp[0] = W0 + static_cast<size_t>(ncol) * K + kbeg + kh * hlen + lg * 8;
-    wp[NB - 1] = W1 + static_cast<size_t>(ncol) * K + kbeg + kh * hlen + lg * 8;
-  } else {
-    wp[0] = (ncol < N0 ? W0 + static_cast<size_t>(ncol) * K
-                       : W1 + static_cast<size_t>(ncol - N0) * K) + kbeg + kh * hlen + lg * 8;
-  }
-  // the activation chunks this thread stages: same (group, row, chunk) in every phase
-  const bf16_t* asrc[NCH];
-  int adst[NCH];
-  bool aval[NCH], ain[NCH];
-#pragma unroll
-  for (int j = 0; j < NCH; ++j) {
-    int e = threadIdx.x + j * NW * 64;
-    ain[j] = EVEN || e < TOT;
-    if (!ain[j]) e = 0;
-    const int h = e / (R * CPR), r = (e / CPR) % R, c = e % CPR;
-    const int m = m0 + r;
-    aval[j] = ain[j] && m < M;
-    const int mm = min(m, M - 1);  // chunks without a row of their own read a valid one and are zeroed
-    const int row = rows ? rows[mm] : mm;
-    asrc[j] = A + static_cast<size_t>(row) * lda + kbeg + h * hlen + c * 8;
-    adst[j] = h * R * LS + r * LS + (c ^ (r % 16)) * 8;
-  }
-  f32x4 acc[NB][RB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int i = 0; i < RB; ++i) acc[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // element offsets, within a 128-wide step, of this lane's four fragment chunks 4c + lg after
-  // the slot permutation of its row (rows mb*16 + ln share row % 16 = ln)
-  int fo[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) fo[c] = ((4 * c + lg) ^ ln) * 8;
-
-  // The activation chunks of the first phase: every load goes out before the first one is used
-  // (rows past M and chunks past the tile read a valid row and are zeroed or dropped afterwards --
-  // a load under "if (row < M)" is a basic block of its own, and the store that follows it then
-  // waits for it before the next load is issued: one trip to memory per chunk), and so do the
-  // first weight pieces, before the activations are waited for.
-  uint4 a0[NCH];
-#pragma unroll
-  for (int j = 0; j < NCH; ++j) a0[j] = *reinterpret_cast<const uint4*>(asrc[j] + rot * KC);
-  // Weight pieces in flight: one whole phase (KC / 128 steps) ahead of the multiplications, in
-  // two register sets that swap roles from phase to phase; a phase is straight-line code (the
-  // last one, which fetches nothing, is a variant of its own; a wavefront without a column block
-  // loads and multiplies like the others), and its barrier is a bare s_barrier behind a wait for
-  // the LDS operations only.  Each of these matters, because the wait counter counts loads in
-  // order and the compiler has to place its waits from what it can prove: (1) with one set,
-  // refilled piece by piece behind a copy of the piece being multiplied, it carries the set
-  // through the loop by copying the freshly loaded registers into place at the end of the body,
-  // and waits for every load of the phase to do so; (2) a __syncthreads() waits for every load in
-  // flight; (3) behind a join of paths that issued different numbers of loads (wavefronts
-  // without a block, the last phase) the activation chunks, the oldest loads of a phase, are
-  // waited for as if no younger load existed.  With any one of the three nothing stayed in
-  // flight across a phase boundary and a phase cost a full trip to memory (adaptive step of
-  // `llada8b` 5.45 -> 5.29 ms).  Three sets, two phases ahead, measured no better than two; nor
-  // did the first weight pieces issued ahead of the row list's wait (the activation chunks,
-  // which come from L2, then return behind them).
-  constexpr int NS = KC / 128;
-  uint4 bset0[NB][NS][4], bset1[NB][NS][4];
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        bset0[b][t][c] = *reinterpret_cast<const uint4*>(wp[b] + (rot * KC + t * 128) * kmul + c * 32);
-#pragma unroll
-  for (int j = 0; j < NCH; ++j) {
-    if (!aval[j]) a0[j] = make_uint4(0u, 0u, 0u, 0u);
-    if (ain[j]) *reinterpret_cast<uint4*>(&As[0][0][adst[j]]) = a0[j];
-  }
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront's stores are complete
-  __builtin_amdgcn_s_barrier();
-
-  // one phase: multiply from `cur`; MORE: fetch the next phase's activation chunks and, as the
-  // steps go by, its weight pieces into `nxt`
-  auto phase = [&](auto more_tag, int ph, const uint4 (&cur)[NB][NS][4], uint4 (&nxt)[NB][NS][4]) {
-    constexpr bool MORE = decltype(more_tag)::value;
-    int pn = ph + 1 + rot;  // the phase fetched during this one
-    if (pn >= nph) pn -= nph;
-    uint4 av[NCH];
-    if (MORE) {
-#pragma unroll
-      for (int j = 0; j < NCH; ++j) av[j] = *reinterpret_cast<const uint4*>(asrc[j] + pn * KC);
-    }
-    const bf16_t* ap = &As[ph & 1][kh][ln * LS];
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      if (MORE) {
-        const int knext = (pn * KC + t * 128) * kmul;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            nxt[b][t][c] = *reinterpret_cast<const uint4*>(wp[b] + knext + c * 32);
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int mb = 0; mb < RB; ++mb) {
-          const bf16x8 af =
-              *reinterpret_cast<const bf16x8*>(ap + mb * 16 * LS + t * 128 + fo[c]);
-#pragma unroll
-          for (int b = 0; b < NB; ++b)
-            acc[b][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                af, __builtin_bit_cast(bf16x8, cur[b][t][c]), acc[b][mb], 0, 0, 0);
-        }
-    }
-    if (MORE) {
-#pragma unroll
-      for (int j = 0; j < NCH; ++j) {
-        if (!aval[j]) av[j] = make_uint4(0u, 0u, 0u, 0u);
-        if (ain[j]) *reinterpret_cast<uint4*>(&As[(ph + 1) & 1][0][adst[j]]) = av[j];
-      }
-    }
-    // this wavefront's fragment reads of the phase and its stores for the next one are complete
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-  };
-  {
-    using yes = std::integral_constant<bool, true>;
-    using no = std::integral_constant<bool, false>;
-    int ph = 0;
-    for (; ph + 2 < nph; ph += 2) {
-      phase(yes{}, ph, bset0, bset1);
-      phase(yes{}, ph + 1, bset1, bset0);
-    }
-    if (nph - ph == 2) {
-      phase(yes{}, ph, bset0, bset1);
-      phase(no{}, ph + 1, bset1, bset0);
-    } else if (nph - ph == 1) {
-      phase(no{}, ph, bset0, bset1);
-    }
-  }
-
-  if (KH > 1) {
-    // hand-over of the other groups' sums: [group - 1][column wavefront][matrix][accumulator
-    // element][lane] (every LDS read of the activation tiles is behind the barrier that ended the
-    // last phase); the first group adds them to its own in group order
-    float* red = reinterpret_cast<float*>(&As[0][0][0]);
-    static_assert((KH - 1) * NWC * NB * 4 * RB * 64 * sizeof(float) <= sizeof(As), "hand-over fits the tiles");
-    if (kh > 0) {
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int mb = 0; mb < RB; ++mb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            red[((((kh - 1) * NWC + wcol) * NB + b) * (4 * RB) + mb * 4 + i) * 64 + lane] = acc[b][mb][i];
-    }
-    __syncthreads();
-    if (kh > 0 || !active) return;
-#pragma unroll
-    for (int g = 1; g < KH; ++g)
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int mb = 0; mb < RB; ++mb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            acc[b][mb][i] += red[((((g - 1) * NWC + wcol) * NB + b) * (4 * RB) + mb * 4 + i) * 64 + lane];
-  }
-
-  if (!active) return;
-  if (DUAL) {
-#pragma unroll
-    for (int mb = 0; mb < RB; ++mb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + mb * 16 + lg * 4 + i;
-        if (m < M) {
-          const float g = acc[0][mb][i], up = acc[NB - 1][mb][i];
-          U[static_cast<size_t>(m) * N + ncol] = f32_to_bf16(g / (1.0f + expf(-g)) * up);
-        }
-      }
-  } else {
-    float* Cs = C + static_cast<size_t>(blockIdx.z) * M * N;
-#pragma unroll
-    for (int mb = 0; mb < RB; ++mb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + mb * 16 + lg * 4 + i;
-        if (m < M) Cs[static_cast<size_t>(m) * N + ncol] = acc[0][mb][i];
-      }
   }
 }
 
@@ -1096,19 +822,6 @@ const GemmTuning& tune() {
 #define g_tune (tune())
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
-template <int NW, int KC, int DUAL, int KH = 1, int RB = 4>
-void launch_stream(dim3 grid, hipStream_t st, const bf16_t* A, int lda, const int* rows, int M,
-                   const bf16_t* W0, const bf16_t* W1, int N0, int N, int K, int kps, float* C,
-                   bf16_t* U, int n_full = -1) {
-  hipLaunchKernelGGL((k_gemm_stream<NW, KC, DUAL, KH, RB>), grid, dim3(NW * 64), 0, st, A, lda, rows, M, W0,
-                     W1, N0, N, K, kps, C, U, n_full < 0 ? static_cast<int>(grid.x) : n_full);
-}
-
-bool stream_shape_ok(int dtype, const void* A, int lda, const void* W0, const void* W1, int K) {
-  return dtype == 1 && (K % 128 == 0) && (lda % 8 == 0) && aligned16(A) && aligned16(W0) &&
-         (W1 == nullptr || aligned16(W1));
-}
 }  // namespace
 
 static thread_local bool t_last_stream = false;
@@ -1124,14 +837,10 @@ TuningScope::TuningScope(const GemmTuning* t) : prev(t_scope) { t_scope = t; }
 TuningScope::~TuningScope() { t_scope = prev; }
 
 void gemm_set_tile_min_m(int m) { std::lock_guard<std::mutex> lock(g_tune_mu); if (m > 0) g_default_tune.tile_min_m = m; }
-void gemm_set_tall_max_m(int m) { std::lock_guard<std::mutex> lock(g_tune_mu); if (m >= 0) g_default_tune.tall_max_m = m; }
 void gemm_set_fat_min_m(int m) { std::lock_guard<std::mutex> lock(g_tune_mu); if (m > 0) g_default_tune.fat_min_m = m; }
 
-void gemm_set_tuning(int nw, int nw_dual, int force_s, int target_wg) {
+void gemm_set_tuning(int force_s, int target_wg) {
   std::lock_guard<std::mutex> lock(g_tune_mu);
-  if (nw == 4 || nw == 8) g_default_tune.nw = nw;
-  if (nw_dual == 4 || nw_dual == 8 || nw_dual == 104 || nw_dual == 106 || nw_dual == 108)
-    g_default_tune.nw_dual = nw_dual;
   if (force_s >= 0) g_default_tune.force_s = force_s;
   if (target_wg > 0) g_default_tune.target_wg = target_wg;
 }
@@ -1139,28 +848,28 @@ void gemm_set_tuning(int nw, int nw_dual, int force_s, int target_wg) {
 
 // Which kernel, how many slices of the contraction index and how long a slice: pure host logic.
 struct GemmPlan {
-  int kind;  // 0 nothing fits, 1 plain, 2 streaming, 3 256x256 LDS-direct, 4 128x128 LDS-direct,
-             // 5 / 6 streaming with 256 / 128 rows per workgroup, 7 float32 on the matrix cores
-  int S, kps, KC, nt, mt;  // KC: phase length of the streaming kernel, tile shape of kind 7
+  int kind;  // 0 nothing fits, 1 plain, 2 weight-streaming, 3 256x256 LDS-direct, 4 128x128 LDS-direct,
+             // 7 float32 on the matrix cores
+  int S, kps, nt, mt;
+  RingPlan ring;  // kind 2
+  F32Plan f32;    // kind 7
 };
 
 GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int N0, int K,
                    size_t c_capacity) {
-  GemmPlan p{0, 0, 0, 0, 0, 0};
+  GemmPlan p{};
   const size_t MN = static_cast<size_t>(M) * N;
   if (M <= 0 || N <= 0 || K <= 0 || c_capacity < MN) return p;
   // most slices the caller's buffer can hold
   const int s_cap = static_cast<int>(c_capacity / MN < static_cast<size_t>(kMaxSlices)
                                          ? c_capacity / MN : static_cast<size_t>(kMaxSlices));
-  const int NW = g_tune.nw;
-  const int BN = 16 * NW;
   if (dtype == 0 && operands_aligned && K % 4 == 0 && lda % 4 == 0) {
-    const F32Plan f = plan_f32(M, N, K, s_cap, g_tune.force_s);
-    p.kind = 7; p.S = f.S; p.kps = f.kps; p.nt = f.nt; p.mt = f.mt; p.KC = f.shape;
+    p.kind = 7;
+    p.f32 = plan_f32(M, N, K, s_cap, g_tune.force_s);
+    p.S = p.f32.S; p.kps = p.f32.kps; p.nt = p.f32.nt; p.mt = p.f32.mt;
     return p;
   }
-  const bool mfma_ok = dtype == 1 && operands_aligned && (K % 128 == 0) && (lda % 8 == 0);
-  if (!(mfma_ok && N % BN == 0 && N0 % BN == 0)) {
+  if (!gemm_ring_ok(dtype, operands_aligned, lda, K)) {
     p.kind = 1; p.S = 1; p.kps = K; p.nt = (N + 63) / 64; p.mt = (M + 63) / 64;
     return p;
   }
@@ -1192,18 +901,6 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     p.S = (K + p.kps - 1) / p.kps;
     return p;
   }
-  if (M >= g_tune.tile_min_m && M <= g_tune.tall_max_m && g_tune.tall_max_m >= 256) {
-    p.kind = 5;
-    p.KC = 128;
-    p.mt = (M + 255) / 256;
-    p.nt = N / BN;
-    int S = g_tune.force_s > 0 ? g_tune.force_s : (g_tune.target_wg + p.mt * p.nt - 1) / (p.mt * p.nt);
-    S = S < 1 ? 1 : (S > s_cap ? s_cap : S);
-    p.kps = ((K + S - 1) / S + p.KC - 1) / p.KC * p.KC;
-    if (p.kps > K) p.kps = K;
-    p.S = (K + p.kps - 1) / p.kps;
-    return p;
-  }
   if (M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0 && K % kFatK == 0) {
     p.kind = 4;
     p.mt = (M + kMidM - 1) / kMidM;
@@ -1223,16 +920,9 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     p.S = (K + p.kps - 1) / p.kps;
     return p;
   }
-  const bool rows128 = g_tune.tall_max_m >= 128 && M > 64 && NW == 8;
-  p.kind = rows128 ? 6 : 2;
-  p.KC = (K % 256 == 0) ? 256 : 128;
-  p.mt = rows128 ? (M + 127) / 128 : (M + 63) / 64;
-  p.nt = N / BN;
-  int S = g_tune.force_s > 0 ? g_tune.force_s : (g_tune.target_wg + p.mt * p.nt - 1) / (p.mt * p.nt);
-  S = S < 1 ? 1 : (S > s_cap ? s_cap : S);
-  p.kps = ((K + S - 1) / S + p.KC - 1) / p.KC * p.KC;
-  if (p.kps > K) p.kps = K;
-  p.S = (K + p.kps - 1) / p.kps;
+  p.kind = 2;
+  p.ring = plan_ring(M, N, K, s_cap, g_tune.force_s);
+  p.S = p.ring.S; p.kps = p.ring.kps; p.nt = p.ring.nt; p.mt = p.ring.mt;
   return p;
 }
 
@@ -1248,7 +938,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
   const bool al = aligned16(A) && aligned16(W0) && (W1 == nullptr || aligned16(W1));
   const GemmPlan p = plan_gemm(dtype, al, lda, M, N, N0, K, c_capacity);
   if (p.kind == 0 || static_cast<size_t>(p.S) * M * N > c_capacity) return 0;  // nothing launched
-  t_last_stream = p.kind == 2 || p.kind == 5 || p.kind == 6;
+  t_last_stream = p.kind == 2;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w0 = static_cast<const bf16_t*>(W0);
   const bf16_t* w1 = static_cast<const bf16_t*>(W1);
@@ -1264,9 +954,12 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                            static_cast<const float*>(W0), static_cast<const float*>(W1), N0, N, K,
                            c_part);
       break;
+    case 2:
+      launch_gemm_ring(p.ring, a, lda, rows, M, w0, w1, N0, N, K, c_part, st);
+      break;
     case 7:
-      launch_gemm_f32(F32Plan{p.KC, p.S, p.kps, p.nt, p.mt, 0.0}, static_cast<const float*>(A), lda, rows, M,
-                      static_cast<const float*>(W0), static_cast<const float*>(W1), N0, N, K, c_part, st);
+      launch_gemm_f32(p.f32, static_cast<const float*>(A), lda, rows, M, static_cast<const float*>(W0),
+                      static_cast<const float*>(W1), N0, N, K, c_part, st);
       break;
     case 3:
       hipLaunchKernelGGL(k_gemm_fat, grid, dim3(512), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps,
@@ -1276,28 +969,6 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
       hipLaunchKernelGGL(k_gemm_mid, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K,
                          p.kps, c_part);
       break;
-    case 6:
-      if (p.KC == 256)
-        launch_stream<8, 256, 0, 1, 8>(grid, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part, nullptr);
-      else
-        launch_stream<8, 128, 0, 1, 8>(grid, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part, nullptr);
-      break;
-    case 5:
-      if (g_tune.nw == 8)
-        launch_stream<8, 128, 0, 1, 16>(grid, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part, nullptr);
-      else
-        launch_stream<4, 128, 0, 1, 16>(grid, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part, nullptr);
-      break;
-    default: {
-#define DLLMC_GS(NWv, KCv) \
-  launch_stream<NWv, KCv, 0>(grid, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part, nullptr)
-      if (g_tune.nw == 8) {
-        if (p.KC == 256) DLLMC_GS(8, 256); else DLLMC_GS(8, 128);
-      } else {
-        if (p.KC == 256) DLLMC_GS(4, 256); else DLLMC_GS(4, 128);
-      }
-#undef DLLMC_GS
-    }
   }
   return p.S;
 }
@@ -1330,15 +1001,8 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
                                   static_cast<const float*>(w_gate), static_cast<const float*>(w_up), m, K,
                                   static_cast<float*>(u), st);
   }
-  // (phases of 128: the two register sets of gate and up pieces of a 256-wide phase do not fit
-  // beside the activation chunks)
-  const int KC = 128;
-  // two wavefront groups over the two halves of K when the halves are whole phases
-  const int KH = (g_tune.nw_dual >= 100 && K % (2 * KC) == 0) ? 2 : 1;
-  int NW = g_tune.nw_dual % 100;  // wavefronts per workgroup
-  if (KH == 1 && NW == 6) NW = 3;  // the two-group shape without the split: one group of its width
-  const int BN = 16 * NW / KH;
-  if (M >= g_tune.tile_min_m && stream_shape_ok(dtype, A, lda, w_gate, w_up, K) && K % kFatK == 0) {
+  if (!gemm_ring_ok(dtype, aligned16(A) && aligned16(w_gate) && aligned16(w_up), lda, K)) return false;
+  if (M >= g_tune.tile_min_m) {
     // many rows: the LDS-direct tile kernels with paired gate/up column blocks, one slice
     const bool fat = M >= g_tune.fat_min_m && m % (kFatN / 2) == 0;
     const bool tall = !fat && M <= 256 && m % 48 == 0;
@@ -1372,52 +1036,9 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
       return true;
     }
   }
-  if (!(stream_shape_ok(dtype, A, lda, w_gate, w_up, K) && m % 16 == 0) || M > 128) return false;
-  const bool rows128 = g_tune.tall_max_m >= 128 && M > 64 && NW == 6 && KH == 2 && K % 256 == 0;
-  dim3 grid((m + BN - 1) / BN, rows128 ? 1 : (M + 63) / 64, 1);
-  // More workgroups than CUs (one runs per CU at a time): rather than rounds of full tiles with
-  // a last round that leaves CUs idle (FFN width 18944: 395 tiles of 48 columns, 2 x 48 columns
-  // on the busiest CU), whole rounds of workgroups of which the first n_full own NWC blocks of
-  // 16 columns and the others NWC - 1 (512 workgroups, 160 of them with 3 blocks: 48 + 32
-  // columns; 91 -> 86 us).  128-wide phases, which let two such workgroups share a CU, measured
-  // slower (90 us).
-  int n_full = -1;
-  {
-    static const int cus = [] {
-      int dev = 0, n = 0;
-      if (hipGetDevice(&dev) != hipSuccess ||
-          hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-        n = 256;
-      return n;
-    }();
-    const int NWC = NW / KH, nblk = m / 16;
-    const int G = (static_cast<int>(grid.x) + cus - 1) / cus * cus;
-    if (grid.y == 1 && NWC >= 2 && static_cast<int>(grid.x) > cus &&
-        static_cast<long long>(G) * (NWC - 1) <= nblk) {
-      n_full = nblk - G * (NWC - 1);
-      grid.x = G;
-    }
-  }
   t_last_stream = true;
-  const bf16_t* a = static_cast<const bf16_t*>(A);
-  const bf16_t* w0 = static_cast<const bf16_t*>(w_gate);
-  const bf16_t* w1 = static_cast<const bf16_t*>(w_up);
-  bf16_t* uo = static_cast<bf16_t*>(u);
-#define DLLMC_GD(NWv, KCv, KHv) \
-  launch_stream<NWv, KCv, 1, KHv>(grid, st, a, lda, rows, M, w0, w1, m, m, K, K, nullptr, uo, n_full)
-  if (rows128) {
-    launch_stream<6, 128, 1, 2, 8>(grid, st, a, lda, rows, M, w0, w1, m, m, K, K, nullptr, uo, n_full);
-    return true;
-  }
-  switch (NW * 10 + KH) {
-    case 62: DLLMC_GD(6, 128, 2); break;
-    case 82: DLLMC_GD(8, 128, 2); break;
-    case 31: DLLMC_GD(3, 128, 1); break;
-    case 81: DLLMC_GD(8, 128, 1); break;
-    case 42: DLLMC_GD(4, 128, 2); break;
-    default: DLLMC_GD(4, 128, 1); break;
-  }
-#undef DLLMC_GD
+  launch_gemm_ring_swiglu(static_cast<const bf16_t*>(A), lda, rows, M, static_cast<const bf16_t*>(w_gate),
+                          static_cast<const bf16_t*>(w_up), m, K, static_cast<bf16_t*>(u), st);
   return true;
 }
 

@@ -1,0 +1,287 @@
+// Gathered linear maps of few rows (an adaptive step's recomputed rows) against a weight matrix that is
+// read once, bf16; also the general kernel for column counts that the 128 / 256-column tiles do not divide.
+//
+// k_gemm_ring<RB, NB, DUAL>: tile = 64 * RB rows x 16 * NB weight rows, one workgroup of eight wavefronts per
+// CU.  Both operands go from global memory straight into LDS (global_load_lds_dwordx4: an instruction
+// copies 8 rows x 128 bytes), through a ring of as many 64-wide stages as 150 KB hold: five to eight steps,
+// 60 to 90 KB of weights, are in flight per CU, never drained before the last steps.  Four wavefronts
+// take 16 * RB rows each for the first half of every step, the other four the same rows for its second half
+// (so that any number of column blocks deals evenly); their sums meet in LDS at the end.
+//   DUAL = 1: NB/2 blocks of W0 (gate) and the same blocks of W1 (up); the epilogue stores
+//             bf16(silu(gate) * up) to U[M, N].  One slice.
+//   otherwise columns [0, N0) come from W0, [N0, N) from W1, float32 partial sums of slice blockIdx.z go
+//             to C[z]; the row kernels add the slices in order (no float atomics: bit-reproducible).
+// Columns past N and rows past M repeat the last one and are dropped at the store: any M and N.
+//
+// Bound by the weight stream: launches take about 4 us + bytes / 5.5 TB/s.  Measured on weights that no cache holds, us, with the kernel
+// before (weight rows straight into the MFMA operand, 16 rows x 64 bytes per load instruction, which
+// a CU takes at half the rate of whole lines; activations through registers into LDS):
+//   64 rows:  4096 x 4096 10.9 -> 10.1 (and 4 slices instead of 8), 8192 x 4096 17.8 -> 16.3 (2 instead of 4),
+//             4096 x 12288 23.2 -> 23.1 (4 instead of 8), 3584 x 18944 33.8 -> 27.7,
+//             gate/up 2 x 12288 x 4096 43.9 -> 38.4, 2 x 18944 x 3584 71.7 -> 51.0
+//   128 rows: 4096 x 4096 14.8 -> 12.6, 8192 x 4096 22.3 -> 19.3, gate/up 59.4 -> 44.9 and 101 -> 59
+//   160 rows: 18.7 -> 15.3, 29.9 -> 23.9, 4096 x 12288 41.7 -> 30.4
+// From 192 rows the 128 x 128 tiles are level or ahead (256 rows: 16.9 / 27.2 / 39.3 us there, 17.4 / 26.8 /
+// 36.6 here; gate/up 62 there, 68 here).
+#include <type_traits>
+
+#include "common.hpp"
+
+namespace dllmc {
+
+namespace {
+
+// (The body is a function of its own, inlined: with the loads issued from the kernel itself the compiler
+// waits for every load in flight before each LDS read.)
+template <int RB, int NB, int DUAL>
+__device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int lda,
+                                               const int* __restrict__ rows, int M,
+                                               const bf16_t* __restrict__ W0,
+                                               const bf16_t* __restrict__ W1, int N0, int N, int K,
+                                               int k_per_slice, float* __restrict__ C,
+                                               bf16_t* __restrict__ U) {
+  constexpr int BM = 64 * RB;
+  constexpr int CB = DUAL ? NB / 2 : NB;               // column blocks of the output
+  constexpr int kStage = (BM + 16 * NB) * 8;           // 16-byte slots
+  constexpr int kFit = (150 * 1024) / (kStage * 16);
+  constexpr int NST = kFit > 8 ? 8 : kFit;
+  constexpr int LA = RB, LBT = 2 * NB;                 // activation loads per wavefront; weight loads of all
+  constexpr int LB0 = LBT / 8, LBR = LBT % 8;          // ... per wavefront, one more for the first LBR
+  __shared__ __attribute__((aligned(1024))) uint4 lds[NST][kStage];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int ln = lane % 16, lg = lane / 16;
+  const int wr = wave % 4, kk = wave / 4;
+  int col_tile, row_tile;
+  xcd_tile_map(col_tile, row_tile);
+  const int m0 = row_tile * BM, cb0 = col_tile * CB;
+  const int kbeg = blockIdx.z * k_per_slice;
+  const int klen = min(K, kbeg + k_per_slice) - kbeg;  // multiple of 64
+  const int nkt = klen / 64;
+
+  // loader: an instruction copies 8 rows x 128 bytes; lane l: row 8q + l/8, slot l%8, chunk (l%8) ^ (l/8)
+  const int chunk = (lane % 8) ^ (lane / 8);
+  const bf16_t* asrc[LA];
+  const bf16_t* bsrc[LB0 + 1];
+#pragma unroll
+  for (int j = 0; j < LA; ++j) {
+    const int m = min(m0 + 8 * (wave + 8 * j) + lane / 8, M - 1);
+    asrc[j] = A + static_cast<size_t>(rows ? rows[m] : m) * lda + kbeg + chunk * 8;
+  }
+#pragma unroll
+  for (int j = 0; j < LB0 + 1; ++j) {
+    const int r = min(8 * (wave + 8 * j), 16 * NB - 8) + lane / 8;  // weight row of the tile
+    const int n = min(cb0 * 16 + (DUAL ? r % (16 * CB) : r), N - 1);
+    const bf16_t* w;
+    if (DUAL) w = (r < 16 * CB ? W0 : W1) + static_cast<size_t>(n) * K;
+    else w = n < N0 ? W0 + static_cast<size_t>(n) * K : W1 + static_cast<size_t>(n - N0) * K;
+    bsrc[j] = w + kbeg + chunk * 8;
+  }
+  // Gate/up of up to 128 rows: the walk starts at a step that depends on the column tile and wraps around.  The
+  // workgroups run nearly in step and their rows are a multiple of 4 KB apart, so unrotated every load
+  // in flight has the same address bits below the row pitch (128 rows 47.6 -> 44.9 us).  The split launches
+  // walk different ranges side by side, and with them, as with more rows, the activation lines that
+  // the workgroups of an XCD share count for more (4096 x 12288 of 128 rows 26.8 us, rotated 30.5).
+  const int rot = DUAL && RB <= 2 ? col_tile % nkt : 0;
+  auto issue = [&](int stage, int kt) {
+    int k = kt + rot;
+    k = (k < nkt ? k : k - nkt) * 64;
+#pragma unroll
+    for (int j = 0; j < LA; ++j)
+      __builtin_amdgcn_global_load_lds(asrc[j] + k, &lds[stage][(wave + 8 * j) * 64], 16, 0, 0);
+#pragma unroll
+    for (int j = 0; j < LB0; ++j)
+      __builtin_amdgcn_global_load_lds(bsrc[j] + k, &lds[stage][BM * 8 + (wave + 8 * j) * 64], 16, 0, 0);
+    if (LBR > 0 && wave < LBR)
+      __builtin_amdgcn_global_load_lds(bsrc[LB0] + k, &lds[stage][BM * 8 + (wave + 8 * LB0) * 64], 16, 0, 0);
+  };
+  // at most `steps` steps of this wavefront's loads in flight, and its LDS reads complete
+  auto wait_steps = [&](auto steps) {
+    constexpr int S = decltype(steps)::value;
+    if (LBR > 0 && wave < LBR) wait_vmcnt_lds<S * (LA + LB0 + 1)>();
+    else wait_vmcnt_lds<S * (LA + LB0)>();
+  };
+
+  f32x4 acc[RB][NB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s)
+    if (s < nkt) issue(s, s);
+  int stage = 0;
+  for (int kt = 0; kt < nkt; ++kt) {
+    // the loads of step kt have landed; the younger steps, at most NST - 2, stay in flight
+    const int rem = nkt - 1 - kt;
+    if (rem >= NST - 2) wait_steps(std::integral_constant<int, NST - 2>{});
+    else if (NST > 7 && rem == 5) wait_steps(std::integral_constant<int, 5>{});
+    else if (NST > 6 && rem == 4) wait_steps(std::integral_constant<int, 4>{});
+    else if (NST > 5 && rem == 3) wait_steps(std::integral_constant<int, 3>{});
+    else if (NST > 4 && rem == 2) wait_steps(std::integral_constant<int, 2>{});
+    else if (NST > 3 && rem == 1) wait_steps(std::integral_constant<int, 1>{});
+    else wait_steps(std::integral_constant<int, 0>{});
+    // ... everybody's, and everybody has finished reading step kt - 1, whose stage is filled next
+    __builtin_amdgcn_s_barrier();
+    const int nxt = stage == 0 ? NST - 1 : stage - 1;
+    if (kt + NST - 1 < nkt) issue(nxt, kt + NST - 1);
+    const uint4* la = &lds[stage][0];
+    const uint4* lb = &lds[stage][BM * 8];
+    const int c = kk * 4 + lg;
+    bf16x8 af[RB], bf[NB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const int r = (wr * RB + i) * 16 + ln;
+      af[i] = __builtin_bit_cast(bf16x8, la[r * 8 + (c ^ (r % 8))]);
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int r = j * 16 + ln;
+      bf[j] = __builtin_bit_cast(bf16x8, lb[r * 8 + (c ^ (r % 8))]);
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+    stage = stage + 1 < NST ? stage + 1 : 0;
+  }
+  // the second halves' sums are handed over through LDS and added to the first's
+  __syncthreads();
+  f32x4* red = reinterpret_cast<f32x4*>(&lds[0][0]);
+  static_assert(4 * RB * NB * 64 * 16 <= NST * kStage * 16, "hand-over fits the ring");
+  if (kk == 1) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) red[((wr * RB + i) * NB + j) * 64 + lane] = acc[i][j];
+  }
+  __syncthreads();
+  if (kk == 1) return;
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] += red[((wr * RB + i) * NB + j) * 64 + lane];
+  float* Cs = DUAL ? nullptr : C + static_cast<size_t>(blockIdx.z) * M * N;
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = m0 + (wr * RB + i) * 16 + lg * 4 + e;
+      if (m >= M) continue;
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        const int n = (cb0 + j) * 16 + ln;
+        if (n >= N) continue;
+        if (DUAL) {
+          const float g = acc[i][j][e], up = acc[i][j + NB - CB][e];
+          U[static_cast<size_t>(m) * N + n] = f32_to_bf16(g / (1.0f + expf(-g)) * up);
+        } else {
+          Cs[static_cast<size_t>(m) * N + n] = acc[i][j][e];
+        }
+      }
+    }
+}
+
+template <int RB, int NB, int DUAL>
+__global__ __launch_bounds__(512) void k_gemm_ring(const bf16_t* __restrict__ A, int lda,
+                                                   const int* __restrict__ rows, int M,
+                                                   const bf16_t* __restrict__ W0,
+                                                   const bf16_t* __restrict__ W1, int N0, int N, int K,
+                                                   int k_per_slice, float* __restrict__ C,
+                                                   bf16_t* __restrict__ U) {
+  gemm_ring_body<RB, NB, DUAL>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C, U);
+}
+
+// Estimated time in us of a launch of `tiles` workgroups (one per CU at a time) of 64 * rb rows x 16 * nb
+// weight rows x k: the weights at the chip's stream rate, everything a CU takes in at ~40 GB/s (measured up
+// to 45), or the MFMAs (rb * nb per wavefront and step, two wavefronts per SIMD).
+double ring_time(long long tiles, int rb, int nb, int k) {
+  const double rounds = static_cast<double>((tiles + 255) / 256);
+  const double t_w = 16.0 * nb * k * 2.0 / 21.5e3;
+  const double t_in = (64.0 * rb + 16.0 * nb) * k * 2.0 / 40e3;
+  const double t_m = k / 64.0 * 2.0 * rb * nb * 16.0 / 2400.0;
+  double t = t_w > t_in ? t_w : t_in;
+  if (t_m > t) t = t_m;
+  return rounds * t;
+}
+
+}  // namespace
+
+bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K) {
+  return dtype == 1 && operands_aligned && K % 64 == 0 && lda % 8 == 0;
+}
+
+// Row blocks, column blocks and slices with the lowest estimate; a slice costs its partial sums twice
+// (written here, read by the row kernel) and 0.3 us there.
+RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s) {
+  RingPlan best{};
+  double best_t = 1e30;
+  for (int rb = 1; rb <= 3; ++rb)
+    for (int nb = 4; nb <= 8; nb += 4) {
+      const int mt = (M + 64 * rb - 1) / (64 * rb), nt = (N + 16 * nb - 1) / (16 * nb);
+      const int s_hi = force_s > 0 ? (force_s < s_cap ? force_s : s_cap) : s_cap;
+      for (int S = force_s > 0 ? s_hi : 1; S <= s_hi; ++S) {
+        int kps = ((K + S - 1) / S + 63) / 64 * 64;
+        if (kps > K) kps = K;
+        const int used = (K + kps - 1) / kps;
+        const double t = ring_time(static_cast<long long>(mt) * nt * used, rb, nb, kps) +
+                         used * (2.0 * M * N * 4.0 / 8e6 + 0.3);
+        if (t < best_t * 0.98) {
+          best_t = t;
+          best = RingPlan{rb, nb, used, kps, nt, mt};
+        }
+      }
+    }
+  return best;
+}
+
+void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
+                      const bf16_t* W1, int N0, int N, int K, float* C, hipStream_t st) {
+  const dim3 grid(p.nt, p.mt, p.S);
+#define DLLMC_R(RB, NB)                                                                               \
+  hipLaunchKernelGGL((k_gemm_ring<RB, NB, 0>), grid, dim3(512), 0, st, A, lda, rows, M, W0, W1, N0, N, K, \
+                     p.kps, C, nullptr)
+  switch (p.rb * 10 + p.nb) {
+    case 14: DLLMC_R(1, 4); break;
+    case 18: DLLMC_R(1, 8); break;
+    case 24: DLLMC_R(2, 4); break;
+    case 28: DLLMC_R(2, 8); break;
+    case 34: DLLMC_R(3, 4); break;
+    default: DLLMC_R(3, 8); break;
+  }
+#undef DLLMC_R
+}
+
+void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,
+                             const bf16_t* w_up, int m, int K, bf16_t* u, hipStream_t st) {
+  // Columns per workgroup: whole rounds over the CUs.  48 for an FFN width of 12288 (256 workgroups), 80 for
+  // 18944 (237: 51 us, 48 columns in two rounds 61), 16 for 3072.
+  int rb = 1, cb = 1;
+  double best_t = 1e30;
+  for (int r = 1; r <= 3; ++r)
+    for (int c = 1; c <= 5; ++c) {
+      const long long tiles = static_cast<long long>((M + 64 * r - 1) / (64 * r)) * ((m + 16 * c - 1) / (16 * c));
+      const double t = ring_time(tiles, r, 2 * c, K);
+      if (t < best_t * 0.98) { best_t = t; rb = r; cb = c; }
+    }
+  const dim3 grid((m + 16 * cb - 1) / (16 * cb), (M + 64 * rb - 1) / (64 * rb), 1);
+#define DLLMC_R(RB, CB)                                                                                 \
+  hipLaunchKernelGGL((k_gemm_ring<RB, 2 * CB, 1>), grid, dim3(512), 0, st, A, lda, rows, M, w_gate, w_up, m, m, \
+                     K, K, nullptr, u)
+#define DLLMC_RC(RB)                 \
+  switch (cb) {                      \
+    case 1: DLLMC_R(RB, 1); break;   \
+    case 2: DLLMC_R(RB, 2); break;   \
+    case 3: DLLMC_R(RB, 3); break;   \
+    case 4: DLLMC_R(RB, 4); break;   \
+    default: DLLMC_R(RB, 5); break;  \
+  }
+  if (rb == 1) { DLLMC_RC(1) }
+  else if (rb == 2) { DLLMC_RC(2) }
+  else { DLLMC_RC(3) }
+#undef DLLMC_RC
+#undef DLLMC_R
+}
+
+}  // namespace dllmc
