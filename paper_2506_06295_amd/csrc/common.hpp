@@ -257,9 +257,19 @@ struct RowKernelArgs {
   float eps;
 };
 
-// x[row] = hidden_in[row]; h[row] = T(rmsnorm(x[row]) * g) for row in rows[0..M)
-void launch_embed_norm(const RowKernelArgs& a, const void* hidden_in, const int* rows, int M,
-                       const void* gain, float* x, void* h, hipStream_t st);
+// Start of a step.  For the Mc carried rows (position first + i % per_seq of sequence i / per_seq):
+// x[row] = hidden_in[row]; h[row] = T(rmsnorm(x[row]) * gain); carried[i] = row; the entries of
+// rows_R / inv of the refreshed prompt rows (first == 0: compact index b * recomputed_per_seq + pos) and, with
+// refresh_response, of the response rows behind them; sel_idx != nullptr (response refresh):
+// sel_idx[l][b][j] = j.  prompt_out != nullptr: hidden_out[b][t] = prompt_out[b][t] for all prompt rows
+// (hidden_out may be hidden_in: then first == L_p and those rows are not read).
+struct PrologueArgs {
+  int B, Mc, first, per_seq, recomputed_per_seq, refresh_response, T;
+  int *carried, *rows_R, *inv, *sel_idx;
+};
+void launch_step_prologue(const RowKernelArgs& a, const PrologueArgs& pa, const void* hidden_in,
+                          const void* gain, float* x, void* h, const void* prompt_out, void* hidden_out,
+                          hipStream_t st);
 
 // V finalize: for i < M: row = (i / per_seq) * n + first + i % per_seq, the carried rows of a
 // step (row = i when per_seq == 0); v = T(sum_s c_part[s][i][:]);
@@ -314,10 +324,6 @@ void launch_down_finalize(const RowKernelArgs& a, const float* c_part, int S, in
                           void* ffn_cache, float* x, const void* next_gain, void* h,
                           void* hidden_out, void* prompt_out, hipStream_t st,
                           const int* rmap = nullptr);
-
-// hidden_out[b][t] = prompt_out[b][t] for all prompt rows
-void launch_copy_prompt(const RowKernelArgs& a, int B, const void* prompt_out, void* hidden_out,
-                        hipStream_t st);
 
 // Bottom-k selection per sequence.  scores: [B, L] float32.  Writes, for sequence b and the
 // pos-th selected index j (ascending):
@@ -374,7 +380,6 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
 // rows[ci] = row (if rows), inv[row] = ci (if inv).
 void launch_iota_rows(int* rows, int* inv, int B, int n, int first, int count, int per_seq,
                       int off, hipStream_t st);
-void launch_fill_i32(int* p, int value, size_t count, hipStream_t st);
 // ---- closed denoising loop (kernels_gen.hip) --------------------------------------------
 // out[r][:] = table[tokens[r]][:] for r < rows; table has vocab_rows rows of width d
 void launch_embed_gather(int dtype, const void* table, int vocab_rows, const int* tokens, int rows,
@@ -405,8 +410,5 @@ void launch_apply_tokens(int* tokens, int B, int n, int L_p, const int* chosen, 
 void launch_probe_copy(const void* src, void* dst, size_t bytes, hipStream_t st);
 void launch_probe_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t st);
 double launch_probe_mfma(int iters, int shape, float* sink, hipStream_t st);
-
-// sel[r][j] = j for r < rows, j < L_r
-void launch_fill_sel_identity(int* sel, int rows, int L_r, hipStream_t st);
 
 }  // namespace dllmc

@@ -420,19 +420,12 @@ int dllmc_step(dllmc_ctx* c, const void* hidden_in, int32_t step_idx, void* hidd
   auto gemm_bytes = [&](double M, double N, double K) { return (N * K + M * K) * esz + M * N * 4.0; };
   auto gemm_flops = [&](double M, double N, double K) { return 2.0 * M * N * K; };
 
-  // row lists of this step
   {
-    Timed t(c, DLLMC_KC_LISTS, 0, 0);
-    launch_iota_rows(carried, nullptr, B, n, P ? 0 : L_p, carried_per_seq, carried_per_seq, 0, st);
-    if (P) launch_iota_rows(rows_R, inv, B, n, 0, L_p, per_seq_of(0), 0, st);
-    if (Rf) {
-      launch_iota_rows(rows_R, inv, B, n, L_p, L_r, per_seq_of(0), sel_off, st);
-      if (sel_idx) launch_fill_sel_identity(sel_idx, T * B, L_r, st);
-    }
-  }
-  {
-    Timed t(c, DLLMC_KC_ROW, Mc * d * (2.0 * esz + 4.0), 0);
-    launch_embed_norm(ra, hidden_in, carried, Mc, c->layers[0].attn_norm_g, x, h, st);
+    // the stream and first norm of the carried rows, this step's row lists, and the prompt rows of the output
+    Timed t(c, DLLMC_KC_ROW, Mc * d * (2.0 * esz + 4.0) + (P ? 0.0 : 2.0 * B * L_p * d * esz), 0);
+    const PrologueArgs pa{B, Mc, P ? 0 : L_p, carried_per_seq, per_seq_of(0), Rf ? 1 : 0, T,
+                          carried, rows_R, inv, Rf ? sel_idx : nullptr};
+    launch_step_prologue(ra, pa, hidden_in, c->layers[0].attn_norm_g, x, h, P ? nullptr : prompt_out, hidden_out, st);
   }
 
   for (int l = 0; l < T; ++l) {
@@ -570,11 +563,6 @@ int dllmc_step(dllmc_ctx* c, const void* hidden_in, int32_t step_idx, void* hidd
                            (last && P) ? prompt_out : nullptr, st, rmap);
     }
   }
-  if (!P) {
-    Timed t(c, DLLMC_KC_LISTS, 2.0 * B * L_p * d * esz, 0);
-    launch_copy_prompt(ra, B, prompt_out, hidden_out, st);
-  }
-
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e);
   if (!Rf) c->have_scores = true;

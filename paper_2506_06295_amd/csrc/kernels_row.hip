@@ -7,6 +7,8 @@
 // All global accesses are 16-byte (or 8-byte for bf16) vectors when the row width allows it
 // (V = 4), issued for the whole row before the first use so that one memory round trip
 // covers a row; V = 1 is the fallback for widths that are not multiples of four.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace dllmc {
@@ -177,33 +179,77 @@ __device__ __forceinline__ void norm_store(const Vec<V> (&keep)[kRegVecs], const
   }
 }
 
-// ---- prologue: residual stream from the embedded tokens, first attention norm ----------
+// ---- prologue of a step, one launch: residual stream from the embedded tokens and first attention
+// norm of the carried rows, the row lists, the identity selection of a response refresh, and the
+// prompt rows of the output (every piece as a launch of its own took ~5 us: an adaptive step three, a
+// response refresh five) ------------------------------------------------------------------
+// Workgroups [0, Mc): carried row i = position first + i % per_seq of sequence i / per_seq.
+// Workgroups from Mc on: prompt row of hidden_out copied from the last prompt refresh.
 template <typename T, int V>
-__global__ __launch_bounds__(kThreads) void k_embed_norm(const T* __restrict__ hidden_in,
-                                                         const int* __restrict__ rows, int d,
-                                                         float eps, const T* __restrict__ gain,
-                                                         float* __restrict__ x, T* __restrict__ h) {
+__global__ __launch_bounds__(kThreads) void k_step_prologue(
+    const T* __restrict__ hidden_in, PrologueArgs a, int n, int L_p, int d, float eps,
+    const T* __restrict__ gain, float* __restrict__ x, T* __restrict__ h,
+    const T* __restrict__ prompt_out, T* __restrict__ hidden_out) {
   __shared__ float red[kNW];
-  const int row = rows[blockIdx.x];
+  const int i = blockIdx.x;
+  if (i >= a.Mc) {
+    const int r = i - a.Mc, b = r / L_p, t = r % L_p;
+    const T* s = prompt_out + (static_cast<size_t>(b) * L_p + t) * d;
+    T* o = hidden_out + (static_cast<size_t>(b) * n + t) * d;
+    if (V == 4) {  // 4 elements of T: 8 or 16 bytes
+      typedef typename std::conditional<sizeof(T) == 4, uint4, uint2>::type piece;
+      for (int c = threadIdx.x * 4; c < d; c += kThreads * 4)
+        *reinterpret_cast<piece*>(o + c) = *reinterpret_cast<const piece*>(s + c);
+    } else {
+      for (int c = threadIdx.x; c < d; c += kThreads) o[c] = s[c];
+    }
+    return;
+  }
+  const int b = i / a.per_seq, pos = a.first + i % a.per_seq;
+  const int row = b * n + pos;
+  if (threadIdx.x == 0) {
+    a.carried[i] = row;
+    // recomputed rows known before the selection: refreshed prompt rows, then the refreshed response rows
+    const bool prompt = pos < L_p;
+    if (prompt || a.refresh_response) {
+      const int ci = b * a.recomputed_per_seq + (a.first == 0 ? pos : pos - L_p);
+      a.rows_R[ci] = row;
+      a.inv[row] = ci;
+    }
+  }
+  if (a.sel_idx != nullptr && pos >= L_p) {  // response refresh: every response row is recomputed
+    const int L_r = n - L_p, j = pos - L_p;
+    for (int l = threadIdx.x; l < a.T; l += kThreads)
+      a.sel_idx[(static_cast<size_t>(l) * a.B + b) * L_r + j] = j;
+  }
   const T* src = hidden_in + static_cast<size_t>(row) * d;
   float* xr = x + static_cast<size_t>(row) * d;
   T* hr = h + static_cast<size_t>(row) * d;
-  float ss = 0.f;
-  for (int c = threadIdx.x * V; c < d; c += kThreads * V) {
-    const Vec<V> a = IO<T, V>::ld(src + c);
-    st_f32<V>(xr + c, a);
+  Vec<V> keep[kRegVecs], gk[kRegVecs];
 #pragma unroll
-    for (int e = 0; e < V; ++e) ss += a.v[e] * a.v[e];
+  for (int it = 0; it < kRegVecs; ++it) {
+    keep[it] = IO<T, V>::ld(src + chunk_col_clamped<V>(0, it, d));
+    gk[it] = IO<T, V>::ld(gain + chunk_col_clamped<V>(0, it, d));
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int it = 0; it < kRegVecs; ++it) {
+    const int c = chunk_col<V>(0, it);
+    if (c < d) {
+      st_f32<V>(xr + c, keep[it]);
+#pragma unroll
+      for (int e = 0; e < V; ++e) ss += keep[it].v[e] * keep[it].v[e];
+    }
+  }
+  for (int c = kChunk(V) + static_cast<int>(threadIdx.x) * V; c < d; c += kThreads * V) {
+    const Vec<V> v = IO<T, V>::ld(src + c);
+    st_f32<V>(xr + c, v);
+#pragma unroll
+    for (int e = 0; e < V; ++e) ss += v.v[e] * v.v[e];
   }
   ss = block_sum<kNW>(ss, red);
   const float rstd = 1.0f / sqrtf(ss / static_cast<float>(d) + eps);
-  for (int c = threadIdx.x * V; c < d; c += kThreads * V) {
-    Vec<V> a = ld_f32<V>(xr + c);  // this thread's own stores
-    const Vec<V> g = IO<T, V>::ld(gain + c);
-#pragma unroll
-    for (int e = 0; e < V; ++e) a.v[e] = a.v[e] * rstd * g.v[e];
-    IO<T, V>::st(hr + c, a);
-  }
+  norm_store<T, V>(keep, gk, xr, gain, rstd, d, hr, nullptr);
 }
 
 // ---- V-verify epilogue: round V_new, score it against the cached row (metric 0: cosine of
@@ -480,7 +526,8 @@ __global__ __launch_bounds__(kThreads) void k_down_finalize(
           xv[it].v[e] += f[it].v[e];
           ss += xv[it].v[e] * xv[it].v[e];
         }
-        st_f32<V>(xr + c, xv[it]);
+        // (the step's last layer: nothing reads the stream again, unless the row does not fit the registers)
+        if (next_gain != nullptr || d > kChunk(V)) st_f32<V>(xr + c, xv[it]);
         if (c0 == 0) keep[it] = xv[it];
       }
     }
@@ -520,16 +567,6 @@ __global__ __launch_bounds__(kThreads) void k_scatter_v(const int* __restrict__ 
   for (int c = threadIdx.x; c < d_kv; c += kThreads) dst[c] = src[c];
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_copy_prompt(const T* __restrict__ prompt_out, int n,
-                                                          int L_p, int d,
-                                                          T* __restrict__ hidden_out) {
-  const int b = blockIdx.y, t = blockIdx.x;
-  const T* s = prompt_out + (static_cast<size_t>(b) * L_p + t) * d;
-  T* o = hidden_out + (static_cast<size_t>(b) * n + t) * d;
-  for (int c = threadIdx.x; c < d; c += kThreads) o[c] = s[c];
-}
-
 // out[row][:] = cache[rmap[row]][:]: a cache tensor in logical row order
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_gather_rows(const T* __restrict__ cache,
@@ -550,16 +587,6 @@ __global__ void k_iota_rows(int* rows, int* inv, int n, int first, int count, in
   const int row = b * n + first + t;
   if (rows) rows[ci] = row;
   if (inv) inv[row] = ci;
-}
-
-__global__ void k_fill_i32(int* p, int value, size_t count) {
-  const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < count) p[i] = value;
-}
-
-__global__ void k_fill_sel_identity(int* sel, int L_r) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < L_r) sel[static_cast<size_t>(blockIdx.y) * L_r + j] = j;
 }
 
 template <typename T> inline T* P(void* p) { return static_cast<T*>(p); }
@@ -590,16 +617,19 @@ inline bool vec_ok(int width, std::initializer_list<const void*> ptrs) {
     else hipLaunchKernelGGL((KERNEL<T, 1>), grid, dim3(kThreads), 0, st, __VA_ARGS__);        \
   } while (0)
 
-void launch_embed_norm(const RowKernelArgs& a, const void* hidden_in, const int* rows, int M,
-                       const void* gain, float* x, void* h, hipStream_t st) {
-  if (M <= 0) return;
-  const bool vec = vec_ok(a.d, {hidden_in, gain, x, h});
+void launch_step_prologue(const RowKernelArgs& a, const PrologueArgs& pa, const void* hidden_in,
+                          const void* gain, float* x, void* h, const void* prompt_out, void* hidden_out,
+                          hipStream_t st) {
+  const int copies = prompt_out != nullptr ? pa.B * a.L_p : 0;
+  if (pa.Mc + copies <= 0) return;
+  const bool vec = vec_ok(a.d, {hidden_in, gain, x, h, prompt_out, hidden_out});
+  const dim3 grid(pa.Mc + copies);
   if (a.dtype == 1) {
-    DLLMC_ROW_LAUNCH(k_embed_norm, bf16_t, vec, dim3(M), st, P<bf16_t>(hidden_in), rows, a.d, a.eps,
-                     P<bf16_t>(gain), x, P<bf16_t>(h));
+    DLLMC_ROW_LAUNCH(k_step_prologue, bf16_t, vec, grid, st, P<bf16_t>(hidden_in), pa, a.n, a.L_p, a.d, a.eps,
+                     P<bf16_t>(gain), x, P<bf16_t>(h), P<bf16_t>(prompt_out), P<bf16_t>(hidden_out));
   } else {
-    DLLMC_ROW_LAUNCH(k_embed_norm, float, vec, dim3(M), st, P<float>(hidden_in), rows, a.d, a.eps,
-                     P<float>(gain), x, P<float>(h));
+    DLLMC_ROW_LAUNCH(k_step_prologue, float, vec, grid, st, P<float>(hidden_in), pa, a.n, a.L_p, a.d, a.eps,
+                     P<float>(gain), x, P<float>(h), P<float>(prompt_out), P<float>(hidden_out));
   }
 }
 
@@ -707,18 +737,6 @@ void launch_down_finalize(const RowKernelArgs& a, const float* c_part, int S, in
   }
 }
 
-void launch_copy_prompt(const RowKernelArgs& a, int B, const void* prompt_out, void* hidden_out,
-                        hipStream_t st) {
-  if (a.L_p <= 0 || B <= 0) return;
-  const dim3 grid(a.L_p, B);
-  if (a.dtype == 1)
-    hipLaunchKernelGGL(k_copy_prompt<bf16_t>, grid, dim3(kThreads), 0, st, P<bf16_t>(prompt_out),
-                       a.n, a.L_p, a.d, P<bf16_t>(hidden_out));
-  else
-    hipLaunchKernelGGL(k_copy_prompt<float>, grid, dim3(kThreads), 0, st, P<float>(prompt_out), a.n,
-                       a.L_p, a.d, P<float>(hidden_out));
-}
-
 void launch_gather_rows(int dtype, const void* cache, const int* rmap, int rows, int width,
                         void* out, hipStream_t st) {
   if (rows <= 0) return;
@@ -735,18 +753,6 @@ void launch_iota_rows(int* rows, int* inv, int B, int n, int first, int count, i
   if (count <= 0 || B <= 0) return;
   hipLaunchKernelGGL(k_iota_rows, dim3((count + 255) / 256, B), dim3(256), 0, st, rows, inv, n,
                      first, count, per_seq, off);
-}
-
-void launch_fill_i32(int* p, int value, size_t count, hipStream_t st) {
-  if (count == 0) return;
-  hipLaunchKernelGGL(k_fill_i32, dim3(static_cast<unsigned>((count + 255) / 256)), dim3(256), 0, st,
-                     p, value, count);
-}
-
-void launch_fill_sel_identity(int* sel, int layers_times_B, int L_r, hipStream_t st) {
-  if (layers_times_B <= 0 || L_r <= 0) return;
-  hipLaunchKernelGGL(k_fill_sel_identity, dim3((L_r + 255) / 256, layers_times_B), dim3(256), 0, st,
-                     sel, L_r);
 }
 
 }  // namespace dllmc
