@@ -14,12 +14,14 @@
 //                     keys of a 32-key block: exactly the B-operand layout of the second
 //                     product O^T = V^T * P^T, so probabilities never leave registers.
 //                     V tiles are transposed once per workgroup through LDS and shared by
-//                     its four 16-query wavefronts.  With few queries (adaptive steps) the
-//                     key range is split over workgroups and k_attn_merge combines the
-//                     partial results in key-range order.  k_attn_mfma handles key ranges of
-//                     up to three blocks (all of it fetched into registers before the first
-//                     use), k_attn_walk longer ones (K and V tiles staged global -> LDS
-//                     several blocks ahead).
+//                     its four 16-query wavefronts.  k_attn_mfma: key ranges of up to three
+//                     blocks (all of it fetched into registers before the first use), the
+//                     key range split over workgroups and the partial results combined in
+//                     key-range order by k_attn_merge; k_attn_walk: whole key ranges (K and V
+//                     tiles staged global -> LDS several blocks ahead).
+//  * k_attn_few    -- fewer than 128 queries where neither of those is the better one: the
+//                     wavefronts of a workgroup split its key range.
+//  * k_attn_tile   -- from 128 queries on.
 #include "common.hpp"
 
 namespace dllmc {
@@ -996,6 +998,301 @@ __global__ __launch_bounds__(256, 2) void k_attn_tile(const bf16_t* __restrict__
   attn_tile_body<PAGED>(q, Mq, kc, vc, n, H_q, H_kv, KS, out, part, rmap);
 }
 
+// ---- few queries ---------------------------------------------------------------------
+// k_attn_few<QB>: fewer than 128 queries per sequence (adaptive steps).  A workgroup is 16 * QB queries of one head
+// against a range of keys; each of its four wavefronts walks every fourth 32-key block of the range
+// by itself -- K and V tile from global memory straight into a two-stage ring in its own part of the
+// LDS, no barrier anywhere in the walk -- and carries all the workgroup's queries, so that every fragment it
+// reads feeds QB products.  The wavefronts' (O, m, l) meet in LDS.  V fragments come out of the
+// row-major tile with transposing reads, as in k_attn_tile (32 keys here).
+template <int QB, bool PAGED>
+__device__ __forceinline__ void attn_few_body(const bf16_t* __restrict__ q, int Mq,
+                                              const bf16_t* __restrict__ kc,
+                                              const bf16_t* __restrict__ vc, int n, int H_q,
+                                              int H_kv, int KS, bf16_t* __restrict__ out,
+                                              float* __restrict__ part,
+                                              const int* __restrict__ rmap) {
+  constexpr int QT = 16 * QB;
+  constexpr int kTile = 32 * 16;                  // 16-byte slots of a 32-key tile
+  constexpr int kWaveVecs = 2 * 2 * kTile;        // [stage][K tile, V tile]
+  constexpr int kOS = kDH + 4;                    // float32 row of the hand-over
+  // Queries through LDS as well, a copy per wavefront (four do not fit): with them loaded into registers the
+  // compiler waits for everything in flight, both blocks of the ring, in front of the first product.
+  constexpr bool kQLds = QB <= 2;
+  constexpr int kQVecs = kQLds ? QT * 16 : 0;
+  constexpr int kRing = 4 * (kWaveVecs + kQVecs);
+  constexpr int kHand = (4 * QT * kOS + 8 * QT) / 4;
+  __shared__ __attribute__((aligned(1024))) uint4 smem[kRing > kHand ? kRing : kHand];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;  // scalar
+  const int ln = lane % 16, lg = lane / 16;
+  const AttnWork wk = attn_work_tile((Mq + QT - 1) / QT, H_q, H_kv, KS);
+  const int a = wk.a, b = wk.b, ks = wk.ks;
+  const int d_q = H_q * kDH, d_kv = H_kv * kDH;
+  const int kv = a / (H_q / H_kv);
+  const int i0 = wk.qtile * QT;
+  const bf16_t* K = kc + kv * kDH;
+  const bf16_t* V = vc + kv * kDH;
+  const int seq0 = b * n;
+  uint4* ring = smem + wave * (kWaveVecs + kQVecs);
+
+  const int nblk = (n + 31) / 32;
+  const int per = (nblk + KS - 1) / KS;
+  const int blk0 = ks * per;
+  const int blk1 = min(nblk, blk0 + per);
+  const int nb = (blk1 - blk0 - wave + 3) / 4;    // blocks blk0 + wave, + 4, ... of this wavefront
+
+  // loader: a tile is 8 instructions of 4 keys x 256 bytes; lane l: key 4j + l/16, slot l%16, chunk
+  // slot ^ (key % 16)
+  int chunk[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) chunk[j] = ((lane % 16) ^ (4 * j + lane / 16)) * 8;
+  // block i of this wavefront; blocks past its last one repeat that (never used: the number of loads in
+  // flight stays the same in every iteration)
+  auto key0_of = [&](int i) { return (blk0 + wave + 4 * min(i, nb - 1)) * 32; };
+  auto rows_of = [&](int i, int (&cr)[8]) {
+    const int key0 = key0_of(i);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int kr = seq0 + min(key0 + 4 * j + lane / 16, n - 1);  // keys past the end are masked in the scores
+      cr[j] = PAGED ? rmap[kr] : kr;
+    }
+  };
+  auto issue = [&](const bf16_t* T, const int (&cr)[8], uint4* tile) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      __builtin_amdgcn_global_load_lds(T + static_cast<size_t>(cr[j]) * d_kv + chunk[j % 4], tile + j * 64, 16, 0, 0);
+  };
+
+  // Q fragments: lane (query ln, group lg) holds dims 32c + 8lg .. +8 (padded queries compute a duplicate
+  // that is never stored)
+  bf16x8 qf[QB][4];
+  uint4* qtile = ring + kWaveVecs;
+  if (kQLds) {
+#pragma unroll
+    for (int j = 0; j < 4 * QB; ++j) {
+      const int qi = min(i0 + 4 * j + lane / 16, Mq - 1);
+      __builtin_amdgcn_global_load_lds(q + (static_cast<size_t>(b) * Mq + qi) * d_q + a * kDH + chunk[j % 4],
+                                       qtile + j * 64, 16, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const int qi = min(i0 + qb * 16 + ln, Mq - 1);
+      const bf16_t* qr = q + (static_cast<size_t>(b) * Mq + qi) * d_q + a * kDH + lg * 8;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) qf[qb][c] = *reinterpret_cast<const bf16x8*>(qr + c * 32);
+    }
+  }
+  const float sl2e = 1.4426950408889634f / sqrtf(static_cast<float>(kDH));  // scale * log2(e)
+  float m_run[QB], l_run[QB];
+  f32x4 o_acc[QB][8];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    m_run[qb] = -INFINITY;
+    l_run[qb] = 0.f;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) o_acc[qb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // transposing reads (see k_attn_tile): byte offset inside a V tile for dim block db, sub-block 0
+  const int krow = 4 * lg + ln / 4;
+  int voff[8];
+#pragma unroll
+  for (int db = 0; db < 8; ++db)
+    voff[db] = (krow * 16 + ((2 * db + (ln % 4) / 2) ^ krow)) * 16 + (ln % 2) * 8;
+
+  if (nb > 0) {
+    int cr[8];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      rows_of(s, cr);
+      issue(K, cr, ring + s * 2 * kTile);
+      issue(V, cr, ring + s * 2 * kTile + kTile);
+    }
+    rows_of(2, cr);
+    if (kQLds) {
+      wait_vmcnt<32 + (PAGED ? 8 : 0)>();  // the queries
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          qf[qb][c] = __builtin_bit_cast(bf16x8, qtile[(qb * 16 + ln) * 16 + ((4 * c + lg) ^ ln)]);
+    }
+    for (int i = 0; i < nb; ++i) {
+      // block i has landed: block i + 1 (16 loads), and in the paged layout the lookups for block i + 2,
+      // may be in flight
+      wait_vmcnt<16 + (PAGED ? 8 : 0)>();
+      __builtin_amdgcn_sched_barrier(0);
+      uint4* kt = ring + (i & 1) * 2 * kTile;
+      const char* vt = reinterpret_cast<const char*>(kt + kTile);
+      const int key0 = (blk0 + wave + 4 * i) * 32;
+      f32x4 st[2][QB];
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        bf16x8 kf[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          kf[c] = __builtin_bit_cast(bf16x8, kt[(sb * 16 + ln) * 16 + ((4 * c + lg) ^ ln)]);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[c], qf[qb][c], acc, 0, 0, 0);
+          st[sb][qb] = acc;
+        }
+      }
+      if (key0 + 32 > n) {  // wavefront-uniform: the block sticks out of the sequence
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (key0 + sb * 16 + 4 * lg + e >= n) {
+#pragma unroll
+              for (int qb = 0; qb < QB; ++qb) st[sb][qb][e] = -INFINITY;
+            }
+      }
+      // running softmax (base 2); the reference point follows the maximum lazily (see k_attn_tile)
+      float m_use[QB], m_new[QB];
+      bool moved = false;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) mx = fmaxf(mx, st[sb][qb][e]);
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float mb = mx * sl2e;
+        m_new[qb] = mb > m_run[qb] + kLazy ? mb : m_run[qb];
+        m_use[qb] = m_new[qb] == -INFINITY ? 0.f : m_new[qb];
+        moved |= m_new[qb] != m_run[qb];
+      }
+      if (__builtin_amdgcn_ballot_w64(moved) != 0) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_use[qb]);
+          l_run[qb] *= alpha;
+          m_run[qb] = m_new[qb];
+#pragma unroll
+          for (int db = 0; db < 8; ++db) o_acc[qb][db] *= alpha;
+        }
+      }
+      // probabilities as a bf16 pair (high part + remainder), in the second product's operand layout
+      bf16x8 pf[QB], pl[QB];
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int e = 0; e < 4; e += 2) {
+            const float e0 = __builtin_amdgcn_exp2f(fmaf(st[sb][qb][e], sl2e, -m_use[qb]));
+            const float e1 = __builtin_amdgcn_exp2f(fmaf(st[sb][qb][e + 1], sl2e, -m_use[qb]));
+            l_run[qb] += e0;
+            l_run[qb] += e1;
+            const uint32_t hi = pack_bf16x2(e0, e1);
+            reinterpret_cast<uint32_t*>(&pf[qb])[sb * 2 + e / 2] = hi;
+            reinterpret_cast<uint32_t*>(&pl[qb])[sb * 2 + e / 2] =
+                pack_bf16x2(e0 - __uint_as_float(hi << 16), e1 - __uint_as_float(hi & 0xffff0000u));
+          }
+#pragma unroll
+      for (int db = 0; db < 8; ++db) {
+        typedef v4i16_t __attribute__((address_space(3))) * lds_v4;
+        typedef short v8i16_t __attribute__((ext_vector_type(8)));
+        const v4i16_t r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(vt + voff[db]));
+        const v4i16_t r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(vt + voff[db] + 4096));
+        const v8i16_t both = {r0[0], r0[1], r0[2], r0[3], r1[0], r1[1], r1[2], r1[3]};
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, both);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          o_acc[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qb], o_acc[qb][db], 0, 0, 0);
+          o_acc[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl[qb], o_acc[qb][db], 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // this wavefront's reads of the stage are complete: block i + 2 takes it.  (The lookups of the block after
+      // go out first: they are then older than these loads, and waiting for them leaves those in flight.)
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      const int now[8] = {cr[0], cr[1], cr[2], cr[3], cr[4], cr[5], cr[6], cr[7]};
+      rows_of(i + 3, cr);
+      issue(K, now, kt);
+      issue(V, now, kt + kTile);
+    }
+  }
+  wait_vmcnt<0>();  // the repeated loads past the range, before the ring is overwritten
+  __syncthreads();
+  float* hand = reinterpret_cast<float*>(smem);                 // [wavefront][query][kOS]
+  float* ml = hand + 4 * QT * kOS;                              // [wavefront][query] m, then l
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    l_run[qb] += __shfl_xor(l_run[qb], 16, 64);
+    l_run[qb] += __shfl_xor(l_run[qb], 32, 64);
+#pragma unroll
+    for (int db = 0; db < 8; ++db)
+      *reinterpret_cast<f32x4*>(&hand[(wave * QT + qb * 16 + ln) * kOS + db * 16 + 4 * lg]) = o_acc[qb][db];
+    if (lg == 0) {
+      ml[wave * QT + qb * 16 + ln] = m_run[qb];
+      ml[4 * QT + wave * QT + qb * 16 + ln] = l_run[qb];
+    }
+  }
+  __syncthreads();
+  // 16 threads per query, eight dims each; the wavefronts' parts in order
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const int ql = qb * 16 + threadIdx.x / 16, t8 = (threadIdx.x % 16) * 8;
+    const int iq = i0 + ql;
+    if (iq >= Mq) continue;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, ml[w * QT + ql]);
+    float L = 0.f, o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float mw = ml[w * QT + ql];
+      const float f = mw == -INFINITY ? 0.f : exp2f(mw - M);
+      L += ml[4 * QT + w * QT + ql] * f;
+      const float* ow = &hand[(w * QT + ql) * kOS + t8];
+      const f32x4 x0 = *reinterpret_cast<const f32x4*>(ow), x1 = *reinterpret_cast<const f32x4*>(ow + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[e] += x0[e] * f;
+        o[4 + e] += x1[e] * f;
+      }
+    }
+    if (KS == 1) {
+      const float inv = 1.0f / L;
+      uint4 u;
+      u.x = pack_bf16x2(o[0] * inv, o[1] * inv);
+      u.y = pack_bf16x2(o[2] * inv, o[3] * inv);
+      u.z = pack_bf16x2(o[4] * inv, o[5] * inv);
+      u.w = pack_bf16x2(o[6] * inv, o[7] * inv);
+      *reinterpret_cast<uint4*>(out + (static_cast<size_t>(b) * Mq + iq) * d_q + a * kDH + t8) = u;
+    } else {
+      float* w = part + ((static_cast<size_t>(b) * Mq + iq) * H_q + a) * KS * (kDH + 2) +
+                 static_cast<size_t>(ks) * (kDH + 2);
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) *reinterpret_cast<float2*>(w + t8 + e) = make_float2(o[e], o[e + 1]);
+      if (t8 == 0) {
+        w[kDH] = M;
+        w[kDH + 1] = L;
+      }
+    }
+  }
+}
+
+template <int QB, bool PAGED>
+__global__ __launch_bounds__(256, QB <= 2 ? 2 : 1) void k_attn_few(const bf16_t* __restrict__ q, int Mq,
+                                                     const bf16_t* __restrict__ kc,
+                                                     const bf16_t* __restrict__ vc, int n, int H_q,
+                                                     int H_kv, int KS, bf16_t* __restrict__ out,
+                                                     float* __restrict__ part,
+                                                     const int* __restrict__ rmap) {
+  attn_few_body<QB, PAGED>(q, Mq, kc, vc, n, H_q, H_kv, KS, out, part, rmap);
+}
+
 // out[query][head][:] = sum_r O_r 2^(m_r - M) / sum_r l_r 2^(m_r - M), in key-range order.
 // One wavefront per (query, head), two dims per lane.
 template <int SLOTS>
@@ -1033,8 +1330,8 @@ __global__ __launch_bounds__(64) void k_attn_merge(const float* __restrict__ par
 
 }  // namespace
 
-// Keys are split only while (workgroups without split) * KS stays below 1024, and a workgroup
-// covers kQT (query, head) pairs per key range, so this bounds the partial results.
+// Keys are split only while (workgroups without split) * KS stays within 256 (k_attn_tile: 128 queries per
+// workgroup; the others 64 or fewer), so this bounds the partial results.
 size_t attention_scratch_floats() { return static_cast<size_t>(kQT) * 1024 * (kDH + 2); }
 
 bool attention_supported(int dtype, int d_h, int n) {
@@ -1073,27 +1370,57 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
         hipLaunchKernelGGL(k_attn_merge<8>, dim3(B * Mq * H_q), dim3(64), 0, st, scratch, KS, oo);
       return;
     }
-    const int qt = (Mq + kQT - 1) / kQT;
-    const int base = B * qt * H_q;  // workgroups without splitting the keys
+    // Fewer than 128 queries.  Three kernels, by estimated time in us (constants fitted to the launches below,
+    // on keys and values that no cache holds):
+    //   few<QB>, KS ranges   4.5, one workgroup per CU, 1.35 / 1.6 / 2.4 per 32-key block of a wavefront's walk at
+    //                        QB = 1 / 2 / 4, and 4.5 plus the partial results' traffic for a merge launch
+    //   walk, whole ranges   4.5, 64 queries per workgroup and four wavefronts on the same block: 1.02 per block,
+    //                        1.6 for two workgroups that share a CU
+    //   mfma                 ranges of three blocks, everything fetched at once: 8.3 with its merge launch, 3.5 more
+    //                        by the time it fills the CUs; beyond that it takes 20 (two workgroups per CU)
+    // Measured (B, queries, keys, heads / KV heads; before: mfma or walk with up to 512 workgroups -> now):
+    //   2, 60, 700, 32 18.4 -> 12.9;  4, 30, 600, 28/4 20.6 -> 10.0;  1, 127, 768, 32 20.7 -> 12.9 (few<1>);
+    //   1, 62, 1254, 28/4 20.2 -> 13.8;  1, 51, 4608, 32 29.1 -> 25.7;  1, 20, 4096, 28/4 20.1 -> 14.7 (few<2>, 4
+    //   to 8 ranges);  4, 100, 4000, 32 135 -> 82 (few<4>);  1, 64, 768, 32 11.8 with mfma, 13.3 with few<1>;
+    //   16, 64, 768, 32 44.7 with walk, 52 with few<4>.
     const int nblk = (n + 31) / 32;
-    int KS = 1;
-    // keys are split only while the queries alone leave CUs without a workgroup (384 workgroups of
-    // a 768-row refresh: 54 us split in two with a merge launch, 45 us whole)
-    if (scratch != nullptr && base < 256) {
-      KS = (512 + base - 1) / base;  // aim for ~512 workgroups
-      if (KS > kMaxKeySplit) KS = kMaxKeySplit;
-      // ranges of three blocks are fetched whole in one trip; shorter ones only add partial
-      // results to merge
-      if (KS > (nblk + 2) / 3) KS = (nblk + 2) / 3;
+    const double kv_us = 2.0 * B * n * H_kv * kDH * 2.0 / 1e6;  // MB of keys and values
+    int QB = 0, KS = 1;  // QB 0: walk
+    const int base = B * ((Mq + kQT - 1) / kQT) * H_q;
+    double best = 4.5 + nblk * (base <= 256 ? 1.02 : 1.6 * ((base + 511) / 512));
+    for (int qb = 1; qb <= 4; qb *= 2) {
+      const int tiles = B * ((Mq + 16 * qb - 1) / (16 * qb)) * H_q;
+      for (int s = 1; s <= kMaxKeySplit; s *= 2) {
+        if (s > 1 && (scratch == nullptr || tiles * s > 256 || 2 * s > nblk)) break;
+        const int blocks = ((nblk + s - 1) / s + 3) / 4;
+        double t = (tiles * s + 255) / 256 * blocks * (qb == 1 ? 1.35 : qb == 2 ? 1.6 : 2.4) + (qb == 4 ? 2.5 : 0.0);
+        if (t < kv_us / 4.0) t = kv_us / 4.0;
+        t += 4.5;
+        if (s > 1) t += 4.5 + static_cast<double>(B) * Mq * H_q * s * (kDH + 2) * 4.0 * 2.0 / 5e6;
+        if (t < best * 0.98) { best = t; QB = qb; KS = s; }
+      }
     }
-    const dim3 grid(qt * H_q * B * KS);
-    const bool whole = (nblk + KS - 1) / KS <= kPreload;
-#define DLLMC_ATTN(KERNEL) \
-  hipLaunchKernelGGL(KERNEL, grid, dim3(256), 0, st, qq, Mq, kk, vv, n, H_q, H_kv, KS, oo, scratch, rmap)
-    if (whole && rmap) DLLMC_ATTN(k_attn_mfma<true>);
-    else if (whole) DLLMC_ATTN(k_attn_mfma<false>);
-    else if (rmap) DLLMC_ATTN(k_attn_walk<true>);
-    else DLLMC_ATTN(k_attn_walk<false>);
+    const int ks3 = (nblk + kPreload - 1) / kPreload;
+    if (scratch != nullptr && ks3 >= 2 && ks3 <= kMaxKeySplit && base * ks3 <= 256 &&
+        8.3 + 3.5 * base * ks3 / 256.0 < best) {
+      QB = -1;
+      KS = ks3;
+    }
+#define DLLMC_ATTN(KERNEL, GRID) \
+  hipLaunchKernelGGL(KERNEL, dim3(GRID), dim3(256), 0, st, qq, Mq, kk, vv, n, H_q, H_kv, KS, oo, scratch, rmap)
+#define DLLMC_ATTN_FEW(Q)                                                                        \
+  do {                                                                                           \
+    const int grid_ = B * ((Mq + 16 * Q - 1) / (16 * Q)) * H_q * KS;                              \
+    if (rmap) DLLMC_ATTN((k_attn_few<Q, true>), grid_); else DLLMC_ATTN((k_attn_few<Q, false>), grid_); \
+  } while (0)
+    switch (QB) {
+      case -1: if (rmap) DLLMC_ATTN(k_attn_mfma<true>, base * KS); else DLLMC_ATTN(k_attn_mfma<false>, base * KS); break;
+      case 0: if (rmap) DLLMC_ATTN(k_attn_walk<true>, base); else DLLMC_ATTN(k_attn_walk<false>, base); break;
+      case 1: DLLMC_ATTN_FEW(1); break;
+      case 2: DLLMC_ATTN_FEW(2); break;
+      default: DLLMC_ATTN_FEW(4); break;
+    }
+#undef DLLMC_ATTN_FEW
 #undef DLLMC_ATTN
     if (KS > 8)
       hipLaunchKernelGGL(k_attn_merge<kMaxKeySplit>, dim3(B * Mq * H_q), dim3(64), 0, st, scratch, KS,
