@@ -10,8 +10,8 @@
 //                      operands both go through LDS by direct global->LDS loads, for
 //                      launches with hundreds of activation rows; the same body with paired
 //                      gate/up column blocks and SwiGLU in the epilogue (k_gemm_*_swiglu,
-//                      k_gemm_tall_swiglu: 256 x 96 for up to 256 rows), and with the head's reduction
-//                      (k_gemm_mid_head).
+//                      k_gemm_tall_swiglu: 256 x 96 for up to 256 rows), with the head's reduction
+//                      (k_gemm_mid_head), and with 192-row tiles (k_gemm_r192_*).
 #include <mutex>
 #include <type_traits>
 
@@ -205,7 +205,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // with 16 KB slots measured 3-8 % slower there).  One workgroup per CU (256-row tiles): five
   // slots of one operand block each (all 160 KB of the CU), one barrier per step, see the main
   // loop.
-  constexpr bool ONE_BARRIER = BM == 256;
+  constexpr bool ONE_BARRIER = BM >= 192;
   constexpr int kSlot = (BM > BN ? BM : BN) * 8;
   constexpr int kLdsTotal = ONE_BARRIER ? 5 * kSlot : 2 * kStage + (EPI == 1 || EPI == 2 ? 2 * BM / 4 : 0);
   static_assert(kLdsTotal * sizeof(uint4) <= 160 * 1024, "LDS of one CU");
@@ -324,11 +324,11 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     // without this they all read fragments at the same time and then all multiply, and the
     // matrix pipes idle for an LDS round trip in front of every group of MFMAs.  The barrier
     // sits in front of the step's last unit.
-    constexpr int AG = 4;            // activation fragments per unit
+    constexpr int AG = MI % 4 == 0 ? 4 : MI;  // activation fragments per unit
     constexpr int UH = MI / AG;      // units per 32 contraction values
     constexpr int NU = 2 * UH;       // units per step
     constexpr int NL = LA + LB;      // loads per wavefront and step: B(kt+2) first, then A(kt+3)
-    static_assert(MI % AG == 0, "units of four activation blocks");
+    static_assert(MI % AG == 0, "whole units");
     auto issue_a = [&](int slot, int kt, int j0, int j1) {
       const int ko = kof(kt);
 #pragma unroll
@@ -788,6 +788,30 @@ __global__ __launch_bounds__(256) void k_gemm_tall_swiglu(const bf16_t* __restri
   gemm_lds_body<4, 1, 4, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 
+// 192-row tiles (five slots of 24 KB): the row count that makes whole rounds of workgroups where 256 rows do not
+// (768 rows: four tiles instead of three; see launch_gemm_swiglu and direct_tile_kind for what they measured).
+// For the float32 slices of the output and down projections they gained nothing: 768 rows in two slices 59
+// us against 56, 8 us less in the two row kernels.
+__global__ __launch_bounds__(512) void k_gemm_r192_swiglu(const bf16_t* __restrict__ A, int lda,
+                                                          const int* __restrict__ rows, int M,
+                                                          const bf16_t* __restrict__ Wg,
+                                                          const bf16_t* __restrict__ Wu, int N, int K,
+                                                          bf16_t* __restrict__ U) {
+  gemm_lds_body<4, 2, 3, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
+}
+__global__ __launch_bounds__(256) void k_gemm_r192_vverify(const bf16_t* __restrict__ A, int lda, int M,
+                                                           const bf16_t* __restrict__ W, int N, int K,
+                                                           TileEpilogue ep) {
+  gemm_lds_body<4, 1, 3, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
+}
+__global__ __launch_bounds__(512) void k_gemm_r192_qk(const bf16_t* __restrict__ A, int lda,
+                                                      const int* __restrict__ rows, int M,
+                                                      const bf16_t* __restrict__ W0,
+                                                      const bf16_t* __restrict__ W1, int N0, int N, int K,
+                                                      TileEpilogue ep) {
+  gemm_lds_body<4, 2, 3, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
+}
+
 __global__ __launch_bounds__(256) void k_reduce_slices(const float* __restrict__ c_part, int S,
                                                        size_t MN, float* __restrict__ out) {
   const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -1003,36 +1027,38 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   }
   if (!gemm_ring_ok(dtype, aligned16(A) && aligned16(w_gate) && aligned16(w_up), lda, K)) return false;
   if (M >= g_tune.tile_min_m) {
-    // many rows: the LDS-direct tile kernels with paired gate/up column blocks, one slice
-    const bool fat = M >= g_tune.fat_min_m && m % (kFatN / 2) == 0;
-    const bool tall = !fat && M <= 256 && m % 48 == 0;
-    if (fat || tall || m % (kMidN / 2) == 0) {
+    // Many rows: the LDS-direct tile kernels with paired gate/up column blocks, one slice; the tile shape whose
+    // rounds over the 256 CUs take least.  Measured us per round and 64-wide step: 256 x (128 + 128) 1.65,
+    // 256 x (96 + 96) 1.41, 192 x (96 + 96) 1.25, one workgroup per CU each; 128 x (64 + 64) 1.16 with two per CU,
+    // 0.78 with one; 256 x (48 + 48) 0.95.  At FFN width 12288: 4608 rows 7 x 1.65 (9 x 1.41, 12 x 1.25), 1024
+    // rows 2 x 1.41, 768 rows 2 x 1.25 (184 -> 160 us against 2 x 1.41), 384 rows 1 x 1.25 (2 x 1.16).
+    struct Tile { int rows, cols, per_cu; double t; };
+    const Tile tiles[5] = {{256, 128, 1, 1.65}, {256, 96, 1, 1.41}, {192, 96, 1, 1.25}, {128, 64, 2, 1.16}, {256, 48, 1, 0.95}};
+    int pick = -1;
+    double best = 1e30;
+    for (int i = 0; i < 5; ++i) {
+      if (m % tiles[i].cols || (i == 0 && M < g_tune.fat_min_m) || (i == 4 && M > 256)) continue;
+      const long long n = static_cast<long long>((M + tiles[i].rows - 1) / tiles[i].rows) * (m / tiles[i].cols);
+      const int slots = 256 * tiles[i].per_cu;
+      const double t = (i == 3 && n <= 256) ? 0.78 : static_cast<double>((n + slots - 1) / slots) * tiles[i].t;
+      if (t < best) { best = t; pick = i; }
+    }
+    if (pick >= 0) {
       t_last_stream = false;
       const bf16_t* a = static_cast<const bf16_t*>(A);
       const bf16_t* w0 = static_cast<const bf16_t*>(w_gate);
       const bf16_t* w1 = static_cast<const bf16_t*>(w_up);
       bf16_t* uo = static_cast<bf16_t*>(u);
-      // 96-column tiles when their rounds over the CUs finish sooner (a tile's time goes with its
-      // columns; the narrower tile pulls a few per cent more operand bytes per flop)
-      bool fat96 = false;
-      if (fat && m % 96 == 0) {
-        const int mt = (M + kFatM - 1) / kFatM, cus = 256;
-        const double c128 = static_cast<double>((mt * (m / 128) + cus - 1) / cus) * 128.0;
-        const double c96 = static_cast<double>((mt * (m / 96) + cus - 1) / cus) * 96.0 * 1.05;
-        fat96 = c96 < c128;
+      const dim3 grid(m / tiles[pick].cols, (M + tiles[pick].rows - 1) / tiles[pick].rows, 1);
+#define DLLMC_SW(KERNEL, NT) hipLaunchKernelGGL(KERNEL, grid, dim3(NT), 0, st, a, lda, rows, M, w0, w1, m, K, uo)
+      switch (pick) {
+        case 0: DLLMC_SW(k_gemm_fat_swiglu, 512); break;
+        case 1: DLLMC_SW(k_gemm_fat96_swiglu, 512); break;
+        case 2: DLLMC_SW(k_gemm_r192_swiglu, 512); break;
+        case 3: DLLMC_SW(k_gemm_mid_swiglu, 256); break;
+        default: DLLMC_SW(k_gemm_tall_swiglu, 256); break;
       }
-      if (tall)
-        hipLaunchKernelGGL(k_gemm_tall_swiglu, dim3(m / 48, 1, 1), dim3(256), 0, st, a, lda, rows, M,
-                           w0, w1, m, K, uo);
-      else if (fat96)
-        hipLaunchKernelGGL(k_gemm_fat96_swiglu, dim3(m / 96, (M + kFatM - 1) / kFatM, 1), dim3(512), 0, st, a,
-                           lda, rows, M, w0, w1, m, K, uo);
-      else if (fat)
-        hipLaunchKernelGGL(k_gemm_fat_swiglu, dim3(m / (kFatN / 2), (M + kFatM - 1) / kFatM, 1),
-                           dim3(512), 0, st, a, lda, rows, M, w0, w1, m, K, uo);
-      else
-        hipLaunchKernelGGL(k_gemm_mid_swiglu, dim3(m / (kMidN / 2), (M + kMidM - 1) / kMidM, 1),
-                           dim3(256), 0, st, a, lda, rows, M, w0, w1, m, K, uo);
+#undef DLLMC_SW
       return true;
     }
   }
@@ -1042,19 +1068,26 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   return true;
 }
 
-// Which tile kernel finishes a launch of M rows x N columns in one slice: 2 = 256 x 256, 1 = 128 x
-// 128, 0 = neither (the launch would leave more than a quarter of the CUs without a workgroup, or
-// the shape does not fit the tiles).
-static int direct_tile_kind(int M, int N, int N0, int K) {
-  if (K % kFatK) return 0;
-  const int cus = 256;
-  if (M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0 &&
-      ((M + kFatM - 1) / kFatM) * (N / kFatN) >= 3 * cus / 4)
-    return 2;
-  if (M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0 &&
-      ((M + kMidM - 1) / kMidM) * (N / kMidN) >= 3 * cus / 4)
-    return 1;
-  return 0;
+// Which tile kernel finishes a launch of M rows x N columns in one slice: 3 = 192 rows x cols192 columns, 2 =
+// 256 x 256, 1 = 128 x 128, 0 = none (every shape that divides the columns would leave more than a quarter of the
+// CUs without a workgroup).  The one whose rounds over the CUs take least, by measured us per round and 64-wide
+// step: 256 x 256 1.6, 128 x 128 1.16 with two workgroups per CU and 0.78 with one, 192 x 128 0.92, 192 x
+// 64 0.74.  (768 rows: Q|K of 8192 columns 192 x 128 in one round of 256 workgroups 58.7 us, 128 x 128 72; V of
+// 4096 columns 192 x 64 47, 128 x 128 51.)
+static int direct_tile_kind(int M, int N, int N0, int K, int cols192) {
+  if (K % kFatK || M < g_tune.tile_min_m) return 0;
+  const int cus = 256, least = 3 * cus / 4;
+  int kind = 0;
+  double best = 1e30;
+  auto tiles = [&](int bm, int bn) { return static_cast<long long>((M + bm - 1) / bm) * (N / bn); };
+  auto offer = [&](int k, double t) { if (t < best) { best = t; kind = k; } };
+  if (M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0 && tiles(kFatM, kFatN) >= least)
+    offer(2, (tiles(kFatM, kFatN) + cus - 1) / cus * 1.6);
+  if (N % kMidN == 0 && N0 % kMidN == 0 && tiles(kMidM, kMidN) >= least)
+    offer(1, tiles(kMidM, kMidN) <= cus ? 0.78 : (tiles(kMidM, kMidN) + 2 * cus - 1) / (2 * cus) * 1.16);
+  if (N % cols192 == 0 && N0 % cols192 == 0 && tiles(192, cols192) >= least)
+    offer(3, (tiles(192, cols192) + cus - 1) / cus * (cols192 == 64 ? 0.74 : 0.92));
+  return kind;
 }
 
 bool launch_gemm_vverify_tiles(int dtype, const void* A, int lda, int M, int first, int per_seq, int n,
@@ -1062,7 +1095,7 @@ bool launch_gemm_vverify_tiles(int dtype, const void* A, int lda, int M, int fir
                                int part_stride, int metric, const int* rmap, hipStream_t st) {
   if (M <= 0) return true;
   if (dtype != 1 || per_seq <= 0 || lda % 8 || !aligned16(A) || !aligned16(W)) return false;
-  const int kind = direct_tile_kind(M, N, N, K);
+  const int kind = direct_tile_kind(M, N, N, K, 64);
   if (kind == 0) return false;
   TileEpilogue ep{};
   ep.first = first; ep.per_seq = per_seq; ep.n = n; ep.L_p = L_p;
@@ -1071,7 +1104,9 @@ bool launch_gemm_vverify_tiles(int dtype, const void* A, int lda, int M, int fir
   t_last_stream = false;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  if (kind == 2)
+  if (kind == 3)
+    hipLaunchKernelGGL(k_gemm_r192_vverify, dim3(N / 64, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, M, w, N, K, ep);
+  else if (kind == 2)
     hipLaunchKernelGGL(k_gemm_fat_vverify, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(512), 0, st, a,
                        lda, M, w, N, K, ep);
   else
@@ -1087,7 +1122,7 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
   if (M <= 0) return true;
   if (dtype != 1 || d_h != 128 || lda % 8 || !aligned16(A) || !aligned16(wq) || !aligned16(w2)) return false;
   const int N = d_q + d_kv;
-  const int kind = direct_tile_kind(M, N, d_q, K);
+  const int kind = direct_tile_kind(M, N, d_q, K, 128);
   if (kind == 0) return false;
   TileEpilogue ep{};
   ep.n = n; ep.cache = static_cast<bf16_t*>(cache); ep.rmap = rmap; ep.tab = rope_tab;
@@ -1096,7 +1131,9 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w0 = static_cast<const bf16_t*>(wq);
   const bf16_t* w1 = static_cast<const bf16_t*>(w2);
-  if (kind == 2)
+  if (kind == 3)
+    hipLaunchKernelGGL(k_gemm_r192_qk, dim3(N / 128, (M + 191) / 192, 1), dim3(512), 0, st, a, lda, rows, M, w0, w1, d_q, N, K, ep);
+  else if (kind == 2)
     hipLaunchKernelGGL(k_gemm_fat_qk, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(512), 0, st, a, lda,
                        rows, M, w0, w1, d_q, N, K, ep);
   else

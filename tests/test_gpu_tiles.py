@@ -1,0 +1,52 @@
+"""Every tile shape of the refresh steps' launches (128, 192 and 256 rows; gate/up, V-verify and Q|K finished in their
+epilogues) at row counts around whole tiles and rounds, against a context with the tile kernels switched off.
+
+Same inputs, other orders of summation: elements may round to neighbouring bf16 values (2^-7 of the value), and
+those flips spread a little behind the attention; a step of a tile multiplied with the wrong operands moves its rows
+by 0.2 rms and more.  The bars are those of the 120-launch test of the 768-row launches."""
+import pytest
+import torch
+
+from paper_2506_06295_amd import binding, inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("base,L_p,L_r", [
+    ("llada8b", 20, 180),    # 200 rows: 128-row tiles, 256 x 96 gate/up
+    ("llada8b", 129, 255),   # 384 rows: two whole 192-row tiles for gate/up
+    ("llada8b", 129, 256),   # 385
+    ("llada8b", 320, 256),   # 576 rows: three 192-row tiles
+    ("llada8b", 513, 256),   # 769: a fifth tile of one row
+    ("llada8b", 900, 130),   # 1030: 256 x 192 gate/up, 256-row tiles from here on
+    ("dream7b", 700, 67),    # 767 rows, grouped KV heads, an FFN width that 96 does not divide
+])
+def test_full_refresh(base, L_p, L_r):
+    cfg = I.CONFIGS[base].replace(T=1, K_p=1, K_r=1, L_p=L_p, L_r=L_r)
+    ws = I.device_weights(cfg)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L_p * 1000 + L_r)
+    make = lambda: binding.CachedDenoiser(
+        n_layers=cfg.T, d_model=cfg.d, n_q_heads=cfg.H_q, n_kv_heads=cfg.H_kv, head_dim=cfg.d_h,
+        d_ffn=cfg.m, batch=cfg.B, dtype=cfg.dtype, weights=ws, L_p=L_p, L_r=L_r, rho=cfg.rho,
+        K_p=cfg.K_p, K_r=cfg.K_r, rms_eps=cfg.rms_eps, rope_theta=cfg.rope_theta)
+    tiles = make()
+    binding.set_gemm_tuning(tile_min_m=1 << 20)
+    try:
+        plain = make()
+    finally:
+        binding.set_gemm_tuning(tile_min_m=192)
+    for i in range(4):
+        hid = torch.randn(cfg.B, cfg.n, cfg.d, device="cuda", generator=gen).to(torch.bfloat16)
+        a_out, _ = tiles.step(hid, i)
+        c_out, _ = plain.step(hid, i)
+        torch.cuda.synchronize()
+        pairs = [(tiles.read_cache(0, w), plain.read_cache(0, w), 0.03 if w < 2 else 0.12) for w in range(4)]
+        pairs.append((a_out, c_out, 0.12))
+        for which, (a, c, slack) in enumerate(pairs):
+            a, c = a.float(), c.float()
+            rms = float(c.pow(2).mean().sqrt())
+            excess = float(((a - c).abs() - 0.03 * c.abs()).max()) / rms
+            assert excess <= slack, (i, which, excess)
+    tiles.close()
+    plain.close()
