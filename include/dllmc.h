@@ -289,9 +289,10 @@ int dllmc_op_head(int32_t dtype, const void* hidden, const int32_t* rows, int32_
  * copy for life, so live contexts are not affected; the single operations (dllmc_op_*) and the
  * closed loop's head use the default in force when they are called.  An argument outside its
  * range leaves that knob unchanged: force_s number of contraction slices (0 = automatic), target_wg
- * workgroups the slice count of the 128 x 128 tile kernel aims for, tile_min_m / fat_min_m number of
- * activation rows (defaults 192 / 512) from which the 128 x 128 / the 256 x 256 LDS-direct tile kernel
- * replaces the weight-streaming kernel.  nw, nw_dual and tall_max_m chose shapes of a kernel that is no
+ * (default 256: automatic) workgroups the slice count of the 128 x 128 tile kernel aims for, tile_min_m /
+ * fat_min_m number of activation rows (defaults 192 / 512) from which the 128 x 128 / the 256 x 256
+ * LDS-direct tile kernel is considered beside the weight-streaming kernel; values other than the defaults
+ * are taken literally: the tile kernel is used from there on.  nw, nw_dual and tall_max_m chose shapes of a kernel that is no
  * longer there: any value is accepted and has no effect.
  * Results are
  * bit-reproducible for fixed settings; different settings change the float32 summation order

@@ -177,9 +177,11 @@ int gemm_max_slices();
 // call is running on this thread (TuningScope), the process default otherwise.
 struct GemmTuning {
   int force_s = 0;          // > 0: number of slices of the contraction index
-  int target_wg = 256;      // workgroups the slice count of the 128 x 128 tile kernel aims for
-  int fat_min_m = 512;      // activation rows from which the 256 x 256 LDS-direct kernel is used
-  int tile_min_m = 192;     // activation rows from which the 128 x 128 LDS-direct kernel is used
+  int target_wg = 256;      // not the default: workgroups the slice count of the 128 x 128 kernel aims for
+  int fat_min_m = 512;      // activation rows from which the 256 x 256 LDS-direct kernel is considered
+  int tile_min_m = 192;     // activation rows from which the 128 x 128 LDS-direct kernel is considered
+                            // (both: a value other than the default is taken literally, the kernel is
+                            // used from there on)
 };
 GemmTuning gemm_default_tuning();
 struct TuningScope {
@@ -198,9 +200,10 @@ void gemm_set_fat_min_m(int m);
 // weight-streaming kernel (k_gemm_ring).
 bool gemm_last_was_stream();
 void gemm_clear_last_stream();  // a matrix product launched by another launcher follows
+// whole != nullptr: a launch of a single slice writes there instead of to c_part.
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
-                hipStream_t st);
+                hipStream_t st, float* whole = nullptr);
 
 // float32 models (kernels_gemm_f32.hip): operands in whole aligned 16-byte pieces; tile shape and
 // slices for a launch (at most s_cap slices; force_s > 0: that many); C gets p.S slices
@@ -221,9 +224,10 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
                         hipStream_t st);
 
 // bf16 maps of few rows and of any column count (kernels_gemm_ring.hip): row and column blocks of a tile, slices
-struct RingPlan { int rb, nb, S, kps, nt, mt; };
+struct RingPlan { int rb, nb, S, kps, nt, mt; double t; };
 bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K);
-RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s);
+// (t: estimated us; 1e30 when every choice has more than max_wg workgroups)
+RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, long long max_wg = 1ll << 40);
 void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
                       const bf16_t* W1, int N0, int N, int K, float* C, hipStream_t st);
 void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,

@@ -733,9 +733,9 @@ int dllmc_op_linear(int32_t dtype, const void* a, const int32_t* row_idx, int32_
   (void)hipGetLastError();
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, scratch,
-                            static_cast<size_t>(M) * N * 8, st);
+                            static_cast<size_t>(M) * N * 8, st, out);
   if (S == 0) return DLLMC_ENOMEM;
-  launch_reduce_slices(scratch, S, M, N, out, st);
+  if (S > 1) launch_reduce_slices(scratch, S, M, N, out, st);
   HIP_TRY(hipGetLastError());
   return DLLMC_OK;
 }
@@ -789,9 +789,9 @@ int dllmc_op_linear_static(int32_t dtype, const void* a, const int32_t* row_idx,
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   // every slice the launch produces is written whole before it is read: nothing to clear
   const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, ptr,
-                            kStaticScratchFloats, st);
+                            kStaticScratchFloats, st, out);
   if (S == 0) return DLLMC_ETOOBIG;
-  launch_reduce_slices(ptr, S, M, N, out, st);
+  if (S > 1) launch_reduce_slices(ptr, S, M, N, out, st);
   HIP_TRY(hipGetLastError());
   return DLLMC_OK;
 }

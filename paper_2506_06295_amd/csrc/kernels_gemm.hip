@@ -12,6 +12,7 @@
 //                      gate/up column blocks and SwiGLU in the epilogue (k_gemm_*_swiglu,
 //                      k_gemm_tall_swiglu: 256 x 96 for up to 256 rows), with the head's reduction
 //                      (k_gemm_mid_head), and with 192-row tiles (k_gemm_r192_*).
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -812,20 +813,46 @@ __global__ __launch_bounds__(512) void k_gemm_r192_qk(const bf16_t* __restrict__
   gemm_lds_body<4, 2, 3, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
 }
 
-__global__ __launch_bounds__(256) void k_reduce_slices(const float* __restrict__ c_part, int S,
-                                                       size_t MN, float* __restrict__ out) {
-  const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+// V floats per thread; every slice's load is issued before the first addition (a loop over the runtime count waits
+// for each), slices in order.
+template <int V, int S>
+__global__ __launch_bounds__(256) void k_reduce_slices(const float* __restrict__ c_part, size_t MN,
+                                                       float* __restrict__ out) {
+  const size_t i = (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x) * V;
   if (i >= MN) return;
-  float t = c_part[i];
-  for (int s = 1; s < S; ++s) t += c_part[static_cast<size_t>(s) * MN + i];
-  out[i] = t;
+  if (V == 4) {
+    f32x4 u[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) u[s] = *reinterpret_cast<const f32x4*>(c_part + static_cast<size_t>(s) * MN + i);
+#pragma unroll
+    for (int s = 1; s < S; ++s) u[0] += u[s];
+    *reinterpret_cast<f32x4*>(out + i) = u[0];
+  } else {
+    float u[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) u[s] = c_part[static_cast<size_t>(s) * MN + i];
+#pragma unroll
+    for (int s = 1; s < S; ++s) u[0] += u[s];
+    out[i] = u[0];
+  }
 }
 
 void launch_reduce_slices(const float* c_part, int S, int M, int N, float* out, hipStream_t st) {
   const size_t MN = static_cast<size_t>(M) * N;
   if (MN == 0) return;
-  hipLaunchKernelGGL(k_reduce_slices, dim3(static_cast<unsigned>((MN + 255) / 256)), dim3(256), 0,
-                     st, c_part, S, MN, out);
+  const bool vec = MN % 4 == 0 &&
+                   ((reinterpret_cast<uintptr_t>(c_part) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0;
+  const dim3 grid(static_cast<unsigned>((MN + (vec ? 1023 : 255)) / (vec ? 1024 : 256)));
+#define DLLMC_RS(Sv)                                                                                         \
+  case Sv:                                                                                                   \
+    if (vec) hipLaunchKernelGGL((k_reduce_slices<4, Sv>), grid, dim3(256), 0, st, c_part, MN, out);           \
+    else hipLaunchKernelGGL((k_reduce_slices<1, Sv>), grid, dim3(256), 0, st, c_part, MN, out);               \
+    break;
+  switch (S) {
+    DLLMC_RS(1) DLLMC_RS(2) DLLMC_RS(3) DLLMC_RS(4) DLLMC_RS(5) DLLMC_RS(6) DLLMC_RS(7) DLLMC_RS(8)
+    default: break;  // no more than kMaxSlices
+  }
+#undef DLLMC_RS
 }
 
 // ------------------------------------------------------------------------------------
@@ -897,51 +924,51 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     p.kind = 1; p.S = 1; p.kps = K; p.nt = (N + 63) / 64; p.mt = (M + 63) / 64;
     return p;
   }
-  if (M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0 && K % kFatK == 0) {
-    p.kind = 3;
-    p.mt = (M + kFatM - 1) / kFatM;
-    p.nt = N / kFatN;
-    // One workgroup per CU (128 KB of LDS).  Choose the slice count with the lowest estimated
-    // time: rounds of tiles over the 256 CUs at the measured ~1.1 PFLOP/s steady rate of this
-    // kernel, plus writing and re-reading the float32 partial sums at ~5 TB/s.
-    int S = 1;
-    if (g_tune.force_s > 0) {
-      S = g_tune.force_s;
-    } else {
-      double best = 1e30;
-      for (int sl = 1; sl <= s_cap; ++sl) {
-        if (K / sl < 8 * kFatK) break;
-        const int kslice = ((K + sl - 1) / sl + kFatK - 1) / kFatK * kFatK;
-        const int rounds = (p.mt * p.nt * sl + 255) / 256;
-        const double t_tile = 2.0 * kFatM * kFatN * kslice / (1.1e15 / 256.0);
-        const double t_part = sl > 1 ? 2.0 * sl * static_cast<double>(MN) * 4.0 / 5e12 : 0.0;
-        const double cost = rounds * t_tile + t_part;
-        if (cost < best * 0.98) { best = cost; S = sl; }
+  const GemmTuning defaults;
+  const bool fat_ok = M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0;
+  const bool mid_ok = M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0;
+  if (fat_ok || mid_ok) {
+    // Estimated us of the tile kernels at every slice count, and of the weight-streaming kernel.  Measured per round
+    // of workgroups and 64-wide step: 256 x 256 1.42 (one per CU), 128 x 128 1.0 with two per CU, 0.62 with one;
+    // the partial sums are written and read again at ~6 TB/s.  The streaming kernel counts while its workgroups
+    // make one round.
+    // op_linear before this rule and with it: 333 rows x 4096 x 4096 28.1 -> 24.9 us (the streaming kernel's
+    // 192-row tiles), x 12288 70.7 -> 48.0; 400 rows x 4096 x 12288 69 -> 58 (128 x 128 in four slices instead
+    // of two); 600 rows x 12288 x 4096 91 -> 68 (128 x 128 whole instead of 256 x 256 in three slices).
+    const bool literal = g_tune.force_s > 0 || g_tune.fat_min_m != defaults.fat_min_m ||
+                         g_tune.tile_min_m != defaults.tile_min_m || g_tune.target_wg != defaults.target_wg;
+    double best = 1e30;
+    auto offer = [&](int kind, int bm, int bn, int S) {
+      int kps = ((K + S - 1) / S + kFatK - 1) / kFatK * kFatK;
+      if (kps > K) kps = K;
+      const int used = (K + kps - 1) / kps, mt = (M + bm - 1) / bm, nt = N / bn;
+      const long long wg = static_cast<long long>(mt) * nt * used;
+      const double round = kind == 3 ? static_cast<double>((wg + 255) / 256) * 1.42
+                                     : (wg <= 256 ? 0.62 : static_cast<double>((wg + 511) / 512) * 1.0);
+      const double bytes = used > 1 ? 2.0 * used * MN * 4.0 : MN * 4.0;
+      const double t = round * (kps / kFatK) + bytes / 6e6 + 0.15 * used;
+      if (t < best * 0.98) {
+        best = t;
+        p.kind = kind; p.S = used; p.kps = kps; p.nt = nt; p.mt = mt;
+      }
+    };
+    const bool only_fat = literal && fat_ok;  // thresholds and slice counts set by the caller
+    const int s_lo = g_tune.force_s > 0 ? (g_tune.force_s < s_cap ? g_tune.force_s : s_cap) : 1;
+    int s_hi = g_tune.force_s > 0 ? s_lo : s_cap, m_lo = s_lo, m_hi = s_hi;
+    if (g_tune.force_s <= 0 && g_tune.target_wg != defaults.target_wg) {
+      const int tiles = ((M + kMidM - 1) / kMidM) * (N / kMidN);
+      m_lo = m_hi = std::max(1, std::min(s_cap, g_tune.target_wg / tiles));
+    }
+    for (int S = s_lo; fat_ok && S <= s_hi; ++S)
+      if (S == s_lo || K / S >= 8 * kFatK) offer(3, kFatM, kFatN, S);
+    for (int S = m_lo; mid_ok && !only_fat && S <= m_hi; ++S)
+      if (S == m_lo || K / S >= 8 * kFatK) offer(4, kMidM, kMidN, S);
+    if (!literal) {
+      const RingPlan r = plan_ring(M, N, K, s_cap, 0, 256);
+      if (r.t < best * 0.98) {
+        p.kind = 2; p.ring = r; p.S = r.S; p.kps = r.kps; p.nt = r.nt; p.mt = r.mt;
       }
     }
-    S = S < 1 ? 1 : (S > s_cap ? s_cap : S);
-    p.kps = ((K + S - 1) / S + kFatK - 1) / kFatK * kFatK;
-    if (p.kps > K) p.kps = K;
-    p.S = (K + p.kps - 1) / p.kps;
-    return p;
-  }
-  if (M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0 && K % kFatK == 0) {
-    p.kind = 4;
-    p.mt = (M + kMidM - 1) / kMidM;
-    p.nt = N / kMidN;
-    // Slices: as many as keep the launch within one workgroup per CU, rounded down (every
-    // slice costs its float32 partial sums twice, written here and read by the row kernel: a
-    // slightly underfilled chip is cheaper than a fifth slice), at least 8 steps of 64 each
-    // unless that leaves more than a fifth of the CUs without a workgroup
-    const int tiles = p.mt * p.nt;
-    int S = g_tune.target_wg / tiles;
-    if (5 * tiles * S <= 4 * g_tune.target_wg) ++S;
-    if (g_tune.force_s > 0) S = g_tune.force_s;
-    S = S < 1 ? 1 : (S > s_cap ? s_cap : S);
-    p.kps = ((K + S - 1) / S + kFatK - 1) / kFatK * kFatK;
-    if (p.kps < 8 * kFatK) p.kps = 8 * kFatK;
-    if (p.kps > K) p.kps = K;
-    p.S = (K + p.kps - 1) / p.kps;
     return p;
   }
   p.kind = 2;
@@ -956,13 +983,14 @@ int gemm_plan_slices(int dtype, int M, int N, int N0, int K, size_t c_capacity) 
 
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
-                hipStream_t st) {
+                hipStream_t st, float* whole) {
   t_last_stream = false;
   if (M <= 0 || N <= 0) return 1;
   const bool al = aligned16(A) && aligned16(W0) && (W1 == nullptr || aligned16(W1));
   const GemmPlan p = plan_gemm(dtype, al, lda, M, N, N0, K, c_capacity);
   if (p.kind == 0 || static_cast<size_t>(p.S) * M * N > c_capacity) return 0;  // nothing launched
   t_last_stream = p.kind == 2;
+  if (whole != nullptr && p.S == 1) c_part = whole;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w0 = static_cast<const bf16_t*>(W0);
   const bf16_t* w1 = static_cast<const bf16_t*>(W1);

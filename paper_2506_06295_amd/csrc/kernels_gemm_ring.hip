@@ -194,12 +194,12 @@ __global__ __launch_bounds__(512) void k_gemm_ring(const bf16_t* __restrict__ A,
 }
 
 // Estimated time in us of a launch of `tiles` workgroups (one per CU at a time) of 64 * rb rows x 16 * nb
-// weight rows x k: the weights at the chip's stream rate, everything a CU takes in at ~40 GB/s (measured up
-// to 45), or the MFMAs (rb * nb per wavefront and step, two wavefronts per SIMD).
+// weight rows x k: the weights at the chip's stream rate, everything a CU takes in at ~40 GB/s (47 for
+// 192-row tiles), or the MFMAs (rb * nb per wavefront and step, two wavefronts per SIMD).
 double ring_time(long long tiles, int rb, int nb, int k) {
   const double rounds = static_cast<double>((tiles + 255) / 256);
   const double t_w = 16.0 * nb * k * 2.0 / 21.5e3;
-  const double t_in = (64.0 * rb + 16.0 * nb) * k * 2.0 / 40e3;
+  const double t_in = (64.0 * rb + 16.0 * nb) * k * 2.0 / (rb == 3 ? 47e3 : 40e3);
   const double t_m = k / 64.0 * 2.0 * rb * nb * 16.0 / 2400.0;
   double t = t_w > t_in ? t_w : t_in;
   if (t_m > t) t = t_m;
@@ -215,8 +215,9 @@ bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K) {
 // Row blocks, column blocks and slices with the lowest estimate; a slice costs its partial sums twice
 // (written here, read by the row kernel; mostly out of the memory-side cache) and 0.15 us there (at twice
 // that price two adaptive Dream-7B steps took 713 instead of 708 us; at half of it 710).
-RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s) {
+RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, long long max_wg) {
   RingPlan best{};
+  best.t = 1e30;
   double best_t = 1e30;
   for (int rb = 1; rb <= 3; ++rb)
     for (int nb = 4; nb <= 8; nb += 4) {
@@ -226,11 +227,12 @@ RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s) {
         int kps = ((K + S - 1) / S + 63) / 64 * 64;
         if (kps > K) kps = K;
         const int used = (K + kps - 1) / kps;
+        if (static_cast<long long>(mt) * nt * used > max_wg) continue;
         const double t = ring_time(static_cast<long long>(mt) * nt * used, rb, nb, kps) +
                          used * (2.0 * M * N * 4.0 / 16e6 + 0.15);
         if (t < best_t * 0.98) {
           best_t = t;
-          best = RingPlan{rb, nb, used, kps, nt, mt};
+          best = RingPlan{rb, nb, used, kps, nt, mt, t};
         }
       }
     }
