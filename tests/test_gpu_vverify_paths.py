@@ -1,0 +1,44 @@
+"""V-verify on both sides of the choice between its one-launch kernel (64 x 64 tiles that fill one or two rounds of the
+CUs), the split contraction with its row kernel, and the tile kernels' epilogue.
+
+bf16 rows are rounded once from float32 sums: isolated last-bit differences (2^-8 of an element) from another order
+of summation; one of them moves a cosine of d_kv elements by at most ~2^-8 / sqrt(d_kv) * |v_i| / rms."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_06295_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,d,d_kv", [
+    (64, 2048, 4096),     # 64 tiles: split
+    (128, 2048, 4096),    # 128: one launch
+    (256, 2048, 4096),    # 256
+    (257, 2048, 4096),    # 320: split
+    (416, 2048, 4096),    # 448: one launch, second round
+    (513, 2048, 4096),    # 576: split
+    (899, 2048, 4096),
+    (900, 2048, 4096),    # tile epilogue
+    (1000, 2048, 512),    # 128 tiles
+    (50, 1024, 64),       # a short walk: one tile
+])
+def test_vverify(rows, d, d_kv):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + d_kv)
+    h = torch.randn((rows, d), generator=g, device="cuda").bfloat16()
+    wv = (0.02 * torch.randn((d_kv, d), generator=g, device="cuda")).bfloat16()
+    v = h.double() @ wv.double().t()
+    old = (v + 0.3 * torch.rand((rows, 1), generator=g, device="cuda").double()
+           * torch.randn((rows, d_kv), generator=g, device="cuda").double()).bfloat16()
+    old[rows // 2] = 0
+    cache = old.clone()
+    scores = binding.op_vverify("bf16", h, wv, cache)
+    vb = v.bfloat16()
+    assert float((cache != vb).double().mean()) < 0.01
+    assert float((cache.double() - vb.double()).norm() / vb.double().norm()) < 1e-3
+    new = cache.double()
+    want = (new * old.double()).sum(1) / (new.norm(dim=1) * old.double().norm(dim=1)).clamp(min=1e-8)
+    assert float((scores.double() - want).abs().max()) < 2.0 ** -24 * np.sqrt(d_kv) * 4
+    assert float(scores[rows // 2]) == 0.0
