@@ -679,6 +679,26 @@ int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t 
   return DLLMC_OK;
 }
 
+}  // extern "C"
+
+namespace {
+// A map of a single slice may be written straight to `out`, unless that overlaps an operand, which the way
+// over the scratch buffer allows.
+bool disjoint(const float* out, const void* a, const int32_t* row_idx, const void* w, int M, int N, int K,
+              int dtype) {
+  const uintptr_t esz = dtype == DLLMC_BF16 ? 2 : 4;
+  const uintptr_t o0 = reinterpret_cast<uintptr_t>(out), o1 = o0 + static_cast<uintptr_t>(M) * N * 4;
+  const auto apart = [&](const void* p, uintptr_t bytes) {
+    const uintptr_t b = reinterpret_cast<uintptr_t>(p);
+    return o1 <= b || o0 >= b + bytes;
+  };
+  return apart(a, static_cast<uintptr_t>(M) * K * esz) && apart(w, static_cast<uintptr_t>(N) * K * esz) &&
+         (row_idx == nullptr || apart(row_idx, static_cast<uintptr_t>(M) * 4));
+}
+}  // namespace
+
+extern "C" {
+
 // ---- single operations ------------------------------------------------------------------
 
 int dllmc_op_select(const float* scores, int32_t B, int32_t L, int32_t k, int32_t* idx_out,
@@ -732,10 +752,11 @@ int dllmc_op_linear(int32_t dtype, const void* a, const int32_t* row_idx, int32_
     return DLLMC_EINVAL;
   (void)hipGetLastError();
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const bool direct = disjoint(out, a, row_idx, w, M, N, K, dtype);
   const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, scratch,
-                            static_cast<size_t>(M) * N * 8, st, out);
+                            static_cast<size_t>(M) * N * 8, st, direct ? out : nullptr);
   if (S == 0) return DLLMC_ENOMEM;
-  if (S > 1) launch_reduce_slices(scratch, S, M, N, out, st);
+  if (S > 1 || !direct) launch_reduce_slices(scratch, S, M, N, out, st);
   HIP_TRY(hipGetLastError());
   return DLLMC_OK;
 }
@@ -788,10 +809,11 @@ int dllmc_op_linear_static(int32_t dtype, const void* a, const int32_t* row_idx,
   HIP_TRY(static_scratch_on_current_device(&ptr));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   // every slice the launch produces is written whole before it is read: nothing to clear
+  const bool direct = disjoint(out, a, row_idx, w, M, N, K, dtype);
   const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, ptr,
-                            kStaticScratchFloats, st, out);
+                            kStaticScratchFloats, st, direct ? out : nullptr);
   if (S == 0) return DLLMC_ETOOBIG;
-  if (S > 1) launch_reduce_slices(ptr, S, M, N, out, st);
+  if (S > 1 || !direct) launch_reduce_slices(ptr, S, M, N, out, st);
   HIP_TRY(hipGetLastError());
   return DLLMC_OK;
 }

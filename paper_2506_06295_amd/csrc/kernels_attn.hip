@@ -1388,7 +1388,8 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
     int QB = 0, KS = 1;  // QB 0: walk
     const int base = B * ((Mq + kQT - 1) / kQT) * H_q;
     double best = 4.5 + nblk * (base <= 256 ? 1.02 : 1.6 * ((base + 511) / 512));
-    for (int qb = 1; qb <= 4; qb *= 2) {
+    const bool wide_out = (reinterpret_cast<uintptr_t>(out) & 15u) == 0;  // few stores 16-byte pieces
+    for (int qb = 1; qb <= 4 && wide_out; qb *= 2) {
       const int tiles = B * ((Mq + 16 * qb - 1) / (16 * qb)) * H_q;
       for (int s = 1; s <= kMaxKeySplit; s *= 2) {
         if (s > 1 && (scratch == nullptr || tiles * s > 256 || 2 * s > nblk)) break;

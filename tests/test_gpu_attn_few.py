@@ -40,3 +40,19 @@ def test_attention(B, Mq, n, H_q, H_kv, split_keys):
         want = O.attention(*(x[b].double().cpu().numpy() for x in (q, k, v)), H_q, H_kv, 128)
         assert rel_err(got[b], want) < 2.0 ** -9
         assert np.max(np.abs(got[b] - want)) <= 2.0 ** -8 * np.max(np.abs(want))
+
+
+def test_result_at_eight_bytes():
+    """A result that is not 16-byte aligned is written by the kernels that store 8 bytes at a time."""
+    B, Mq, n, H = 1, 33, 129, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    q, k, v = (torch.randn((B, rows, H * 128), generator=g, device="cuda").bfloat16() for rows in (Mq, n, n))
+    want = binding.op_attention("bf16", q, k, v, H, H, 128, split_keys=False).float()
+    room = torch.zeros(q.numel() + 8, dtype=torch.bfloat16, device="cuda")
+    out = room[4:4 + q.numel()]
+    rc = binding.lib().dllmc_op_attention(1, q.data_ptr(), B, Mq, k.data_ptr(), v.data_ptr(), n, H, H, 128,
+                                          out.data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    assert rel_err(out.float().cpu().numpy(), want.flatten().cpu().numpy()) < 2.0 ** -8  # two roundings
+    assert not room[:4].any() and not room[4 + q.numel():].any()

@@ -50,3 +50,21 @@ def test_full_refresh(base, L_p, L_r):
             assert excess <= slack, (i, which, excess)
     tiles.close()
     plain.close()
+
+
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 1024, 4096, 512), ("bf16", 512, 512, 256), ("f32", 200, 256, 192)])
+@pytest.mark.parametrize("over", ["a", "w"])
+def test_result_over_an_operand(dtype, M, N, K, over):
+    """A single slice goes straight to the result unless that lies over an operand."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + K)
+    src = {"a": torch.randn((M, K), generator=g, device="cuda").to(dt),
+           "w": (0.05 * torch.randn((N, K), generator=g, device="cuda")).to(dt)}
+    want = binding.op_linear_static(dtype, src["a"], src["w"], torch.empty((M, N), device="cuda"))
+    out = torch.empty(max(M * N, src[over].numel()), device="cuda")  # holds the operand, then the result
+    held = out.view(dt)[:src[over].numel()].view(src[over].shape)
+    held.copy_(src[over])
+    ops = {**src, over: held}
+    got = binding.op_linear_static(dtype, ops["a"], ops["w"], out[:M * N].view(M, N))
+    assert torch.equal(got, want)
