@@ -26,10 +26,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16
 FP32_VALU_PEAK_TFLOPS = 157.3
 # HBM bytes per launch of the streaming GEMM (reads + writes): NOT measured by this program.  The
 # figure comes from separate rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this benchmark,
-# scaled by the counters' reading for a 256 MiB copy (profiles/k_gemm_stream_<workload>_hbm_counters.txt);
+# scaled by the counters' reading for a 256 MiB copy (profiles/k_gemm_ring_<workload>_hbm_counters.txt);
 # None where no such run has been recorded for the workload.
-TRAFFIC_BYTES_PER_LAUNCH = {"llada8b": 114.8e6}
-TRAFFIC_SOURCE = "profiles/k_gemm_stream_{name}_hbm_counters.txt (separate rocprofv3 --pmc runs, not this run)"
+TRAFFIC_BYTES_PER_LAUNCH = {"llada8b": 109.8e6}
+TRAFFIC_SOURCE = "profiles/k_gemm_ring_{name}_hbm_counters.txt (separate rocprofv3 --pmc runs, not this run)"
 
 
 def make_denoiser(binding, cfg, weights, **over):
@@ -325,10 +325,10 @@ def main():
             t_fl = sum(g["flops"] for g in gemm) - ks["flops"]
             t_n = sum(g["launches"] for g in gemm) - ks["launches"]
             tf = t_fl / (t_ms * 1e-3) / 1e12 if t_ms > 0 else 0.0
-            f32 = cfg.dtype == "f32"   # float32 models run the plain vector-ALU GEMM
+            f32 = cfg.dtype == "f32"   # float32 models: the float32 matrix instructions, whose peak is the vector one
             peak = FP32_VECTOR_PEAK_TFLOPS if f32 else MFMA_BF16_PEAK_TFLOPS
             result["roofline"] = {
-                "kernel": ("k_gemm_simple (float32, vector ALU)" if f32 else
+                "kernel": ("k_gemm_f32 (float32 matrix instructions)" if f32 else
                            "k_gemm_fat / k_gemm_mid (every launch of the LDS-direct tile kernels)"),
                 "bound": "alu" if f32 else "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s",
                 "frac": tf / peak, "traffic": None, "launches": t_n,

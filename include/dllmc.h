@@ -324,7 +324,8 @@ int dllmc_op_vverify(int32_t dtype, const void* h, const void* wv, void* v_cache
 
 /* Gathered linear map: out[i, :] = a[row_idx[i], :] * w^T in float32, i < M.  a: device
  * [*, K] model dtype; row_idx: device int32 [M] or NULL for the identity; w: [N, K];
- * out: float32 [M, N]; scratch: device float32 [M * N * 8]. */
+ * out: float32 [M, N]; scratch: device float32 [M * N * 8], unused where the
+ * contraction is not split and out overlaps no operand. */
 int dllmc_op_linear(int32_t dtype, const void* a, const int32_t* row_idx, int32_t M, const void* w,
                     int32_t N, int32_t K, float* out, float* scratch, void* hip_stream);
 
