@@ -324,10 +324,15 @@ int dllmc_op_vverify(int32_t dtype, const void* h, const void* wv, void* v_cache
 
 /* Gathered linear map: out[i, :] = a[row_idx[i], :] * w^T in float32, i < M.  a: device
  * [*, K] model dtype; row_idx: device int32 [M] or NULL for the identity; w: [N, K];
- * out: float32 [M, N]; scratch: device float32 [M * N * 8], unused where the
- * contraction is not split and out overlaps no operand. */
+ * out: float32 [M, N], may overlap an operand; scratch: device float32 [M * N * 8], apart from
+ * the operands, unused where the contraction is not split and out is known to overlap no operand
+ * (the row count of a gathered `a` is not: only an out that ends at or before `a` counts). */
 int dllmc_op_linear(int32_t dtype, const void* a, const int32_t* row_idx, int32_t M, const void* w,
                     int32_t N, int32_t K, float* out, float* scratch, void* hip_stream);
+/* The same with the row count of `a` stated (every row_idx in [0, a_rows)): results that lie
+ * behind a gathered `a` need no scratch either. */
+int dllmc_op_linear_rows(int32_t dtype, const void* a, int32_t a_rows, const int32_t* row_idx, int32_t M,
+                         const void* w, int32_t N, int32_t K, float* out, float* scratch, void* hip_stream);
 
 /* dllmc_op_linear for callers that cannot allocate device memory or pass a scratch buffer
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the

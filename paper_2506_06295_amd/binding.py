@@ -29,7 +29,7 @@ EXPORTS = (
     "dllmc_gen_workspace_bytes", "dllmc_gen_create", "dllmc_gen_step", "dllmc_gen_read",
     "dllmc_gen_destroy", "dllmc_op_head_scratch_bytes", "dllmc_op_head", "dllmc_set_policy",
     "dllmc_set_layer_rho", "dllmc_layer_num_selected", "dllmc_probe_copy", "dllmc_probe_read", "dllmc_probe_mfma",
-    "dllmc_op_linear_static", "dllmc_op_linear_static_max_elements",
+    "dllmc_op_linear_static", "dllmc_op_linear_static_max_elements", "dllmc_op_linear_rows",
     "dllmc_pool_bytes", "dllmc_workspace_bytes_paged", "dllmc_create_paged", "dllmc_set_page_table",
     "dllmc_pool_create", "dllmc_pool_available", "dllmc_pool_alloc", "dllmc_pool_free", "dllmc_pool_destroy",
 )
@@ -127,6 +127,9 @@ def lib() -> C.CDLL:
         L.dllmc_op_linear.restype = C.c_int
         L.dllmc_op_linear.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p,
                                       C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
+        L.dllmc_op_linear_rows.restype = C.c_int
+        L.dllmc_op_linear_rows.argtypes = [C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p,
+                                           C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
         L.dllmc_op_linear_static.restype = C.c_int
         L.dllmc_op_linear_static.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p,
                                              C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
@@ -482,9 +485,9 @@ def op_linear(dtype: str, a: torch.Tensor, w: torch.Tensor, row_idx: Optional[to
     M = a.shape[0] if row_idx is None else row_idx.numel()
     out = torch.empty((M, N), dtype=torch.float32, device="cuda")
     scratch = torch.empty(M * N * 8, dtype=torch.float32, device="cuda")
-    _check(lib().dllmc_op_linear(_DTYPES[dtype][0], a.data_ptr(), _ptr(row_idx), M, w.data_ptr(), N, K,
-                                 out.data_ptr(), scratch.data_ptr(), _stream_handle()),
-           "dllmc_op_linear")
+    _check(lib().dllmc_op_linear_rows(_DTYPES[dtype][0], a.data_ptr(), a.shape[0], _ptr(row_idx), M, w.data_ptr(),
+                                      N, K, out.data_ptr(), scratch.data_ptr(), _stream_handle()),
+           "dllmc_op_linear_rows")
     return out
 
 

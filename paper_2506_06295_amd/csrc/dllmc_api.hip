@@ -682,18 +682,38 @@ int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t 
 }  // extern "C"
 
 namespace {
-// A map of a single slice may be written straight to `out`, unless that overlaps an operand, which the way
-// over the scratch buffer allows.
-bool disjoint(const float* out, const void* a, const int32_t* row_idx, const void* w, int M, int N, int K,
-              int dtype) {
+// A map of a single slice may be written straight to `out`, unless that may overlap an operand, which the way
+// over the scratch buffer allows.  a_rows: rows of `a`, 0 where the call does not say: a gathered map then reads
+// any row from `a` on, and only a result that ends before `a` is known to lie clear of it.
+bool disjoint(const float* out, const void* a, int a_rows, const int32_t* row_idx, const void* w, int M, int N,
+              int K, int dtype) {
   const uintptr_t esz = dtype == DLLMC_BF16 ? 2 : 4;
   const uintptr_t o0 = reinterpret_cast<uintptr_t>(out), o1 = o0 + static_cast<uintptr_t>(M) * N * 4;
   const auto apart = [&](const void* p, uintptr_t bytes) {
     const uintptr_t b = reinterpret_cast<uintptr_t>(p);
     return o1 <= b || o0 >= b + bytes;
   };
-  return apart(a, static_cast<uintptr_t>(M) * K * esz) && apart(w, static_cast<uintptr_t>(N) * K * esz) &&
-         (row_idx == nullptr || apart(row_idx, static_cast<uintptr_t>(M) * 4));
+  if (!apart(w, static_cast<uintptr_t>(N) * K * esz)) return false;
+  if (row_idx == nullptr) return apart(a, static_cast<uintptr_t>(M) * K * esz);
+  if (!apart(row_idx, static_cast<uintptr_t>(M) * 4)) return false;
+  if (a_rows == 0) return o1 <= reinterpret_cast<uintptr_t>(a);
+  return apart(a, static_cast<uintptr_t>(a_rows) * K * esz);
+}
+
+int op_linear(int32_t dtype, const void* a, int32_t a_rows, const int32_t* row_idx, int32_t M, const void* w,
+              int32_t N, int32_t K, float* out, float* scratch, void* hip_stream) {
+  if ((dtype != DLLMC_F32 && dtype != DLLMC_BF16) || !a || !w || !out || !scratch || M < 1 ||
+      N < 1 || K < 1)
+    return DLLMC_EINVAL;
+  (void)hipGetLastError();
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const bool direct = disjoint(out, a, a_rows, row_idx, w, M, N, K, dtype);
+  const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, scratch,
+                            static_cast<size_t>(M) * N * 8, st, direct ? out : nullptr);
+  if (S == 0) return DLLMC_ENOMEM;
+  if (S > 1 || !direct) launch_reduce_slices(scratch, S, M, N, out, st);
+  HIP_TRY(hipGetLastError());
+  return DLLMC_OK;
 }
 }  // namespace
 
@@ -747,18 +767,13 @@ int dllmc_op_vverify(int32_t dtype, const void* h, const void* wv, void* v_cache
 
 int dllmc_op_linear(int32_t dtype, const void* a, const int32_t* row_idx, int32_t M, const void* w,
                     int32_t N, int32_t K, float* out, float* scratch, void* hip_stream) {
-  if ((dtype != DLLMC_F32 && dtype != DLLMC_BF16) || !a || !w || !out || !scratch || M < 1 ||
-      N < 1 || K < 1)
-    return DLLMC_EINVAL;
-  (void)hipGetLastError();
-  hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const bool direct = disjoint(out, a, row_idx, w, M, N, K, dtype);
-  const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, scratch,
-                            static_cast<size_t>(M) * N * 8, st, direct ? out : nullptr);
-  if (S == 0) return DLLMC_ENOMEM;
-  if (S > 1 || !direct) launch_reduce_slices(scratch, S, M, N, out, st);
-  HIP_TRY(hipGetLastError());
-  return DLLMC_OK;
+  return op_linear(dtype, a, 0, row_idx, M, w, N, K, out, scratch, hip_stream);
+}
+
+int dllmc_op_linear_rows(int32_t dtype, const void* a, int32_t a_rows, const int32_t* row_idx, int32_t M,
+                         const void* w, int32_t N, int32_t K, float* out, float* scratch, void* hip_stream) {
+  if (a_rows < (row_idx == nullptr ? M : 1)) return DLLMC_EINVAL;
+  return op_linear(dtype, a, a_rows, row_idx, M, w, N, K, out, scratch, hip_stream);
 }
 
 // ---- gathered linear map for callers that cannot allocate ---------------------------------
@@ -809,7 +824,7 @@ int dllmc_op_linear_static(int32_t dtype, const void* a, const int32_t* row_idx,
   HIP_TRY(static_scratch_on_current_device(&ptr));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   // every slice the launch produces is written whole before it is read: nothing to clear
-  const bool direct = disjoint(out, a, row_idx, w, M, N, K, dtype);
+  const bool direct = disjoint(out, a, 0, row_idx, w, M, N, K, dtype);
   const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, ptr,
                             kStaticScratchFloats, st, direct ? out : nullptr);
   if (S == 0) return DLLMC_ETOOBIG;

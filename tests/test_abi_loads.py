@@ -62,3 +62,8 @@ def test_argument_checks_of_the_later_entry_points_need_no_gpu():
     assert L.dllmc_probe_read(None, 1024, None, None) == -1
     assert L.dllmc_probe_mfma(0, 0, None, None, None) == -1
     assert L.dllmc_gen_destroy(None) == -1
+    # a gathered map reads some row, an ungathered one M of them
+    some = ctypes.c_void_p(4096)
+    assert L.dllmc_op_linear_rows(1, some, 0, some, 4, some, 8, 64, some, some, None) == -1
+    assert L.dllmc_op_linear_rows(1, some, 3, None, 4, some, 8, 64, some, some, None) == -1
+    assert L.dllmc_op_linear_rows(1, some, 4, None, 4, some, 8, 64, some, None, None) == -1

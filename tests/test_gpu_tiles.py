@@ -68,3 +68,31 @@ def test_result_over_an_operand(dtype, M, N, K, over):
     ops = {**src, over: held}
     got = binding.op_linear_static(dtype, ops["a"], ops["w"], out[:M * N].view(M, N))
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 1024, 4096, 512), ("f32", 200, 512, 64)])
+@pytest.mark.parametrize("entry", ["static", "scratch"])
+def test_result_over_rows_that_are_gathered(dtype, M, N, K, entry):
+    """The rows that a gathered map reads may lie behind the first M of its operand, and the result over them."""
+    dt, code = (torch.bfloat16, 1) if dtype == "bf16" else (torch.float32, 0)
+    L = binding.lib()
+    assert L.dllmc_plan_gemm_slices(code, M, N, N, K, 8 * M * N) == 1  # a single slice, in many tiles
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * N)
+    w = (0.05 * torch.randn((N, K), generator=g, device="cuda")).to(dt)
+    more = -(-M * N * 4 // (K * w.element_size()))  # rows that the result covers
+    room = torch.empty((M + more) * K * w.element_size() // 4, device="cuda")
+    a = room.view(dt).view(M + more, K)
+    a.copy_(torch.randn((M + more, K), generator=g, device="cuda"))
+    idx = (M + torch.randperm(more, generator=g, device="cuda")[:M]).to(torch.int32)
+    want = binding.op_linear_static(dtype, a[idx.long()], w, torch.empty((M, N), device="cuda"))
+    assert torch.equal(binding.op_linear(dtype, a, w, idx), want)
+    out = room[room.numel() - M * N:].view(M, N)
+    assert out.data_ptr() >= a[M].data_ptr()
+    if entry == "static":
+        binding.op_linear_static(dtype, a, w, out, idx)
+    else:
+        scratch = torch.empty(8 * M * N, device="cuda")
+        assert L.dllmc_op_linear(code, a.data_ptr(), idx.data_ptr(), M, w.data_ptr(), N, K, out.data_ptr(),
+                                 scratch.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(out, want)
