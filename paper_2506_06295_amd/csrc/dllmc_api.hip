@@ -682,22 +682,23 @@ int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t 
 }  // extern "C"
 
 namespace {
+// no byte of [p, p + pn) lies in [q, q + qn)
+bool apart(const void* p, size_t pn, const void* q, size_t qn) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return a + pn <= b || b + qn <= a;
+}
+
 // A map of a single slice may be written straight to `out`, unless that may overlap an operand, which the way
 // over the scratch buffer allows.  a_rows: rows of `a`, 0 where the call does not say: a gathered map then reads
 // any row from `a` on, and only a result that ends before `a` is known to lie clear of it.
 bool disjoint(const float* out, const void* a, int a_rows, const int32_t* row_idx, const void* w, int M, int N,
               int K, int dtype) {
-  const uintptr_t esz = dtype == DLLMC_BF16 ? 2 : 4;
-  const uintptr_t o0 = reinterpret_cast<uintptr_t>(out), o1 = o0 + static_cast<uintptr_t>(M) * N * 4;
-  const auto apart = [&](const void* p, uintptr_t bytes) {
-    const uintptr_t b = reinterpret_cast<uintptr_t>(p);
-    return o1 <= b || o0 >= b + bytes;
-  };
-  if (!apart(w, static_cast<uintptr_t>(N) * K * esz)) return false;
-  if (row_idx == nullptr) return apart(a, static_cast<uintptr_t>(M) * K * esz);
-  if (!apart(row_idx, static_cast<uintptr_t>(M) * 4)) return false;
-  if (a_rows == 0) return o1 <= reinterpret_cast<uintptr_t>(a);
-  return apart(a, static_cast<uintptr_t>(a_rows) * K * esz);
+  const size_t row = static_cast<size_t>(K) * (dtype == DLLMC_BF16 ? 2 : 4), on = static_cast<size_t>(M) * N * 4;
+  if (!apart(out, on, w, N * row)) return false;
+  if (row_idx == nullptr) return apart(out, on, a, M * row);
+  if (!apart(out, on, row_idx, static_cast<size_t>(M) * 4)) return false;
+  if (a_rows == 0) return reinterpret_cast<uintptr_t>(out) + on <= reinterpret_cast<uintptr_t>(a);
+  return apart(out, on, a, a_rows * row);
 }
 
 int op_linear(int32_t dtype, const void* a, int32_t a_rows, const int32_t* row_idx, int32_t M, const void* w,
@@ -739,8 +740,13 @@ int dllmc_op_vverify(int32_t dtype, const void* h, const void* wv, void* v_cache
     return DLLMC_EINVAL;
   (void)hipGetLastError();
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (vverify_fused_ok(dtype, h, d, rows, wv, d_kv, d, v_cache) &&
-      vverify_part_floats(d_kv, rows) <= static_cast<size_t>(rows) * d_kv * 8) {
+  // Both ways in one launch overwrite cached rows while other tiles still read their operands: only for a cache apart
+  // from those.
+  const size_t esz = dtype == DLLMC_BF16 ? 2 : 4, cache_bytes = static_cast<size_t>(rows) * d_kv * esz;
+  const bool one_launch = vverify_part_floats(d_kv, rows) <= static_cast<size_t>(rows) * d_kv * 8 &&
+                          apart(v_cache, cache_bytes, h, static_cast<size_t>(rows) * d * esz) &&
+                          apart(v_cache, cache_bytes, wv, static_cast<size_t>(d_kv) * d * esz);
+  if (one_launch && vverify_fused_ok(dtype, h, d, rows, wv, d_kv, d, v_cache)) {
     launch_vverify_fused(h, d, rows, 0, 0, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, st);
     launch_scores_from_part(scratch, vverify_col_tiles(d_kv), rows, 0, scores, st);
     HIP_TRY(hipGetLastError());
@@ -748,8 +754,7 @@ int dllmc_op_vverify(int32_t dtype, const void* h, const void* wv, void* v_cache
   }
   // Many rows: finished in the tile kernels' epilogue, as in a step (one sequence of `rows` response rows).  4096
   // columns: 2048 rows 78 us, split contraction and row kernel 85; 1000 rows 53 and 55; 600 rows 49 and 42.
-  if (rows >= 900 && (reinterpret_cast<uintptr_t>(v_cache) & 15u) == 0 &&
-      vverify_part_floats(d_kv, rows) <= static_cast<size_t>(rows) * d_kv * 8 &&
+  if (one_launch && rows >= 900 && (reinterpret_cast<uintptr_t>(v_cache) & 15u) == 0 &&
       launch_gemm_vverify_tiles(dtype, h, d, rows, 0, rows, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, nullptr,
                                 st)) {
     launch_scores_from_part(scratch, vverify_col_tiles(d_kv), rows, 0, scores, st);

@@ -42,3 +42,23 @@ def test_vverify(rows, d, d_kv):
     want = (new * old.double()).sum(1) / (new.norm(dim=1) * old.double().norm(dim=1)).clamp(min=1e-8)
     assert float((scores.double() - want).abs().max()) < 2.0 ** -24 * np.sqrt(d_kv) * 4
     assert float(scores[rows // 2]) == 0.0
+
+
+@pytest.mark.parametrize("rows,d", [(1024, 4096), (256, 2048)])
+@pytest.mark.parametrize("over", ["h", "wv"])
+def test_cache_over_an_operand(rows, d, over):
+    """Cached rows that are also read as activations or weights, at sizes that take one launch otherwise.  Another
+    order of summation: isolated last-bit differences, as above."""
+    d_kv = d
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    h = torch.randn((rows, d), generator=g, device="cuda").bfloat16()
+    wv = (0.02 * torch.randn((d_kv, d), generator=g, device="cuda")).bfloat16()
+    old = (h if over == "h" else wv[:rows]).clone()
+    want_cache = old.clone()
+    want = binding.op_vverify("bf16", h, wv, want_cache)
+    cache = h if over == "h" else wv[:rows]
+    got = binding.op_vverify("bf16", h, wv, cache)
+    assert float((cache != want_cache).double().mean()) < 0.01
+    assert float((cache.double() - want_cache.double()).norm() / want_cache.double().norm()) < 1e-3
+    assert float((got - want).abs().max()) < 2.0 ** -8 / np.sqrt(d_kv) * 4
