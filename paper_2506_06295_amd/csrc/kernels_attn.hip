@@ -632,6 +632,8 @@ __device__ __forceinline__ void attn_walk_body(const bf16_t* __restrict__ q, int
     // along the dims spend 7 of 8 LDS cycles on conflicts.
     const int kp = threadIdx.x % 16, vch = threadIdx.x / 16;
     uint32_t* vt32 = reinterpret_cast<uint32_t*>(Vt);
+    // (paged layout: block 0 is older than the loads of the blocks after it, wherever the compiler has put the lookups)
+    if (PAGED) wait_vmcnt<4 * (kWalkStages - 2)>();
     for (int i = 0; i < nb; ++i) {
       const int stage = i % kWalkStages;
       // 4 loads per block and wavefront, kWalkStages - 1 blocks in flight: the oldest has landed
@@ -640,8 +642,7 @@ __device__ __forceinline__ void attn_walk_body(const bf16_t* __restrict__ q, int
       // everybody's loads of block i have landed, and everybody is done with block i - 1: its
       // stage and Vt may be overwritten
       __builtin_amdgcn_s_barrier();
-      // The lookups for the block after the one issued now go out first: they are then older
-      // than this block's loads, and waiting for them in the next iteration leaves those in flight.
+      // (paged layout: the compiler waits for the lookups with vmcnt(0), see k_attn_few)
       const int cr_use[2] = {cr_next[0], cr_next[1]};
       rows_of(min(blk0 + i + kWalkStages, blk1 - 1), cr_next);
       issue(cr_use, (i + kWalkStages - 1) % kWalkStages);
@@ -1109,8 +1110,10 @@ __device__ __forceinline__ void attn_few_body(const bf16_t* __restrict__ q, int 
       issue(V, cr, ring + s * 2 * kTile + kTile);
     }
     rows_of(2, cr);
+    // (paged layout: nothing keeps the row-map lookups behind the tile loads in front of them; counts that hold
+    // wherever the compiler has put them)
     if (kQLds) {
-      wait_vmcnt<32 + (PAGED ? 8 : 0)>();  // the queries
+      wait_vmcnt<32>();  // the queries: older than the 32 tile loads
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb)
@@ -1118,9 +1121,10 @@ __device__ __forceinline__ void attn_few_body(const bf16_t* __restrict__ q, int 
         for (int c = 0; c < 4; ++c)
           qf[qb][c] = __builtin_bit_cast(bf16x8, qtile[(qb * 16 + ln) * 16 + ((4 * c + lg) ^ ln)]);
     }
+    if (PAGED) wait_vmcnt<16>();  // block 0: older than the 16 loads of block 1
     for (int i = 0; i < nb; ++i) {
-      // block i has landed: block i + 1 (16 loads), and in the paged layout the lookups for block i + 2,
-      // may be in flight
+      // block i has landed: block i + 1 (16 loads), and in the paged layout the lookups of the iteration
+      // before (8, on either side of those loads), may be in flight
       wait_vmcnt<16 + (PAGED ? 8 : 0)>();
       __builtin_amdgcn_sched_barrier(0);
       uint4* kt = ring + (i & 1) * 2 * kTile;
@@ -1211,13 +1215,13 @@ __device__ __forceinline__ void attn_few_body(const bf16_t* __restrict__ q, int 
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      // this wavefront's reads of the stage are complete: block i + 2 takes it.  (The lookups of the block after
-      // go out first: they are then older than these loads, and waiting for them leaves those in flight.)
+      // This wavefront's reads of the stage are complete: block i + 2 takes it.  (Paged layout: with tile loads in
+      // flight the compiler waits for a lookup with vmcnt(0), so here block i + 1 lands first and a wavefront has one
+      // block in flight, not two.  The lookups of the block after go out last: not one of them is waited for fresh.)
       __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-      const int now[8] = {cr[0], cr[1], cr[2], cr[3], cr[4], cr[5], cr[6], cr[7]};
+      issue(K, cr, kt);
+      issue(V, cr, kt + kTile);
       rows_of(i + 3, cr);
-      issue(K, now, kt);
-      issue(V, now, kt + kTile);
     }
   }
   wait_vmcnt<0>();  // the repeated loads past the range, before the ring is overwritten

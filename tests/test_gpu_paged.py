@@ -95,6 +95,34 @@ def test_paged_context_matches_the_oracle():
     gpu.close()
 
 
+# Attention of few queries whose wavefronts split the keys: 16, 32 and 64 queries per workgroup, wavefronts with one
+# block of 32 keys, two and more, none at all, ragged last blocks, and key ranges with a merge.
+FEW = I.Config("few", T=1, d=256, H_q=4, H_kv=2, d_h=128, m=256, B=1, L_p=60, L_r=40, steps=3, rho=0.25, K_p=9, K_r=9,
+               dtype="bf16", vocab=256)
+FEW_QUERIES = [
+    FEW.replace(L_p=27, L_r=20),                                    # 16 queries: two blocks for four wavefronts
+    FEW,                                                            # one block each
+    FEW.replace(L_p=167), FEW.replace(L_p=290),                     # two, three
+    FEW.replace(B=4, H_q=32, H_kv=4, L_p=20, L_r=80, rho=0.5),      # 32 queries: one block each
+    FEW.replace(B=4, H_q=32, H_kv=4, L_p=221, L_r=80, rho=0.5),     # three and two
+    FEW.replace(B=8, H_q=32, H_kv=4, L_p=330, L_r=96, rho=0.5),     # 64 queries: four and three
+    FEW.replace(H_q=28, H_kv=4, L_p=4016, L_r=80),                  # ranges
+    FEW.replace(B=8, H_q=64, H_kv=8, L_p=130, L_r=120, rho=0.5),    # every wavefront on the same block
+]
+
+
+@pytest.mark.parametrize("cfg", FEW_QUERIES, ids=lambda c: f"B{c.B}_H{c.H_q}_q{int(c.rho * c.L_r)}_n{c.n}")
+@pytest.mark.parametrize("page_rows", [16, 5])
+def test_attention_of_few_queries_paged(cfg, page_rows):
+    ws = I.device_weights(cfg)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(cfg.n)
+    hid = [torch.randn((cfg.B, cfg.n, cfg.d), device="cuda", generator=g).to(torch.bfloat16) for _ in range(3)]
+    flat, paged = run_twins(cfg, lambda i: hid[i], range(3), paging_for(cfg, page_rows, seed=cfg.n), weights=ws)
+    flat.close()
+    paged.close()
+
+
 def test_long_prompt_at_full_width_paged():
     """L_p = 4096, L_r = 512 at the LLaDA-8B width (two layers): 72 pages of 64 rows scattered
     over a pool of 100; all four step kinds; bit-identical to the flat context."""
