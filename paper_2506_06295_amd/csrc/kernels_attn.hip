@@ -1268,12 +1268,10 @@ __device__ __forceinline__ void attn_few_body(const bf16_t* __restrict__ q, int 
     }
     if (KS == 1) {
       const float inv = 1.0f / L;
-      uint4 u;
-      u.x = pack_bf16x2(o[0] * inv, o[1] * inv);
-      u.y = pack_bf16x2(o[2] * inv, o[3] * inv);
-      u.z = pack_bf16x2(o[4] * inv, o[5] * inv);
-      u.w = pack_bf16x2(o[6] * inv, o[7] * inv);
-      *reinterpret_cast<uint4*>(out + (static_cast<size_t>(b) * Mq + iq) * d_q + a * kDH + t8) = u;
+      // (two 8-byte stores, as the other kernels: a result need not start at 16 bytes)
+      uint2* dst = reinterpret_cast<uint2*>(out + (static_cast<size_t>(b) * Mq + iq) * d_q + a * kDH + t8);
+      dst[0] = make_uint2(pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv));
+      dst[1] = make_uint2(pack_bf16x2(o[4] * inv, o[5] * inv), pack_bf16x2(o[6] * inv, o[7] * inv));
     } else {
       float* w = part + ((static_cast<size_t>(b) * Mq + iq) * H_q + a) * KS * (kDH + 2) +
                  static_cast<size_t>(ks) * (kDH + 2);
@@ -1392,8 +1390,7 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
     int QB = 0, KS = 1;  // QB 0: walk
     const int base = B * ((Mq + kQT - 1) / kQT) * H_q;
     double best = 4.5 + nblk * (base <= 256 ? 1.02 : 1.6 * ((base + 511) / 512));
-    const bool wide_out = (reinterpret_cast<uintptr_t>(out) & 15u) == 0;  // few stores 16-byte pieces
-    for (int qb = 1; qb <= 4 && wide_out; qb *= 2) {
+    for (int qb = 1; qb <= 4; qb *= 2) {
       const int tiles = B * ((Mq + 16 * qb - 1) / (16 * qb)) * H_q;
       for (int s = 1; s <= kMaxKeySplit; s *= 2) {
         if (s > 1 && (scratch == nullptr || tiles * s > 256 || 2 * s > nblk)) break;

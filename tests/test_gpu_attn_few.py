@@ -42,17 +42,26 @@ def test_attention(B, Mq, n, H_q, H_kv, split_keys):
         assert np.max(np.abs(got[b] - want)) <= 2.0 ** -8 * np.max(np.abs(want))
 
 
-def test_result_at_eight_bytes():
-    """A result that is not 16-byte aligned is written by the kernels that store 8 bytes at a time."""
-    B, Mq, n, H = 1, 33, 129, 4
+@pytest.mark.parametrize("B,Mq,n,H,split_keys", [
+    (1, 33, 129, 4, False),      # 16 queries per workgroup
+    (4, 40, 100, 32, False),     # 32
+    (8, 48, 426, 32, False),     # 64
+    (1, 51, 4608, 32, True),     # key ranges: a few workgroups do not walk all of them
+    (1, 64, 768, 32, True),      # ranges of three blocks
+    (8, 64, 250, 64, False),     # whole ranges, 64-query tiles
+])
+def test_result_at_eight_bytes(B, Mq, n, H, split_keys):
+    """A result that is not 16-byte aligned comes from the same launches: the same bits, nothing beside them."""
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
     q, k, v = (torch.randn((B, rows, H * 128), generator=g, device="cuda").bfloat16() for rows in (Mq, n, n))
-    want = binding.op_attention("bf16", q, k, v, H, H, 128, split_keys=False).float()
+    want = binding.op_attention("bf16", q, k, v, H, H, 128, split_keys=split_keys)
     room = torch.zeros(q.numel() + 8, dtype=torch.bfloat16, device="cuda")
     out = room[4:4 + q.numel()]
-    rc = binding.lib().dllmc_op_attention(1, q.data_ptr(), B, Mq, k.data_ptr(), v.data_ptr(), n, H, H, 128,
-                                          out.data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    L = binding.lib()
+    scratch = torch.empty(L.dllmc_op_attention_scratch_bytes(), dtype=torch.uint8, device="cuda") if split_keys else None
+    rc = L.dllmc_op_attention(1, q.data_ptr(), B, Mq, k.data_ptr(), v.data_ptr(), n, H, H, 128, out.data_ptr(),
+                              scratch.data_ptr() if split_keys else None, torch.cuda.current_stream().cuda_stream)
     assert rc == 0
-    assert rel_err(out.float().cpu().numpy(), want.flatten().cpu().numpy()) < 2.0 ** -8  # two roundings
+    assert torch.equal(out, want.flatten())
     assert not room[:4].any() and not room[4 + q.numel():].any()
