@@ -522,8 +522,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // ---- long key ranges -----------------------------------------------------------------
-// k_attn_walk: the same tiling and arithmetic as k_attn_mfma for key ranges of more than kPreload
-// blocks (many queries, or long sequences).  A block-by-block walk that fetches one block ahead
+// k_attn_walk: the same tiling and arithmetic as k_attn_mfma for all keys of a sequence (enough
+// workgroups to fill the chip without splitting them).  A block-by-block walk that fetches one block ahead
 // into registers is bound by the memory latency of every block; here the K and V tiles of a
 // block go from global memory straight into LDS (global_load_lds: no registers held while they
 // are in flight), kWalkStages - 1 blocks ahead.  K fragments are then read from LDS (slot =
@@ -541,8 +541,7 @@ template <bool PAGED>
 __device__ __forceinline__ void attn_walk_body(const bf16_t* __restrict__ q, int Mq,
                                                const bf16_t* __restrict__ kc,
                                                const bf16_t* __restrict__ vc, int n, int H_q,
-                                               int H_kv, int KS, bf16_t* __restrict__ out,
-                                               float* __restrict__ part,
+                                               int H_kv, bf16_t* __restrict__ out,
                                                const int* __restrict__ rmap) {
   // [stage][K tile, V tile][32 keys][16 slots of 16 bytes], then the transposed V tile.  One LDS
   // object on purpose: with two, the compiler cannot tell reads of the landed stage from the
@@ -553,8 +552,8 @@ __device__ __forceinline__ void attn_walk_body(const bf16_t* __restrict__ q, int
   bf16_t* Vt = reinterpret_cast<bf16_t*>(smem + kTileVecs);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;  // scalar
   const int ln = lane % 16, lg = lane / 16;
-  const AttnWork wk = attn_work((Mq + kQT - 1) / kQT, H_q, H_kv, KS);
-  const int a = wk.a, b = wk.b, ks = wk.ks;
+  const AttnWork wk = attn_work((Mq + kQT - 1) / kQT, H_q, H_kv, 1);
+  const int a = wk.a, b = wk.b;
   const int d_q = H_q * kDH, d_kv = H_kv * kDH;
   const int kv = a / (H_q / H_kv);
   const int i0 = wk.qtile * kQT + wave * 16;
@@ -576,111 +575,103 @@ __device__ __forceinline__ void attn_walk_body(const bf16_t* __restrict__ q, int
 #pragma unroll
   for (int db = 0; db < 8; ++db) o_acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int nblk = (n + 31) / 32;
-  const int per = (nblk + KS - 1) / KS;
-  const int blk0 = ks * per;
-  const int blk1 = min(nblk, blk0 + per);
-  const int nb = blk1 - blk0;
-
-  if (nb > 0) {
-    // loader: a tile is 8 wavefront instructions of 4 keys x 256 bytes; wavefront w issues
-    // instructions 2w and 2w+1 of the K and of the V tile.  Lane l: key 4q + l/16, slot l%16.
-    // LDS slot l%16 of a key's row holds chunk slot ^ (key % 16) of K (the 16 keys of a
-    // fragment read hit 16 slots) and chunk slot ^ (key/2 % 16) of V (so do the 16 key pairs
-    // of the transposition)
-    int lkey[2], kchunk[2], vchunk[2];
+  const int nb = (n + 31) / 32;
+  // loader: a tile is 8 wavefront instructions of 4 keys x 256 bytes; wavefront w issues
+  // instructions 2w and 2w+1 of the K and of the V tile.  Lane l: key 4q + l/16, slot l%16.
+  // LDS slot l%16 of a key's row holds chunk slot ^ (key % 16) of K (the 16 keys of a
+  // fragment read hit 16 slots) and chunk slot ^ (key/2 % 16) of V (so do the 16 key pairs
+  // of the transposition)
+  int lkey[2], kchunk[2], vchunk[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    lkey[j] = 4 * (2 * wave + j) + lane / 16;
+    kchunk[j] = (lane % 16) ^ (lkey[j] % 16);
+    vchunk[j] = (lane % 16) ^ ((lkey[j] >> 1) % 16);
+  }
+  // cache rows of this lane's two keys of a block: the rows themselves, or (paged layout) the
+  // row map's entries, looked up one block before the block's loads are issued
+  auto rows_of = [&](int blk, int (&cr)[2]) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      lkey[j] = 4 * (2 * wave + j) + lane / 16;
-      kchunk[j] = (lane % 16) ^ (lkey[j] % 16);
-      vchunk[j] = (lane % 16) ^ ((lkey[j] >> 1) % 16);
+      int kr = blk * 32 + lkey[j];
+      if (kr >= n) kr = n - 1;  // masked in the scores; any finite value will do
+      cr[j] = PAGED ? rmap[seq0 + kr] : seq0 + kr;
     }
-    // cache rows of this lane's two keys of a block: the rows themselves, or (paged layout) the
-    // row map's entries, looked up one block before the block's loads are issued
-    auto rows_of = [&](int blk, int (&cr)[2]) {
+  };
+  auto issue = [&](const int (&cr)[2], int stage) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        int kr = blk * 32 + lkey[j];
-        if (kr >= n) kr = n - 1;  // masked in the scores; any finite value will do
-        cr[j] = PAGED ? rmap[seq0 + kr] : seq0 + kr;
-      }
-    };
-    auto issue = [&](const int (&cr)[2], int stage) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const size_t row = static_cast<size_t>(cr[j]) * d_kv;
-        __builtin_amdgcn_global_load_lds(K + row + kchunk[j] * 8, &tiles[stage][0][(2 * wave + j) * 64],
-                                         16, 0, 0);
-        __builtin_amdgcn_global_load_lds(V + row + vchunk[j] * 8, &tiles[stage][1][(2 * wave + j) * 64],
-                                         16, 0, 0);
-      }
-    };
-    // blocks past the range repeat the last one (never used): the number of loads in flight
-    // stays the same in every iteration
-    int cr_next[2];
-#pragma unroll
-    for (int s = 0; s < kWalkStages - 1; ++s) {
-      rows_of(min(blk0 + s, blk1 - 1), cr_next);
-      issue(cr_next, s);
+    for (int j = 0; j < 2; ++j) {
+      const size_t row = static_cast<size_t>(cr[j]) * d_kv;
+      __builtin_amdgcn_global_load_lds(K + row + kchunk[j] * 8, &tiles[stage][0][(2 * wave + j) * 64],
+                                       16, 0, 0);
+      __builtin_amdgcn_global_load_lds(V + row + vchunk[j] * 8, &tiles[stage][1][(2 * wave + j) * 64],
+                                       16, 0, 0);
     }
-    rows_of(min(blk0 + kWalkStages - 1, blk1 - 1), cr_next);
-
-    // V transposition: thread = (key pair kp, 16-byte chunk vch); it reads the chunk of keys 2kp
-    // and 2kp+1 and writes, per dim, one 32-bit word holding both keys.  Consecutive lanes write
-    // consecutive words of a Vt row and the four chunks of a wavefront sit 16 banks apart (row
-    // stride 36 elements), so the writes are free of bank conflicts; 16-bit stores with lanes
-    // along the dims spend 7 of 8 LDS cycles on conflicts.
-    const int kp = threadIdx.x % 16, vch = threadIdx.x / 16;
-    uint32_t* vt32 = reinterpret_cast<uint32_t*>(Vt);
-    // (paged layout: block 0 is older than the loads of the blocks after it, wherever the compiler has put the lookups)
-    if (PAGED) wait_vmcnt<4 * (kWalkStages - 2)>();
-    for (int i = 0; i < nb; ++i) {
-      const int stage = i % kWalkStages;
-      // 4 loads per block and wavefront, kWalkStages - 1 blocks in flight: the oldest has landed
-      // (paged layout: the two row-map lookups of the block after those are in flight as well)
-      wait_vmcnt<4 * (kWalkStages - 2) + (PAGED ? 2 : 0)>();
-      // everybody's loads of block i have landed, and everybody is done with block i - 1: its
-      // stage and Vt may be overwritten
-      __builtin_amdgcn_s_barrier();
-      // (paged layout: the compiler waits for the lookups with vmcnt(0), see k_attn_few)
-      const int cr_use[2] = {cr_next[0], cr_next[1]};
-      rows_of(min(blk0 + i + kWalkStages, blk1 - 1), cr_next);
-      issue(cr_use, (i + kWalkStages - 1) % kWalkStages);
-      {
-        const uint4 r0 = tiles[stage][1][(2 * kp) * 16 + (vch ^ kp)];
-        const uint4 r1 = tiles[stage][1][(2 * kp + 1) * 16 + (vch ^ kp)];
-        const uint32_t e0[4] = {r0.x, r0.y, r0.z, r0.w}, e1[4] = {r1.x, r1.y, r1.z, r1.w};
+  };
+  // blocks past the range repeat the last one (never used): the number of loads in flight
+  // stays the same in every iteration
+  int cr_next[2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int dim = vch * 8 + 2 * j;
-          vt32[(dim * kVtStrideW) / 2 + kp] = (e0[j] & 0xffffu) | (e1[j] << 16);
-          vt32[((dim + 1) * kVtStrideW) / 2 + kp] = (e0[j] >> 16) | (e1[j] & 0xffff0000u);
-        }
-      }
-      // K fragments of this wavefront: key sb*16 + ln, dims 32c + 8lg .. +8 = chunk 4c + lg
-      bf16x8 kf[2][4];
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          kf[sb][c] = __builtin_bit_cast(bf16x8, tiles[stage][0][(sb * 16 + ln) * 16 + ((4 * c + lg) ^ ln)]);
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // LDS writes of Vt done (lgkmcnt 0); global loads stay in flight
-      __builtin_amdgcn_s_barrier();
-      attn_block<kVtStrideW, false>(kf, qf, Vt, (blk0 + i) * 32, n, ln, lg, sl2e, m_run, l_run, o_acc);
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // the repeated loads past the range, before the LDS goes away
+  for (int s = 0; s < kWalkStages - 1; ++s) {
+    rows_of(min(s, nb - 1), cr_next);
+    issue(cr_next, s);
   }
-  attn_finish(o_acc, m_run, l_run, i0 + ln, Mq, b, a, ks, KS, H_q, lg, out, part);
+  rows_of(min(kWalkStages - 1, nb - 1), cr_next);
+
+  // V transposition: thread = (key pair kp, 16-byte chunk vch); it reads the chunk of keys 2kp
+  // and 2kp+1 and writes, per dim, one 32-bit word holding both keys.  Consecutive lanes write
+  // consecutive words of a Vt row and the four chunks of a wavefront sit 16 banks apart (row
+  // stride 36 elements), so the writes are free of bank conflicts; 16-bit stores with lanes
+  // along the dims spend 7 of 8 LDS cycles on conflicts.
+  const int kp = threadIdx.x % 16, vch = threadIdx.x / 16;
+  uint32_t* vt32 = reinterpret_cast<uint32_t*>(Vt);
+  // (paged layout: block 0 is older than the loads of the blocks after it, wherever the compiler has put the lookups)
+  if (PAGED) wait_vmcnt<4 * (kWalkStages - 2)>();
+  for (int i = 0; i < nb; ++i) {
+    const int stage = i % kWalkStages;
+    // 4 loads per block and wavefront, kWalkStages - 1 blocks in flight: the oldest has landed
+    // (paged layout: the two row-map lookups of the block after those are in flight as well)
+    wait_vmcnt<4 * (kWalkStages - 2) + (PAGED ? 2 : 0)>();
+    // everybody's loads of block i have landed, and everybody is done with block i - 1: its
+    // stage and Vt may be overwritten
+    __builtin_amdgcn_s_barrier();
+    // (paged layout: the compiler waits for the lookups with vmcnt(0), see k_attn_few)
+    const int cr_use[2] = {cr_next[0], cr_next[1]};
+    rows_of(min(i + kWalkStages, nb - 1), cr_next);
+    issue(cr_use, (i + kWalkStages - 1) % kWalkStages);
+    {
+      const uint4 r0 = tiles[stage][1][(2 * kp) * 16 + (vch ^ kp)];
+      const uint4 r1 = tiles[stage][1][(2 * kp + 1) * 16 + (vch ^ kp)];
+      const uint32_t e0[4] = {r0.x, r0.y, r0.z, r0.w}, e1[4] = {r1.x, r1.y, r1.z, r1.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int dim = vch * 8 + 2 * j;
+        vt32[(dim * kVtStrideW) / 2 + kp] = (e0[j] & 0xffffu) | (e1[j] << 16);
+        vt32[((dim + 1) * kVtStrideW) / 2 + kp] = (e0[j] >> 16) | (e1[j] & 0xffff0000u);
+      }
+    }
+    // K fragments of this wavefront: key sb*16 + ln, dims 32c + 8lg .. +8 = chunk 4c + lg
+    bf16x8 kf[2][4];
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        kf[sb][c] = __builtin_bit_cast(bf16x8, tiles[stage][0][(sb * 16 + ln) * 16 + ((4 * c + lg) ^ ln)]);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // LDS writes of Vt done (lgkmcnt 0); global loads stay in flight
+    __builtin_amdgcn_s_barrier();
+    attn_block<kVtStrideW, false>(kf, qf, Vt, i * 32, n, ln, lg, sl2e, m_run, l_run, o_acc);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // the repeated loads past the range, before the LDS goes away
+  attn_finish(o_acc, m_run, l_run, i0 + ln, Mq, b, a, 0, 1, H_q, lg, out, nullptr);
 }
 
 template <bool PAGED>
 __global__ __launch_bounds__(256) void k_attn_walk(const bf16_t* __restrict__ q, int Mq,
                                                    const bf16_t* __restrict__ kc,
                                                    const bf16_t* __restrict__ vc, int n, int H_q,
-                                                   int H_kv, int KS, bf16_t* __restrict__ out,
-                                                   float* __restrict__ part,
+                                                   int H_kv, bf16_t* __restrict__ out,
                                                    const int* __restrict__ rmap) {
-  attn_walk_body<PAGED>(q, Mq, kc, vc, n, H_q, H_kv, KS, out, part, rmap);
+  attn_walk_body<PAGED>(q, Mq, kc, vc, n, H_q, H_kv, out, rmap);
 }
 
 // ---- many queries --------------------------------------------------------------------
@@ -1410,6 +1401,8 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
     }
 #define DLLMC_ATTN(KERNEL, GRID) \
   hipLaunchKernelGGL(KERNEL, dim3(GRID), dim3(256), 0, st, qq, Mq, kk, vv, n, H_q, H_kv, KS, oo, scratch, rmap)
+#define DLLMC_ATTN_WALK(KERNEL) \
+  hipLaunchKernelGGL(KERNEL, dim3(base), dim3(256), 0, st, qq, Mq, kk, vv, n, H_q, H_kv, oo, rmap)
 #define DLLMC_ATTN_FEW(Q)                                                                        \
   do {                                                                                           \
     const int grid_ = B * ((Mq + 16 * Q - 1) / (16 * Q)) * H_q * KS;                              \
@@ -1417,12 +1410,13 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
   } while (0)
     switch (QB) {
       case -1: if (rmap) DLLMC_ATTN(k_attn_mfma<true>, base * KS); else DLLMC_ATTN(k_attn_mfma<false>, base * KS); break;
-      case 0: if (rmap) DLLMC_ATTN(k_attn_walk<true>, base); else DLLMC_ATTN(k_attn_walk<false>, base); break;
+      case 0: if (rmap) DLLMC_ATTN_WALK(k_attn_walk<true>); else DLLMC_ATTN_WALK(k_attn_walk<false>); break;
       case 1: DLLMC_ATTN_FEW(1); break;
       case 2: DLLMC_ATTN_FEW(2); break;
       default: DLLMC_ATTN_FEW(4); break;
     }
 #undef DLLMC_ATTN_FEW
+#undef DLLMC_ATTN_WALK
 #undef DLLMC_ATTN
     if (KS > 8)
       hipLaunchKernelGGL(k_attn_merge<kMaxKeySplit>, dim3(B * Mq * H_q), dim3(64), 0, st, scratch, KS,
