@@ -159,7 +159,7 @@ __global__ __launch_bounds__(64 * kFW, 2) void k_attn_f32(const T* __restrict__ 
       for (int c = 0; c < C / 4; ++c) t.v[j][c] = *reinterpret_cast<const raw_t*>(vr + c * 4);
     }
   };
-  auto use = [&](int blk, const Block& t) {
+  auto use = [&](int blk, Block& t) {
     f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0;  // (two chains: an instruction may not wait for its predecessor)
 #pragma unroll
     for (int c = 0; c < C; c += 2) {
@@ -192,6 +192,17 @@ __global__ __launch_bounds__(64 * kFW, 2) void k_attn_f32(const T* __restrict__ 
     for (int e = 0; e < 4; ++e) {
       p[e] = expf(p[e] - m_use);
       l_run += p[e];
+    }
+    // The values of masked keys do not count, not even an infinity times 0.  (40 queries, 1001 keys, 8 heads of 128:
+    // 28.0 us without this, 28.9 with it; selects in the product 31.4, a row of zeros to load instead 35.7, the last
+    // block as a variant of its own 29.7.)
+    if (blk * 16 + 16 > n) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (blk * 16 + 4 * lg + j >= n) {
+#pragma unroll
+          for (int c = 0; c < C / 4; ++c) t.v[j][c] = raw_t{};
+        }
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j)

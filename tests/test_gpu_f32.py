@@ -93,6 +93,21 @@ def test_attention(dtype, B, Mq, n, H_q, H_kv, d_h):
         assert rel_err(got[b], want) < bar
 
 
+@pytest.mark.parametrize("dtype,n,d_h", [("f32", 1, 64), ("f32", 37, 128), ("f32", 48, 64), ("bf16", 65, 64)])
+def test_attention_non_finite_values_stay_in_their_columns(dtype, n, d_h):
+    """Values of the last key among others; no key past it may count, not even times zero."""
+    r = np.random.default_rng(n)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    q, k, v = (torch.from_numpy(0.3 * r.standard_normal((1, rows, 2 * d_h)).astype(np.float32)).to(t) for rows in (19, n, n))
+    v[0, n - 1, 3], v[0, n - 1, d_h + 5], v[0, 0, 7], v[0, n // 2, 9] = float("inf"), float("-inf"), float("nan"), float("inf")
+    got = binding.op_attention(dtype, q.cuda(), k.cuda(), v.cuda(), 2, 2, d_h).float().cpu().numpy()[0]
+    want = O.attention(*(x[0].double().numpy() for x in (q, k, v)), 2, 2, d_h)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    fin = np.isfinite(want)
+    assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True)
+    assert np.allclose(got[fin], want[fin], rtol=2.0 ** -7 if dtype == "bf16" else 1e-5, atol=1e-5 if dtype == "f32" else 1e-3)
+
+
 @pytest.mark.parametrize("cfg", [MINI_LLADA.replace(dtype="f32"), MINI_DREAM.replace(dtype="f32", m=2436),
                                  MINI_LLADA.replace(dtype="f32", B=1, L_p=20, L_r=17, m=3000)],
                          ids=["mini_llada", "mini_dream", "few_rows"])
