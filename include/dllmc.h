@@ -179,7 +179,7 @@ int32_t dllmc_layer_num_selected(const dllmc_ctx* ctx, int32_t layer);
  *              first *n_sel entries are the response-row indices (0-based inside the
  *              response) that were recomputed, ascending; the rest is left untouched.
  *   n_sel      host out, may be NULL: floor(rho*L_r) on adaptive steps, L_r on refresh steps.
- * hidden_in and hidden_out may alias. */
+ * hidden_in and hidden_out may be the same buffer or overlap. */
 int dllmc_step(dllmc_ctx* ctx, const void* hidden_in, int32_t step_idx, void* hidden_out,
                int32_t* sel_idx, int32_t* n_sel);
 

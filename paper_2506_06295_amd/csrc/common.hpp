@@ -266,7 +266,8 @@ struct RowKernelArgs {
 // rows_R / inv of the refreshed prompt rows (first == 0: compact index b * recomputed_per_seq + pos) and, with
 // refresh_response, of the response rows behind them; sel_idx != nullptr (response refresh):
 // sel_idx[l][b][j] = j.  prompt_out != nullptr: hidden_out[b][t] = prompt_out[b][t] for all prompt rows
-// (hidden_out may be hidden_in: then first == L_p and those rows are not read).
+// (hidden_out may be hidden_in: then first == L_p and those rows are not read; buffers that overlap otherwise take
+// two launches, the prompt rows, with Mc == 0, at the end of the step).
 struct PrologueArgs {
   int B, Mc, first, per_seq, recomputed_per_seq, refresh_response, T;
   int *carried, *rows_R, *inv, *sel_idx;

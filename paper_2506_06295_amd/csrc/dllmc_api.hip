@@ -14,6 +14,11 @@
 using namespace dllmc;
 
 namespace {
+// no byte of [p, p + pn) lies in [q, q + qn)
+bool apart(const void* p, size_t pn, const void* q, size_t qn) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return a + pn <= b || b + qn <= a;
+}
 
 thread_local int g_last_hip_error = 0;
 
@@ -420,12 +425,18 @@ int dllmc_step(dllmc_ctx* c, const void* hidden_in, int32_t step_idx, void* hidd
   auto gemm_bytes = [&](double M, double N, double K) { return (N * K + M * K) * esz + M * N * 4.0; };
   auto gemm_flops = [&](double M, double N, double K) { return 2.0 * M * N * K; };
 
+  // The prompt rows of the output may be written first, unless they could lie over rows of an input that is still
+  // read: buffers that overlap without being the same (the same one's prompt rows are not read then).
+  const size_t io_bytes = static_cast<size_t>(B) * n * d * c->lay.esz;
+  const bool copy_last = !P && hidden_in != hidden_out && !apart(hidden_in, io_bytes, hidden_out, io_bytes);
+  const double copy_bytes = P ? 0.0 : 2.0 * B * L_p * d * esz;
+  PrologueArgs pa{B, Mc, P ? 0 : L_p, carried_per_seq, per_seq_of(0), Rf ? 1 : 0, T,
+                  carried, rows_R, inv, Rf ? sel_idx : nullptr};
   {
     // the stream and first norm of the carried rows, this step's row lists, and the prompt rows of the output
-    Timed t(c, DLLMC_KC_ROW, Mc * d * (2.0 * esz + 4.0) + (P ? 0.0 : 2.0 * B * L_p * d * esz), 0);
-    const PrologueArgs pa{B, Mc, P ? 0 : L_p, carried_per_seq, per_seq_of(0), Rf ? 1 : 0, T,
-                          carried, rows_R, inv, Rf ? sel_idx : nullptr};
-    launch_step_prologue(ra, pa, hidden_in, c->layers[0].attn_norm_g, x, h, P ? nullptr : prompt_out, hidden_out, st);
+    Timed t(c, DLLMC_KC_ROW, Mc * d * (2.0 * esz + 4.0) + (copy_last ? 0.0 : copy_bytes), 0);
+    launch_step_prologue(ra, pa, hidden_in, c->layers[0].attn_norm_g, x, h, P || copy_last ? nullptr : prompt_out,
+                         hidden_out, st);
   }
 
   for (int l = 0; l < T; ++l) {
@@ -563,6 +574,11 @@ int dllmc_step(dllmc_ctx* c, const void* hidden_in, int32_t step_idx, void* hidd
                            (last && P) ? prompt_out : nullptr, st, rmap);
     }
   }
+  if (copy_last) {
+    Timed t(c, DLLMC_KC_ROW, copy_bytes, 0);
+    pa.Mc = 0;  // nothing but the prompt rows
+    launch_step_prologue(ra, pa, hidden_in, c->layers[0].attn_norm_g, x, h, prompt_out, hidden_out, st);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e);
   if (!Rf) c->have_scores = true;
@@ -682,12 +698,6 @@ int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t 
 }  // extern "C"
 
 namespace {
-// no byte of [p, p + pn) lies in [q, q + qn)
-bool apart(const void* p, size_t pn, const void* q, size_t qn) {
-  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
-  return a + pn <= b || b + qn <= a;
-}
-
 // A map of a single slice may be written straight to `out`, unless that may overlap an operand, which the way
 // over the scratch buffer allows.  a_rows: rows of `a`, 0 where the call does not say: a gathered map then reads
 // any row from `a` on, and only a result that ends before `a` is known to lie clear of it.

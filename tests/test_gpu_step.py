@@ -287,6 +287,28 @@ def test_bit_reproducible_across_runs():
         assert torch.equal(o1, o2) and torch.equal(s1, s2)
 
 
+@pytest.mark.parametrize("cfg", [MINI_LLADA, I.CONFIGS["toy"]], ids=lambda c: c.name)
+@pytest.mark.parametrize("rows_in,rows_out", [(0, 0), (0, 1), (1, 0), (0, 90), (130, 0)])
+def test_input_and_output_in_one_buffer(cfg, rows_in, rows_out):
+    """The same buffer, and buffers that overlap by all but some rows either way: every step kind gives the bits of
+    separate buffers."""
+    ws = I.all_weights(cfg)
+    sched = I.TokenSchedule(cfg, stress=True)
+    apart, shared = (PU.make_pair(cfg, ws, K_p=4, K_r=3)[0] for _ in range(2))
+    count = cfg.B * cfg.n
+    room = torch.empty((count + max(rows_in, rows_out), cfg.d), dtype=PU.torch_dtype(cfg), device="cuda")
+    hin, hout = (room[r:r + count].view(cfg.B, cfg.n, cfg.d) for r in (rows_in, rows_out))
+    for i in range(6):  # full, adaptive, adaptive, response, prompt, adaptive
+        hid = PU.to_device(cfg, sched.hidden_in(i))
+        want, _ = apart.step(hid, i)
+        hin.copy_(hid)
+        shared.step(hin, i, hidden_out=hout)
+        torch.cuda.synchronize()
+        assert torch.equal(hout, want), i
+    apart.close()
+    shared.close()
+
+
 def test_call_order_and_argument_errors():
     cfg = I.CONFIGS["toy"]
     ws = I.all_weights(cfg)
