@@ -271,8 +271,9 @@ struct RowKernelArgs {
 struct PrologueArgs {
   int B, Mc, first, per_seq, recomputed_per_seq, refresh_response, T;
   int *carried, *rows_R, *inv, *sel_idx;
+  int copy_pieces;  // set by the launcher: prompt rows copied four elements at a time
 };
-void launch_step_prologue(const RowKernelArgs& a, const PrologueArgs& pa, const void* hidden_in,
+void launch_step_prologue(const RowKernelArgs& a, PrologueArgs pa, const void* hidden_in,
                           const void* gain, float* x, void* h, const void* prompt_out, void* hidden_out,
                           hipStream_t st);
 

@@ -431,7 +431,7 @@ int dllmc_step(dllmc_ctx* c, const void* hidden_in, int32_t step_idx, void* hidd
   const bool copy_last = !P && hidden_in != hidden_out && !apart(hidden_in, io_bytes, hidden_out, io_bytes);
   const double copy_bytes = P ? 0.0 : 2.0 * B * L_p * d * esz;
   PrologueArgs pa{B, Mc, P ? 0 : L_p, carried_per_seq, per_seq_of(0), Rf ? 1 : 0, T,
-                  carried, rows_R, inv, Rf ? sel_idx : nullptr};
+                  carried, rows_R, inv, Rf ? sel_idx : nullptr, 0};
   {
     // the stream and first norm of the carried rows, this step's row lists, and the prompt rows of the output
     Timed t(c, DLLMC_KC_ROW, Mc * d * (2.0 * esz + 4.0) + (copy_last ? 0.0 : copy_bytes), 0);

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kThreads) void k_step_prologue(
     const int r = i - a.Mc, b = r / L_p, t = r % L_p;
     const T* s = prompt_out + (static_cast<size_t>(b) * L_p + t) * d;
     T* o = hidden_out + (static_cast<size_t>(b) * n + t) * d;
-    if (V == 4) {  // 4 elements of T: 8 or 16 bytes
+    if (a.copy_pieces) {  // 4 elements of T: 8 or 16 bytes
       typedef typename std::conditional<sizeof(T) == 4, uint4, uint2>::type piece;
       for (int c = threadIdx.x * 4; c < d; c += kThreads * 4)
         *reinterpret_cast<piece*>(o + c) = *reinterpret_cast<const piece*>(s + c);
@@ -617,12 +617,14 @@ inline bool vec_ok(int width, std::initializer_list<const void*> ptrs) {
     else hipLaunchKernelGGL((KERNEL<T, 1>), grid, dim3(kThreads), 0, st, __VA_ARGS__);        \
   } while (0)
 
-void launch_step_prologue(const RowKernelArgs& a, const PrologueArgs& pa, const void* hidden_in,
+void launch_step_prologue(const RowKernelArgs& a, PrologueArgs pa, const void* hidden_in,
                           const void* gain, float* x, void* h, const void* prompt_out, void* hidden_out,
                           hipStream_t st) {
   const int copies = prompt_out != nullptr ? pa.B * a.L_p : 0;
   if (pa.Mc + copies <= 0) return;
-  const bool vec = vec_ok(a.d, {hidden_in, gain, x, h, prompt_out, hidden_out});
+  // (the output's address decides how its rows are copied, not how the input is read and summed)
+  const bool vec = vec_ok(a.d, {hidden_in, gain, x, h});
+  pa.copy_pieces = vec_ok(a.d, {prompt_out, hidden_out});
   const dim3 grid(pa.Mc + copies);
   if (a.dtype == 1) {
     DLLMC_ROW_LAUNCH(k_step_prologue, bf16_t, vec, grid, st, P<bf16_t>(hidden_in), pa, a.n, a.L_p, a.d, a.eps,

@@ -309,6 +309,26 @@ def test_input_and_output_in_one_buffer(cfg, rows_in, rows_out):
     shared.close()
 
 
+@pytest.mark.parametrize("cfg", [MINI_LLADA.replace(T=1), I.CONFIGS["toy"].replace(T=1)], ids=lambda c: c.name)
+def test_output_at_any_address(cfg):
+    """Where the output starts decides how it is stored, not how the input is read and summed: the same bits (one
+    layer: between layers the last row kernel's norm does depend on it)."""
+    ws = I.all_weights(cfg)
+    sched = I.TokenSchedule(cfg, stress=True)
+    plain, odd = (PU.make_pair(cfg, ws, K_p=4, K_r=3)[0] for _ in range(2))
+    room = torch.zeros(cfg.B * cfg.n * cfg.d + 2, dtype=PU.torch_dtype(cfg), device="cuda")
+    hout = room[1:-1].view(cfg.B, cfg.n, cfg.d)
+    for i in range(6):
+        hid = PU.to_device(cfg, sched.hidden_in(i))
+        want, _ = plain.step(hid, i)
+        odd.step(hid, i, hidden_out=hout)
+        torch.cuda.synchronize()
+        assert torch.equal(hout, want), i
+        assert not room[0] and not room[-1]
+    plain.close()
+    odd.close()
+
+
 def test_call_order_and_argument_errors():
     cfg = I.CONFIGS["toy"]
     ws = I.all_weights(cfg)
