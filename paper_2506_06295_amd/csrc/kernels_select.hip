@@ -233,6 +233,7 @@ __global__ __launch_bounds__(kThreads) void k_select_regs(float* scores, int L, 
     const int j = r * kWave + lane;
     key[r] = j >= L ? 0xFFFFFFFFu : part != nullptr ? keys[j] : order_key(s[j]);
   }
+  __syncthreads();  // everybody has the scores: the indices may be written over them
   const auto below = [&](uint32_t t) {
     int c = 0;
 #pragma unroll

@@ -29,3 +29,16 @@ def test_select(L, values):
     for k in sorted({0, 1, L // 4, L // 2, L - 1, L}):
         got = binding.op_select(torch.from_numpy(s).cuda(), k).cpu().numpy()
         assert np.array_equal(got, expected(s, k)), (L, k)
+
+
+@pytest.mark.parametrize("L", [40, 64, 200, 512, 900])
+def test_indices_over_the_scores(L):
+    """One sequence's indices may take the place of its scores."""
+    r = np.random.default_rng(L)
+    for k in (1, L // 3, L):
+        s = r.uniform(-1, 1, (1, L)).astype(np.float32)
+        room = torch.from_numpy(s).cuda()
+        rc = binding.lib().dllmc_op_select(room.data_ptr(), 1, L, k, room.data_ptr(),
+                                           torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        assert np.array_equal(room.view(torch.int32).cpu().numpy()[:, :k], expected(s, k)), (L, k)
