@@ -307,6 +307,13 @@ int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t 
 int32_t dllmc_plan_gemm_slices(int32_t dtype, int32_t M, int32_t N, int32_t N0, int32_t K,
                                size_t capacity_floats);
 
+/* Host-only: the number of key ranges of a bf16 attention of Mq < 128 queries per sequence with head width 128
+ * (split_keys: with a scratch buffer).  *queries (may be NULL): queries per workgroup of the kernel whose
+ * wavefronts split the keys, 16, 32 or 64; 0: 64 queries whose wavefronts walk all keys together; -1: the
+ * kernel that fetches ranges of three blocks of 32 keys at once. */
+int32_t dllmc_plan_attention(int32_t B, int32_t Mq, int32_t n, int32_t H_q, int32_t H_kv, int32_t split_keys,
+                             int32_t* queries);
+
 /* ---- single operations of the step, exposed for unit parity tests and micro-benchmarks ---- */
 
 /* Bottom-k selection (Sec. 3.2.2): for each of B rows of `scores` (device float32 [B, L]),

@@ -377,6 +377,10 @@ void launch_scores_from_part(const float* part, int n_ct, int count, int metric,
 bool attention_supported(int dtype, int d_h, int n);
 // scratch (may be null): attention_scratch_floats() floats for the split-key partial results.
 size_t attention_scratch_floats();
+// bf16, head width 128, fewer than 128 queries: QB 1 / 2 / 4 = k_attn_few with 16 QB queries per workgroup, 0 = k_attn_walk,
+// -1 = k_attn_mfma; KS key ranges (split_keys: the caller has scratch)
+struct FewPlan { int QB, KS; };
+FewPlan plan_attention_few(int B, int Mq, int n, int H_q, int H_kv, bool split_keys);
 // rmap (paged layout): key row j of sequence b is row rmap[b * n + j] of k_cache / v_cache.
 void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cache,
                       const void* v_cache, int n, int H_q, int H_kv, int d_h, void* out,

@@ -686,6 +686,14 @@ int32_t dllmc_plan_gemm_slices(int32_t dtype, int32_t M, int32_t N, int32_t N0, 
   return gemm_plan_slices(dtype, M, N, N0, K, capacity_floats);
 }
 
+int32_t dllmc_plan_attention(int32_t B, int32_t Mq, int32_t n, int32_t H_q, int32_t H_kv, int32_t split_keys,
+                             int32_t* queries) {
+  if (B < 1 || Mq < 1 || Mq > 127 || n < 1 || H_kv < 1 || H_q < H_kv || H_q % H_kv) return DLLMC_EINVAL;
+  const FewPlan p = plan_attention_few(B, Mq, n, H_q, H_kv, split_keys != 0);
+  if (queries) *queries = p.QB > 0 ? 16 * p.QB : p.QB;
+  return p.KS;
+}
+
 int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t target_wg,
                           int32_t tile_min_m, int32_t fat_min_m, int32_t tall_max_m) {
   (void)nw; (void)nw_dual; (void)tall_max_m;  // shapes of a kernel that is gone

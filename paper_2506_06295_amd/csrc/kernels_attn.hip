@@ -1343,6 +1343,45 @@ bool attention_supported(int dtype, int d_h, int n) {
   return static_cast<size_t>(d_h + n) * sizeof(float) <= 60 * 1024;
 }
 
+// Fewer than 128 queries per sequence: three kernels, by estimated time in us, fitted to 3336 shapes (1 to 16 sequences, 1
+// to 127 queries, 50 to 4608 keys, heads 32, 28/4, 7/1 and 8) that were timed with every kernel and number of key
+// ranges, on keys and values that mostly no cache holds.  MB: keys and values; P: MB of partial results, written and read.
+//   few<QB>, KS ranges   1.4 + rounds of 256 workgroups (one per CU) x (2.8 / 3.85 / 7.0 + 1.07 / 1.37 / 2.08 per 32-key block
+//                        of a wavefront's walk, at QB = 1 / 2 / 4) + MB / 14, and 2.1 + P / 4.3 for a merge launch
+//   walk, whole ranges   4.5 + 1.0 per block + MB / 14 for up to 256 workgroups (64 queries each, four wavefronts on the
+//                        same block), 1.4 per block for 512, which share the CUs; again for every further 512
+//   mfma                 8.0 + P / 5 with its merge launch: ranges of three blocks, everything fetched at once; only while
+//                        they do not share CUs
+// The choice is on average 0.7 % slower than the best of all (at worst 30 %: 10 us), and nowhere more than 5 % slower than
+// mfma and walk alone with up to 512 workgroups, which were 36 % slower on average.  (A first estimate counted no fixed
+// time per round of k_attn_few and gave it launches of several rounds that belong to walk: 16 sequences, 100 queries, 100
+// keys, 28/4 heads 41.5 us, now 21.5; 8, 51, 300, 32 22.2 -> 17.2; 2, 20, 2500, 32 24.3 -> 22.)
+FewPlan plan_attention_few(int B, int Mq, int n, int H_q, int H_kv, bool split_keys) {
+  const int nblk = (n + 31) / 32;
+  const double t_kv = 4.0 * B * n * H_kv * kDH / 1e6 / 14.0;
+  const double mb_part = static_cast<double>(B) * Mq * H_q * (kDH + 2) * 8.0 / 1e6;  // per key range
+  const int base = B * ((Mq + kQT - 1) / kQT) * H_q, rem = base % 512;
+  FewPlan best{0, 1};  // walk
+  double t_best = base / 512 * (4.5 + 1.4 * nblk) + t_kv;
+  if (rem > 0) t_best += 4.5 + nblk * (rem <= 256 ? 1.0 : 1.4);
+  double margin = 0.97;  // (walk is taken at a tie: its estimate strays less)
+  for (int qb = 1; qb <= 4; qb *= 2) {
+    const int tiles = B * ((Mq + 16 * qb - 1) / (16 * qb)) * H_q;
+    const double start = qb == 1 ? 2.8 : qb == 2 ? 3.85 : 7.0, block = qb == 1 ? 1.07 : qb == 2 ? 1.37 : 2.08;
+    for (int s = 1; s <= kMaxKeySplit; s *= 2) {
+      if (s > 1 && (!split_keys || tiles * s > 256 || 2 * s > nblk)) break;
+      const int blocks = ((nblk + s - 1) / s + 3) / 4;
+      double t = 1.4 + (tiles * s + 255) / 256 * (start + blocks * block) + t_kv;
+      if (s > 1) t += 2.1 + s * mb_part / 4.3;
+      if (t < t_best * margin) { t_best = t; best = FewPlan{qb, s}; margin = 0.98; }
+    }
+  }
+  const int ks3 = (nblk + kPreload - 1) / kPreload;
+  if (split_keys && ks3 >= 2 && ks3 <= kMaxKeySplit && base * ks3 <= 256 && 8.0 + ks3 * mb_part / 5.0 < t_best)
+    best = FewPlan{-1, ks3};
+  return best;
+}
+
 void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cache,
                       const void* v_cache, int n, int H_q, int H_kv, int d_h, void* out,
                       float* scratch, hipStream_t st, const int* rmap) {
@@ -1374,42 +1413,8 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
         hipLaunchKernelGGL(k_attn_merge<8>, dim3(B * Mq * H_q), dim3(64), 0, st, scratch, KS, oo);
       return;
     }
-    // Fewer than 128 queries.  Three kernels, by estimated time in us (constants fitted to the launches below,
-    // on keys and values that no cache holds):
-    //   few<QB>, KS ranges   4.5, one workgroup per CU, 1.35 / 1.6 / 2.4 per 32-key block of a wavefront's walk at
-    //                        QB = 1 / 2 / 4, and 4.5 plus the partial results' traffic for a merge launch
-    //   walk, whole ranges   4.5, 64 queries per workgroup and four wavefronts on the same block: 1.02 per block,
-    //                        1.6 for two workgroups that share a CU
-    //   mfma                 ranges of three blocks, everything fetched at once: 8.3 with its merge launch, 3.5 more
-    //                        by the time it fills the CUs; beyond that it takes 20 (two workgroups per CU)
-    // Measured (B, queries, keys, heads / KV heads; before: mfma or walk with up to 512 workgroups -> now):
-    //   2, 60, 700, 32 18.4 -> 12.9;  4, 30, 600, 28/4 20.6 -> 10.0;  1, 127, 768, 32 20.7 -> 12.9 (few<1>);
-    //   1, 62, 1254, 28/4 20.2 -> 13.8;  1, 51, 4608, 32 29.1 -> 25.7;  1, 20, 4096, 28/4 20.1 -> 14.7 (few<2>, 4
-    //   to 8 ranges);  4, 100, 4000, 32 135 -> 82 (few<4>);  1, 64, 768, 32 11.8 with mfma, 13.3 with few<1>;
-    //   16, 64, 768, 32 44.7 with walk, 52 with few<4>.
-    const int nblk = (n + 31) / 32;
-    const double kv_us = 2.0 * B * n * H_kv * kDH * 2.0 / 1e6;  // MB of keys and values
-    int QB = 0, KS = 1;  // QB 0: walk
-    const int base = B * ((Mq + kQT - 1) / kQT) * H_q;
-    double best = 4.5 + nblk * (base <= 256 ? 1.02 : 1.6 * ((base + 511) / 512));
-    for (int qb = 1; qb <= 4; qb *= 2) {
-      const int tiles = B * ((Mq + 16 * qb - 1) / (16 * qb)) * H_q;
-      for (int s = 1; s <= kMaxKeySplit; s *= 2) {
-        if (s > 1 && (scratch == nullptr || tiles * s > 256 || 2 * s > nblk)) break;
-        const int blocks = ((nblk + s - 1) / s + 3) / 4;
-        double t = (tiles * s + 255) / 256 * blocks * (qb == 1 ? 1.35 : qb == 2 ? 1.6 : 2.4) + (qb == 4 ? 2.5 : 0.0);
-        if (t < kv_us / 4.0) t = kv_us / 4.0;
-        t += 4.5;
-        if (s > 1) t += 4.5 + static_cast<double>(B) * Mq * H_q * s * (kDH + 2) * 4.0 * 2.0 / 5e6;
-        if (t < best * 0.98) { best = t; QB = qb; KS = s; }
-      }
-    }
-    const int ks3 = (nblk + kPreload - 1) / kPreload;
-    if (scratch != nullptr && ks3 >= 2 && ks3 <= kMaxKeySplit && base * ks3 <= 256 &&
-        8.3 + 3.5 * base * ks3 / 256.0 < best) {
-      QB = -1;
-      KS = ks3;
-    }
+    const FewPlan pl = plan_attention_few(B, Mq, n, H_q, H_kv, scratch != nullptr);
+    const int KS = pl.KS, base = B * ((Mq + kQT - 1) / kQT) * H_q;
 #define DLLMC_ATTN(KERNEL, GRID) \
   hipLaunchKernelGGL(KERNEL, dim3(GRID), dim3(256), 0, st, qq, Mq, kk, vv, n, H_q, H_kv, KS, oo, scratch, rmap)
 #define DLLMC_ATTN_WALK(KERNEL) \
@@ -1419,7 +1424,7 @@ void launch_attention(int dtype, const void* q, int B, int Mq, const void* k_cac
     const int grid_ = B * ((Mq + 16 * Q - 1) / (16 * Q)) * H_q * KS;                              \
     if (rmap) DLLMC_ATTN((k_attn_few<Q, true>), grid_); else DLLMC_ATTN((k_attn_few<Q, false>), grid_); \
   } while (0)
-    switch (QB) {
+    switch (pl.QB) {
       case -1: if (rmap) DLLMC_ATTN(k_attn_mfma<true>, base * KS); else DLLMC_ATTN(k_attn_mfma<false>, base * KS); break;
       case 0: if (rmap) DLLMC_ATTN_WALK(k_attn_walk<true>); else DLLMC_ATTN_WALK(k_attn_walk<false>); break;
       case 1: DLLMC_ATTN_FEW(1); break;

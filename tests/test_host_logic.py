@@ -72,3 +72,29 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=60)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_attention_of_few_queries_plan():
+    """Kernel and key ranges by estimated time: many workgroups on short sequences walk their keys together (the kernel
+    whose wavefronts split them starts anew with every round over the CUs); few of them split, as scratch allows."""
+    L = binding.lib()
+
+    def plan(B, Mq, n, H_q, H_kv, split=1):
+        queries = ctypes.c_int32(99)
+        ranges = L.dllmc_plan_attention(B, Mq, n, H_q, H_kv, split, ctypes.byref(queries))
+        return queries.value, ranges
+
+    for B, Mq, n, H_q, H_kv in [(16, 100, 100, 28, 4), (16, 127, 250, 32, 32), (8, 51, 300, 32, 32), (8, 65, 100, 28, 4),
+                                (8, 33, 100, 32, 32)]:
+        assert plan(B, Mq, n, H_q, H_kv) == (0, 1), (B, Mq, n)
+    assert plan(1, 51, 4608, 32, 32) == (32, 4)
+    assert plan(1, 51, 4608, 32, 32, split=0)[1] == 1
+    for B in (1, 3, 8):
+        for Mq in (1, 17, 64, 127):
+            for n in (1, 33, 700, 5000):
+                q0, r0 = plan(B, Mq, n, 28, 4)
+                per = {-1: 64, 0: 64}.get(q0, q0)
+                assert 1 <= r0 <= 16 and (r0 == 1 or B * -(-Mq // per) * 28 * r0 <= 256)
+                assert q0 != -1 or -(-(-(-n // 32)) // r0) <= 3  # ranges that are fetched at once
+    assert L.dllmc_plan_attention(1, 128, 100, 4, 4, 1, None) < 0
+    assert L.dllmc_plan_attention(1, 8, 100, 4, 3, 1, None) < 0
