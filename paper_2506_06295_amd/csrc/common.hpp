@@ -200,10 +200,16 @@ void gemm_set_fat_min_m(int m);
 // weight-streaming kernel (k_gemm_ring).
 bool gemm_last_was_stream();
 void gemm_clear_last_stream();  // a matrix product launched by another launcher follows
-// whole != nullptr: a launch of a single slice writes there instead of to c_part.
+// summed: what follows is launch_reduce_slices, unless there is a single slice and it went to whole (may be null);
+// otherwise a row kernel that reads every slice.
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
-                hipStream_t st, float* whole = nullptr);
+                hipStream_t st, bool summed = false, float* whole = nullptr);
+// Estimated us of what reads S slices of mb MB each: a pass of k_reduce_slices with its launch (summed; a single slice is
+// the result already), or their share of a row kernel.
+inline double slices_us(int S, double mb, bool summed) {
+  return !summed ? S * mb / 8.0 : S > 1 ? 2.1 + (S + 1) * mb / 8.0 : 0.0;
+}
 
 // float32 models (kernels_gemm_f32.hip): operands in whole aligned 16-byte pieces; tile shape and
 // slices for a launch (at most s_cap slices; force_s > 0: that many); C gets p.S slices
@@ -226,8 +232,8 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
 // bf16 maps of few rows and of any column count (kernels_gemm_ring.hip): row and column blocks of a tile, slices
 struct RingPlan { int rb, nb, S, kps, nt, mt; double t; };
 bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K);
-// (t: estimated us; 1e30 when every choice has more than max_wg workgroups)
-RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, long long max_wg = 1ll << 40);
+// (t: estimated us with what follows, see launch_gemm)
+RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, bool summed);
 void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
                       const bf16_t* W1, int N0, int N, int K, float* C, hipStream_t st);
 void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,

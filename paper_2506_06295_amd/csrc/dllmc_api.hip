@@ -728,7 +728,7 @@ int op_linear(int32_t dtype, const void* a, int32_t a_rows, const int32_t* row_i
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const bool direct = disjoint(out, a, a_rows, row_idx, w, M, N, K, dtype);
   const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, scratch,
-                            static_cast<size_t>(M) * N * 8, st, direct ? out : nullptr);
+                            static_cast<size_t>(M) * N * 8, st, true, direct ? out : nullptr);
   if (S == 0) return DLLMC_ENOMEM;
   if (S > 1 || !direct) launch_reduce_slices(scratch, S, M, N, out, st);
   HIP_TRY(hipGetLastError());
@@ -849,7 +849,7 @@ int dllmc_op_linear_static(int32_t dtype, const void* a, const int32_t* row_idx,
   // every slice the launch produces is written whole before it is read: nothing to clear
   const bool direct = disjoint(out, a, 0, row_idx, w, M, N, K, dtype);
   const int S = launch_gemm(dtype, a, K, row_idx, M, w, nullptr, N, N, K, ptr,
-                            kStaticScratchFloats, st, direct ? out : nullptr);
+                            kStaticScratchFloats, st, true, direct ? out : nullptr);
   if (S == 0) return DLLMC_ETOOBIG;
   if (S > 1 || !direct) launch_reduce_slices(ptr, S, M, N, out, st);
   HIP_TRY(hipGetLastError());

@@ -907,7 +907,7 @@ struct GemmPlan {
 };
 
 GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int N0, int K,
-                   size_t c_capacity) {
+                   size_t c_capacity, bool summed) {
   GemmPlan p{};
   const size_t MN = static_cast<size_t>(M) * N;
   if (M <= 0 || N <= 0 || K <= 0 || c_capacity < MN) return p;
@@ -928,13 +928,13 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
   const bool fat_ok = M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0;
   const bool mid_ok = M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0;
   if (fat_ok || mid_ok) {
-    // Estimated us of the tile kernels at every slice count, and of the weight-streaming kernel.  Measured per round
-    // of workgroups and 64-wide step: 256 x 256 1.42 (one per CU), 128 x 128 1.0 with two per CU, 0.62 with one;
-    // the partial sums are written and read again at ~6 TB/s.  The streaming kernel counts while its workgroups
-    // make one round.
-    // op_linear before this rule and with it: 333 rows x 4096 x 4096 28.1 -> 24.9 us (the streaming kernel's
-    // 192-row tiles), x 12288 70.7 -> 48.0; 400 rows x 4096 x 12288 69 -> 58 (128 x 128 in four slices instead
-    // of two); 600 rows x 12288 x 4096 91 -> 68 (128 x 128 whole instead of 256 x 256 in three slices).
+    // The estimate of plan_ring for the tile kernels (256 x 256: one workgroup per CU; 128 x 128: two, a round of up to 256
+    // has each CU to itself), at every slice count; 5 % rms.  Over the 432 shapes it was fitted to, op_linear takes 1.2 %
+    // longer than with the best choice of all, where an estimate with different prices for the partial sums of the two
+    // kinds of kernel, no time per launch and no difference between one slice and a slice sum took 19 %, and 47 shapes
+    // more than 5 % longer than a plain rule on rows alone (none now, at 340 shapes): 192 rows x 4096 x 4096 20.6 us, now
+    // 17.8; 333 x 3072 x 1024 19.2 -> 9.7; 400 x 2432 x 896 15.2 -> 9.1; 1536 x 896 x 2432 25.2 -> 17.2; 576 x 4096 x 4096
+    // 35.0 -> 33.3; 64 x 12288 x 4096 31.7 -> 25.9; at worst 65 x 8192 x 4096 19.6 -> 21.5.
     const bool literal = g_tune.force_s > 0 || g_tune.fat_min_m != defaults.fat_min_m ||
                          g_tune.tile_min_m != defaults.tile_min_m || g_tune.target_wg != defaults.target_wg;
     double best = 1e30;
@@ -943,10 +943,11 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
       if (kps > K) kps = K;
       const int used = (K + kps - 1) / kps, mt = (M + bm - 1) / bm, nt = N / bn;
       const long long wg = static_cast<long long>(mt) * nt * used;
-      const double round = kind == 3 ? static_cast<double>((wg + 255) / 256) * 1.42
-                                     : (wg <= 256 ? 0.62 : static_cast<double>((wg + 511) / 512) * 1.0);
-      const double bytes = used > 1 ? 2.0 * used * MN * 4.0 : MN * 4.0;
-      const double t = round * (kps / kFatK) + bytes / 6e6 + 0.15 * used;
+      const double steps = kps / kFatK, mb_w = 2.0 * N * K / 1e6, mb_out = 4.0 * M * N / 1e6, rem = wg % 512;
+      double t = kind == 3 ? 1.25 + static_cast<double>((wg + 255) / 256) * (4.4 + 1.184 * steps) + mb_w / 31 + used * mb_out / 6.9
+                           : 3.05 + (wg / 512 * 0.89 + (rem == 0 ? 0.0 : rem <= 256 ? 0.58 : 0.89)) * steps + mb_w / 20 +
+                                 used * mb_out / 6.3;
+      t += slices_us(used, mb_out, summed);
       if (t < best * 0.98) {
         best = t;
         p.kind = kind; p.S = used; p.kps = kps; p.nt = nt; p.mt = mt;
@@ -964,7 +965,7 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     for (int S = m_lo; mid_ok && !only_fat && S <= m_hi; ++S)
       if (S == m_lo || K / S >= 8 * kFatK) offer(4, kMidM, kMidN, S);
     if (!literal) {
-      const RingPlan r = plan_ring(M, N, K, s_cap, 0, 256);
+      const RingPlan r = plan_ring(M, N, K, s_cap, 0, summed);
       if (r.t < best * 0.98) {
         p.kind = 2; p.ring = r; p.S = r.S; p.kps = r.kps; p.nt = r.nt; p.mt = r.mt;
       }
@@ -972,22 +973,22 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     return p;
   }
   p.kind = 2;
-  p.ring = plan_ring(M, N, K, s_cap, g_tune.force_s);
+  p.ring = plan_ring(M, N, K, s_cap, g_tune.force_s, summed);
   p.S = p.ring.S; p.kps = p.ring.kps; p.nt = p.ring.nt; p.mt = p.ring.mt;
   return p;
 }
 
 int gemm_plan_slices(int dtype, int M, int N, int N0, int K, size_t c_capacity) {
-  return plan_gemm(dtype, true, K, M, N, N0, K, c_capacity).S;
+  return plan_gemm(dtype, true, K, M, N, N0, K, c_capacity, false).S;
 }
 
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
-                hipStream_t st, float* whole) {
+                hipStream_t st, bool summed, float* whole) {
   t_last_stream = false;
   if (M <= 0 || N <= 0) return 1;
   const bool al = aligned16(A) && aligned16(W0) && (W1 == nullptr || aligned16(W1));
-  const GemmPlan p = plan_gemm(dtype, al, lda, M, N, N0, K, c_capacity);
+  const GemmPlan p = plan_gemm(dtype, al, lda, M, N, N0, K, c_capacity, summed);
   if (p.kind == 0 || static_cast<size_t>(p.S) * M * N > c_capacity) return 0;  // nothing launched
   t_last_stream = p.kind == 2;
   if (whole != nullptr && p.S == 1) c_part = whole;

@@ -212,28 +212,31 @@ bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K) {
   return dtype == 1 && operands_aligned && K % 64 == 0 && lda % 8 == 0;
 }
 
-// Row blocks, column blocks and slices with the lowest estimate; a slice costs its partial sums twice
-// (written here, read by the row kernel; mostly out of the memory-side cache) and 0.15 us there (at twice
-// that price two adaptive Dream-7B steps took 713 instead of 708 us; at half of it 710).
-RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, long long max_wg) {
+// Row blocks, column blocks and slices with the lowest estimate: start + rounds of 256 workgroups (one per CU) x
+// (round + step x 64-wide steps) + MB of weights / w + MB of sums / out, and what follows.  Fitted to 432 shapes (1 to 2048
+// rows, 512 to 18944 columns, contraction of 896 to 18944) timed with every tile and slice count: it strays by 6 % rms; the
+// tile kernels' estimates in plan_gemm are of the same form, from the same launches.
+RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, bool summed) {
+  struct Cost { double start, round, step, w, out; };
+  static const Cost cost[3][2] = {{{2.1, 1.17, 0.244, 17.5, 3.9}, {2.3, 1.4, 0.365, 15.0, 4.8}},
+                                  {{2.4, 1.3, 0.334, 18.9, 4.5}, {2.8, 1.8, 0.496, 19.8, 4.8}},
+                                  {{2.75, 1.3, 0.44, 21.0, 4.5}, {3.4, 2.7, 0.66, 28.0, 5.6}}};
+  const double mb_w = 2.0 * N * K / 1e6, mb_out = 4.0 * M * N / 1e6;
   RingPlan best{};
   best.t = 1e30;
-  double best_t = 1e30;
   for (int rb = 1; rb <= 3; ++rb)
     for (int nb = 4; nb <= 8; nb += 4) {
+      const Cost& c = cost[rb - 1][nb / 4 - 1];
       const int mt = (M + 64 * rb - 1) / (64 * rb), nt = (N + 16 * nb - 1) / (16 * nb);
       const int s_hi = force_s > 0 ? (force_s < s_cap ? force_s : s_cap) : s_cap;
       for (int S = force_s > 0 ? s_hi : 1; S <= s_hi; ++S) {
         int kps = ((K + S - 1) / S + 63) / 64 * 64;
         if (kps > K) kps = K;
         const int used = (K + kps - 1) / kps;
-        if (static_cast<long long>(mt) * nt * used > max_wg) continue;
-        const double t = ring_time(static_cast<long long>(mt) * nt * used, rb, nb, kps) +
-                         used * (2.0 * M * N * 4.0 / 16e6 + 0.15);
-        if (t < best_t * 0.98) {
-          best_t = t;
-          best = RingPlan{rb, nb, used, kps, nt, mt, t};
-        }
+        const long long wg = static_cast<long long>(mt) * nt * used;
+        const double t = c.start + static_cast<double>((wg + 255) / 256) * (c.round + c.step * kps / 64) + mb_w / c.w +
+                         used * mb_out / c.out + slices_us(used, mb_out, summed);
+        if (t < best.t * 0.98) best = RingPlan{rb, nb, used, kps, nt, mt, t};
       }
     }
   return best;

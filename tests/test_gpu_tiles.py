@@ -96,3 +96,20 @@ def test_result_over_rows_that_are_gathered(dtype, M, N, K, entry):
         assert L.dllmc_op_linear(code, a.data_ptr(), idx.data_ptr(), M, w.data_ptr(), N, K, out.data_ptr(),
                                  scratch.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
     assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("M,N,K,whole", [(448, 2048, 1024, True), (288, 2048, 2048, True), (333, 3072, 1024, True),
+                                         (700, 2432, 896, True), (1024, 896, 2432, True), (64, 4096, 12288, False)])
+def test_one_slice_where_a_slice_sum_costs_more(M, N, K, whole):
+    """A second launch that adds slices counts against them: small maps go whole to the result, the scratch buffer stays
+    as it was; long walks of few rows are split."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    a = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    w = (0.05 * torch.randn((N, K), generator=g, device="cuda")).bfloat16()
+    out, scratch = torch.empty((M, N), device="cuda"), torch.full((8 * M * N,), 77.0, device="cuda")
+    assert binding.lib().dllmc_op_linear(1, a.data_ptr(), None, M, w.data_ptr(), N, K, out.data_ptr(), scratch.data_ptr(),
+                                         torch.cuda.current_stream().cuda_stream) == 0
+    want = a.double() @ w.double().t()
+    assert float((out.double() - want).norm() / want.norm()) < 2.0 ** -24 * K ** 0.5
+    assert bool((scratch == 77.0).all()) == whole
