@@ -206,9 +206,11 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
                 hipStream_t st, bool summed = false, float* whole = nullptr);
 // Estimated us of what reads S slices of mb MB each: a pass of k_reduce_slices with its launch (summed; a single slice is
-// the result already), or their share of a row kernel.
+// the result already), or their share of a row kernel (5 TB/s, with many rows 8; at 8 throughout a response refresh of 256
+// rows took eight slices of the down projection instead of four, 217 us per layer instead of 213).
 inline double slices_us(int S, double mb, bool summed) {
-  return !summed ? S * mb / 8.0 : S > 1 ? 2.1 + (S + 1) * mb / 8.0 : 0.0;
+  if (!summed) return S * (mb < 6.7 ? mb / 5.0 : 0.5 + mb / 8.0);
+  return S > 1 ? 2.1 + (S + 1) * mb / 8.0 : 0.0;
 }
 
 // float32 models (kernels_gemm_f32.hip): operands in whole aligned 16-byte pieces; tile shape and
