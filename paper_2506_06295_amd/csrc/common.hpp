@@ -355,20 +355,21 @@ void launch_select(float* scores, int B, int L, int k, int* sel_out, int sel_str
 // + first + i % per_seq, or i when per_seq == 0); when part != nullptr, for every response row
 // (position >= L_p) and 64-column tile t the sums (v . old, |v|^2, |old|^2) (metric 1: (|v -
 // old|^2, 0, 0)) over the tile's columns go to part[(c * n_ct + t) * part_stride + seq * (n -
-// L_p) + pos - L_p]; then v_cache[row] = v.  vverify_fused_ok says whether the shape is handled.
-bool vverify_fused_ok(int dtype, const void* A, int lda, int M, const void* W, int N, int K,
-                      const void* v_cache);
+// L_p) + pos - L_p]; then v_cache[row] = v.  plan_vverify says whether the shape is handled.
+// Ways through V-verify of M rows: split contraction (launch_gemm with c_capacity floats) and row kernel, the tile kernels'
+// epilogue (128 x 128, 256 x 256, 192 x 64), or the 64 x 64 tiles of launch_vverify_fused.
+enum VWay { kVSplit = 0, kVMid = 1, kVFat = 2, kVR192 = 3, kVFused = 4 };
+int plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K, size_t c_capacity, bool in_step);
 size_t vverify_part_floats(int N, size_t scored_rows);
 int vverify_col_tiles(int N);
 void launch_vverify_fused(const void* A, int lda, int M, int first, int per_seq, int n, int L_p,
                           const void* W, int N, int K, void* v_cache, float* part, int part_stride,
                           int metric, hipStream_t st, const int* rmap = nullptr);
-// The same V-verify, and the Q | K projection with RoPE and the cache scatter, finished in the
-// epilogue of the 128 x 128 / 256 x 256 tile kernels (one slice, no float32 partial sums, no row
-// kernel) for launches with enough rows to fill the chip that way.  Arguments as for
-// launch_vverify_fused / launch_gemm + launch_qk_finalize.  Return false (nothing launched) when
-// the shape is not handled.
-bool launch_gemm_vverify_tiles(int dtype, const void* A, int lda, int M, int first, int per_seq, int n,
+// The same V-verify (way: kVMid, kVFat or kVR192), and the Q | K projection with RoPE and the cache
+// scatter, finished in the epilogue of the tile kernels (one slice, no float32 partial sums, no row
+// kernel).  Arguments as for launch_vverify_fused / launch_gemm + launch_qk_finalize.
+// launch_gemm_qk_tiles returns false (nothing launched) when the shape is not handled or would not fill the chip.
+void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first, int per_seq, int n,
                                int L_p, const void* W, int N, int K, void* v_cache, float* part,
                                int part_stride, int metric, const int* rmap, hipStream_t st);
 bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, int M, const void* wq,

@@ -20,6 +20,8 @@ bool apart(const void* p, size_t pn, const void* q, size_t qn) {
   return a + pn <= b || b + qn <= a;
 }
 
+inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
 thread_local int g_last_hip_error = 0;
 
 inline int hip_fail(hipError_t e) {
@@ -460,25 +462,24 @@ int dllmc_step(dllmc_ctx* c, const void* hidden_in, int32_t step_idx, void* hidd
     // (free until this layer's attention) for the selection
     const bool defer_v = c->v_selected_only && !Rf;
     // The default method in one launch: projection, rounding, the sums of Eq. (cos_sim) per row
-    // and column tile, cache overwrite (the selection kernel forms the scores): 64 x 64 tiles over
-    // the whole contraction range for up to two tiles per CU, the epilogue of the 128 x 128 /
-    // 256 x 256 tile kernels for launches that fill the chip in one slice; else the split
-    // contraction and a row kernel.
+    // and column tile, cache overwrite (the selection kernel forms the scores): 64 x 64 tiles, or
+    // the epilogue of the larger tile kernels; else the split contraction and a row kernel.
     const bool want_scores = !Rf && !c->random_sel;
     bool fused_v = false;
     {
       Timed t(c, DLLMC_KC_GEMM_V, gemm_bytes(Mc, d_kv, d), gemm_flops(Mc, d_kv, d));
       if (!ksrc && !defer_v) {
-        if (vverify_fused_ok(dt, h, d, Mc, w.wv, d_kv, d, Vc)) {
+        const int way = plan_vverify(dt, aligned16(h) && aligned16(w.wv) && aligned16(Vc), d, Mc, d_kv, d, cws_cap,
+                                     true);
+        if (way == kVFused) {
           gemm_clear_last_stream();
           launch_vverify_fused(h, d, Mc, P ? 0 : L_p, carried_per_seq, n, L_p, w.wv, d_kv, d, Vc,
                                want_scores ? part : nullptr, B * L_r, c->metric, st, rmap);
-          fused_v = true;
-        } else {
-          fused_v = launch_gemm_vverify_tiles(dt, h, d, Mc, P ? 0 : L_p, carried_per_seq, n, L_p, w.wv,
-                                              d_kv, d, Vc, want_scores ? part : nullptr, B * L_r,
-                                              c->metric, rmap, st);
+        } else if (way != kVSplit) {
+          launch_gemm_vverify_tiles(way, h, d, Mc, P ? 0 : L_p, carried_per_seq, n, L_p, w.wv, d_kv, d, Vc,
+                                    want_scores ? part : nullptr, B * L_r, c->metric, rmap, st);
         }
+        fused_v = way != kVSplit;
       }
       if (fused_v) {
         t.bytes = (static_cast<double>(d_kv) * d + static_cast<double>(Mc) * d) * esz +
@@ -686,6 +687,11 @@ int32_t dllmc_plan_gemm_slices(int32_t dtype, int32_t M, int32_t N, int32_t N0, 
   return gemm_plan_slices(dtype, M, N, N0, K, capacity_floats);
 }
 
+int32_t dllmc_plan_vverify(int32_t dtype, int32_t rows, int32_t d, int32_t d_kv) {
+  if ((dtype != DLLMC_F32 && dtype != DLLMC_BF16) || rows < 1 || d < 1 || d_kv < 1) return DLLMC_EINVAL;
+  return plan_vverify(dtype, true, d, rows, d_kv, d, static_cast<size_t>(rows) * d_kv * 8, false);
+}
+
 int32_t dllmc_plan_attention(int32_t B, int32_t Mq, int32_t n, int32_t H_q, int32_t H_kv, int32_t split_keys,
                              int32_t* queries) {
   if (B < 1 || Mq < 1 || Mq > 127 || n < 1 || H_kv < 1 || H_q < H_kv || H_q % H_kv) return DLLMC_EINVAL;
@@ -764,23 +770,21 @@ int dllmc_op_vverify(int32_t dtype, const void* h, const void* wv, void* v_cache
   const bool one_launch = vverify_part_floats(d_kv, rows) <= static_cast<size_t>(rows) * d_kv * 8 &&
                           apart(v_cache, cache_bytes, h, static_cast<size_t>(rows) * d * esz) &&
                           apart(v_cache, cache_bytes, wv, static_cast<size_t>(d_kv) * d * esz);
-  if (one_launch && vverify_fused_ok(dtype, h, d, rows, wv, d_kv, d, v_cache)) {
-    launch_vverify_fused(h, d, rows, 0, 0, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, st);
-    launch_scores_from_part(scratch, vverify_col_tiles(d_kv), rows, 0, scores, st);
-    HIP_TRY(hipGetLastError());
-    return DLLMC_OK;
-  }
-  // Many rows: finished in the tile kernels' epilogue, as in a step (one sequence of `rows` response rows).  4096
-  // columns: 2048 rows 78 us, split contraction and row kernel 85; 1000 rows 53 and 55; 600 rows 49 and 42.
-  if (one_launch && rows >= 900 && (reinterpret_cast<uintptr_t>(v_cache) & 15u) == 0 &&
-      launch_gemm_vverify_tiles(dtype, h, d, rows, 0, rows, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, nullptr,
-                                st)) {
+  const size_t capacity = static_cast<size_t>(rows) * d_kv * 8;
+  const int way = !one_launch ? kVSplit
+                              : plan_vverify(dtype, aligned16(h) && aligned16(wv) && aligned16(v_cache), d, rows, d_kv, d,
+                                             capacity, false);
+  if (way != kVSplit) {
+    if (way == kVFused)
+      launch_vverify_fused(h, d, rows, 0, 0, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, st);
+    else  // one sequence of `rows` response rows
+      launch_gemm_vverify_tiles(way, h, d, rows, 0, rows, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, nullptr, st);
     launch_scores_from_part(scratch, vverify_col_tiles(d_kv), rows, 0, scores, st);
     HIP_TRY(hipGetLastError());
     return DLLMC_OK;
   }
   const int S = launch_gemm(dtype, h, d, nullptr, rows, wv, nullptr, d_kv, d_kv, d, scratch,
-                            static_cast<size_t>(rows) * d_kv * 8, st);
+                            capacity, st);
   if (S == 0) return DLLMC_ENOMEM;
   const RowKernelArgs ra{dtype, rows, 0, d, 0.f};
   launch_v_finalize(ra, scratch, S, 0, 0, rows, d_kv, v_cache, scores, 0, nullptr, st);

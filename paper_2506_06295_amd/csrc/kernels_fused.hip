@@ -280,25 +280,7 @@ __global__ __launch_bounds__(256) void k_scores_from_part(const float* __restric
   score[i] = metric == 0 ? r[0] / fmaxf(sqrtf(r[1]) * sqrtf(r[2]), 1e-8f) : -sqrtf(r[0]);
 }
 
-inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 }  // namespace
-
-bool vverify_fused_ok(int dtype, const void* A, int lda, int M, const void* W, int N, int K,
-                      const void* v_cache) {
-  if (dtype != 1 || M < 1 || N % kVT || K % kVK || lda % 8) return false;
-  if (!aligned16(A) || !aligned16(W) || !aligned16(v_cache)) return false;
-  // One 64 x 64 tile per CU walks the whole contraction range, ~0.28 us per 64-wide step, and leaves the selection the
-  // tile sums to add.  That beats the split contraction with its row kernel where the tiles fill one or two
-  // rounds of the CUs, or the walk is short.  us per adaptive layer, here / split: LLaDA-8B width (K 4096) 64
-  // tiles 149 / 141, 128 153 / 154, 192 158 / 163, 256 165 / 168, 320 199 / 186, 384 206 / 193, 448 195 / 207,
-  // 512 222 / 229; Dream-7B (512 columns, K 3584) 8 tiles 155 / 146, 32 175 / 167, 64 212 / 206; 1024-wide
-  // models (16 steps) level.  (Beyond two rounds the 128 x 128 and larger tiles pull half as many operand bytes into
-  // a CU per flop.)
-  const long long tiles = static_cast<long long>((M + kVT - 1) / kVT) * (N / kVT);
-  if (tiles > 512) return false;
-  return K <= 1024 || (tiles >= 128 && tiles <= 256) || tiles > 416;
-}
 
 size_t vverify_part_floats(int N, size_t scored_rows) {
   return static_cast<size_t>(3) * ((N + kVT - 1) / kVT) * scored_rows;

@@ -790,7 +790,7 @@ __global__ __launch_bounds__(256) void k_gemm_tall_swiglu(const bf16_t* __restri
 }
 
 // 192-row tiles (five slots of 24 KB): the row count that makes whole rounds of workgroups where 256 rows do not
-// (768 rows: four tiles instead of three; see launch_gemm_swiglu and direct_tile_kind for what they measured).
+// (768 rows: four tiles instead of three; see launch_gemm_swiglu, plan_vverify and qk_tile_kind for what they measured).
 // For the float32 slices of the output and down projections they gained nothing: 768 rows in two slices 59
 // us against 56, 8 us less in the two row kernels.
 __global__ __launch_bounds__(512) void k_gemm_r192_swiglu(const bf16_t* __restrict__ A, int lda,
@@ -902,6 +902,7 @@ struct GemmPlan {
   int kind;  // 0 nothing fits, 1 plain, 2 weight-streaming, 3 256x256 LDS-direct, 4 128x128 LDS-direct,
              // 7 float32 on the matrix cores
   int S, kps, nt, mt;
+  double t;       // estimated us (kinds 2, 3 and 4)
   RingPlan ring;  // kind 2
   F32Plan f32;    // kind 7
 };
@@ -932,7 +933,7 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     // has each CU to itself), at every slice count; 5 % rms.  Over the 432 shapes it was fitted to, op_linear takes 1.2 %
     // longer than with the best choice of all, where an estimate with different prices for the partial sums of the two
     // kinds of kernel, no time per launch and no difference between one slice and a slice sum took 19 %, and 47 shapes
-    // more than 5 % longer than a plain rule on rows alone (none now, at 340 shapes): 192 rows x 4096 x 4096 20.6 us, now
+    // more than 5 % longer than a plain rule on rows alone (none of 340 now): 192 rows x 4096 x 4096 20.6 us, now
     // 17.8; 333 x 3072 x 1024 19.2 -> 9.7; 400 x 2432 x 896 15.2 -> 9.1; 1536 x 896 x 2432 25.2 -> 17.2; 576 x 4096 x 4096
     // 35.0 -> 33.3; 64 x 12288 x 4096 31.7 -> 25.9; at worst 65 x 8192 x 4096 19.6 -> 21.5.
     const bool literal = g_tune.force_s > 0 || g_tune.fat_min_m != defaults.fat_min_m ||
@@ -950,7 +951,7 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
       t += slices_us(used, mb_out, summed);
       if (t < best * 0.98) {
         best = t;
-        p.kind = kind; p.S = used; p.kps = kps; p.nt = nt; p.mt = mt;
+        p.kind = kind; p.S = used; p.kps = kps; p.nt = nt; p.mt = mt; p.t = t;
       }
     };
     const bool only_fat = literal && fat_ok;  // thresholds and slice counts set by the caller
@@ -967,14 +968,14 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     if (!literal) {
       const RingPlan r = plan_ring(M, N, K, s_cap, 0, summed);
       if (r.t < best * 0.98) {
-        p.kind = 2; p.ring = r; p.S = r.S; p.kps = r.kps; p.nt = r.nt; p.mt = r.mt;
+        p.kind = 2; p.ring = r; p.S = r.S; p.kps = r.kps; p.nt = r.nt; p.mt = r.mt; p.t = r.t;
       }
     }
     return p;
   }
   p.kind = 2;
   p.ring = plan_ring(M, N, K, s_cap, g_tune.force_s, summed);
-  p.S = p.ring.S; p.kps = p.ring.kps; p.nt = p.ring.nt; p.mt = p.ring.mt;
+  p.S = p.ring.S; p.kps = p.ring.kps; p.nt = p.ring.nt; p.mt = p.ring.mt; p.t = p.ring.t;
   return p;
 }
 
@@ -1097,13 +1098,41 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   return true;
 }
 
-// Which tile kernel finishes a launch of M rows x N columns in one slice: 3 = 192 rows x cols192 columns, 2 =
-// 256 x 256, 1 = 128 x 128, 0 = none (every shape that divides the columns would leave more than a quarter of the
-// CUs without a workgroup).  The one whose rounds over the CUs take least, by measured us per round and 64-wide
-// step: 256 x 256 1.6, 128 x 128 1.16 with two workgroups per CU and 0.78 with one, 192 x 128 0.92, 192 x
-// 64 0.74.  (768 rows: Q|K of 8192 columns 192 x 128 in one round of 256 workgroups 58.7 us, 128 x 128 72; V of
-// 4096 columns 192 x 64 47, 128 x 128 51.)
-static int direct_tile_kind(int M, int N, int N0, int K, int cols192) {
+// The way through V-verify that takes least, by estimates in us of the form of plan_ring's, with what follows the launch
+// (launch_scores_from_part, or the row kernel; in a step the selection adds the sums, which spares the former's launch).  Fitted to 270 shapes (1 to 4096 rows, 128 to 8192 columns, contraction of 896
+// to 8192) timed each way: rms 4.7 % (64 x 64 tiles), 2.5 (128 x 128), 2.7 (256 x 256), 4.1 (192 x 64), 8.2 (split).  The
+// choice is 0.3 % from the best way on average there, and 0.1 % in steps of four widths (64 to 4096 carried rows), where
+// bands of tile counts read off two widths, and a fixed 900 rows for the single operation, were 0.5 %: LLaDA-8B width, us per
+// adaptive layer, 448 rows 201 -> 194, 576 227 -> 217, 768 241 -> 233; 1280 rows as a single operation 69 -> 60.
+int plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K, size_t c_capacity, bool in_step) {
+  if (dtype != 1 || M < 1 || !operands_aligned || lda % 8 || K % kFatK || N % 64) return kVSplit;
+  const double steps = K / kFatK, mb_w = 2.0 * N * K / 1e6, mb_v = 2.0 * M * N / 1e6;
+  auto tiles = [&](int bm, int bn) { return static_cast<long long>((M + bm - 1) / bm) * (N / bn); };
+  auto rounds = [&](int bm, int bn) { return static_cast<double>((tiles(bm, bn) + 255) / 256); };
+  int way = kVFused;
+  double best = 3.9 + rounds(64, 64) * (1.7 + 0.21 * steps) + mb_w / 12.9 + mb_v / 1.2;
+  auto offer = [&](int w, double t) { if (t < best) { best = t; way = w; } };
+  if (M >= g_tune.tile_min_m) {
+    if (N % kMidN == 0) {  // two workgroups per CU
+      const long long t = tiles(kMidM, kMidN), rem = t % 512;
+      offer(kVMid, 3.7 + t / 512 * (6.0 + 0.849 * steps) + (rem == 0 ? 0.0 : 6.0 + (rem <= 256 ? 0.583 : 0.849) * steps) +
+                       mb_w / 17 + mb_v / 3.2);
+    }
+    offer(kVR192, 3.5 + rounds(192, 64) * (5.0 + 0.47 * steps) + mb_w / 6 + mb_v / 2.8);
+    if (M >= g_tune.fat_min_m && N % kFatN == 0)
+      offer(kVFat, rounds(kFatM, kFatN) * (16.6 + 1.13 * steps) + mb_w / 15 + mb_v / 2.7);
+  }
+  const GemmPlan p = plan_gemm(dtype, true, lda, M, N, N, K, c_capacity, false);
+  if (p.kind != 0 && 3.8 + p.t + mb_v / 10.2 + M / 358.0 < best - (in_step ? 2.0 : 0.0)) way = kVSplit;
+  return way;
+}
+
+// Which tile kernel finishes Q | K of M rows x N columns in one slice: 3 = 192 x 128, 2 = 256 x 256, 1 = 128 x 128, 0 =
+// none (every shape that divides the columns would leave more than a quarter of the CUs without a workgroup).  The one
+// whose rounds over the CUs take least, by measured us per round and 64-wide step: 256 x 256 1.6, 128 x 128 1.16 with two
+// workgroups per CU and 0.78 with one, 192 x 128 0.92.  (768 rows x 8192 columns: 192 x 128 in one round of 256
+// workgroups 58.7 us, 128 x 128 72.)
+static int qk_tile_kind(int M, int N, int N0, int K) {
   if (K % kFatK || M < g_tune.tile_min_m) return 0;
   const int cus = 256, least = 3 * cus / 4;
   int kind = 0;
@@ -1114,18 +1143,13 @@ static int direct_tile_kind(int M, int N, int N0, int K, int cols192) {
     offer(2, (tiles(kFatM, kFatN) + cus - 1) / cus * 1.6);
   if (N % kMidN == 0 && N0 % kMidN == 0 && tiles(kMidM, kMidN) >= least)
     offer(1, tiles(kMidM, kMidN) <= cus ? 0.78 : (tiles(kMidM, kMidN) + 2 * cus - 1) / (2 * cus) * 1.16);
-  if (N % cols192 == 0 && N0 % cols192 == 0 && tiles(192, cols192) >= least)
-    offer(3, (tiles(192, cols192) + cus - 1) / cus * (cols192 == 64 ? 0.74 : 0.92));
+  if (N % 128 == 0 && N0 % 128 == 0 && tiles(192, 128) >= least) offer(3, (tiles(192, 128) + cus - 1) / cus * 0.92);
   return kind;
 }
 
-bool launch_gemm_vverify_tiles(int dtype, const void* A, int lda, int M, int first, int per_seq, int n,
+void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first, int per_seq, int n,
                                int L_p, const void* W, int N, int K, void* v_cache, float* part,
                                int part_stride, int metric, const int* rmap, hipStream_t st) {
-  if (M <= 0) return true;
-  if (dtype != 1 || per_seq <= 0 || lda % 8 || !aligned16(A) || !aligned16(W)) return false;
-  const int kind = direct_tile_kind(M, N, N, K, 64);
-  if (kind == 0) return false;
   TileEpilogue ep{};
   ep.first = first; ep.per_seq = per_seq; ep.n = n; ep.L_p = L_p;
   ep.cache = static_cast<bf16_t*>(v_cache);
@@ -1133,15 +1157,14 @@ bool launch_gemm_vverify_tiles(int dtype, const void* A, int lda, int M, int fir
   t_last_stream = false;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  if (kind == 3)
+  if (way == kVR192)
     hipLaunchKernelGGL(k_gemm_r192_vverify, dim3(N / 64, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, M, w, N, K, ep);
-  else if (kind == 2)
+  else if (way == kVFat)
     hipLaunchKernelGGL(k_gemm_fat_vverify, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(512), 0, st, a,
                        lda, M, w, N, K, ep);
   else
     hipLaunchKernelGGL(k_gemm_mid_vverify, dim3(N / kMidN, (M + kMidM - 1) / kMidM, 1), dim3(256), 0, st, a,
                        lda, M, w, N, K, ep);
-  return true;
 }
 
 bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, int M, const void* wq,
@@ -1151,7 +1174,7 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
   if (M <= 0) return true;
   if (dtype != 1 || d_h != 128 || lda % 8 || !aligned16(A) || !aligned16(wq) || !aligned16(w2)) return false;
   const int N = d_q + d_kv;
-  const int kind = direct_tile_kind(M, N, d_q, K, 128);
+  const int kind = qk_tile_kind(M, N, d_q, K);
   if (kind == 0) return false;
   TileEpilogue ep{};
   ep.n = n; ep.cache = static_cast<bf16_t*>(cache); ep.rmap = rmap; ep.tab = rope_tab;

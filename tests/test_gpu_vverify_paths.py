@@ -1,5 +1,5 @@
-"""V-verify on both sides of the choice between its one-launch kernel (64 x 64 tiles that fill one or two rounds of the
-CUs), the split contraction with its row kernel, and the tile kernels' epilogue.
+"""Every way through V-verify, at ragged sizes and around the choice between them: the split contraction with its row
+kernel, 64 x 64 tiles in one launch, and the epilogue of the larger tile kernels.
 
 bf16 rows are rounded once from float32 sums: isolated last-bit differences (2^-8 of an element) from another order
 of summation; one of them moves a cosine of d_kv elements by at most ~2^-8 / sqrt(d_kv) * |v_i| / rms."""
@@ -12,19 +12,27 @@ from paper_2506_06295_amd import binding
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,d,d_kv", [
-    (64, 2048, 4096),     # 64 tiles: split
-    (128, 2048, 4096),    # 128: one launch
-    (256, 2048, 4096),    # 256
-    (257, 2048, 4096),    # 320: split
-    (416, 2048, 4096),    # 448: one launch, second round
-    (513, 2048, 4096),    # 576: split
-    (899, 2048, 4096),
-    (900, 2048, 4096),    # tile epilogue
-    (1000, 2048, 512),    # 128 tiles
-    (50, 1024, 64),       # a short walk: one tile
+SPLIT, T128, T256, T192, T64 = range(5)
+
+
+@pytest.mark.parametrize("rows,d,d_kv,way", [
+    (64, 2048, 4096, SPLIT),
+    (128, 2048, 4096, SPLIT),
+    (251, 2048, 4096, T64),     # one round of the CUs, a ragged row tile
+    (256, 2048, 4096, T64),
+    (257, 2048, 4096, SPLIT),
+    (416, 2048, 4096, SPLIT),
+    (513, 2048, 4096, T192),    # a third row tile of 129 rows
+    (1000, 2560, 2560, T192),   # a sixth row tile of 40 rows
+    (899, 2048, 4096, T128),
+    (900, 2048, 4096, T128),
+    (1000, 2048, 512, T64),
+    (50, 1024, 64, SPLIT),
+    (3073, 512, 4096, T256),    # a thirteenth row tile of one row
+    (1100, 1024, 64, T64),      # one column tile
 ])
-def test_vverify(rows, d, d_kv):
+def test_vverify(rows, d, d_kv, way):
+    assert binding.lib().dllmc_plan_vverify(1, rows, d, d_kv) == way
     g = torch.Generator(device="cuda")
     g.manual_seed(rows + d_kv)
     h = torch.randn((rows, d), generator=g, device="cuda").bfloat16()
@@ -44,12 +52,13 @@ def test_vverify(rows, d, d_kv):
     assert float(scores[rows // 2]) == 0.0
 
 
-@pytest.mark.parametrize("rows,d", [(1024, 4096), (256, 2048)])
+@pytest.mark.parametrize("rows,d", [(2048, 4096), (256, 2048)])
 @pytest.mark.parametrize("over", ["h", "wv"])
 def test_cache_over_an_operand(rows, d, over):
     """Cached rows that are also read as activations or weights, at sizes that take one launch otherwise.  Another
     order of summation: isolated last-bit differences, as above."""
     d_kv = d
+    assert binding.lib().dllmc_plan_vverify(1, rows, d, d_kv) != SPLIT
     g = torch.Generator(device="cuda")
     g.manual_seed(rows)
     h = torch.randn((rows, d), generator=g, device="cuda").bfloat16()

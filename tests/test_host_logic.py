@@ -98,3 +98,17 @@ def test_attention_of_few_queries_plan():
                 assert q0 != -1 or -(-(-(-n // 32)) // r0) <= 3  # ranges that are fetched at once
     assert L.dllmc_plan_attention(1, 128, 100, 4, 4, 1, None) < 0
     assert L.dllmc_plan_attention(1, 8, 100, 4, 3, 1, None) < 0
+
+
+def test_vverify_plan():
+    """By estimated time: one round of 64 x 64 tiles, the larger tiles where they fill their rounds, else the split
+    contraction (in the gaps between whole rounds it is ahead at every width)."""
+    plan = binding.lib().dllmc_plan_vverify
+    for rows, d, d_kv, way in [(64, 4096, 4096, 0), (256, 4096, 4096, 4), (448, 4096, 4096, 0), (576, 4096, 4096, 0),
+                               (768, 4096, 4096, 0), (900, 4096, 4096, 0), (1280, 4096, 4096, 0), (1280, 8192, 8192, 0),
+                               (2048, 4096, 4096, 1), (4096, 4096, 4096, 2), (1000, 2560, 2560, 3), (1280, 3584, 512, 4)]:
+        assert plan(1, rows, d, d_kv) == way, (rows, d, d_kv)
+    assert plan(0, 256, 4096, 4096) == 0            # float32
+    assert plan(1, 256, 4096, 4100) == 0            # columns that 64 does not divide
+    assert plan(1, 256, 4100, 4096) == 0            # nor the contraction
+    assert plan(1, 0, 64, 64) < 0 and plan(2, 1, 64, 64) < 0
