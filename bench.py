@@ -113,7 +113,7 @@ def main():
                     "line from the first to the last layer (cross-layer allocation study)")
     ap.add_argument("--policy", default="", help="variant of the paper's ablations, e.g. "
                     "source=k,metric=l2,selection=random,v_update=selected,seed=1")
-    ap.add_argument("--tune", default="", help="GEMM tuning knobs, e.g. nw=8,nw_dual=4,force_s=0,target_wg=256")
+    ap.add_argument("--tune", default="", help="GEMM tuning knobs, e.g. force_s=2,tile_min_m=128,fat_min_m=256")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on one GPU only (sequences would shard across GPUs "

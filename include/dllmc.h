@@ -307,6 +307,11 @@ int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t 
 int32_t dllmc_plan_gemm_slices(int32_t dtype, int32_t M, int32_t N, int32_t N0, int32_t K,
                                size_t capacity_floats);
 
+/* Host-only: rows per workgroup of the weight-streaming kernel's bf16 gate/up projection of M rows (it takes those
+ * below tile_min_m, and any count where the tile kernels' columns do not divide d_ffn); *cols (may be NULL): its
+ * columns of each matrix. */
+int32_t dllmc_plan_gate_up(int32_t M, int32_t d_ffn, int32_t d, int32_t* cols);
+
 /* Host-only: how dllmc_op_vverify takes `rows` rows (16-byte aligned operands, cache apart from both): 0 split
  * contraction and a row kernel, else one launch that overwrites the cache, of 128 x 128 (1), 256 x 256 (2), 192 x
  * 64 (3) or 64 x 64 (4) tiles. */

@@ -687,6 +687,14 @@ int32_t dllmc_plan_gemm_slices(int32_t dtype, int32_t M, int32_t N, int32_t N0, 
   return gemm_plan_slices(dtype, M, N, N0, K, capacity_floats);
 }
 
+int32_t dllmc_plan_gate_up(int32_t M, int32_t d_ffn, int32_t d, int32_t* cols) {
+  if (M < 1 || d_ffn < 1 || d < 1) return DLLMC_EINVAL;
+  int rb, cb;
+  plan_ring_swiglu(M, d_ffn, d, rb, cb);
+  if (cols) *cols = 16 * cb;
+  return 64 * rb;
+}
+
 int32_t dllmc_plan_vverify(int32_t dtype, int32_t rows, int32_t d, int32_t d_kv) {
   if ((dtype != DLLMC_F32 && dtype != DLLMC_BF16) || rows < 1 || d < 1 || d_kv < 1) return DLLMC_EINVAL;
   return plan_vverify(dtype, true, d, rows, d_kv, d, static_cast<size_t>(rows) * d_kv * 8, false);

@@ -259,11 +259,10 @@ void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* ro
 #undef DLLMC_R
 }
 
-void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,
-                             const bf16_t* w_up, int m, int K, bf16_t* u, hipStream_t st) {
-  // Columns per workgroup: whole rounds over the CUs.  48 for an FFN width of 12288 (256 workgroups), 80 for
-  // 18944 (237: 51 us, 48 columns in two rounds 61), 16 for 3072.
-  int rb = 1, cb = 1;
+// Columns per workgroup: whole rounds over the CUs.  48 for an FFN width of 12288 (256 workgroups), 80 for
+// 18944 (237: 51 us, 48 columns in two rounds 61), 16 for 3072.
+void plan_ring_swiglu(int M, int m, int K, int& rb, int& cb) {
+  rb = cb = 1;
   double best_t = 1e30;
   for (int r = 1; r <= 3; ++r)
     for (int c = 1; c <= 5; ++c) {
@@ -271,6 +270,12 @@ void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, c
       const double t = ring_time(tiles, r, 2 * c, K);
       if (t < best_t * 0.98) { best_t = t; rb = r; cb = c; }
     }
+}
+
+void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,
+                             const bf16_t* w_up, int m, int K, bf16_t* u, hipStream_t st) {
+  int rb, cb;
+  plan_ring_swiglu(M, m, K, rb, cb);
   const dim3 grid((m + 16 * cb - 1) / (16 * cb), (M + 64 * rb - 1) / (64 * rb), 1);
 #define DLLMC_R(RB, CB)                                                                                 \
   hipLaunchKernelGGL((k_gemm_ring<RB, 2 * CB, 1>), grid, dim3(512), 0, st, A, lda, rows, M, w_gate, w_up, m, m, \

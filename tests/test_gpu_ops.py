@@ -90,18 +90,18 @@ def test_select_rejects_bad_k():
 # ------------------------------------------------------------------ linear (gather GEMM)
 @pytest.mark.parametrize("dtype,M,N,K,gather", [
     ("f32", 8, 256, 256, False), ("f32", 96, 704, 256, True), ("f32", 33, 100, 72, True),
-    ("bf16", 64, 4096, 4096, True),      # MFMA streaming kernel, one row tile, split contraction
+    ("bf16", 64, 4096, 4096, True),      # weight-streaming kernel, one row tile, split contraction
     ("bf16", 51, 1024, 1024, True),      # ragged rows
     ("bf16", 200, 512, 3584, True),      # several row tiles, K = 28 * 128
     ("bf16", 20, 2432, 896, False),      # N = 19 * 128
     ("bf16", 40, 896, 2432, False),
     ("bf16", 17, 200, 72, True),         # falls back to the plain kernel
-    ("bf16", 100, 1024, 1024, True),     # streaming kernel, 128 rows per workgroup
-    ("bf16", 128, 512, 896, False),      # the same with phases of 128
-    ("bf16", 150, 512, 1024, True),      # two such tiles, the second ragged
-    ("bf16", 256, 1024, 4096, True),     # 128 x 128 LDS-direct kernel, split contraction
-    ("bf16", 300, 512, 896, True),       # tile kernel, ragged last row tile, K = 14 * 64
-    ("bf16", 768, 2432, 1024, False),    # tile kernel, N = 19 * 128
+    ("bf16", 100, 1024, 1024, True),     # more rows than 64
+    ("bf16", 128, 512, 896, False),
+    ("bf16", 150, 512, 1024, True),
+    ("bf16", 256, 1024, 4096, True),     # rows of the tile kernels, which a small map may do without
+    ("bf16", 300, 512, 896, True),
+    ("bf16", 768, 2432, 1024, False),    # N = 19 * 128
 ])
 def test_linear_matches_matmul(dtype, M, N, K, gather):
     run_linear_case(dtype, M, N, K, gather)
@@ -109,6 +109,7 @@ def test_linear_matches_matmul(dtype, M, N, K, gather):
 
 @pytest.mark.parametrize("M,N,K", [(256, 1024, 4096), (300, 512, 896), (768, 2432, 1024)])
 def test_linear_tile_kernel(M, N, K):
+    """The 128 x 128 tiles (and the 256 x 256 ones at 768 rows where they divide the columns), whatever the estimates."""
     binding.set_gemm_tuning(tile_min_m=128)
     try:
         run_linear_case("bf16", M, N, K, True)
@@ -127,9 +128,8 @@ def test_linear_fat_kernel(M, N, K):
 
 @pytest.mark.parametrize("K", [128, 256, 384, 512, 768, 1024, 1280, 1536])
 @pytest.mark.parametrize("M,N", [(40, 128), (64, 256)])
-def test_linear_streaming_kernel_phase_counts(M, N, K):
-    """One slice, so that the workgroup walks K / 256 (or K / 128) phases: one to six, through the
-    paired loop and each of its tails."""
+def test_linear_streaming_kernel_step_counts(M, N, K):
+    """One slice, so that the workgroup walks K / 64 steps: 2 to 24, fewer and more than its ring has stages."""
     binding.set_gemm_tuning(force_s=1)
     try:
         run_linear_case("bf16", M, N, K, True)
@@ -137,14 +137,25 @@ def test_linear_streaming_kernel_phase_counts(M, N, K):
         binding.set_gemm_tuning(force_s=0)
 
 
-@pytest.mark.parametrize("nw", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(256, 1024, 4096), (200, 512, 896), (300, 2304, 1024), (512, 1024, 512)])
-def test_linear_streaming_kernel_with_256_rows_per_workgroup(M, N, K, nw):
-    binding.set_gemm_tuning(tall_max_m=512, nw=nw)
+def test_linear_streaming_kernel_of_hundreds_of_rows(M, N, K):
+    """The tile kernels switched off."""
+    binding.set_gemm_tuning(tile_min_m=1 << 20, fat_min_m=1 << 20)
     try:
         run_linear_case("bf16", M, N, K, True)
     finally:
-        binding.set_gemm_tuning(tall_max_m=128, nw=8)
+        binding.set_gemm_tuning(tile_min_m=192, fat_min_m=512)
+
+
+def test_knobs_of_a_kernel_that_is_gone_change_nothing():
+    a = torch.randn((100, 512), device="cuda").bfloat16()
+    w = torch.randn((256, 512), device="cuda").bfloat16()
+    want = binding.op_linear("bf16", a, w)
+    binding.set_gemm_tuning(nw=4, nw_dual=104, tall_max_m=512)
+    try:
+        assert torch.equal(binding.op_linear("bf16", a, w), want)
+    finally:
+        binding.set_gemm_tuning(nw=8, nw_dual=106, tall_max_m=128)
 
 
 def run_linear_case(dtype, M, N, K, gather):

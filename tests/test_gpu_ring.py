@@ -3,11 +3,13 @@ at the edges of its tiles, rings and slices.
 
 bf16 products are exact in float32; a float32 sum of K of them is off by about 2^-24 sqrt(K / 6) of its size in any
 order: the bar is 2^-24 sqrt(K) + 2^-23."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
-from paper_2506_06295_amd import binding
+from paper_2506_06295_amd import binding, inputs as I
 from tests import parity_util as PU
 from tests.test_gpu_step import MINI_DREAM, MINI_LLADA, run_schedule
 
@@ -68,3 +70,40 @@ def test_schedule(cfg):
     assert st.worst_rel <= 2e-2
     PU.compare_caches(cfg, gpu, ora, st)
     gpu.close()
+
+
+FFN = I.Config("ffn", T=1, d=256, H_q=2, H_kv=2, d_h=128, m=1000, B=1, L_p=20, L_r=30, steps=2, rho=0.5, K_p=4, K_r=4,
+               dtype="bf16", vocab=64)
+
+
+# gate/up of a refresh, every workgroup shape that is chosen: 64, 128 and 192 rows x 16 to 80 columns of each matrix, last
+# row and column tiles ragged; d = 256 is fewer steps than the ring has stages, d = 1024 more, from another start per tile
+@pytest.mark.parametrize("M,m,d,rows,cols", [
+    (50, 1000, 256, 64, 16), (50, 4136, 256, 64, 32), (50, 8208, 256, 64, 48), (50, 12312, 256, 64, 64),
+    (50, 16424, 256, 64, 80), (384, 1358, 256, 128, 16), (100, 6176, 256, 128, 32), (100, 8208, 256, 128, 48),
+    (100, 12312, 256, 128, 64), (100, 16424, 256, 128, 80), (150, 4136, 256, 192, 32), (150, 8208, 256, 192, 48),
+    (150, 12312, 256, 192, 64), (150, 16424, 256, 192, 80),
+    (50, 8208, 1024, 64, 48), (100, 6176, 1024, 128, 32), (150, 4136, 1024, 192, 32),
+])
+def test_gate_up_shapes(M, m, d, rows, cols):
+    c = ctypes.c_int32()
+    assert binding.lib().dllmc_plan_gate_up(M, m, d, ctypes.byref(c)) == rows and c.value == cols
+    cfg = FFN.replace(m=m, d=d, L_p=M - 30)
+    ws = I.device_weights(cfg)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + m + d)
+    hid = torch.randn((1, M, d), generator=g, device="cuda").bfloat16()
+    den = binding.CachedDenoiser(n_layers=1, d_model=d, n_q_heads=2, n_kv_heads=2, head_dim=128, d_ffn=m, batch=1,
+                                 dtype="bf16", weights=ws, L_p=M - 30, L_r=30, rho=0.5, K_p=4, K_r=4,
+                                 rms_eps=cfg.rms_eps, rope_theta=cfg.rope_theta)
+    den.step(hid, 0)
+    attn, ffn = den.read_cache(0, 2)[0], den.read_cache(0, 3)[0]
+    w = {k: v.double() for k, v in ws[0].items()}
+    x = (hid[0].float() + attn.float()).double()
+    z = (x / (x.square().mean(1, keepdim=True) + cfg.rms_eps).sqrt() * w["ffn_norm_g"]).bfloat16().double()
+    u = (torch.nn.functional.silu(z @ w["w_gate"].t()) * (z @ w["w_up"].t())).bfloat16().double()
+    want = u @ w["w_down"].t()
+    # three roundings of 2^-9 / sqrt(3); 16 columns of u left out or taken twice are sqrt(16 / m) > 2^-5 of the norm
+    err = (ffn.double() - want).norm(dim=1) / want.norm(dim=1)
+    assert float(err.max()) < 2.0 ** -7
+    den.close()

@@ -23,8 +23,6 @@ MINI_DREAM = I.Config("mini_dream", T=2, d=896, H_q=7, H_kv=1, d_h=128, m=2432, 
 MINI_LONG = I.Config("mini_long", T=2, d=512, H_q=4, H_kv=4, d_h=128, m=1536, B=1, L_p=700,
                      L_r=130, steps=5, rho=0.1, K_p=4, K_r=3, dtype="bf16", vocab=4096)
 
-DEFAULT_NW_DUAL = 106  # the library's default shape of the fused gate/up kernel
-
 
 def run_schedule(cfg, stress=False, steps=None, **over):
     ws = I.all_weights(cfg)
@@ -88,19 +86,18 @@ def test_bf16_stress_schedule_exact_indices(cfg):
     gpu.close()
 
 
-@pytest.mark.parametrize("nw_dual", [4, 8, 104, 106, 108])
 @pytest.mark.parametrize("cfg", [MINI_LLADA, MINI_LONG], ids=lambda c: c.name)
-def test_fused_gate_up_kernel_variants(cfg, nw_dual):
-    """Every workgroup shape of the fused gate/up kernel (wavefronts per workgroup, one or two
-    wavefront groups over the contraction range) against the oracle."""
-    binding.set_gemm_tuning(nw_dual=nw_dual)
+def test_fused_gate_up_without_the_tile_kernels(cfg):
+    """Refresh steps whose hundreds of rows all go through the weight-streaming kernel, against the oracle (its workgroup
+    shapes one by one: test_gpu_ring)."""
+    binding.set_gemm_tuning(tile_min_m=1 << 20)
     try:
         gpu, ora, st = run_schedule(cfg.replace(steps=4), stress=True)
         assert st.failed == 0, st.failures
         assert st.worst_rel <= 2e-2
         gpu.close()
     finally:
-        binding.set_gemm_tuning(nw_dual=DEFAULT_NW_DUAL)
+        binding.set_gemm_tuning(tile_min_m=192)
 
 
 @pytest.mark.parametrize("cfg", [I.CONFIGS["toy"].replace(L_p=0, K_p=3), MINI_LLADA.replace(L_p=0, steps=5),
@@ -461,11 +458,11 @@ def test_tuning_is_copied_at_creation_and_live_contexts_keep_theirs():
     want = [ref.step(hid[i], i)[0].clone() for i in range(cfg.steps)]
     live, _ = PU.make_pair(cfg, ws)
     got = [live.step(hid[0], 0)[0].clone()]
-    binding.set_gemm_tuning(nw_dual=4, nw=4, force_s=2)
+    binding.set_gemm_tuning(force_s=2, tile_min_m=64)
     try:
         got += [live.step(hid[i], i)[0].clone() for i in range(1, cfg.steps)]
     finally:
-        binding.set_gemm_tuning(nw_dual=DEFAULT_NW_DUAL, nw=8, force_s=0)
+        binding.set_gemm_tuning(force_s=0, tile_min_m=192)
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(got, want))
     ref.close()
@@ -512,9 +509,9 @@ def test_distance_under_both_readings_of_the_bf16_rounding_points(cfg):
 
 
 def test_tile_kernels_agree_with_the_streaming_kernels_over_many_launches():
-    """One LLaDA-8B-width layer, every step a full refresh (768 rows: the 128 x 128 LDS-direct tile
-    kernels, V-verify and Q|K RoPE finished in their epilogues), against a context created with the
-    tile kernels switched off (streaming kernels, split contraction, row kernels).  Same inputs, so
+    """One LLaDA-8B-width layer, every step a full refresh (768 rows: the LDS-direct tile kernels,
+    Q|K RoPE and SwiGLU finished in their epilogues), against a context created with the
+    tile kernels switched off (streaming kernel, split contraction, row kernels).  Same inputs, so
     the caches may differ by rounding flips only.  A fragment read overtaken by the next load into
     its LDS stage corrupts one 64-wide step of a 16-row block (about 0.2 absolute on K) in a few
     launches per hundred: 120 launches of every projection."""
@@ -528,11 +525,11 @@ def test_tile_kernels_agree_with_the_streaming_kernels_over_many_launches():
         d_ffn=cfg.m, batch=cfg.B, dtype=cfg.dtype, weights=ws, L_p=cfg.L_p, L_r=cfg.L_r, rho=cfg.rho,
         K_p=cfg.K_p, K_r=cfg.K_r, rms_eps=cfg.rms_eps, rope_theta=cfg.rope_theta)
     tiles = mk()
-    binding.set_gemm_tuning(tile_min_m=1 << 20)
+    binding.set_gemm_tuning(tile_min_m=1 << 20, fat_min_m=1 << 20)
     try:
         stream = mk()
     finally:
-        binding.set_gemm_tuning(tile_min_m=192)
+        binding.set_gemm_tuning(tile_min_m=192, fat_min_m=512)
     worst = {}
     for i in range(120):
         hid = torch.randn(cfg.B, n, cfg.d, device="cuda", generator=gen).to(torch.bfloat16)

@@ -1,5 +1,6 @@
 """Every tile shape of the refresh steps' launches (128, 192 and 256 rows; gate/up, V-verify and Q|K finished in their
-epilogues) at row counts around whole tiles and rounds, against a context with the tile kernels switched off.
+epilogues) at row counts around whole tiles and rounds, against a context whose maps of fewer than 2^20 rows all go through
+the weight-streaming kernel.
 
 Same inputs, other orders of summation: elements may round to neighbouring bf16 values (2^-7 of the value), and
 those flips spread a little behind the attention; a step of a tile multiplied with the wrong operands moves its rows
@@ -12,17 +13,26 @@ from paper_2506_06295_amd import binding, inputs as I
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("base,L_p,L_r", [
-    ("llada8b", 20, 180),    # 200 rows: 128-row tiles, 256 x 96 gate/up
-    ("llada8b", 129, 255),   # 384 rows: two whole 192-row tiles for gate/up
-    ("llada8b", 129, 256),   # 385
-    ("llada8b", 320, 256),   # 576 rows: three 192-row tiles
-    ("llada8b", 513, 256),   # 769: a fifth tile of one row
-    ("llada8b", 900, 130),   # 1030: 256 x 192 gate/up, 256-row tiles from here on
-    ("dream7b", 700, 67),    # 767 rows, grouped KV heads, an FFN width that 96 does not divide
+BASES = {name: I.CONFIGS[name] for name in ("llada8b", "dream7b")}
+BASES["2560_wide"] = BASES["llada8b"].replace(d=2560, H_q=20, H_kv=20, m=1536)
+
+
+# (V-verify: 0 split contraction, 1 / 2 / 3 tiles of 128, 256 and 192 rows, 4 64 x 64 tiles)
+@pytest.mark.parametrize("base,L_p,L_r,v_way", [
+    ("llada8b", 20, 180, 4),     # 200 rows: 256 x 96 gate/up
+    ("llada8b", 129, 255, 0),    # 384 rows: two whole 192-row tiles for gate/up
+    ("llada8b", 129, 256, 0),    # 385
+    ("llada8b", 320, 256, 0),    # 576 rows: three 192-row tiles
+    ("llada8b", 513, 256, 0),    # 769: a fifth tile of one row
+    ("llada8b", 900, 130, 0),    # 1030: 256 x 192 gate/up
+    ("llada8b", 1900, 147, 1),   # 2047: a ragged sixteenth tile
+    ("llada8b", 2800, 273, 2),   # 3073: a thirteenth 256-row tile of one row
+    ("dream7b", 700, 67, 0),     # 767 rows, grouped KV heads, an FFN width that 96 does not divide
+    ("2560_wide", 800, 200, 3),  # 1000: a sixth 192-row tile of 40 rows
 ])
-def test_full_refresh(base, L_p, L_r):
-    cfg = I.CONFIGS[base].replace(T=1, K_p=1, K_r=1, L_p=L_p, L_r=L_r)
+def test_full_refresh(base, L_p, L_r, v_way):
+    cfg = BASES[base].replace(T=1, K_p=1, K_r=1, L_p=L_p, L_r=L_r)
+    assert binding.lib().dllmc_plan_vverify(1, L_p + L_r, cfg.d, cfg.d_kv) == v_way
     ws = I.device_weights(cfg)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(L_p * 1000 + L_r)
@@ -31,11 +41,11 @@ def test_full_refresh(base, L_p, L_r):
         d_ffn=cfg.m, batch=cfg.B, dtype=cfg.dtype, weights=ws, L_p=L_p, L_r=L_r, rho=cfg.rho,
         K_p=cfg.K_p, K_r=cfg.K_r, rms_eps=cfg.rms_eps, rope_theta=cfg.rope_theta)
     tiles = make()
-    binding.set_gemm_tuning(tile_min_m=1 << 20)
+    binding.set_gemm_tuning(tile_min_m=1 << 20, fat_min_m=1 << 20)
     try:
         plain = make()
     finally:
-        binding.set_gemm_tuning(tile_min_m=192)
+        binding.set_gemm_tuning(tile_min_m=192, fat_min_m=512)
     for i in range(4):
         hid = torch.randn(cfg.B, cfg.n, cfg.d, device="cuda", generator=gen).to(torch.bfloat16)
         a_out, _ = tiles.step(hid, i)
