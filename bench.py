@@ -304,8 +304,8 @@ def main():
         achieved = ks["alg_bytes"] / (k_ms * 1e-3) / 1e9 if k_ms > 0 else 0.0
         traffic = TRAFFIC_BYTES_PER_LAUNCH.get(cfg.name)
         result["roofline"] = {
-            "kernel": "k_gemm_ring (every launch: fused gate/up, Q|K, output and down projections "
-                      "of the recomputed rows)",
+            "kernel": "k_gemm_ring (every launch: the maps of few rows, and those of hundreds where it is the "
+                      "quicker kernel)",
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
             "traffic_source": TRAFFIC_SOURCE.format(name=cfg.name) if traffic else None,

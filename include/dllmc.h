@@ -203,7 +203,8 @@ enum {
   DLLMC_KC_GEMM_DOWN, DLLMC_KC_ATTENTION, DLLMC_KC_SELECT, DLLMC_KC_ROW, DLLMC_KC_LISTS,
   DLLMC_KC_EVENT_OVERHEAD, /* an empty span per step: what one event record adds to a span */
   DLLMC_KC_STREAM_KERNEL,  /* the launches of the five gemm classes that ran the weight-streaming
-                              kernel (k_gemm_ring), counted here a second time: one kernel's
+                              kernel (k_gemm_ring; the class is named "k_gemm_stream"),
+                              counted here a second time: one kernel's
                               figures, comparable with a profiler's per-kernel average */
   DLLMC_KC_HEAD_GEMM,      /* closed loop: vocabulary projection of the masked rows */
   DLLMC_KC_GEN_OTHER,      /* closed loop: final norm, greedy token + confidence, eligibility,

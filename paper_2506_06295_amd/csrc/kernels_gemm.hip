@@ -140,6 +140,10 @@ struct TileEpilogue {
 // exp, first index of the maximum) by TPR neighbouring threads and stored to part[row * tiles + tile].
 // The results cross through LDS for this: reducing them in the accumulator layout, 16 lanes to a row,
 // takes four times the vector instructions.
+// The exponentials are the hardware's 2^x of a float32 product: 6e-8 |l - maximum| relative on a term that weighs
+// exp(l - maximum), so at most ~3e-7 of the sum, less than adding 64 terms in float32 costs.  Confidences against 64 bits, rms
+// (expf in its place): 100 rows of 126464 9.78e-6 (9.78e-6), 128 of 152064 1.88e-6 (1.87e-6), 100 of 4096 6.8e-7 (7.0e-7);
+// 190.5 us (195.5) for the first.
 template <int TPR>
 __device__ __forceinline__ void head_tile_reduce(const float* tile, int m0, int M, int col_tile, int tiles,
                                                  HeadPart* __restrict__ part) {

@@ -3,8 +3,9 @@
 //
 // k_gemm_ring<RB, NB, DUAL>: tile = 64 * RB rows x 16 * NB weight rows, one workgroup of eight wavefronts per
 // CU.  Both operands go from global memory straight into LDS (global_load_lds_dwordx4: an instruction
-// copies 8 rows x 128 bytes), through a ring of as many 64-wide stages as 150 KB hold: five to eight steps,
-// 60 to 90 KB of weights, are in flight per CU, never drained before the last steps.  Four wavefronts
+// copies 8 rows x 128 bytes), through a ring of as many 64-wide stages as 150 KB hold, at most eight.  All but one
+// of them are in flight per CU, seven steps of the smallest tiles (56 KB of weights at NB = 4), two of the largest (32 to 40
+// KB at RB = 3, NB = 8 and 10), and not drained before the last steps.  Four wavefronts
 // take 16 * RB rows each for the first half of every step, the other four the same rows for its second half
 // (so that any number of column blocks deals evenly); their sums meet in LDS at the end.
 //   DUAL = 1: NB/2 blocks of W0 (gate) and the same blocks of W1 (up); the epilogue stores
