@@ -237,7 +237,7 @@ bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K);
 // (t: estimated us with what follows, see launch_gemm)
 RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, bool summed);
 void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
-                      const bf16_t* W1, int N0, int N, int K, float* C, hipStream_t st);
+                      const bf16_t* W1, int N0, int N, int K, float* C, bool fine, hipStream_t st);
 // row blocks of 64 and column blocks of 16 (of each matrix) of the next one's workgroups
 void plan_ring_swiglu(int M, int m, int K, int& rb, int& cb);
 void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,

@@ -187,7 +187,7 @@ __device__ __forceinline__ void head_tile_reduce(const float* tile, int m0, int 
     part[static_cast<size_t>(m0 + r) * tiles + col_tile] = HeadPart{mx, sum, col_tile * 128 + first, 0};
 }
 
-template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0>
+template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0, bool FINE = false>
 __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int lda,
                                               const int* __restrict__ rows, int M,
                                               const bf16_t* __restrict__ W0,
@@ -457,7 +457,9 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     }
   } else {
   DLLMC_LDS_ISSUE(0, rot)
-  for (int kt = 0; kt < nkt; ++kt) {
+  // (FINE, see k_gemm_ring: the first and the second half of the steps in sums of their own.  Halves, because even and odd
+  // steps apart, two copies of the loop body in turn, took a third longer.)
+  auto step = [&](int kt, f32x4 (&sum)[MI][NJ]) {
     const int cur = kt & 1;
     const bool more = kt + 1 < nkt;
     {
@@ -492,7 +494,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+          sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], sum[i][j], 0, 0, 0);
     }
     // all fragment reads of this stage are complete before the loads issued at the top of the
     // next iteration overwrite it.  The explicit wait matters: without it the compiler puts the
@@ -501,6 +503,23 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     // before those reads execute.
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
+  };
+  if (FINE) {
+    f32x4 late[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) late[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int half = nkt / 2;
+    int kt = 0;
+    for (; kt < half; ++kt) step(kt, acc);
+    for (; kt < nkt; ++kt) step(kt, late);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] += late[i][j];
+  } else {
+    for (int kt = 0; kt < nkt; ++kt) step(kt, acc);
   }
   }
 #undef DLLMC_LDS_ISSUE
@@ -717,6 +736,14 @@ __global__ __launch_bounds__(256) void k_gemm_mid(const bf16_t* __restrict__ A, 
                                                   const bf16_t* __restrict__ W1, int N0, int N,
                                                   int K, int k_per_slice, float* __restrict__ C) {
   gemm_lds_body<2, 2, 4, 4>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
+}
+
+__global__ __launch_bounds__(256) void k_gemm_mid_fine(const bf16_t* __restrict__ A, int lda,
+                                                       const int* __restrict__ rows, int M,
+                                                       const bf16_t* __restrict__ W0,
+                                                       const bf16_t* __restrict__ W1, int N0, int N,
+                                                       int K, int k_per_slice, float* __restrict__ C) {
+  gemm_lds_body<2, 2, 4, 4, 0, 0, true>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
 }
 
 // Tile kernels that finish the step's work in their epilogue (single slice): V-verify and Q | K
@@ -938,8 +965,8 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     // longer than with the best choice of all, where an estimate with different prices for the partial sums of the two
     // kinds of kernel, no time per launch and no difference between one slice and a slice sum took 19 %, and 47 shapes
     // more than 5 % longer than a plain rule on rows alone (none of 340 now): 192 rows x 4096 x 4096 20.6 us, now
-    // 17.8; 333 x 3072 x 1024 19.2 -> 9.7; 400 x 2432 x 896 15.2 -> 9.1; 1536 x 896 x 2432 25.2 -> 17.2; 576 x 4096 x 4096
-    // 35.0 -> 33.3; 64 x 12288 x 4096 31.7 -> 25.9; at worst 65 x 8192 x 4096 19.6 -> 21.5.
+    // 18.2; 333 x 3072 x 1024 19.2 -> 9.9; 400 x 2432 x 896 15.2 -> 9.5; 1536 x 896 x 2432 25.2 -> 17.8; 576 x 4096 x 4096
+    // 35.0 -> 33.2; 64 x 12288 x 4096 31.7 -> 26.1; at worst 191 x 8192 x 4096 27.5 -> 29.5.
     const bool literal = g_tune.force_s > 0 || g_tune.fat_min_m != defaults.fat_min_m ||
                          g_tune.tile_min_m != defaults.tile_min_m || g_tune.target_wg != defaults.target_wg;
     double best = 1e30;
@@ -1013,7 +1040,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                            c_part);
       break;
     case 2:
-      launch_gemm_ring(p.ring, a, lda, rows, M, w0, w1, N0, N, K, c_part, st);
+      launch_gemm_ring(p.ring, a, lda, rows, M, w0, w1, N0, N, K, c_part, summed, st);
       break;
     case 7:
       launch_gemm_f32(p.f32, static_cast<const float*>(A), lda, rows, M, static_cast<const float*>(W0),
@@ -1024,8 +1051,10 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                          c_part);
       break;
     case 4:
-      hipLaunchKernelGGL(k_gemm_mid, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K,
-                         p.kps, c_part);
+      if (summed)
+        hipLaunchKernelGGL(k_gemm_mid_fine, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part);
+      else
+        hipLaunchKernelGGL(k_gemm_mid, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part);
       break;
   }
   return p.S;

@@ -10,6 +10,9 @@
 // (so that any number of column blocks deals evenly); their sums meet in LDS at the end.
 //   DUAL = 1: NB/2 blocks of W0 (gate) and the same blocks of W1 (up); the epilogue stores
 //             bf16(silu(gate) * up) to U[M, N].  One slice.
+//   FINE: the float32 sums are the caller's result, not what a row kernel rounds: fewer slices mean longer chains of
+//             additions, so the steps are dealt to two or four sums per element, at 0.1 to 0.4 us (error against 64 bits, one
+//             slice of 333 x 3072 x 1024: 1.28e-7 -> 7.7e-8; two of 333 x 4096 x 4096: 1.69e-7 -> 1.23e-7).
 //   otherwise columns [0, N0) come from W0, [N0, N) from W1, float32 partial sums of slice blockIdx.z go
 //             to C[z]; the row kernels add the slices in order (no float atomics: bit-reproducible).
 // Columns past N and rows past M repeat the last one and are dropped at the store: any M and N.
@@ -34,7 +37,7 @@ namespace {
 
 // (The body is a function of its own, inlined: with the loads issued from the kernel itself the compiler
 // waits for every load in flight before each LDS read.)
-template <int RB, int NB, int DUAL>
+template <int RB, int NB, int DUAL, bool FINE = false>
 __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int lda,
                                                const int* __restrict__ rows, int M,
                                                const bf16_t* __restrict__ W0,
@@ -48,6 +51,8 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
   constexpr int NST = kFit > 8 ? 8 : kFit;
   constexpr int LA = RB, LBT = 2 * NB;                 // activation loads per wavefront; weight loads of all
   constexpr int LB0 = LBT / 8, LBR = LBT % 8;          // ... per wavefront, one more for the first LBR
+  // FINE: sums of the steps kt % NA = 0, 1, ... apart, NA shorter chains of additions that are added up at the end
+  constexpr int NA = !FINE ? 1 : RB * NB <= 12 ? 4 : 2;
   __shared__ __attribute__((aligned(1024))) uint4 lds[NST][kStage];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int ln = lane % 16, lg = lane / 16;
@@ -102,17 +107,20 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
     else wait_vmcnt_lds<S * (LA + LB0)>();
   };
 
-  f32x4 acc[RB][NB];
+  f32x4 sums[NA][RB][NB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
+  for (int u = 0; u < NA; ++u)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) sums[u][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 (&acc)[RB][NB] = sums[0];
 
 #pragma unroll
   for (int s = 0; s < NST - 1; ++s)
     if (s < nkt) issue(s, s);
   int stage = 0;
-  for (int kt = 0; kt < nkt; ++kt) {
+  auto step = [&](int kt, f32x4 (&sum)[RB][NB]) {
     // the loads of step kt have landed; the younger steps, at most NST - 2, stay in flight
     const int rem = nkt - 1 - kt;
     if (rem >= NST - 2) wait_steps(std::integral_constant<int, NST - 2>{});
@@ -144,9 +152,20 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int i = 0; i < RB; ++i)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+        sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], sum[i][j], 0, 0, 0);
     stage = stage + 1 < NST ? stage + 1 : 0;
+  };
+  for (int kt = 0; kt < nkt; kt += NA) {
+#pragma unroll
+    for (int u = 0; u < NA; ++u)
+      if (u == 0 || kt + u < nkt) step(kt + u, sums[u]);
   }
+#pragma unroll
+  for (int u = 1; u < NA; ++u)
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] += sums[u][i][j];
   // the second halves' sums are handed over through LDS and added to the first's
   __syncthreads();
   f32x4* red = reinterpret_cast<f32x4*>(&lds[0][0]);
@@ -184,14 +203,14 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
     }
 }
 
-template <int RB, int NB, int DUAL>
+template <int RB, int NB, int DUAL, bool FINE = false>
 __global__ __launch_bounds__(512) void k_gemm_ring(const bf16_t* __restrict__ A, int lda,
                                                    const int* __restrict__ rows, int M,
                                                    const bf16_t* __restrict__ W0,
                                                    const bf16_t* __restrict__ W1, int N0, int N, int K,
                                                    int k_per_slice, float* __restrict__ C,
                                                    bf16_t* __restrict__ U) {
-  gemm_ring_body<RB, NB, DUAL>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C, U);
+  gemm_ring_body<RB, NB, DUAL, FINE>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C, U);
 }
 
 // Estimated time in us of a launch of `tiles` workgroups (one per CU at a time) of 64 * rb rows x 16 * nb
@@ -244,11 +263,15 @@ RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, bool summed) {
 }
 
 void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
-                      const bf16_t* W1, int N0, int N, int K, float* C, hipStream_t st) {
+                      const bf16_t* W1, int N0, int N, int K, float* C, bool fine, hipStream_t st) {
   const dim3 grid(p.nt, p.mt, p.S);
-#define DLLMC_R(RB, NB)                                                                               \
-  hipLaunchKernelGGL((k_gemm_ring<RB, NB, 0>), grid, dim3(512), 0, st, A, lda, rows, M, W0, W1, N0, N, K, \
-                     p.kps, C, nullptr)
+#define DLLMC_R(RB, NB)                                                                                           \
+  do {                                                                                                            \
+    if (fine) hipLaunchKernelGGL((k_gemm_ring<RB, NB, 0, true>), grid, dim3(512), 0, st, A, lda, rows, M, W0, W1, N0, N, \
+                                 K, p.kps, C, nullptr);                                                           \
+    else hipLaunchKernelGGL((k_gemm_ring<RB, NB, 0>), grid, dim3(512), 0, st, A, lda, rows, M, W0, W1, N0, N, K,     \
+                            p.kps, C, nullptr);                                                                   \
+  } while (0)
   switch (p.rb * 10 + p.nb) {
     case 14: DLLMC_R(1, 4); break;
     case 18: DLLMC_R(1, 8); break;
