@@ -302,9 +302,10 @@ int dllmc_set_gemm_tuning(int32_t nw, int32_t nw_dual, int32_t force_s, int32_t 
                           int32_t tile_min_m, int32_t fat_min_m, int32_t tall_max_m);
 
 /* Host-only: the number of contraction-index slices the library would use for a gathered
- * linear map of M rows, N columns (the first N0 from one matrix), contraction length K, given a
+ * linear map of M rows, N columns (the first N0 from one matrix), contraction length K in a step, given a
  * float32 slice buffer of capacity_floats elements and 16-byte aligned operands; 0 if M*N
- * floats do not fit.  slices * M * N never exceeds capacity_floats. */
+ * floats do not fit.  slices * M * N never exceeds capacity_floats.  (The single operations add the slices in
+ * a launch of its own, so they may take fewer.) */
 int32_t dllmc_plan_gemm_slices(int32_t dtype, int32_t M, int32_t N, int32_t N0, int32_t K,
                                size_t capacity_floats);
 
