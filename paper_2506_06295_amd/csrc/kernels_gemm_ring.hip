@@ -25,8 +25,8 @@
 //             gate/up 2 x 12288 x 4096 43.9 -> 38.4, 2 x 18944 x 3584 71.7 -> 51.0
 //   128 rows: 4096 x 4096 14.8 -> 12.6, 8192 x 4096 22.3 -> 19.3, gate/up 59.4 -> 44.9 and 101 -> 59
 //   160 rows: 18.7 -> 15.3, 29.9 -> 23.9, 4096 x 12288 41.7 -> 30.4
-// From 192 rows the 128 x 128 tiles are level or ahead (256 rows: 16.9 / 27.2 / 39.3 us there, 17.4 / 26.8 /
-// 36.6 here; gate/up 62 there, 68 here).
+// From 192 rows the 128 x 128 tiles are level or ahead in many places (256 rows: 16.9 / 27.2 / 39.3 us there, 17.4 / 26.8 /
+// 36.6 here; gate/up 62 there, 68 here), and plan_gemm takes the one with the lower estimate.
 #include <type_traits>
 
 #include "common.hpp"
