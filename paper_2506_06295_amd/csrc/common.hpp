@@ -182,7 +182,10 @@ struct GemmTuning {
   int tile_min_m = 192;     // activation rows from which the 128 x 128 LDS-direct kernel is considered
                             // (both: a value other than the default is taken literally, the kernel is
                             // used from there on)
+  bool weights_once = false;  // the context's weights exceed kMemorySideCache: none is still cached at its next use
 };
+// AMD Instinct MI355X: 256 MB of memory-side cache in front of the HBM
+constexpr size_t kMemorySideCache = static_cast<size_t>(256) << 20;
 GemmTuning gemm_default_tuning();
 struct TuningScope {
   const GemmTuning* prev;
@@ -236,12 +239,13 @@ struct RingPlan { int rb, nb, S, kps, nt, mt; double t; };
 bool gemm_ring_ok(int dtype, bool operands_aligned, int lda, int K);
 // (t: estimated us with what follows, see launch_gemm)
 RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, bool summed);
+// (once: weights no cache holds from use to use, see GemmTuning::weights_once)
 void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
-                      const bf16_t* W1, int N0, int N, int K, float* C, bool fine, hipStream_t st);
+                      const bf16_t* W1, int N0, int N, int K, float* C, bool fine, bool once, hipStream_t st);
 // row blocks of 64 and column blocks of 16 (of each matrix) of the next one's workgroups
 void plan_ring_swiglu(int M, int m, int K, int& rb, int& cb);
 void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,
-                             const bf16_t* w_up, int m, int K, bf16_t* u, hipStream_t st);
+                             const bf16_t* w_up, int m, int K, bf16_t* u, bool once, hipStream_t st);
 
 // Vocabulary projection that leaves, instead of the logits, their reduction per row and 128-column
 // tile: part[i * tiles + t] for i < M.  Returns the number of tiles, 0 (nothing launched) when the shape is not

@@ -244,6 +244,10 @@ int create_impl(dllmc_ctx** out, const dllmc_model* model, const dllmc_layer_wei
   if (c->k_sel > L_r) c->k_sel = L_r;
   c->k_layer.assign(model->n_layers, c->k_sel);
   c->tune = gemm_default_tuning();
+  const size_t d = model->d_model, d_q = static_cast<size_t>(model->n_q_heads) * model->head_dim,
+               d_kv = static_cast<size_t>(model->n_kv_heads) * model->head_dim;
+  c->tune.weights_once =
+      model->n_layers * (2 * d * d_q + 2 * d * d_kv + 3 * d * model->d_ffn) * lay.esz > kMemorySideCache;
   c->st = static_cast<hipStream_t>(hip_stream);
   c->last_step = -1;
   c->lay = lay;

@@ -187,7 +187,7 @@ __device__ __forceinline__ void head_tile_reduce(const float* tile, int m0, int 
     part[static_cast<size_t>(m0 + r) * tiles + col_tile] = HeadPart{mx, sum, col_tile * 128 + first, 0};
 }
 
-template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0, bool FINE = false>
+template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0, bool FINE = false, bool NT = false>
 __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int lda,
                                               const int* __restrict__ rows, int M,
                                               const bf16_t* __restrict__ W0,
@@ -199,6 +199,9 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   constexpr int BM = WM * MI * 16, BN = WN * NJ * 16;
   constexpr int LA = BM / 8 / NWV, LB = BN / 8 / NWV;  // load instructions per wavefront and step
   static_assert(BM % (8 * NWV) == 0 && BN % (8 * NWV) == 0, "loader must divide evenly");
+  // NT: non-temporal weight loads, where a single row tile reads weights that no cache will hold at their next use (see
+  // k_gemm_ring; with two row tiles to a weight tile they cost the second one its hits: head of 200 rows 294 -> 354 us)
+  constexpr int kAux = NT ? 2 : 0;
   // [stage][activation rows, then weight rows][8 slots], 16 bytes each
   // (EPI: followed by two ints per tile row, see below.  One LDS object on purpose: with a second
   // one the compiler can no longer tell the fragment reads from the loads in flight into the
@@ -293,7 +296,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     _Pragma("unroll") for (int j = 0; j < LA; ++j) __builtin_amdgcn_global_load_lds(            \
         asrc[j] + (kt) * kFatK, &lds[stage][(LA * wave + j) * 64], 16, 0, 0);                   \
     _Pragma("unroll") for (int j = 0; j < LB; ++j) __builtin_amdgcn_global_load_lds(            \
-        bsrc[j] + (kt) * kFatK, &lds[stage][BM * 8 + (LB * wave + j) * 64], 16, 0, 0);          \
+        bsrc[j] + (kt) * kFatK, &lds[stage][BM * 8 + (LB * wave + j) * 64], 16, 0, kAux);       \
   }
 
   f32x4 acc[MI][NJ];
@@ -362,7 +365,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
         uint32_t o = boff;
         asm volatile("" : "+v"(o));
         __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint4*>(bp + o),
-                                         &lds_all[slot * kSlot + (LB * wave + j) * 64], 16, 0, 0);
+                                         &lds_all[slot * kSlot + (LB * wave + j) * 64], 16, 0, kAux);
       }
     };
     // loads [i0, i1) of the NL that the barrier of step kb makes room for (slots sa_b, sb_b of that
@@ -773,10 +776,11 @@ __global__ __launch_bounds__(256) void k_gemm_mid_qk(const bf16_t* __restrict__ 
   gemm_lds_body<2, 2, 4, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
 }
 
+template <bool NT>
 __global__ __launch_bounds__(256) void k_gemm_mid_head(const bf16_t* __restrict__ A, int lda, int M,
                                                        const bf16_t* __restrict__ W, int N, int K,
                                                        float* __restrict__ C) {
-  gemm_lds_body<2, 2, 4, 4, 0, 3>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C);
+  gemm_lds_body<2, 2, 4, 4, 0, 3, false, NT>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C);
 }
 
 // fused gate/up + SwiGLU for many rows: N is the FFN width, grid.x = N / 128 (fat) or N / 64 (mid)
@@ -811,13 +815,15 @@ __global__ __launch_bounds__(512) void k_gemm_fat96_swiglu(const bf16_t* __restr
 // 256 rows x (48 gate + 48 up) columns, four wavefronts of 64 x 96 each: for up to 256 rows and
 // an FFN width that is a multiple of 48 the grid is one workgroup per 48 columns (12288 / 48 =
 // 256, one per CU), where the 128 x 128 tiles leave half of the CUs with twice the work (a
-// response refresh of 256 rows: 80 -> 69 us per layer; two workgroups of 128 x 96 per CU: 73).
+// response refresh of 256 rows: 80 -> 69 us per layer; two workgroups of 128 x 96 per CU: 73; with non-temporal
+// weight loads 65.7 -> 62.7).
+template <bool NT>
 __global__ __launch_bounds__(256) void k_gemm_tall_swiglu(const bf16_t* __restrict__ A, int lda,
                                                           const int* __restrict__ rows, int M,
                                                           const bf16_t* __restrict__ Wg,
                                                           const bf16_t* __restrict__ Wu, int N, int K,
                                                           bf16_t* __restrict__ U) {
-  gemm_lds_body<4, 1, 4, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
+  gemm_lds_body<4, 1, 4, 6, 1, 0, false, NT>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 
 // 192-row tiles (five slots of 24 KB): the row count that makes whole rounds of workgroups where 256 rows do not
@@ -1042,7 +1048,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                            c_part);
       break;
     case 2:
-      launch_gemm_ring(p.ring, a, lda, rows, M, w0, w1, N0, N, K, c_part, summed, st);
+      launch_gemm_ring(p.ring, a, lda, rows, M, w0, w1, N0, N, K, c_part, summed, g_tune.weights_once, st);
       break;
     case 7:
       launch_gemm_f32(p.f32, static_cast<const float*>(A), lda, rows, M, static_cast<const float*>(W0),
@@ -1073,8 +1079,10 @@ int launch_gemm_head(int dtype, const void* A, int lda, int M, const void* W, in
   if (!aligned16(A) || !aligned16(W) || !aligned16(part)) return 0;
   if (static_cast<size_t>(M) * (N / kMidN) > part_capacity) return 0;
   t_last_stream = false;
-  hipLaunchKernelGGL(k_gemm_mid_head, dim3(N / kMidN, (M + kMidM - 1) / kMidM), dim3(256), 0, st,
-                     static_cast<const bf16_t*>(A), lda, M, static_cast<const bf16_t*>(W), N, K,
+  // (weights beyond the memory-side cache: 100 rows x 126464 x 4096 191 -> 180 us, 4 rows 178 -> 163)
+  const bool nt = M <= kMidM && static_cast<size_t>(N) * K * 2 > kMemorySideCache;
+  hipLaunchKernelGGL(nt ? k_gemm_mid_head<true> : k_gemm_mid_head<false>, dim3(N / kMidN, (M + kMidM - 1) / kMidM),
+                     dim3(256), 0, st, static_cast<const bf16_t*>(A), lda, M, static_cast<const bf16_t*>(W), N, K,
                      reinterpret_cast<float*>(part));
   return N / kMidN;
 }
@@ -1121,7 +1129,10 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
         case 1: DLLMC_SW(k_gemm_fat96_swiglu, 512); break;
         case 2: DLLMC_SW(k_gemm_r192_swiglu, 512); break;
         case 3: DLLMC_SW(k_gemm_mid_swiglu, 256); break;
-        default: DLLMC_SW(k_gemm_tall_swiglu, 256); break;
+        default:  // one row tile
+          if (g_tune.weights_once) DLLMC_SW(k_gemm_tall_swiglu<true>, 256);
+          else DLLMC_SW(k_gemm_tall_swiglu<false>, 256);
+          break;
       }
 #undef DLLMC_SW
       return true;
@@ -1129,7 +1140,8 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   }
   t_last_stream = true;
   launch_gemm_ring_swiglu(static_cast<const bf16_t*>(A), lda, rows, M, static_cast<const bf16_t*>(w_gate),
-                          static_cast<const bf16_t*>(w_up), m, K, static_cast<bf16_t*>(u), st);
+                          static_cast<const bf16_t*>(w_up), m, K, static_cast<bf16_t*>(u),
+                          g_tune.weights_once, st);
   return true;
 }
 

@@ -13,6 +13,12 @@
 //   FINE: the float32 sums are the caller's result, not what a row kernel rounds: fewer slices mean longer chains of
 //             additions, so the steps are dealt to two or four sums per element, at 0.1 to 0.4 us (error against 64 bits, one
 //             slice of 333 x 3072 x 1024: 1.28e-7 -> 7.7e-8; two of 333 x 4096 x 4096: 1.69e-7 -> 1.23e-7).
+//   NT: non-temporal weight loads, for weights that only one workgroup reads and that no cache will hold when they are
+//             read again (launches of one row tile in models whose weights exceed the 256 MB memory-side cache): they then displace
+//             neither what the launch's workgroups share nor what the next launches read, and come at 6.0 TB/s
+//             instead of 5.3 (a loop of nothing but these loads, 201 MB of weights beside 64 activation rows: 37.8 -> 33.7 us).
+//             Layer of an adaptive step of 64 rows, 4096 wide: gate/up 45.5 -> 38.6 us, down 29.8 -> 25.9, Q|K 20.8 -> 19.2, and
+//             the launches between them 3 us less; of 62 rows, 3584 wide: 57.7 -> 50.2, 34.6 -> 30.8.
 //   otherwise columns [0, N0) come from W0, [N0, N) from W1, float32 partial sums of slice blockIdx.z go
 //             to C[z]; the row kernels add the slices in order (no float atomics: bit-reproducible).
 // Columns past N and rows past M repeat the last one and are dropped at the store: any M and N.
@@ -37,7 +43,7 @@ namespace {
 
 // (The body is a function of its own, inlined: with the loads issued from the kernel itself the compiler
 // waits for every load in flight before each LDS read.)
-template <int RB, int NB, int DUAL, bool FINE = false>
+template <int RB, int NB, int DUAL, bool FINE, bool NT>
 __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int lda,
                                                const int* __restrict__ rows, int M,
                                                const bf16_t* __restrict__ W0,
@@ -51,6 +57,7 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
   constexpr int NST = kFit > 8 ? 8 : kFit;
   constexpr int LA = RB, LBT = 2 * NB;                 // activation loads per wavefront; weight loads of all
   constexpr int LB0 = LBT / 8, LBR = LBT % 8;          // ... per wavefront, one more for the first LBR
+  constexpr int kAux = NT ? 2 : 0;                     // non-temporal weight loads
   // FINE: sums of the steps kt % NA = 0, 1, ... apart, NA shorter chains of additions that are added up at the end
   constexpr int NA = !FINE ? 1 : RB * NB <= 12 ? 4 : 2;
   __shared__ __attribute__((aligned(1024))) uint4 lds[NST][kStage];
@@ -82,12 +89,15 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
     else w = n < N0 ? W0 + static_cast<size_t>(n) * K : W1 + static_cast<size_t>(n - N0) * K;
     bsrc[j] = w + kbeg + chunk * 8;
   }
-  // Gate/up of up to 128 rows: the walk starts at a step that depends on the column tile and wraps around.  The
+  // The walk starts at a step that depends on the column tile and wraps around.  The
   // workgroups run nearly in step and their rows are a multiple of 4 KB apart, so unrotated every load
-  // in flight has the same address bits below the row pitch (128 rows 47.6 -> 44.9 us).  The split launches
-  // walk different ranges side by side, and with them, as with more rows, the activation lines that
-  // the workgroups of an XCD share count for more (4096 x 12288 of 128 rows 26.8 us, rotated 30.5).
-  const int rot = DUAL && RB <= 2 ? col_tile % nkt : 0;
+  // in flight has the same address bits below the row pitch (gate/up of 128 rows 47.6 -> 44.9 us, of 179 non-temporal 61.7
+  // -> 56.6).  Split launches: starts that lie 8 steps apart from XCD to XCD and one apart within (one apart from tile to
+  // tile, down projection of 179 rows 45.0 us; unrotated 39.8; so 38.1).  Many slices walk different ranges side by side
+  // already: 64 rows in four slices are 0.2 us slower rotated, in two 0.4 us faster.  Cached weights (NT = false) gain in
+  // gate/up of up to 128 rows only.
+  const int rot = DUAL ? (RB <= 2 || NT ? col_tile % nkt : 0)
+                       : NT && (RB >= 2 || gridDim.z <= 2) ? (col_tile % 8 * 8 + col_tile / 8) % nkt : 0;
   auto issue = [&](int stage, int kt) {
     int k = kt + rot;
     k = (k < nkt ? k : k - nkt) * 64;
@@ -96,9 +106,9 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
       __builtin_amdgcn_global_load_lds(asrc[j] + k, &lds[stage][(wave + 8 * j) * 64], 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < LB0; ++j)
-      __builtin_amdgcn_global_load_lds(bsrc[j] + k, &lds[stage][BM * 8 + (wave + 8 * j) * 64], 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(bsrc[j] + k, &lds[stage][BM * 8 + (wave + 8 * j) * 64], 16, 0, kAux);
     if (LBR > 0 && wave < LBR)
-      __builtin_amdgcn_global_load_lds(bsrc[LB0] + k, &lds[stage][BM * 8 + (wave + 8 * LB0) * 64], 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(bsrc[LB0] + k, &lds[stage][BM * 8 + (wave + 8 * LB0) * 64], 16, 0, kAux);
   };
   // at most `steps` steps of this wavefront's loads in flight, and its LDS reads complete
   auto wait_steps = [&](auto steps) {
@@ -203,14 +213,14 @@ __device__ __forceinline__ void gemm_ring_body(const bf16_t* __restrict__ A, int
     }
 }
 
-template <int RB, int NB, int DUAL, bool FINE = false>
+template <int RB, int NB, int DUAL, bool FINE, bool NT>
 __global__ __launch_bounds__(512) void k_gemm_ring(const bf16_t* __restrict__ A, int lda,
                                                    const int* __restrict__ rows, int M,
                                                    const bf16_t* __restrict__ W0,
                                                    const bf16_t* __restrict__ W1, int N0, int N, int K,
                                                    int k_per_slice, float* __restrict__ C,
                                                    bf16_t* __restrict__ U) {
-  gemm_ring_body<RB, NB, DUAL, FINE>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C, U);
+  gemm_ring_body<RB, NB, DUAL, FINE, NT>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C, U);
 }
 
 // Estimated time in us of a launch of `tiles` workgroups (one per CU at a time) of 64 * rb rows x 16 * nb
@@ -263,14 +273,17 @@ RingPlan plan_ring(int M, int N, int K, int s_cap, int force_s, bool summed) {
 }
 
 void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* rows, int M, const bf16_t* W0,
-                      const bf16_t* W1, int N0, int N, int K, float* C, bool fine, hipStream_t st) {
+                      const bf16_t* W1, int N0, int N, int K, float* C, bool fine, bool once, hipStream_t st) {
   const dim3 grid(p.nt, p.mt, p.S);
-#define DLLMC_R(RB, NB)                                                                                           \
-  do {                                                                                                            \
-    if (fine) hipLaunchKernelGGL((k_gemm_ring<RB, NB, 0, true>), grid, dim3(512), 0, st, A, lda, rows, M, W0, W1, N0, N, \
-                                 K, p.kps, C, nullptr);                                                           \
-    else hipLaunchKernelGGL((k_gemm_ring<RB, NB, 0>), grid, dim3(512), 0, st, A, lda, rows, M, W0, W1, N0, N, K,     \
-                            p.kps, C, nullptr);                                                                   \
+  const bool nt = once && p.mt == 1;
+#define DLLMC_RL(RB, NB, FINE, NT)                                                                                  \
+  hipLaunchKernelGGL((k_gemm_ring<RB, NB, 0, FINE, NT>), grid, dim3(512), 0, st, A, lda, rows, M, W0, W1, N0, N, K, \
+                     p.kps, C, nullptr)
+#define DLLMC_R(RB, NB)                     \
+  do {                                      \
+    if (fine) DLLMC_RL(RB, NB, true, false); \
+    else if (nt) DLLMC_RL(RB, NB, false, true); \
+    else DLLMC_RL(RB, NB, false, false);    \
   } while (0)
   switch (p.rb * 10 + p.nb) {
     case 14: DLLMC_R(1, 4); break;
@@ -281,6 +294,7 @@ void launch_gemm_ring(const RingPlan& p, const bf16_t* A, int lda, const int* ro
     default: DLLMC_R(3, 8); break;
   }
 #undef DLLMC_R
+#undef DLLMC_RL
 }
 
 // Columns per workgroup: whole rounds over the CUs.  48 for an FFN width of 12288 (256 workgroups), 80 for
@@ -297,13 +311,19 @@ void plan_ring_swiglu(int M, int m, int K, int& rb, int& cb) {
 }
 
 void launch_gemm_ring_swiglu(const bf16_t* A, int lda, const int* rows, int M, const bf16_t* w_gate,
-                             const bf16_t* w_up, int m, int K, bf16_t* u, hipStream_t st) {
+                             const bf16_t* w_up, int m, int K, bf16_t* u, bool once, hipStream_t st) {
   int rb, cb;
   plan_ring_swiglu(M, m, K, rb, cb);
   const dim3 grid((m + 16 * cb - 1) / (16 * cb), (M + 64 * rb - 1) / (64 * rb), 1);
-#define DLLMC_R(RB, CB)                                                                                 \
-  hipLaunchKernelGGL((k_gemm_ring<RB, 2 * CB, 1>), grid, dim3(512), 0, st, A, lda, rows, M, w_gate, w_up, m, m, \
-                     K, K, nullptr, u)
+#define DLLMC_R(RB, CB)                                                                                      \
+  do {                                                                                                       \
+    if (once && grid.y == 1)                                                                                 \
+      hipLaunchKernelGGL((k_gemm_ring<RB, 2 * CB, 1, false, true>), grid, dim3(512), 0, st, A, lda, rows, M, w_gate, \
+                         w_up, m, m, K, K, nullptr, u);                                                      \
+    else                                                                                                     \
+      hipLaunchKernelGGL((k_gemm_ring<RB, 2 * CB, 1, false, false>), grid, dim3(512), 0, st, A, lda, rows, M, w_gate, \
+                         w_up, m, m, K, K, nullptr, u);                                                      \
+  } while (0)
 #define DLLMC_RC(RB)                 \
   switch (cb) {                      \
     case 1: DLLMC_R(RB, 1); break;   \

@@ -120,3 +120,36 @@ def test_gate_up_shapes(M, m, d, rows, cols):
     err = (ffn.double() - want).norm(dim=1) / want.norm(dim=1)
     assert float(err.max()) < 2.0 ** -7
     den.close()
+
+
+@pytest.mark.parametrize("L_r,rho", [(100, 0.37), (128, 0.5), (128, 1.0), (180, 0.99)])  # 37, 64, 128, 178 rows
+def test_weights_beyond_the_memory_side_cache(L_r, rho):
+    """A model of more than 256 MB of weights streams them past the caches, one of a single layer does not: other loads
+    and another walk over the contraction index, the same products.  Eleven layers that add nothing (zero output and
+    down projections) behind the first make the one out of the other.
+
+    Both add the same exact products in float32, so about 1e-3 of the elements of a bf16 result round the other way:
+    2^-8 sqrt(1e-3) = 1.2e-4 per tensor, a few of which lie on the way to the output."""
+    d, m, H, L_p = 1024, 3072, 8, 40
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L_r)
+    shapes = {"wq": (d, d), "wk": (d, d), "wv": (d, d), "wo": (d, d), "w_gate": (m, d), "w_up": (m, d), "w_down": (d, m)}
+    first = {k: (0.02 * torch.randn(s, generator=g, device="cuda")).bfloat16() for k, s in shapes.items()}
+    for k in ("attn_norm_g", "ffn_norm_g"):
+        first[k] = torch.ones(d, device="cuda").bfloat16()
+    rest = dict(first, wo=torch.zeros_like(first["wo"]), w_down=torch.zeros_like(first["w_down"]))
+    h0 = torch.randn((1, L_p + L_r, d), generator=g, device="cuda").bfloat16()
+    h1 = h0.clone()
+    h1[:, L_p::3] = torch.randn_like(h1[:, L_p::3])
+    got = []
+    for layers in ([first], [first] + [rest] * 11):
+        den = binding.CachedDenoiser(n_layers=len(layers), d_model=d, n_q_heads=H, n_kv_heads=H, head_dim=128, d_ffn=m,
+                                     batch=1, dtype="bf16", weights=layers, L_p=L_p, L_r=L_r, rho=rho, K_p=99, K_r=99)
+        den.step(h0, 0)
+        out, n_sel = den.step(h1, 1)
+        got.append([out, den.sel_idx[0, :, :n_sel].clone()] + [den.read_cache(0, w) for w in range(4)])
+        den.close()
+    assert torch.equal(got[0][1], got[1][1])
+    for a, b in zip(got[0], got[1]):
+        a, b = a.double(), b.double()
+        assert float((a - b).norm() / a.norm()) < 1e-3
