@@ -1,0 +1,364 @@
+// Body of the LDS-direct tile kernels with one workgroup per CU (tiles of 192 and 256 rows), included by kernels_gemm.hip.
+//
+// Four wavefronts, one per SIMD, of 16 MI rows x 16 NJ columns each.  Operands, LDS layout and the meaning of PAIR, EPI and
+// NT are those of gemm_lds_body; the products are taken as W A^T, so that a lane holds four neighbouring columns of one row and
+// every result leaves as 8- or 16-byte pieces.
+//
+// Bound by the matrix cores and the power they may draw: a 256 x 256 x 64 step of nothing but MFMAs takes 0.89 us on zeros and
+// 1.03 on random data (8 wavefronts; 32 x 32 x 16 MFMAs 1.10), with the fragment reads, the barrier and loads that
+// always hit 1.01 and 1.14.  This loop: 0.96 and 1.35 (4096 x 4096 x 4096 .. 12288, slope); eight wavefronts of 128 x 64 with
+// the reads of 16 MFMAs ahead 1.11 and 1.46, as two groups that multiply and load in turn the same.  What counts:
+//   * 128 x 128 per wavefront reads 128 KB of fragments per step from LDS, 128 x 64 192 KB;
+//   * with one wavefront per SIMD nothing else fills the matrix pipe, so the reads of the next 32 contraction values and the
+//     loads go out singly between MFMAs (2.5 MFMAs apart; in groups of four reads and four loads 1.43 and 1.69, loads every second
+//     MFMA 1.01 and 1.37), without branches: the last two steps load the last block again;
+//   * gate/up's epilogue, see silu_mul.  In the step (us, before: eight wavefronts): gate/up of 4608 rows x 12288 x 4096 735 -> 672, of
+//     1024 185 -> 158, of 768 156 -> 138, of 256 64 -> 57; down projection of 1024 rows 92 -> 81, of 4608 401 -> 377;
+//   * the accumulators are held in the accumulation registers by the constraint of an asm statement: left to the
+//     compiler, which has 256 of them and 130 other live registers, 48 to 540 moves enter the loop (none now; a move inside
+//     the loop would have to keep 11 wait states from the asm statement whose result it reads).
+#pragma once
+
+namespace dllmc {
+namespace {
+
+// silu(g) * up with at most 2 units in the last place of error: exp(-|g|) as 2^t (1 + r ln 2), t + r = -|g| log2(e) in two
+// parts, and a reciprocal with one Newton step (its argument is in [1, 2]).  Half the instructions of expf and a division, which
+// were a tenth of a 256 x 256 tile's time.
+__device__ __forceinline__ float silu_mul(float g, float up) {
+  const float x = fmaxf(-fabsf(g), -126.f);
+  const float t = x * 1.44269502f;
+  const float r = fmaf(x, 1.92596303e-8f, fmaf(x, 1.44269502f, -t));
+  const float e2 = __builtin_amdgcn_exp2f(t);
+  const float s = fmaf(e2, r * 0.693147182f, e2);
+  const float d = 1.f + s;
+  const float c = __builtin_amdgcn_rcpf(d);
+  return (g < 0.f ? g * s : g) * fmaf(fmaf(-d, c, 1.f), c, c) * up;
+}
+
+// Depths of the rings of BM and BN rows (128 bytes each): 1280 rows in all.
+template <int BM, int BN> struct WideRing {
+  static constexpr int kWhole = 1280 / (BM + BN);  // of both
+  static constexpr int kLeft = 1280 - kWhole * (BM + BN);
+  static constexpr int DA = kWhole + (kLeft >= BM && (BM >= BN || kLeft < BN) ? 1 : 0);
+  static constexpr int DB = kWhole + (DA == kWhole && kLeft >= BN ? 1 : 0);
+};
+
+template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0, bool NT = false>
+__device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
+                                               const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0, int N,
+                                               int K, int k_per_slice, float* __restrict__ C, bf16_t* __restrict__ U = nullptr,
+                                               const TileEpilogue* ep = nullptr) {
+  constexpr int BM = WM * MI * 16, BN = WN * NJ * 16;
+  constexpr int LA = BM / 32, LB = BN / 32;  // load instructions per wavefront and step
+  static_assert(WM * WN == 4 && BM % 32 == 0 && BN % 32 == 0, "four wavefronts, whole load instructions");
+  static_assert(!PAIR || NJ % 2 == 0, "gate and up column blocks come in pairs");
+  static_assert(EPI == 0 || (NJ % 4 == 0 && (EPI == 1 || WN * NJ % 8 == 0)), "blocks of 64 columns; a head is two");
+  constexpr int kAux = NT ? 2 : 0;
+  // A ring of LDS slots for each operand's blocks of 64 contraction values, as deep as 160 KB allow.  The barrier of step
+  // kt -- everybody has read all of A(kt) and B(kt), everybody's loads of step kt + 1 have landed -- stands between the two
+  // halves of the step and makes room for the next block of operand X, loaded during the second half, and of operand
+  // Y, the one with the deeper ring, loaded during the first half of the next step.  256 x 256: X = B two deep, Y = A three;
+  // A(kt+2) stays in flight across the barrier.
+  typedef WideRing<BM, BN> Ring;
+  constexpr int DA = Ring::DA, DB = Ring::DB;
+  constexpr bool XB = DA >= DB;  // X is B
+  constexpr int DX = XB ? DB : DA, DY = XB ? DA : DB, LX = XB ? LB : LA, LY = XB ? LA : LB;
+  constexpr int kSlotA = BM * 8, kSlotB = BN * 8;
+  static_assert((DA * kSlotA + DB * kSlotB) * sizeof(uint4) <= 160 * 1024 && DX >= 2, "LDS of one CU");
+  __shared__ __attribute__((aligned(1024))) uint4 lds[DA * kSlotA + DB * kSlotB];  // A's slots, then B's
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int ln = lane % 16, lg = lane / 16;
+  const int wm = wave / WN, wn = wave % WN;
+  int col_tile, row_tile;
+  xcd_tile_map_blocked(col_tile, row_tile);
+  const int m0 = row_tile * BM, n0 = col_tile * (PAIR ? BN / 2 : BN);
+  const int kbeg = blockIdx.z * k_per_slice;
+  const int nkt = (min(K, kbeg + k_per_slice) - kbeg) / kFatK;
+
+  // loader: wavefront w issues instructions L*w .. L*w+L-1 of an operand, 8 rows each; lane l: row l/8, slot l%8, global
+  // chunk (l%8) ^ (row%8)
+  const bf16_t* asrc[LA];
+  const char* bbase[LB];
+#pragma unroll
+  for (int j = 0; j < LA; ++j) {
+    const int r = 8 * (LA * wave + j) + lane / 8;
+    const int m = min(m0 + r, M - 1);
+    int row;
+    if (EPI == 1) row = (m / ep->per_seq) * ep->n + ep->first + m % ep->per_seq;
+    else row = rows ? rows[m] : m;
+    asrc[j] = A + static_cast<size_t>(row) * lda + kbeg + ((lane % 8) ^ (r % 8)) * 8;
+  }
+  // The 8 weight rows of an instruction are consecutive rows of one matrix (the tile origins and the W0 | W1 boundary
+  // are multiples of 8): the address is a scalar base plus the same lane offset for every instruction.
+#pragma unroll
+  for (int j = 0; j < LB; ++j) {
+    const int r = 8 * (LB * wave + j);
+    const bf16_t* w;
+    if (PAIR) {
+      w = (r < BN / 2 ? W0 : W1) + static_cast<size_t>(n0 + r % (BN / 2)) * K;
+    } else {
+      // EPI 2: LDS weight row 64 b + 16 j + c is column (j/2)*64 + (b%2)*32 + (j%2)*16 + c of head b/2 of the tile, so
+      // that a lane's accumulators j and j + 2 are rotation pairs
+      const int nn = n0 + (EPI == 2 ? (r / 128) * 128 + ((r % 64) / 32) * 64 + ((r / 64) % 2) * 32 + r % 32 : r);
+      w = nn < N0 ? W0 + static_cast<size_t>(nn) * K : W1 + static_cast<size_t>(nn - N0) * K;
+    }
+    bbase[j] = wave_uniform_ptr(reinterpret_cast<const char*>(w + kbeg));
+  }
+  const uint32_t boff = static_cast<uint32_t>((lane / 8) * K + ((lane % 8) ^ (lane / 8)) * 8) * sizeof(bf16_t);
+  // the walk starts at a step that depends on the XCD, see gemm_lds_body
+  const int rot = (((blockIdx.x + gridDim.x * blockIdx.y) & 7) * nkt) >> 3;
+  auto kof = [&](int kt) { const int k = kt + rot; return (k < nkt ? k : k - nkt) * kFatK; };
+  auto issue_a = [&](int slot, int ko, int j) {
+    __builtin_amdgcn_global_load_lds(asrc[j] + ko, &lds[slot * kSlotA + (LA * wave + j) * 64], 16, 0, 0);
+  };
+  // (the scalar sum re-read as a wavefront constant and the offset through an empty asm: otherwise the compiler folds the
+  // two into per-lane pointers)
+  auto issue_b = [&](int slot, int ko, int j) {
+    const char* bp = wave_uniform_ptr(bbase[j] + ko * static_cast<int>(sizeof(bf16_t)));
+    uint32_t o = boff;
+    asm volatile("" : "+v"(o));
+    __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint4*>(bp + o),
+                                     &lds[DA * kSlotA + slot * kSlotB + (LB * wave + j) * 64], 16, 0, kAux);
+  };
+  auto issue_x = [&](int slot, int ko, int j) { if (XB) issue_b(slot, ko, j); else issue_a(slot, ko, j); };
+  auto issue_y = [&](int slot, int ko, int j) { if (XB) issue_a(slot, ko, j); else issue_b(slot, ko, j); };
+  auto block_x = [&](int t) {
+    const int ko = kof(min(t, nkt - 1));
+#pragma unroll
+    for (int j = 0; j < LX; ++j) issue_x(t, ko, j);
+  };
+  auto block_y = [&](int t) {
+    const int ko = kof(min(t, nkt - 1));
+#pragma unroll
+    for (int j = 0; j < LY; ++j) issue_y(t, ko, j);
+  };
+  // in the order of the main loop: X(t), Y(t + DY - DX); Y(DY - 1) goes out in step 0
+#pragma unroll
+  for (int t = 0; t < DY - DX; ++t) block_y(t);
+#pragma unroll
+  for (int t = 0; t < DX - 1; ++t) {
+    block_x(t);
+    block_y(t + DY - DX);
+  }
+  block_x(DX - 1);
+  f32x4 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  bf16x8 af[2][MI], bf[2][NJ];
+  // q-th fragment of 32 contraction values: the weights' and the first activations' are needed first
+  auto read = [&](int slot_a, int slot_b, int kk, int q) {
+    const int c = kk * 4 + lg;
+    if (q < NJ) {
+      const int r = PAIR ? (q / (NJ / 2)) * (BN / 2) + wn * (NJ / 2 * 16) + (q % (NJ / 2)) * 16 + ln : wn * (NJ * 16) + q * 16 + ln;
+      bf[kk][q] = __builtin_bit_cast(bf16x8, lds[DA * kSlotA + slot_b * kSlotB + r * 8 + (c ^ (r % 8))]);
+    } else {
+      const int r = wm * (MI * 16) + (q - NJ) * 16 + ln;
+      af[kk][q - NJ] = __builtin_bit_cast(bf16x8, lds[slot_a * kSlotA + r * 8 + (c ^ (r % 8))]);
+    }
+  };
+  // The MFMAs of 32 contraction values; `between` gets the number of those before it.  The last four of a step are the
+  // compiler's: it knows how long their results take (11 wait states) and keeps that distance to whatever reads them behind
+  // the loop; those of the asm statements are four MFMAs old by then.
+  constexpr bool kPin = MI * NJ > 24;  // (fewer accumulators: the compiler has registers enough)
+  auto half = [&](auto kk_, auto&& between) {
+    constexpr int kk = decltype(kk_)::value;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (!kPin || (kk == 1 && i * NJ + j >= MI * NJ - 4))
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+        else
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(bf[kk][j]), "v"(af[kk][i]));
+        __builtin_amdgcn_sched_barrier(0);
+        between(i * NJ + j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  };
+  constexpr int kSpan = MI * NJ * 5 / 8;  // reads and loads are spread over this many MFMAs: the last have time to land
+
+  wait_vmcnt_lds<(DX - 1) * LX + (DY > DX ? DX - 1 : DX - 2) * LY>();  // X(0) and Y(0) have landed
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int q = 0; q < MI + NJ; ++q) read(0, 0, 0, q);
+  // loads that may be in flight across a barrier: what a wavefront issued last, from the end Y, X, Y, ..., as far as none of
+  // them belongs to the next step
+  constexpr int kFly = DY == 2 ? 0 : (DX - 2) * (LX + LY) + (DY > DX ? LY : 0);
+  int sa = 0, sb = 0;          // slots of A(kt) and B(kt)
+  int sy = DY - 1;             // slot of Y(kt - 1)
+  for (int kt = 0; kt < nkt; ++kt) {
+    const int sa1 = sa + 1 < DA ? sa + 1 : 0, sb1 = sb + 1 < DB ? sb + 1 : 0;
+    const int ky = kof(min(kt + DY - 1, nkt - 1)), kx = kof(min(kt + DX, nkt - 1));
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+    half(std::integral_constant<int, 0>{}, [&](int t) {
+#pragma unroll
+      for (int q = 0; q < MI + NJ; ++q)
+        if (1 + q * kSpan / (MI + NJ) == t) read(sa, sb, 1, q);
+#pragma unroll
+      for (int l = 0; l < LY; ++l)
+        if (l * kSpan / LY == t) issue_y(sy, ky, l);
+    });
+    wait_vmcnt_lds<kFly>();
+    __builtin_amdgcn_s_barrier();
+    half(std::integral_constant<int, 1>{}, [&](int t) {
+#pragma unroll
+      for (int q = 0; q < MI + NJ; ++q)
+        if (1 + q * kSpan / (MI + NJ) == t) read(sa1, sb1, 0, q);
+#pragma unroll
+      for (int l = 0; l < LX; ++l)
+        if (l * kSpan / LX == t) issue_x(XB ? sb : sa, kx, l);
+    });
+    sy = XB ? sa : sb;
+    sa = sa1;
+    sb = sb1;
+  }
+  // the loads of the last steps have landed before the workgroup's LDS is given back
+  wait_vmcnt_lds<0>();
+  __builtin_amdgcn_sched_barrier(0);
+
+  // row of this lane's elements of block i; their columns are 16 j + 4 lg .. + 3 of the wavefront's
+  auto row_of = [&](int i) { return m0 + wm * (MI * 16) + i * 16 + ln; };
+  if constexpr (EPI == 1) {
+    const int n_ct = N / 64;
+    // cache row and score index (-1: not scored) of every block's row; old values of a 64-column block at once: one trip to
+    // memory per block
+    size_t crow[MI];
+    int sidx[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int m = min(row_of(i), M - 1);
+      const int seq = m / ep->per_seq, pos = ep->first + m % ep->per_seq, row = seq * ep->n + pos;
+      crow[i] = ep->rmap ? ep->rmap[row] : row;
+      sidx[i] = row_of(i) < M && ep->part != nullptr && pos >= ep->L_p ? seq * (ep->n - ep->L_p) + (pos - ep->L_p) : -1;
+    }
+#pragma unroll
+    for (int jh = 0; jh < NJ / 4; ++jh) {
+      const int wv = wn * (NJ / 4) + jh, ct = col_tile * (BN / 64) + wv;
+      bf16_t* base = ep->cache + n0 + wv * 64 + lg * 4;
+      uint2 old[MI][4];
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          old[i][j] = make_uint2(0u, 0u);
+          if (sidx[i] >= 0) old[i][j] = *reinterpret_cast<const uint2*>(base + crow[i] * N + j * 16);
+        }
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        float dot = 0.f, nn = 0.f, no = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const f32x4 v = acc[i][4 * jh + j];
+          const uint2 nv = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+          if (ep->part != nullptr) {  // uniform
+            const uint32_t nw[2] = {nv.x, nv.y}, ow[2] = {old[i][j].x, old[i][j].y};
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+              const float a0 = __uint_as_float(nw[t] << 16), a1 = __uint_as_float(nw[t] & 0xffff0000u);
+              const float b0 = __uint_as_float(ow[t] << 16), b1 = __uint_as_float(ow[t] & 0xffff0000u);
+              if (ep->metric == 0) {
+                dot += a0 * b0; nn += a0 * a0; no += b0 * b0;
+                dot += a1 * b1; nn += a1 * a1; no += b1 * b1;
+              } else {
+                const float d0 = a0 - b0, d1 = a1 - b1;
+                dot += d0 * d0;
+                dot += d1 * d1;
+              }
+            }
+          }
+          if (row_of(i) < M) *reinterpret_cast<uint2*>(base + crow[i] * N + j * 16) = nv;
+        }
+        if (ep->part != nullptr) {
+#pragma unroll
+          for (int o = 16; o < 64; o <<= 1) {
+            dot += __shfl_xor(dot, o, 64); nn += __shfl_xor(nn, o, 64); no += __shfl_xor(no, o, 64);
+          }
+          if (sidx[i] >= 0 && lg == 0) {
+            ep->part[(static_cast<size_t>(0) * n_ct + ct) * ep->part_stride + sidx[i]] = dot;
+            ep->part[(static_cast<size_t>(1) * n_ct + ct) * ep->part_stride + sidx[i]] = nn;
+            ep->part[(static_cast<size_t>(2) * n_ct + ct) * ep->part_stride + sidx[i]] = no;
+          }
+        }
+      }
+    }
+  } else if constexpr (EPI == 2) {
+    int pos[MI];
+    size_t crow[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int m = min(row_of(i), M - 1), row = rows ? rows[m] : m;
+      pos[i] = row % ep->n;
+      crow[i] = ep->rmap ? ep->rmap[row] : row;
+    }
+#pragma unroll
+    for (int jh = 0; jh < NJ / 4; ++jh) {
+      const int wv = wn * (NJ / 4) + jh;
+      const int head0 = n0 + (wv / 2) * 128;  // first column of the head in [W0; W1]
+      const int t0 = (wv % 2) * 32 + lg * 4;  // first pair of this lane's (j = 0; + 16 for j = 1)
+      const bool is_q = head0 < N0, rotate = is_q || ep->rope_second != 0;
+      // rotation factors of all rows at once: one trip to memory
+      float4 cs[MI][4];
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          cs[i][u] = make_float4(1.f, 0.f, 1.f, 0.f);
+          if (rotate)
+            cs[i][u] = *reinterpret_cast<const float4*>(ep->tab + static_cast<size_t>(pos[i]) * 64 + t0 + u / 2 * 16 + u % 2 * 2);
+        }
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        bf16_t* dst = (is_q ? ep->q_out + static_cast<size_t>(row_of(i)) * N0 + head0
+                            : ep->cache + crow[i] * ep->d_kv + (head0 - N0)) + t0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const f32x4 x0 = acc[i][4 * jh + j], x1 = acc[i][4 * jh + j + 2];
+          const float c[4] = {cs[i][2 * j].x, cs[i][2 * j].z, cs[i][2 * j + 1].x, cs[i][2 * j + 1].z};
+          const float s[4] = {cs[i][2 * j].y, cs[i][2 * j].w, cs[i][2 * j + 1].y, cs[i][2 * j + 1].w};
+          float lo[4], hi[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            lo[e] = x0[e] * c[e] - x1[e] * s[e];
+            hi[e] = x1[e] * c[e] + x0[e] * s[e];
+          }
+          if (row_of(i) < M) {
+            *reinterpret_cast<uint2*>(dst + j * 16) = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
+            *reinterpret_cast<uint2*>(dst + j * 16 + 64) = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
+          }
+        }
+      }
+    }
+  } else if constexpr (PAIR) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      bf16_t* dst = U + static_cast<size_t>(row_of(i)) * N + n0 + wn * (NJ / 2 * 16) + lg * 4;
+#pragma unroll
+      for (int j = 0; j < NJ / 2; ++j) {
+        const f32x4 g = acc[i][j], up = acc[i][j + NJ / 2];
+        if (row_of(i) < M)
+          *reinterpret_cast<uint2*>(dst + j * 16) =
+              make_uint2(pack_bf16x2(silu_mul(g[0], up[0]), silu_mul(g[1], up[1])),
+                         pack_bf16x2(silu_mul(g[2], up[2]), silu_mul(g[3], up[3])));
+      }
+    }
+  } else {
+    typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));  // (the caller's result may lie anywhere)
+    float* Cs = C + static_cast<size_t>(blockIdx.z) * M * N + n0 + wn * (NJ * 16) + lg * 4;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const f32x4 v = acc[i][j];
+        if (row_of(i) < M)
+          *reinterpret_cast<float4_any*>(Cs + static_cast<size_t>(row_of(i)) * N + j * 16) = float4_any{v[0], v[1], v[2], v[3]};
+      }
+  }
+}
+
+}  // namespace
+}  // namespace dllmc

@@ -96,10 +96,10 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, in
 // contiguous bytes (64 values of the contraction index) into 1 KB of LDS in lane order, i.e.
 // LDS holds [row][8 slots of 16 bytes]; the slot of chunk c of row r is c ^ (r % 8) so that
 // the 16-byte fragment reads of 8 consecutive rows hit 8 different bank groups.  Two LDS
-// stages (128-row tiles) or five slots of one operand block (256-row tiles): later steps'
+// stages (128-row tiles) or a ring of slots per operand (192- and 256-row tiles, gemm_wide_body): later steps'
 // loads are in flight while step t is multiplied.
 // Rows beyond M read a valid row again and are dropped at the store.
-//   fat: 2 x 4 wavefronts of 128 x 64 -> 256 x 256 tile (every byte pulled from L2 feeds 128
+//   fat: 2 x 2 wavefronts of 128 x 128 -> 256 x 256 tile (every byte pulled from L2 feeds 128
 //        flops), all 160 KB of LDS, one workgroup per CU: M >= fat_min_m.
 //   mid: 2 x 2 wavefronts of  64 x 64 -> 128 x 128 tile, 64 KB of LDS, two workgroups per CU:
 //        enough tiles to fill the chip when M is a few hundred rows.
@@ -134,6 +134,10 @@ struct TileEpilogue {
   bf16_t* q_out;         // [M, N0]
   int d_kv, rope_second;
 };
+
+}  // namespace dllmc
+#include "gemm_wide.hpp"
+namespace dllmc {
 
 // Head: a tile of logits in LDS (128 columns per row, column c of row r at c ^ 16 * (r / 4 % 4): the four
 // rows that a wavefront stores at once hit different banks) is reduced per row to (maximum, sum of
@@ -207,20 +211,13 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // one the compiler can no longer tell the fragment reads from the loads in flight into the
   // other stage and waits for those before every read.)
   constexpr int kStage = (BM + BN) * 8;
-  // Two ways through the contraction.  Two workgroups per CU (128 x 128, four wavefronts): two
-  // stages of both operands; the loads of step kt+1 go out before the wait for step kt and a
-  // second barrier at the end of the step protects the stage they overwrite (the five-slot loop
-  // with 16 KB slots measured 3-8 % slower there).  One workgroup per CU (256-row tiles): five
-  // slots of one operand block each (all 160 KB of the CU), one barrier per step, see the main
-  // loop.
-  constexpr bool ONE_BARRIER = BM >= 192;
-  constexpr int kSlot = (BM > BN ? BM : BN) * 8;
-  constexpr int kLdsTotal = ONE_BARRIER ? 5 * kSlot : 2 * kStage + (EPI == 1 || EPI == 2 ? 2 * BM / 4 : 0);
-  static_assert(kLdsTotal * sizeof(uint4) <= 160 * 1024, "LDS of one CU");
+  // Two workgroups per CU (128 x 128, four wavefronts), two stages of both operands: the loads of step kt+1 go out before
+  // the wait for step kt and a second barrier at the end of the step protects the stage they overwrite (a five-slot loop
+  // with 16 KB slots measured 3-8 % slower).
+  constexpr int kLdsTotal = 2 * kStage + (EPI == 1 || EPI == 2 ? 2 * BM / 4 : 0);
   __shared__ __attribute__((aligned(1024))) uint4 lds_all[kLdsTotal];
   uint4 (*lds)[kStage] = reinterpret_cast<uint4 (*)[kStage]>(lds_all);
-  // (five slots: the table lives in the last slot, written after the main loop)
-  int (*meta)[BM] = reinterpret_cast<int (*)[BM]>(lds_all + (ONE_BARRIER ? 4 * kSlot : 2 * kStage));
+  int (*meta)[BM] = reinterpret_cast<int (*)[BM]>(lds_all + 2 * kStage);
   // (the wavefront index as a scalar: the LDS addresses of the loads, which go through M0, are then
   // scalar arithmetic instead of vector instructions and v_readfirstlane in every step)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
@@ -269,26 +266,19 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // EPI: what the epilogue needs to know about the tile's rows, looked up here so that the trips
   // to memory pass under the main loop.  EPI 1: cache row, index of the row's score (-1: not
   // scored); EPI 2: position in the sequence, cache row.
-  // (with five slots there is no room for the table during the main loop: the thread keeps its
-  // row's two entries in registers and writes them to the last slot afterwards)
-  int meta_r0 = 0, meta_r1 = 0;
   if ((EPI == 1 || EPI == 2) && threadIdx.x < BM) {
     const int r = threadIdx.x;
     const int m = min(m0 + r, M - 1);
     if (EPI == 1) {
       const int seq = m / ep->per_seq, pos = ep->first + m % ep->per_seq;
       const int row = seq * ep->n + pos;
-      meta_r0 = ep->rmap ? ep->rmap[row] : row;
-      meta_r1 = (m0 + r < M && ep->part != nullptr && pos >= ep->L_p)
+      meta[0][r] = ep->rmap ? ep->rmap[row] : row;
+      meta[1][r] = (m0 + r < M && ep->part != nullptr && pos >= ep->L_p)
                                  ? seq * (ep->n - ep->L_p) + (pos - ep->L_p) : -1;
     } else {
       const int row = rows ? rows[m] : m;
-      meta_r0 = row % ep->n;
-      meta_r1 = ep->rmap ? ep->rmap[row] : row;
-    }
-    if (!ONE_BARRIER) {
-      meta[0][r] = meta_r0;
-      meta[1][r] = meta_r1;
+      meta[0][r] = row % ep->n;
+      meta[1][r] = ep->rmap ? ep->rmap[row] : row;
     }
   }
 #define DLLMC_LDS_ISSUE(stage, kt)                                                              \
@@ -313,152 +303,6 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // (EPI 3: no such start -- equal rows of the vocabulary projection have to give equal logits whatever tile
   // they are in, so that the lowest token wins, and a sum's bits depend on where its walk begins)
   const int rot = EPI == 3 ? 0 : (((blockIdx.x + gridDim.x * blockIdx.y) & 7) * nkt) >> 3;
-  auto kof = [&](int kt) { const int k = kt + rot; return (k < nkt ? k : k - nkt) * kFatK; };
-  if (ONE_BARRIER) {
-    // Five slots of one operand block (256 rows x 64 contraction values) each.  Blocks are
-    // numbered in the order they are needed, A(0), B(0), A(1), B(1), ...; block p lives in slot
-    // p % 5.  While step kt multiplies A(kt) and B(kt), A(kt+1), B(kt+1) and A(kt+2) are landing
-    // or have landed, and the barrier of step kt -- everybody has finished the fragment reads of
-    // step kt, everybody's loads up to B(kt+1) have landed -- makes room for B(kt+2) and A(kt+3):
-    // 96 KB in flight per CU instead of the 64 KB of two stages, A(kt+2) stays in flight across
-    // the barrier (the memory pipeline never drains), and the new loads go out two per MFMA unit
-    // over the following step instead of all behind the barrier, where sixteen wavefronts'
-    // worth of address work kept the matrix pipes waiting (the 256 x 256 x 64 step: 1.12 ->
-    // 1.38 PFLOP/s on 12288 x 4096 x 12288).
-    //
-    // The step's MFMAs go in units of 4 activation blocks x NJ weight blocks x 32 contraction
-    // values, and the fragments of unit u + 1 are read from LDS into a second register set while
-    // the MFMAs of unit u run: the wavefronts of a workgroup leave every barrier together, so
-    // without this they all read fragments at the same time and then all multiply, and the
-    // matrix pipes idle for an LDS round trip in front of every group of MFMAs.  The barrier
-    // sits in front of the step's last unit.
-    constexpr int AG = MI % 4 == 0 ? 4 : MI;  // activation fragments per unit
-    constexpr int UH = MI / AG;      // units per 32 contraction values
-    constexpr int NU = 2 * UH;       // units per step
-    constexpr int NL = LA + LB;      // loads per wavefront and step: B(kt+2) first, then A(kt+3)
-    static_assert(MI % AG == 0, "whole units");
-    auto issue_a = [&](int slot, int kt, int j0, int j1) {
-      const int ko = kof(kt);
-#pragma unroll
-      for (int j = j0; j < j1; ++j)
-        __builtin_amdgcn_global_load_lds(asrc[j] + ko, &lds_all[slot * kSlot + (LA * wave + j) * 64],
-                                         16, 0, 0);
-    };
-    // Weight loads take their address as a scalar base + a 32-bit lane offset (no vector
-    // arithmetic per load): the 8 rows of one load instruction are consecutive rows of one
-    // matrix (the tile origins and the W0 | W1 boundary are multiples of 8), so the lane offset
-    // -- row lane/8, chunk (lane%8) ^ (lane/8) -- is the same for every instruction and the base
-    // is lane 0's address.  The scalar sum is re-read as a wavefront constant and the offset
-    // passes through an empty asm so that the compiler neither folds the two into per-lane
-    // 64-bit pointers outside the loop nor moves the zero-extension away from the load, either
-    // of which loses the addressing form.
-    const char* bbase[LB];
-#pragma unroll
-    for (int j = 0; j < LB; ++j) bbase[j] = wave_uniform_ptr(reinterpret_cast<const char*>(bsrc[j]));
-    const uint32_t boff =
-        static_cast<uint32_t>(reinterpret_cast<const char*>(bsrc[0]) - bbase[0]);
-    auto issue_b = [&](int slot, int kt, int j0, int j1) {
-      const int ko = kof(kt);
-#pragma unroll
-      for (int j = j0; j < j1; ++j) {
-        const char* bp = wave_uniform_ptr(bbase[j] + ko * static_cast<int>(sizeof(bf16_t)));
-        uint32_t o = boff;
-        asm volatile("" : "+v"(o));
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint4*>(bp + o),
-                                         &lds_all[slot * kSlot + (LB * wave + j) * 64], 16, 0, kAux);
-      }
-    };
-    // loads [i0, i1) of the NL that the barrier of step kb makes room for (slots sa_b, sb_b of that
-    // step's operands)
-    auto issue_some = [&](int kb, int sa_b, int sb_b, int i0, int i1) {
-      const int b0 = min(i0, LB), b1 = min(i1, LB);
-      const int a0 = max(i0, LB) - LB, a1 = max(i1, LB) - LB;
-      if (b1 > b0 && kb + 2 < nkt) issue_b(sa_b, kb + 2, b0, b1);
-      if (a1 > a0 && kb + 3 < nkt) issue_a(sb_b, kb + 3, a0, a1);
-    };
-    bf16x8 af[2][AG], bf[2][NJ];
-    auto read_a = [&](int slot, int u, bf16x8 (&dst)[AG]) {
-      const uint4* la = &lds_all[slot * kSlot];
-      const int c = (u / UH) * 4 + lg;
-#pragma unroll
-      for (int i = 0; i < AG; ++i) {
-        const int r = wm * (MI * 16) + ((u % UH) * AG + i) * 16 + ln;
-        dst[i] = __builtin_bit_cast(bf16x8, la[r * 8 + (c ^ (r % 8))]);
-      }
-    };
-    auto read_b = [&](int slot, int kk, bf16x8 (&dst)[NJ]) {
-      const uint4* lb = &lds_all[slot * kSlot];
-      const int c = kk * 4 + lg;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int r = PAIR ? (j / (NJ / 2)) * (BN / 2) + wn * (NJ / 2 * 16) + (j % (NJ / 2)) * 16 + ln
-                           : wn * (NJ * 16) + j * 16 + ln;
-        dst[j] = __builtin_bit_cast(bf16x8, lb[r * 8 + (c ^ (r % 8))]);
-      }
-    };
-    issue_a(0, 0, 0, LA);
-    issue_b(1, 0, 0, LB);
-    if (nkt > 1) {
-      issue_a(2, 1, 0, LA);
-      issue_b(3, 1, 0, LB);
-    }
-    if (nkt > 2) {
-      issue_a(4, 2, 0, LA);
-      wait_vmcnt_lds<2 * LA + LB>();
-    } else if (nkt > 1) {
-      wait_vmcnt_lds<LA + LB>();
-    } else {
-      wait_vmcnt_lds<0>();
-    }
-    __builtin_amdgcn_s_barrier();
-    read_a(0, 0, af[0]);
-    read_b(1, 0, bf[0]);
-    int sa = 0;            // slot of A(kt); B(kt) is in the next one (mod 5)
-    int sap = 0, sbp = 0;  // the slots of the step before
-    for (int kt = 0; kt < nkt; ++kt) {
-      const int sb = sa + 1 < 5 ? sa + 1 : sa - 4;
-      const int sa1 = sb + 1 < 5 ? sb + 1 : sb - 4;     // A(kt+1)
-      const int sb1 = sa1 + 1 < 5 ? sa1 + 1 : sa1 - 4;  // B(kt+1)
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        // The first row of MFMAs of the unit goes first: the compiler waits for every LDS read
-        // issued so far (lgkmcnt(0)) in front of a unit's first MFMA whatever the reads are for,
-        // so the reads for the next unit are issued behind it and have the rest of the unit.
-        auto mfma_rows = [&](int i0, int i1) {
-#pragma unroll
-          for (int i = i0; i < i1; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-              acc[(u % UH) * AG + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  af[u & 1][i], bf[(u / UH) & 1][j], acc[(u % UH) * AG + i][j], 0, 0, 0);
-        };
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_rows(0, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (u + 1 < NU) {
-          read_a(sa, u + 1, af[(u + 1) & 1]);
-          if ((u + 1) % UH == 0) read_b(sb, (u + 1) / UH, bf[((u + 1) / UH) & 1]);
-          // this unit's share of what the barrier of the step before made room for
-          if (kt > 0) issue_some(kt - 1, sap, sbp, (u + 1) * NL / NU, (u + 2) * NL / NU);
-        } else if (kt + 1 < nkt) {
-          // this wavefront's loads up to B(kt+1) have landed (A(kt+2), the last LA loads it
-          // issued, may be in flight) and its fragment reads of step kt are complete (not merely
-          // issued: the loads that follow overwrite their slots)
-          if (kt + 2 < nkt) wait_vmcnt_lds<LA>(); else wait_vmcnt_lds<0>();
-          __builtin_amdgcn_s_barrier();
-          issue_some(kt, sa, sb, 0, NL / NU);
-          read_a(sa1, 0, af[0]);
-          read_b(sb1, 0, bf[0]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_rows(1, AG);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      sap = sa;
-      sbp = sb;
-      sa = sa1;
-    }
-  } else {
   DLLMC_LDS_ISSUE(0, rot)
   // (FINE, see k_gemm_ring: the first and the second half of the steps in sums of their own.  Halves, because even and odd
   // steps apart, two copies of the loop body in turn, took a third longer.)
@@ -524,7 +368,6 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   } else {
     for (int kt = 0; kt < nkt; ++kt) step(kt, acc);
   }
-  }
 #undef DLLMC_LDS_ISSUE
 
   if (EPI == 3) {
@@ -553,15 +396,6 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     constexpr int kStg = 72;  // staging row stride in elements: 64 columns + 16 bytes
     static_assert(NWV * 16 * kStg * sizeof(bf16_t) <= kStage * sizeof(uint4), "staging fits a stage");
     __syncthreads();  // everybody has finished the fragment reads of the last step
-    if (ONE_BARRIER) {
-      static_assert(!ONE_BARRIER || NWV * 16 * kStg * sizeof(bf16_t) <= 4 * kSlot * sizeof(uint4),
-                    "staging stays clear of the table");
-      if (threadIdx.x < BM) {
-        meta[0][threadIdx.x] = meta_r0;
-        meta[1][threadIdx.x] = meta_r1;
-      }
-      __syncthreads();
-    }
     uint32_t* stg32 = reinterpret_cast<uint32_t*>(&lds[0][0]) + wave * (16 * kStg / 2);
     const bf16_t* stg = reinterpret_cast<const bf16_t*>(stg32);
     const int rr = lane / 8, ch = lane % 8;
@@ -725,12 +559,12 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     }
 }
 
-__global__ __launch_bounds__(512) void k_gemm_fat(const bf16_t* __restrict__ A, int lda,
+__global__ __launch_bounds__(256) void k_gemm_fat(const bf16_t* __restrict__ A, int lda,
                                                   const int* __restrict__ rows, int M,
                                                   const bf16_t* __restrict__ W0,
                                                   const bf16_t* __restrict__ W1, int N0, int N,
                                                   int K, int k_per_slice, float* __restrict__ C) {
-  gemm_lds_body<2, 4, 8, 4>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
+  gemm_wide_body<2, 2, 8, 8>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
 }
 
 __global__ __launch_bounds__(256) void k_gemm_mid(const bf16_t* __restrict__ A, int lda,
@@ -751,22 +585,22 @@ __global__ __launch_bounds__(256) void k_gemm_mid_fine(const bf16_t* __restrict_
 
 // Tile kernels that finish the step's work in their epilogue (single slice): V-verify and Q | K
 // with RoPE (see EPI above).
-__global__ __launch_bounds__(512) void k_gemm_fat_vverify(const bf16_t* __restrict__ A, int lda, int M,
+__global__ __launch_bounds__(256) void k_gemm_fat_vverify(const bf16_t* __restrict__ A, int lda, int M,
                                                           const bf16_t* __restrict__ W, int N, int K,
                                                           TileEpilogue ep) {
-  gemm_lds_body<2, 4, 8, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
+  gemm_wide_body<2, 2, 8, 8, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
 }
 __global__ __launch_bounds__(256) void k_gemm_mid_vverify(const bf16_t* __restrict__ A, int lda, int M,
                                                           const bf16_t* __restrict__ W, int N, int K,
                                                           TileEpilogue ep) {
   gemm_lds_body<2, 2, 4, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
 }
-__global__ __launch_bounds__(512) void k_gemm_fat_qk(const bf16_t* __restrict__ A, int lda,
+__global__ __launch_bounds__(256) void k_gemm_fat_qk(const bf16_t* __restrict__ A, int lda,
                                                      const int* __restrict__ rows, int M,
                                                      const bf16_t* __restrict__ W0,
                                                      const bf16_t* __restrict__ W1, int N0, int N, int K,
                                                      TileEpilogue ep) {
-  gemm_lds_body<2, 4, 8, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
+  gemm_wide_body<2, 2, 8, 8, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
 }
 __global__ __launch_bounds__(256) void k_gemm_mid_qk(const bf16_t* __restrict__ A, int lda,
                                                      const int* __restrict__ rows, int M,
@@ -784,12 +618,12 @@ __global__ __launch_bounds__(256) void k_gemm_mid_head(const bf16_t* __restrict_
 }
 
 // fused gate/up + SwiGLU for many rows: N is the FFN width, grid.x = N / 128 (fat) or N / 64 (mid)
-__global__ __launch_bounds__(512) void k_gemm_fat_swiglu(const bf16_t* __restrict__ A, int lda,
+__global__ __launch_bounds__(256) void k_gemm_fat_swiglu(const bf16_t* __restrict__ A, int lda,
                                                          const int* __restrict__ rows, int M,
                                                          const bf16_t* __restrict__ Wg,
                                                          const bf16_t* __restrict__ Wu, int N, int K,
                                                          bf16_t* __restrict__ U) {
-  gemm_lds_body<2, 4, 8, 4, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
+  gemm_wide_body<2, 2, 8, 8, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 
 __global__ __launch_bounds__(256) void k_gemm_mid_swiglu(const bf16_t* __restrict__ A, int lda,
@@ -800,54 +634,54 @@ __global__ __launch_bounds__(256) void k_gemm_mid_swiglu(const bf16_t* __restric
   gemm_lds_body<2, 2, 4, 4, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 
-// 256 rows x (96 gate + 96 up) columns, 4 x 2 wavefronts of 64 x 96 each, one workgroup per CU: the
+// 256 rows x (96 gate + 96 up) columns, 2 x 2 wavefronts of 128 x 96 each, one workgroup per CU: the
 // column count that makes whole rounds of workgroups when the 256 x (128 + 128) tiles do not
 // (1024 rows x FFN width 12288: 384 tiles of the latter are a full round and a half-empty one,
 // 512 of these are two full rounds of tiles three quarters the size).
-__global__ __launch_bounds__(512) void k_gemm_fat96_swiglu(const bf16_t* __restrict__ A, int lda,
+__global__ __launch_bounds__(256) void k_gemm_fat96_swiglu(const bf16_t* __restrict__ A, int lda,
                                                            const int* __restrict__ rows, int M,
                                                            const bf16_t* __restrict__ Wg,
                                                            const bf16_t* __restrict__ Wu, int N, int K,
                                                            bf16_t* __restrict__ U) {
-  gemm_lds_body<4, 2, 4, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
+  gemm_wide_body<2, 2, 8, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 
 // 256 rows x (48 gate + 48 up) columns, four wavefronts of 64 x 96 each: for up to 256 rows and
 // an FFN width that is a multiple of 48 the grid is one workgroup per 48 columns (12288 / 48 =
 // 256, one per CU), where the 128 x 128 tiles leave half of the CUs with twice the work (a
 // response refresh of 256 rows: 80 -> 69 us per layer; two workgroups of 128 x 96 per CU: 73; with non-temporal
-// weight loads 65.7 -> 62.7).
+// weight loads 65.7 -> 62.7; with the body of one wavefront per SIMD 57).
 template <bool NT>
 __global__ __launch_bounds__(256) void k_gemm_tall_swiglu(const bf16_t* __restrict__ A, int lda,
                                                           const int* __restrict__ rows, int M,
                                                           const bf16_t* __restrict__ Wg,
                                                           const bf16_t* __restrict__ Wu, int N, int K,
                                                           bf16_t* __restrict__ U) {
-  gemm_lds_body<4, 1, 4, 6, 1, 0, false, NT>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
+  gemm_wide_body<4, 1, 4, 6, 1, 0, NT>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 
-// 192-row tiles (five slots of 24 KB): the row count that makes whole rounds of workgroups where 256 rows do not
+// 192-row tiles: the row count that makes whole rounds of workgroups where 256 rows do not
 // (768 rows: four tiles instead of three; see launch_gemm_swiglu, plan_vverify and qk_tile_kind for what they measured).
 // For the float32 slices of the output and down projections they gained nothing: 768 rows in two slices 59
 // us against 56, 8 us less in the two row kernels.
-__global__ __launch_bounds__(512) void k_gemm_r192_swiglu(const bf16_t* __restrict__ A, int lda,
+__global__ __launch_bounds__(256) void k_gemm_r192_swiglu(const bf16_t* __restrict__ A, int lda,
                                                           const int* __restrict__ rows, int M,
                                                           const bf16_t* __restrict__ Wg,
                                                           const bf16_t* __restrict__ Wu, int N, int K,
                                                           bf16_t* __restrict__ U) {
-  gemm_lds_body<4, 2, 3, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
+  gemm_wide_body<2, 2, 6, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 __global__ __launch_bounds__(256) void k_gemm_r192_vverify(const bf16_t* __restrict__ A, int lda, int M,
                                                            const bf16_t* __restrict__ W, int N, int K,
                                                            TileEpilogue ep) {
-  gemm_lds_body<4, 1, 3, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
+  gemm_wide_body<4, 1, 3, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
 }
-__global__ __launch_bounds__(512) void k_gemm_r192_qk(const bf16_t* __restrict__ A, int lda,
+__global__ __launch_bounds__(256) void k_gemm_r192_qk(const bf16_t* __restrict__ A, int lda,
                                                       const int* __restrict__ rows, int M,
                                                       const bf16_t* __restrict__ W0,
                                                       const bf16_t* __restrict__ W1, int N0, int N, int K,
                                                       TileEpilogue ep) {
-  gemm_lds_body<4, 2, 3, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
+  gemm_wide_body<2, 2, 6, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
 }
 
 // V floats per thread; every slice's load is issued before the first addition (a loop over the runtime count waits
@@ -1055,7 +889,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                       static_cast<const float*>(W1), N0, N, K, c_part, st);
       break;
     case 3:
-      hipLaunchKernelGGL(k_gemm_fat, grid, dim3(512), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps,
+      hipLaunchKernelGGL(k_gemm_fat, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps,
                          c_part);
       break;
     case 4:
@@ -1125,9 +959,9 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
       const dim3 grid(m / tiles[pick].cols, (M + tiles[pick].rows - 1) / tiles[pick].rows, 1);
 #define DLLMC_SW(KERNEL, NT) hipLaunchKernelGGL(KERNEL, grid, dim3(NT), 0, st, a, lda, rows, M, w0, w1, m, K, uo)
       switch (pick) {
-        case 0: DLLMC_SW(k_gemm_fat_swiglu, 512); break;
-        case 1: DLLMC_SW(k_gemm_fat96_swiglu, 512); break;
-        case 2: DLLMC_SW(k_gemm_r192_swiglu, 512); break;
+        case 0: DLLMC_SW(k_gemm_fat_swiglu, 256); break;
+        case 1: DLLMC_SW(k_gemm_fat96_swiglu, 256); break;
+        case 2: DLLMC_SW(k_gemm_r192_swiglu, 256); break;
         case 3: DLLMC_SW(k_gemm_mid_swiglu, 256); break;
         default:  // one row tile
           if (g_tune.weights_once) DLLMC_SW(k_gemm_tall_swiglu<true>, 256);
@@ -1207,7 +1041,7 @@ void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first
   if (way == kVR192)
     hipLaunchKernelGGL(k_gemm_r192_vverify, dim3(N / 64, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, M, w, N, K, ep);
   else if (way == kVFat)
-    hipLaunchKernelGGL(k_gemm_fat_vverify, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(512), 0, st, a,
+    hipLaunchKernelGGL(k_gemm_fat_vverify, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(256), 0, st, a,
                        lda, M, w, N, K, ep);
   else
     hipLaunchKernelGGL(k_gemm_mid_vverify, dim3(N / kMidN, (M + kMidM - 1) / kMidM, 1), dim3(256), 0, st, a,
@@ -1231,9 +1065,9 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
   const bf16_t* w0 = static_cast<const bf16_t*>(wq);
   const bf16_t* w1 = static_cast<const bf16_t*>(w2);
   if (kind == 3)
-    hipLaunchKernelGGL(k_gemm_r192_qk, dim3(N / 128, (M + 191) / 192, 1), dim3(512), 0, st, a, lda, rows, M, w0, w1, d_q, N, K, ep);
+    hipLaunchKernelGGL(k_gemm_r192_qk, dim3(N / 128, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, rows, M, w0, w1, d_q, N, K, ep);
   else if (kind == 2)
-    hipLaunchKernelGGL(k_gemm_fat_qk, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(512), 0, st, a, lda,
+    hipLaunchKernelGGL(k_gemm_fat_qk, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(256), 0, st, a, lda,
                        rows, M, w0, w1, d_q, N, K, ep);
   else
     hipLaunchKernelGGL(k_gemm_mid_qk, dim3(N / kMidN, (M + kMidM - 1) / kMidM, 1), dim3(256), 0, st, a, lda,

@@ -123,3 +123,46 @@ def test_one_slice_where_a_slice_sum_costs_more(M, N, K, whole):
     want = a.double() @ w.double().t()
     assert float((out.double() - want).norm() / want.norm()) < 2.0 ** -24 * K ** 0.5
     assert bool((scratch == 77.0).all()) == whole
+
+
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 448])
+@pytest.mark.parametrize("M", [256, 301])
+def test_fewer_steps_than_the_ring_holds(M, K):
+    """256 x 256 tiles whose whole contraction is one to seven 64-wide steps.  Exact products, at most K float32 additions:
+    K 2^-24 of the sum of their magnitudes."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + K)
+    a = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    w = torch.randn((512, K), generator=g, device="cuda").bfloat16()
+    binding.set_gemm_tuning(fat_min_m=200)
+    try:
+        got = binding.op_linear("bf16", a, w).double()
+    finally:
+        binding.set_gemm_tuning(fat_min_m=512)
+    want, bound = a.double() @ w.double().t(), K * 2.0 ** -24 * (a.double().abs() @ w.double().abs().t())
+    assert bool(((got - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("H,rows", [(1, 256), (1, 700), (2, 1100), (3, 640)])
+def test_narrow_models(H, rows):
+    """Two to six steps in gate/up, Q|K, V-verify: every shape of tile against the streaming kernel, bars as above."""
+    cfg = BASES["llada8b"].replace(T=1, K_p=1, K_r=1, L_p=rows - 90, L_r=90, d=128 * H, H_q=H, H_kv=H, m=1536)
+    ws = I.device_weights(cfg)
+    make = lambda: binding.CachedDenoiser(
+        n_layers=1, d_model=cfg.d, n_q_heads=H, n_kv_heads=H, head_dim=128, d_ffn=cfg.m, batch=1, dtype=cfg.dtype,
+        weights=ws, L_p=cfg.L_p, L_r=cfg.L_r, rho=cfg.rho, K_p=1, K_r=1, rms_eps=cfg.rms_eps, rope_theta=cfg.rope_theta)
+    tiles = make()
+    binding.set_gemm_tuning(tile_min_m=1 << 20, fat_min_m=1 << 20)
+    try:
+        plain = make()
+    finally:
+        binding.set_gemm_tuning(tile_min_m=192, fat_min_m=512)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    hid = torch.randn(1, rows, cfg.d, device="cuda", generator=gen).to(torch.bfloat16)
+    a_out, c_out = tiles.step(hid, 0)[0], plain.step(hid, 0)[0]
+    for a, c in [(tiles.read_cache(0, w), plain.read_cache(0, w)) for w in range(4)] + [(a_out, c_out)]:
+        a, c = a.float(), c.float()
+        assert float(((a - c).abs() - 0.03 * c.abs()).max()) <= 0.12 * float(c.pow(2).mean().sqrt())
+    tiles.close()
+    plain.close()
