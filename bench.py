@@ -329,7 +329,7 @@ def main():
             peak = FP32_VECTOR_PEAK_TFLOPS if f32 else MFMA_BF16_PEAK_TFLOPS
             result["roofline"] = {
                 "kernel": ("k_gemm_f32 (float32 matrix instructions)" if f32 else
-                           "k_gemm_fat / k_gemm_mid (every launch of the LDS-direct tile kernels)"),
+                           "k_gemm_wide / k_gemm_mid (every launch of the LDS-direct tile kernels)"),
                 "bound": "alu" if f32 else "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s",
                 "frac": tf / peak, "traffic": None, "launches": t_n,
                 "avg_launch_us": 1e3 * t_ms / max(t_n, 1), "event_overhead_us": 1e3 * ov_ms,

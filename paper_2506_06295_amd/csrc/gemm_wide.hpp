@@ -160,18 +160,18 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
       af[kk][q - NJ] = __builtin_bit_cast(bf16x8, lds[slot_a * kSlotA + r * 8 + (c ^ (r % 8))]);
     }
   };
-  // The MFMAs of 32 contraction values; `between` gets the number of those before it.  The last four of a step are the
-  // compiler's: it knows how long their results take (11 wait states) and keeps that distance to whatever reads them behind
-  // the loop; those of the asm statements are four MFMAs old by then.
-  constexpr bool kPin = MI * NJ > 24;  // (fewer accumulators: the compiler has registers enough)
+  // The MFMAs of 32 contraction values; `between` gets the number of those before it.  The compiler does not know how long the
+  // results of an asm statement take (8 wait states) and may read accumulators as soon as the loop ends: the last
+  // statement of a step waits itself.  Inside the loop nothing but these statements may touch them (no moves; with the last four
+  // MFMAs left to the compiler it moved their results right in front of a statement that reads them).
   auto half = [&](auto kk_, auto&& between) {
     constexpr int kk = decltype(kk_)::value;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        if (!kPin || (kk == 1 && i * NJ + j >= MI * NJ - 4))
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+        if (kk == 1 && i * NJ + j == MI * NJ - 1)
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(acc[i][j]) : "v"(bf[kk][j]), "v"(af[kk][i]));
         else
           asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(bf[kk][j]), "v"(af[kk][i]));
         __builtin_amdgcn_sched_barrier(0);
@@ -179,8 +179,33 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
         __builtin_amdgcn_sched_barrier(0);
       }
   };
-  constexpr int kSpan = MI * NJ * 5 / 8;  // reads and loads are spread over this many MFMAs: the last have time to land
+  // reads and loads are spread over this many MFMAs, so that the last have time to land (256 x 256: three quarters of them
+  // 1 to 2 % slower; the others up to 4 % faster)
+  constexpr int kSpan = MI * NJ >= 64 ? MI * NJ * 5 / 8 : MI * NJ * 3 / 4;
 
+  // row of this lane's elements of block i; their columns are 16 j + 4 lg .. + 3 of the wavefront's
+  auto row_of = [&](int i) { return m0 + wm * (MI * 16) + i * 16 + ln; };
+  // EPI: cache row of every block's row, and the index of its score (-1: not scored; EPI 1) or its position (EPI 2), looked up
+  // while the first blocks are on their way
+  int crow[MI], meta[MI];
+  if (EPI != 0) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int m = min(row_of(i), M - 1);
+      int row;
+      if (EPI == 1) {
+        const int seq = m / ep->per_seq, pos = ep->first + m % ep->per_seq;
+        row = seq * ep->n + pos;
+        meta[i] = row_of(i) < M && ep->part != nullptr && pos >= ep->L_p ? seq * (ep->n - ep->L_p) + (pos - ep->L_p) : -1;
+      } else {
+        row = rows ? rows[m] : m;
+        meta[i] = row % ep->n;
+      }
+      crow[i] = ep->rmap ? ep->rmap[row] : row;
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(crow[i]), "+v"(meta[i]));  // (here, not behind the loop)
+  }
   wait_vmcnt_lds<(DX - 1) * LX + (DY > DX ? DX - 1 : DX - 2) * LY>();  // X(0) and Y(0) have landed
   __builtin_amdgcn_s_barrier();
 #pragma unroll
@@ -221,21 +246,9 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
   wait_vmcnt_lds<0>();
   __builtin_amdgcn_sched_barrier(0);
 
-  // row of this lane's elements of block i; their columns are 16 j + 4 lg .. + 3 of the wavefront's
-  auto row_of = [&](int i) { return m0 + wm * (MI * 16) + i * 16 + ln; };
   if constexpr (EPI == 1) {
     const int n_ct = N / 64;
-    // cache row and score index (-1: not scored) of every block's row; old values of a 64-column block at once: one trip to
-    // memory per block
-    size_t crow[MI];
-    int sidx[MI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int m = min(row_of(i), M - 1);
-      const int seq = m / ep->per_seq, pos = ep->first + m % ep->per_seq, row = seq * ep->n + pos;
-      crow[i] = ep->rmap ? ep->rmap[row] : row;
-      sidx[i] = row_of(i) < M && ep->part != nullptr && pos >= ep->L_p ? seq * (ep->n - ep->L_p) + (pos - ep->L_p) : -1;
-    }
+    // the old values of a 64-column block are requested at once: one trip to memory per block
 #pragma unroll
     for (int jh = 0; jh < NJ / 4; ++jh) {
       const int wv = wn * (NJ / 4) + jh, ct = col_tile * (BN / 64) + wv;
@@ -246,7 +259,7 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           old[i][j] = make_uint2(0u, 0u);
-          if (sidx[i] >= 0) old[i][j] = *reinterpret_cast<const uint2*>(base + crow[i] * N + j * 16);
+          if (meta[i] >= 0) old[i][j] = *reinterpret_cast<const uint2*>(base + static_cast<size_t>(crow[i]) * N + j * 16);
         }
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
@@ -271,30 +284,22 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
               }
             }
           }
-          if (row_of(i) < M) *reinterpret_cast<uint2*>(base + crow[i] * N + j * 16) = nv;
+          if (row_of(i) < M) *reinterpret_cast<uint2*>(base + static_cast<size_t>(crow[i]) * N + j * 16) = nv;
         }
         if (ep->part != nullptr) {
 #pragma unroll
           for (int o = 16; o < 64; o <<= 1) {
             dot += __shfl_xor(dot, o, 64); nn += __shfl_xor(nn, o, 64); no += __shfl_xor(no, o, 64);
           }
-          if (sidx[i] >= 0 && lg == 0) {
-            ep->part[(static_cast<size_t>(0) * n_ct + ct) * ep->part_stride + sidx[i]] = dot;
-            ep->part[(static_cast<size_t>(1) * n_ct + ct) * ep->part_stride + sidx[i]] = nn;
-            ep->part[(static_cast<size_t>(2) * n_ct + ct) * ep->part_stride + sidx[i]] = no;
+          if (meta[i] >= 0 && lg == 0) {
+            ep->part[(static_cast<size_t>(0) * n_ct + ct) * ep->part_stride + meta[i]] = dot;
+            ep->part[(static_cast<size_t>(1) * n_ct + ct) * ep->part_stride + meta[i]] = nn;
+            ep->part[(static_cast<size_t>(2) * n_ct + ct) * ep->part_stride + meta[i]] = no;
           }
         }
       }
     }
   } else if constexpr (EPI == 2) {
-    int pos[MI];
-    size_t crow[MI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int m = min(row_of(i), M - 1), row = rows ? rows[m] : m;
-      pos[i] = row % ep->n;
-      crow[i] = ep->rmap ? ep->rmap[row] : row;
-    }
 #pragma unroll
     for (int jh = 0; jh < NJ / 4; ++jh) {
       const int wv = wn * (NJ / 4) + jh;
@@ -309,12 +314,12 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
         for (int u = 0; u < 4; ++u) {
           cs[i][u] = make_float4(1.f, 0.f, 1.f, 0.f);
           if (rotate)
-            cs[i][u] = *reinterpret_cast<const float4*>(ep->tab + static_cast<size_t>(pos[i]) * 64 + t0 + u / 2 * 16 + u % 2 * 2);
+            cs[i][u] = *reinterpret_cast<const float4*>(ep->tab + static_cast<size_t>(meta[i]) * 64 + t0 + u / 2 * 16 + u % 2 * 2);
         }
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
         bf16_t* dst = (is_q ? ep->q_out + static_cast<size_t>(row_of(i)) * N0 + head0
-                            : ep->cache + crow[i] * ep->d_kv + (head0 - N0)) + t0;
+                            : ep->cache + static_cast<size_t>(crow[i]) * ep->d_kv + (head0 - N0)) + t0;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const f32x4 x0 = acc[i][4 * jh + j], x1 = acc[i][4 * jh + j + 2];

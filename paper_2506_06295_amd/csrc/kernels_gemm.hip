@@ -559,12 +559,31 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     }
 }
 
-__global__ __launch_bounds__(256) void k_gemm_fat(const bf16_t* __restrict__ A, int lda,
-                                                  const int* __restrict__ rows, int M,
-                                                  const bf16_t* __restrict__ W0,
-                                                  const bf16_t* __restrict__ W1, int N0, int N,
-                                                  int K, int k_per_slice, float* __restrict__ C) {
-  gemm_wide_body<2, 2, 8, 8>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
+// The tile kernels of one workgroup per CU (gemm_wide_body): 2 x 2 wavefronts of 16 MI x 16 NJ, tiles of 32 MI x 32 NJ.
+template <int MI, int NJ>
+__global__ __launch_bounds__(256) void k_gemm_wide(const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
+                                                   const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0, int N,
+                                                   int K, int k_per_slice, float* __restrict__ C) {
+  gemm_wide_body<2, 2, MI, NJ>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
+}
+// gate/up + SwiGLU: N is the FFN width, a tile has 16 NJ columns of each
+template <int MI, int NJ>
+__global__ __launch_bounds__(256) void k_gemm_wide_swiglu(const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows,
+                                                          int M, const bf16_t* __restrict__ Wg, const bf16_t* __restrict__ Wu,
+                                                          int N, int K, bf16_t* __restrict__ U) {
+  gemm_wide_body<2, 2, MI, NJ, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
+}
+// tile kernels that finish the step's work in their epilogue (single slice): V-verify and Q | K with RoPE (see EPI above)
+template <int WM, int WN, int MI, int NJ>
+__global__ __launch_bounds__(256) void k_gemm_wide_vverify(const bf16_t* __restrict__ A, int lda, int M,
+                                                           const bf16_t* __restrict__ W, int N, int K, TileEpilogue ep) {
+  gemm_wide_body<WM, WN, MI, NJ, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
+}
+template <int MI, int NJ>
+__global__ __launch_bounds__(256) void k_gemm_wide_qk(const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
+                                                      const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0,
+                                                      int N, int K, TileEpilogue ep) {
+  gemm_wide_body<2, 2, MI, NJ, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
 }
 
 __global__ __launch_bounds__(256) void k_gemm_mid(const bf16_t* __restrict__ A, int lda,
@@ -583,31 +602,10 @@ __global__ __launch_bounds__(256) void k_gemm_mid_fine(const bf16_t* __restrict_
   gemm_lds_body<2, 2, 4, 4, 0, 0, true>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
 }
 
-// Tile kernels that finish the step's work in their epilogue (single slice): V-verify and Q | K
-// with RoPE (see EPI above).
-__global__ __launch_bounds__(256) void k_gemm_fat_vverify(const bf16_t* __restrict__ A, int lda, int M,
-                                                          const bf16_t* __restrict__ W, int N, int K,
-                                                          TileEpilogue ep) {
-  gemm_wide_body<2, 2, 8, 8, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
-}
 __global__ __launch_bounds__(256) void k_gemm_mid_vverify(const bf16_t* __restrict__ A, int lda, int M,
                                                           const bf16_t* __restrict__ W, int N, int K,
                                                           TileEpilogue ep) {
   gemm_lds_body<2, 2, 4, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
-}
-__global__ __launch_bounds__(256) void k_gemm_fat_qk(const bf16_t* __restrict__ A, int lda,
-                                                     const int* __restrict__ rows, int M,
-                                                     const bf16_t* __restrict__ W0,
-                                                     const bf16_t* __restrict__ W1, int N0, int N, int K,
-                                                     TileEpilogue ep) {
-  gemm_wide_body<2, 2, 8, 8, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
-}
-__global__ __launch_bounds__(256) void k_gemm_mid_qk(const bf16_t* __restrict__ A, int lda,
-                                                     const int* __restrict__ rows, int M,
-                                                     const bf16_t* __restrict__ W0,
-                                                     const bf16_t* __restrict__ W1, int N0, int N, int K,
-                                                     TileEpilogue ep) {
-  gemm_lds_body<2, 2, 4, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
 }
 
 template <bool NT>
@@ -615,35 +613,6 @@ __global__ __launch_bounds__(256) void k_gemm_mid_head(const bf16_t* __restrict_
                                                        const bf16_t* __restrict__ W, int N, int K,
                                                        float* __restrict__ C) {
   gemm_lds_body<2, 2, 4, 4, 0, 3, false, NT>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C);
-}
-
-// fused gate/up + SwiGLU for many rows: N is the FFN width, grid.x = N / 128 (fat) or N / 64 (mid)
-__global__ __launch_bounds__(256) void k_gemm_fat_swiglu(const bf16_t* __restrict__ A, int lda,
-                                                         const int* __restrict__ rows, int M,
-                                                         const bf16_t* __restrict__ Wg,
-                                                         const bf16_t* __restrict__ Wu, int N, int K,
-                                                         bf16_t* __restrict__ U) {
-  gemm_wide_body<2, 2, 8, 8, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
-}
-
-__global__ __launch_bounds__(256) void k_gemm_mid_swiglu(const bf16_t* __restrict__ A, int lda,
-                                                         const int* __restrict__ rows, int M,
-                                                         const bf16_t* __restrict__ Wg,
-                                                         const bf16_t* __restrict__ Wu, int N, int K,
-                                                         bf16_t* __restrict__ U) {
-  gemm_lds_body<2, 2, 4, 4, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
-}
-
-// 256 rows x (96 gate + 96 up) columns, 2 x 2 wavefronts of 128 x 96 each, one workgroup per CU: the
-// column count that makes whole rounds of workgroups when the 256 x (128 + 128) tiles do not
-// (1024 rows x FFN width 12288: 384 tiles of the latter are a full round and a half-empty one,
-// 512 of these are two full rounds of tiles three quarters the size).
-__global__ __launch_bounds__(256) void k_gemm_fat96_swiglu(const bf16_t* __restrict__ A, int lda,
-                                                           const int* __restrict__ rows, int M,
-                                                           const bf16_t* __restrict__ Wg,
-                                                           const bf16_t* __restrict__ Wu, int N, int K,
-                                                           bf16_t* __restrict__ U) {
-  gemm_wide_body<2, 2, 8, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
 }
 
 // 256 rows x (48 gate + 48 up) columns, four wavefronts of 64 x 96 each: for up to 256 rows and
@@ -658,30 +627,6 @@ __global__ __launch_bounds__(256) void k_gemm_tall_swiglu(const bf16_t* __restri
                                                           const bf16_t* __restrict__ Wu, int N, int K,
                                                           bf16_t* __restrict__ U) {
   gemm_wide_body<4, 1, 4, 6, 1, 0, NT>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
-}
-
-// 192-row tiles: the row count that makes whole rounds of workgroups where 256 rows do not
-// (768 rows: four tiles instead of three; see launch_gemm_swiglu, plan_vverify and qk_tile_kind for what they measured).
-// For the float32 slices of the output and down projections they gained nothing: 768 rows in two slices 59
-// us against 56, 8 us less in the two row kernels.
-__global__ __launch_bounds__(256) void k_gemm_r192_swiglu(const bf16_t* __restrict__ A, int lda,
-                                                          const int* __restrict__ rows, int M,
-                                                          const bf16_t* __restrict__ Wg,
-                                                          const bf16_t* __restrict__ Wu, int N, int K,
-                                                          bf16_t* __restrict__ U) {
-  gemm_wide_body<2, 2, 6, 6, 1>(A, lda, rows, M, Wg, Wu, N, N, K, K, nullptr, U);
-}
-__global__ __launch_bounds__(256) void k_gemm_r192_vverify(const bf16_t* __restrict__ A, int lda, int M,
-                                                           const bf16_t* __restrict__ W, int N, int K,
-                                                           TileEpilogue ep) {
-  gemm_wide_body<4, 1, 3, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
-}
-__global__ __launch_bounds__(256) void k_gemm_r192_qk(const bf16_t* __restrict__ A, int lda,
-                                                      const int* __restrict__ rows, int M,
-                                                      const bf16_t* __restrict__ W0,
-                                                      const bf16_t* __restrict__ W1, int N0, int N, int K,
-                                                      TileEpilogue ep) {
-  gemm_wide_body<2, 2, 6, 4, 0, 2>(A, lda, rows, M, W0, W1, N0, N, K, K, nullptr, nullptr, &ep);
 }
 
 // V floats per thread; every slice's load is issued before the first addition (a loop over the runtime count waits
@@ -768,10 +713,19 @@ void gemm_set_tuning(int force_s, int target_wg) {
 }
 #define g_tune (tune())
 
+// Shapes of k_gemm_wide and their estimates: us = start + rounds over the 256 CUs x (round + step x 64-wide steps) + MB of
+// weights / w + MB of float32 results / out.  Fitted to 2480 launches (256 to 4608 rows, maps of 1024 x 1024 to 3584 x 18944,
+// one to eight slices; 3 to 5 % rms).
+struct WideShape { int bm, bn; double start, round, step, w, out; };
+constexpr WideShape kWide[6] = {{256, 256, 3.85, 5.6, 1.182, 26, 6.8}, {192, 256, 4.23, 3.42, 0.987, 27, 6.2},
+                                {256, 128, 3.18, 2.59, 0.717, 23, 4.7}, {128, 256, 3.27, 2.86, 0.767, 22, 5.4},
+                                {192, 128, 2.49, 2.32, 0.615, 24, 4.4}, {128, 128, 2.07, 1.35, 0.477, 12, 3.7}};
+
 // Which kernel, how many slices of the contraction index and how long a slice: pure host logic.
 struct GemmPlan {
-  int kind;  // 0 nothing fits, 1 plain, 2 weight-streaming, 3 256x256 LDS-direct, 4 128x128 LDS-direct,
-             // 7 float32 on the matrix cores
+  int kind;  // 0 nothing fits, 1 plain, 2 weight-streaming, 3 LDS-direct tiles of one workgroup per CU, 4 128x128
+             // LDS-direct of two, 7 float32 on the matrix cores
+  int wide;  // kind 3: index into kWide
   int S, kps, nt, mt;
   double t;       // estimated us (kinds 2, 3 and 4)
   RingPlan ring;  // kind 2
@@ -798,7 +752,7 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
   }
   const GemmTuning defaults;
   const bool fat_ok = M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0;
-  const bool mid_ok = M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0;
+  const bool mid_ok = M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0;  // (and the other shapes of k_gemm_wide)
   if (fat_ok || mid_ok) {
     // The estimate of plan_ring for the tile kernels (256 x 256: one workgroup per CU; 128 x 128: two, a round of up to 256
     // has each CU to itself), at every slice count; 5 % rms.  Over the 432 shapes it was fitted to, op_linear takes 1.2 %
@@ -810,19 +764,21 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
     const bool literal = g_tune.force_s > 0 || g_tune.fat_min_m != defaults.fat_min_m ||
                          g_tune.tile_min_m != defaults.tile_min_m || g_tune.target_wg != defaults.target_wg;
     double best = 1e30;
-    auto offer = [&](int kind, int bm, int bn, int S) {
+    auto offer = [&](int kind, int wide, int S) {
+      const int bm = wide < 0 ? kMidM : kWide[wide].bm, bn = wide < 0 ? kMidN : kWide[wide].bn;
       int kps = ((K + S - 1) / S + kFatK - 1) / kFatK * kFatK;
       if (kps > K) kps = K;
       const int used = (K + kps - 1) / kps, mt = (M + bm - 1) / bm, nt = N / bn;
       const long long wg = static_cast<long long>(mt) * nt * used;
       const double steps = kps / kFatK, mb_w = 2.0 * N * K / 1e6, mb_out = 4.0 * M * N / 1e6, rem = wg % 512;
-      double t = kind == 3 ? 1.25 + static_cast<double>((wg + 255) / 256) * (4.4 + 1.184 * steps) + mb_w / 31 + used * mb_out / 6.9
+      double t = kind == 3 ? kWide[wide].start + static_cast<double>((wg + 255) / 256) * (kWide[wide].round + kWide[wide].step * steps) +
+                                 mb_w / kWide[wide].w + used * mb_out / kWide[wide].out
                            : 3.05 + (wg / 512 * 0.89 + (rem == 0 ? 0.0 : rem <= 256 ? 0.58 : 0.89)) * steps + mb_w / 20 +
                                  used * mb_out / 6.3;
       t += slices_us(used, mb_out, summed);
       if (t < best * 0.98) {
         best = t;
-        p.kind = kind; p.S = used; p.kps = kps; p.nt = nt; p.mt = mt; p.t = t;
+        p.kind = kind; p.wide = wide; p.S = used; p.kps = kps; p.nt = nt; p.mt = mt; p.t = t;
       }
     };
     const bool only_fat = literal && fat_ok;  // thresholds and slice counts set by the caller
@@ -833,14 +789,18 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
       m_lo = m_hi = std::max(1, std::min(s_cap, g_tune.target_wg / tiles));
     }
     for (int S = s_lo; fat_ok && S <= s_hi; ++S)
-      if (S == s_lo || K / S >= 8 * kFatK) offer(3, kFatM, kFatN, S);
+      if (S == s_lo || K / S >= 8 * kFatK) offer(3, 0, S);
     for (int S = m_lo; mid_ok && !only_fat && S <= m_hi; ++S)
-      if (S == m_lo || K / S >= 8 * kFatK) offer(4, kMidM, kMidN, S);
+      if (S == m_lo || K / S >= 8 * kFatK) offer(4, -1, S);
+    // (not for sums that are the caller's result: the 128 x 128 kernel deals them to two per element)
+    for (int i = 1; i < 6 && !summed && !literal; ++i)
+      for (int S = s_lo; N % kWide[i].bn == 0 && N0 % 8 == 0 && S <= s_hi; ++S)
+        if (S == s_lo || K / S >= 8 * kFatK) offer(3, i, S);
     if (!literal) {
       const RingPlan r = plan_ring(M, N, K, s_cap, 0, summed);
-      // (a row kernel reads the streaming kernel's sums ~1 us slower than the tile kernels': 256 rows x 4096 x 12288 in a
-      // response refresh, level by themselves, 214.8 us per layer against 212.4)
-      if (r.t < best * (summed ? 0.98 : 0.95)) {
+      // (in a step the streaming kernel and the row kernel behind it take up to 4 us longer than by themselves: output
+      // projection of 256 rows x 4096 x 4096 in two slices 21.6 + 8.1 us there, 128 x 128 tiles in four 18.5 + 8.4)
+      if (r.t < best * (summed ? 0.98 : 0.90)) {
         p.kind = 2; p.ring = r; p.S = r.S; p.kps = r.kps; p.nt = r.nt; p.mt = r.mt; p.t = r.t;
       }
     }
@@ -889,8 +849,17 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                       static_cast<const float*>(W1), N0, N, K, c_part, st);
       break;
     case 3:
-      hipLaunchKernelGGL(k_gemm_fat, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps,
-                         c_part);
+#define DLLMC_W(MI, NJ) \
+  hipLaunchKernelGGL((k_gemm_wide<MI, NJ>), grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part)
+      switch (p.wide) {
+        case 0: DLLMC_W(8, 8); break;
+        case 1: DLLMC_W(6, 8); break;
+        case 2: DLLMC_W(8, 4); break;
+        case 3: DLLMC_W(4, 8); break;
+        case 4: DLLMC_W(6, 4); break;
+        default: DLLMC_W(4, 4); break;
+      }
+#undef DLLMC_W
       break;
     case 4:
       if (summed)
@@ -934,20 +903,23 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   }
   if (!gemm_ring_ok(dtype, aligned16(A) && aligned16(w_gate) && aligned16(w_up), lda, K)) return false;
   if (M >= g_tune.tile_min_m) {
-    // Many rows: the LDS-direct tile kernels with paired gate/up column blocks, one slice; the tile shape whose
-    // rounds over the 256 CUs take least.  Measured us per round and 64-wide step: 256 x (128 + 128) 1.65,
-    // 256 x (96 + 96) 1.41, 192 x (96 + 96) 1.25, one workgroup per CU each; 128 x (64 + 64) 1.16 with two per CU,
-    // 0.78 with one; 256 x (48 + 48) 0.95.  At FFN width 12288: 4608 rows 7 x 1.65 (9 x 1.41, 12 x 1.25), 1024
-    // rows 2 x 1.41, 768 rows 2 x 1.25 (184 -> 160 us against 2 x 1.41), 384 rows 1 x 1.25 (2 x 1.16).
-    struct Tile { int rows, cols, per_cu; double t; };
-    const Tile tiles[5] = {{256, 128, 1, 1.65}, {256, 96, 1, 1.41}, {192, 96, 1, 1.25}, {128, 64, 2, 1.16}, {256, 48, 1, 0.95}};
+    // Many rows: the LDS-direct tile kernels with paired gate/up column blocks, one slice; the tile shape with the lowest
+    // estimate, of the form of kWide's (rows and columns of each matrix; 310 launches of 256 to 4608 rows, FFN
+    // widths 3072, 12288 and 18944; 2 to 5 % rms).  us at FFN width 12288: 256 rows 57 (256 x 48), 384 rows 72 (192 x 96), 576
+    // rows 121 (128 x 128), 768 rows 134 (192 x 96), 1024 157 (256 x 96), 4608 692 (256 x 128); width 3072, 256 rows 11.5 (128 x
+    // 64; before 22); width 18944, 333 rows 103 (128 x 128).
+    struct Tile { int rows, cols; double start, round, step, w, out; };
+    const Tile tiles[10] = {{256, 128, 1.9, 3.27, 1.349, 318, 2.1}, {256, 96, 0.5, 3.3, 1.038, 30, 2.3}, {192, 96, 1.1, 2.0, 0.866, 20, 2.0},
+                            {192, 128, 2.7, 0.65, 1.045, 35, 1.6}, {256, 64, 1.5, 1.54, 0.761, 30, 1.6}, {128, 128, 1.2, 2.16, 0.797, 37, 2.1},
+                            {192, 64, 1.9, 1.13, 0.654, 54, 1.8}, {128, 96, 0.6, 2.0, 0.614, 13, 1.9}, {128, 64, 1.1, 0.88, 0.503, 25, 1.8},
+                            {256, 48, 1.9, 1.3, 0.72, 50, 2.0}};
     int pick = -1;
     double best = 1e30;
-    for (int i = 0; i < 5; ++i) {
-      if (m % tiles[i].cols || (i == 0 && M < g_tune.fat_min_m) || (i == 4 && M > 256)) continue;
+    for (int i = 0; i < 10; ++i) {
+      if (m % tiles[i].cols || (i == 0 && M < g_tune.fat_min_m) || (i == 9 && M > 256)) continue;
       const long long n = static_cast<long long>((M + tiles[i].rows - 1) / tiles[i].rows) * (m / tiles[i].cols);
-      const int slots = 256 * tiles[i].per_cu;
-      const double t = (i == 3 && n <= 256) ? 0.78 : static_cast<double>((n + slots - 1) / slots) * tiles[i].t;
+      const double t = tiles[i].start + static_cast<double>((n + 255) / 256) * (tiles[i].round + tiles[i].step * (K / kFatK)) +
+                       4e-6 * m * K / tiles[i].w + 2e-6 * M * m / tiles[i].out;
       if (t < best) { best = t; pick = i; }
     }
     if (pick >= 0) {
@@ -957,15 +929,20 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
       const bf16_t* w1 = static_cast<const bf16_t*>(w_up);
       bf16_t* uo = static_cast<bf16_t*>(u);
       const dim3 grid(m / tiles[pick].cols, (M + tiles[pick].rows - 1) / tiles[pick].rows, 1);
-#define DLLMC_SW(KERNEL, NT) hipLaunchKernelGGL(KERNEL, grid, dim3(NT), 0, st, a, lda, rows, M, w0, w1, m, K, uo)
+#define DLLMC_SW(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, m, K, uo)
       switch (pick) {
-        case 0: DLLMC_SW(k_gemm_fat_swiglu, 256); break;
-        case 1: DLLMC_SW(k_gemm_fat96_swiglu, 256); break;
-        case 2: DLLMC_SW(k_gemm_r192_swiglu, 256); break;
-        case 3: DLLMC_SW(k_gemm_mid_swiglu, 256); break;
+        case 0: DLLMC_SW(k_gemm_wide_swiglu<8, 8>); break;
+        case 1: DLLMC_SW(k_gemm_wide_swiglu<8, 6>); break;
+        case 2: DLLMC_SW(k_gemm_wide_swiglu<6, 6>); break;
+        case 3: DLLMC_SW(k_gemm_wide_swiglu<6, 8>); break;
+        case 4: DLLMC_SW(k_gemm_wide_swiglu<8, 4>); break;
+        case 5: DLLMC_SW(k_gemm_wide_swiglu<4, 8>); break;
+        case 6: DLLMC_SW(k_gemm_wide_swiglu<6, 4>); break;
+        case 7: DLLMC_SW(k_gemm_wide_swiglu<4, 6>); break;
+        case 8: DLLMC_SW(k_gemm_wide_swiglu<4, 4>); break;
         default:  // one row tile
-          if (g_tune.weights_once) DLLMC_SW(k_gemm_tall_swiglu<true>, 256);
-          else DLLMC_SW(k_gemm_tall_swiglu<false>, 256);
+          if (g_tune.weights_once) DLLMC_SW(k_gemm_tall_swiglu<true>);
+          else DLLMC_SW(k_gemm_tall_swiglu<false>);
           break;
       }
 #undef DLLMC_SW
@@ -1008,24 +985,24 @@ int plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K,
   return way;
 }
 
-// Which tile kernel finishes Q | K of M rows x N columns in one slice: 3 = 192 x 128, 2 = 256 x 256, 1 = 128 x 128, 0 =
-// none (every shape that divides the columns would leave more than a quarter of the CUs without a workgroup).  The one
-// whose rounds over the CUs take least, by measured us per round and 64-wide step: 256 x 256 1.6, 128 x 128 1.16 with two
-// workgroups per CU and 0.78 with one, 192 x 128 0.92.  (768 rows x 8192 columns: 192 x 128 in one round of 256
-// workgroups 58.7 us, 128 x 128 72.)
-static int qk_tile_kind(int M, int N, int N0, int K) {
-  if (K % kFatK || M < g_tune.tile_min_m) return 0;
+// Shape of kWide whose tiles finish Q | K of M rows x N columns in one slice, -1: none (every shape that divides the
+// columns would leave more than a quarter of the CUs without a workgroup).  By the estimates of the plain maps without their
+// float32 results; 2 us per round more for the epilogue (1024 rows x 8192 columns: 256 x 128 63 us, 128 x 128 with two
+// workgroups per CU 76; 4608 rows: 192 x 256 250, 256 x 256 297; 768 rows: 192 x 128 48).
+int qk_tile_shape(int M, int N, int N0, int K) {
+  if (K % kFatK || M < g_tune.tile_min_m) return -1;
   const int cus = 256, least = 3 * cus / 4;
-  int kind = 0;
+  int shape = -1;
   double best = 1e30;
-  auto tiles = [&](int bm, int bn) { return static_cast<long long>((M + bm - 1) / bm) * (N / bn); };
-  auto offer = [&](int k, double t) { if (t < best) { best = t; kind = k; } };
-  if (M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0 && tiles(kFatM, kFatN) >= least)
-    offer(2, (tiles(kFatM, kFatN) + cus - 1) / cus * 1.6);
-  if (N % kMidN == 0 && N0 % kMidN == 0 && tiles(kMidM, kMidN) >= least)
-    offer(1, tiles(kMidM, kMidN) <= cus ? 0.78 : (tiles(kMidM, kMidN) + 2 * cus - 1) / (2 * cus) * 1.16);
-  if (N % 128 == 0 && N0 % 128 == 0 && tiles(192, 128) >= least) offer(3, (tiles(192, 128) + cus - 1) / cus * 0.92);
-  return kind;
+  for (int i = 0; i < 6; ++i) {
+    const WideShape& w = kWide[i];
+    if (N % w.bn || N0 % 128 || (i == 0 && M < g_tune.fat_min_m)) continue;
+    const long long tiles = static_cast<long long>((M + w.bm - 1) / w.bm) * (N / w.bn);
+    if (tiles < least) continue;
+    const double t = w.start + static_cast<double>((tiles + cus - 1) / cus) * (w.round + 2.0 + w.step * (K / kFatK)) + 2e-6 * N * K / w.w;
+    if (t < best) { best = t; shape = i; }
+  }
+  return shape;
 }
 
 void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first, int per_seq, int n,
@@ -1039,9 +1016,9 @@ void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
   if (way == kVR192)
-    hipLaunchKernelGGL(k_gemm_r192_vverify, dim3(N / 64, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, M, w, N, K, ep);
+    hipLaunchKernelGGL((k_gemm_wide_vverify<4, 1, 3, 4>), dim3(N / 64, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, M, w, N, K, ep);
   else if (way == kVFat)
-    hipLaunchKernelGGL(k_gemm_fat_vverify, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(256), 0, st, a,
+    hipLaunchKernelGGL((k_gemm_wide_vverify<2, 2, 8, 8>), dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(256), 0, st, a,
                        lda, M, w, N, K, ep);
   else
     hipLaunchKernelGGL(k_gemm_mid_vverify, dim3(N / kMidN, (M + kMidM - 1) / kMidM, 1), dim3(256), 0, st, a,
@@ -1055,8 +1032,8 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
   if (M <= 0) return true;
   if (dtype != 1 || d_h != 128 || lda % 8 || !aligned16(A) || !aligned16(wq) || !aligned16(w2)) return false;
   const int N = d_q + d_kv;
-  const int kind = qk_tile_kind(M, N, d_q, K);
-  if (kind == 0) return false;
+  const int shape = qk_tile_shape(M, N, d_q, K);
+  if (shape < 0) return false;
   TileEpilogue ep{};
   ep.n = n; ep.cache = static_cast<bf16_t*>(cache); ep.rmap = rmap; ep.tab = rope_tab;
   ep.q_out = static_cast<bf16_t*>(q_out); ep.d_kv = d_kv; ep.rope_second = rope_second ? 1 : 0;
@@ -1064,14 +1041,17 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w0 = static_cast<const bf16_t*>(wq);
   const bf16_t* w1 = static_cast<const bf16_t*>(w2);
-  if (kind == 3)
-    hipLaunchKernelGGL(k_gemm_r192_qk, dim3(N / 128, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, rows, M, w0, w1, d_q, N, K, ep);
-  else if (kind == 2)
-    hipLaunchKernelGGL(k_gemm_fat_qk, dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(256), 0, st, a, lda,
-                       rows, M, w0, w1, d_q, N, K, ep);
-  else
-    hipLaunchKernelGGL(k_gemm_mid_qk, dim3(N / kMidN, (M + kMidM - 1) / kMidM, 1), dim3(256), 0, st, a, lda,
-                       rows, M, w0, w1, d_q, N, K, ep);
+  const dim3 grid(N / kWide[shape].bn, (M + kWide[shape].bm - 1) / kWide[shape].bm, 1);
+#define DLLMC_QK(MI, NJ) hipLaunchKernelGGL((k_gemm_wide_qk<MI, NJ>), grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, d_q, N, K, ep)
+  switch (shape) {
+    case 0: DLLMC_QK(8, 8); break;
+    case 1: DLLMC_QK(6, 8); break;
+    case 2: DLLMC_QK(8, 4); break;
+    case 3: DLLMC_QK(4, 8); break;
+    case 4: DLLMC_QK(6, 4); break;
+    default: DLLMC_QK(4, 4); break;
+  }
+#undef DLLMC_QK
   return true;
 }
 

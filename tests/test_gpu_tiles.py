@@ -166,3 +166,42 @@ def test_narrow_models(H, rows):
         assert float(((a - c).abs() - 0.03 * c.abs()).max()) <= 0.12 * float(c.pow(2).mean().sqrt())
     tiles.close()
     plain.close()
+
+
+@pytest.mark.parametrize("H,m,L_p,L_r", [
+    (8, 3072, 300, 90),     # 390 rows: 128-row tiles throughout
+    (16, 3072, 900, 124),   # 1024: Q|K of 256 x 128
+    (32, 6144, 1100, 180),  # 1280: a seventh 192-row tile of 128 rows
+    (16, 2432, 1400, 137),  # 1537: rows past whole tiles of 128, 192 and 256; gate/up of 64 columns
+    (24, 1536, 2700, 200),  # 2900
+])
+@pytest.mark.parametrize("paged", [False, True])
+def test_shapes_between_the_two_widths(H, m, L_p, L_r, paged):
+    """Steps that take the 128 x 128, 192 x 128, 256 x 128, 128 x 256 and 192 x 256 tiles somewhere, bars as above; paged
+    caches reach the epilogues' rows through the row map."""
+    cfg = BASES["llada8b"].replace(T=1, K_p=1, K_r=1, L_p=L_p, L_r=L_r, d=128 * H, H_q=H, H_kv=H, m=m)
+    ws = I.device_weights(cfg)
+    n = L_p + L_r
+    per = -(-n // 16)
+    paging = None
+    if paged:
+        order = torch.randperm(per + 3, generator=torch.Generator().manual_seed(n))[:per].reshape(1, per)
+        paging = {"page_rows": 16, "pool_pages": per + 3, "page_table": order.tolist()}
+    make = lambda: binding.CachedDenoiser(
+        n_layers=1, d_model=cfg.d, n_q_heads=H, n_kv_heads=H, head_dim=128, d_ffn=m, batch=1, dtype=cfg.dtype, weights=ws,
+        L_p=L_p, L_r=L_r, rho=cfg.rho, K_p=1, K_r=1, rms_eps=cfg.rms_eps, rope_theta=cfg.rope_theta, paging=paging)
+    tiles = make()
+    binding.set_gemm_tuning(tile_min_m=1 << 20, fat_min_m=1 << 20)
+    try:
+        plain = make()
+    finally:
+        binding.set_gemm_tuning(tile_min_m=192, fat_min_m=512)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    hid = torch.randn(1, n, cfg.d, device="cuda", generator=gen).to(torch.bfloat16)
+    a_out, c_out = tiles.step(hid, 0)[0], plain.step(hid, 0)[0]
+    for a, c in [(tiles.read_cache(0, w), plain.read_cache(0, w)) for w in range(4)] + [(a_out, c_out)]:
+        a, c = a.float(), c.float()
+        assert float(((a - c).abs() - 0.03 * c.abs()).max()) <= 0.12 * float(c.pow(2).mean().sqrt())
+    tiles.close()
+    plain.close()
