@@ -956,6 +956,32 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   return true;
 }
 
+// Shape of kWide that takes a V-verify of `way` (rows per tile) instead of the 128 x 128 tiles with two workgroups per CU or the
+// 192 x 64 ones, if its estimate (that of the plain map without float32 results; 3 us per round and the cached
+// rows at 2.8 MB / us for the epilogue) is below t; -1: none is.  4608 rows x 4096 x 4096: 192 x 256 tiles 148
+// us, 128 x 128 162 to 168.
+int vverify_shape(int way, int M, int N, int K, double& t) {
+  int shape = -1;
+  for (int i : {1, 3}) {
+    const WideShape& w = kWide[i];
+    if (w.bm != (way == kVMid ? 128 : 192) || N % w.bn) continue;
+    const double rounds = static_cast<double>((static_cast<long long>((M + w.bm - 1) / w.bm) * (N / w.bn) + 255) / 256);
+    const double e = w.start + rounds * (w.round + 3.0 + w.step * (K / kFatK)) + 2e-6 * N * K / w.w + 2e-6 * M * N / 2.8;
+    if (e < t) { t = e; shape = i; }
+  }
+  return shape;
+}
+double vverify_mid_us(int M, int N, int K) {  // 128 x 128, two workgroups per CU
+  const long long t = static_cast<long long>((M + kMidM - 1) / kMidM) * (N / kMidN), rem = t % 512;
+  const double steps = K / kFatK;
+  return 3.7 + t / 512 * (6.0 + 0.849 * steps) + (rem == 0 ? 0.0 : 6.0 + (rem <= 256 ? 0.583 : 0.849) * steps) +
+         2e-6 * N * K / 17 + 2e-6 * M * N / 3.2;
+}
+double vverify_192_us(int M, int N, int K) {  // 192 x 64
+  const double rounds = static_cast<double>((static_cast<long long>((M + 191) / 192) * (N / 64) + 255) / 256);
+  return 3.5 + rounds * (5.0 + 0.47 * (K / kFatK)) + 2e-6 * N * K / 6 + 2e-6 * M * N / 2.8;
+}
+
 // The way through V-verify that takes least, by estimates in us of the form of plan_ring's, with what follows the launch
 // (launch_scores_from_part, or the row kernel; in a step the selection adds the sums, which spares the former's launch).  Fitted to 270 shapes (1 to 4096 rows, 128 to 8192 columns, contraction of 896
 // to 8192) timed each way: rms 4.7 % (64 x 64 tiles), 2.5 (128 x 128), 2.7 (256 x 256), 4.1 (192 x 64), 8.2 (split).  The
@@ -971,12 +997,14 @@ int plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K,
   double best = 3.9 + rounds(64, 64) * (1.7 + 0.21 * steps) + mb_w / 12.9 + mb_v / 1.2;
   auto offer = [&](int w, double t) { if (t < best) { best = t; way = w; } };
   if (M >= g_tune.tile_min_m) {
-    if (N % kMidN == 0) {  // two workgroups per CU
-      const long long t = tiles(kMidM, kMidN), rem = t % 512;
-      offer(kVMid, 3.7 + t / 512 * (6.0 + 0.849 * steps) + (rem == 0 ? 0.0 : 6.0 + (rem <= 256 ? 0.583 : 0.849) * steps) +
-                       mb_w / 17 + mb_v / 3.2);
+    if (N % kMidN == 0) {
+      double t = vverify_mid_us(M, N, K);
+      vverify_shape(kVMid, M, N, K, t);
+      offer(kVMid, t);
     }
-    offer(kVR192, 3.5 + rounds(192, 64) * (5.0 + 0.47 * steps) + mb_w / 6 + mb_v / 2.8);
+    double t192 = vverify_192_us(M, N, K);
+    vverify_shape(kVR192, M, N, K, t192);
+    offer(kVR192, t192);
     if (M >= g_tune.fat_min_m && N % kFatN == 0)
       offer(kVFat, rounds(kFatM, kFatN) * (16.6 + 1.13 * steps) + mb_w / 15 + mb_v / 2.7);
   }
@@ -1015,14 +1043,17 @@ void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first
   t_last_stream = false;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  if (way == kVR192)
-    hipLaunchKernelGGL((k_gemm_wide_vverify<4, 1, 3, 4>), dim3(N / 64, (M + 191) / 192, 1), dim3(256), 0, st, a, lda, M, w, N, K, ep);
-  else if (way == kVFat)
-    hipLaunchKernelGGL((k_gemm_wide_vverify<2, 2, 8, 8>), dim3(N / kFatN, (M + kFatM - 1) / kFatM, 1), dim3(256), 0, st, a,
-                       lda, M, w, N, K, ep);
-  else
-    hipLaunchKernelGGL(k_gemm_mid_vverify, dim3(N / kMidN, (M + kMidM - 1) / kMidM, 1), dim3(256), 0, st, a,
-                       lda, M, w, N, K, ep);
+  double t = way == kVMid ? vverify_mid_us(M, N, K) : way == kVR192 ? vverify_192_us(M, N, K) : 0.0;
+  const int shape = way == kVFat ? 0 : vverify_shape(way, M, N, K, t);
+  const dim3 grid = shape >= 0 ? dim3(N / kWide[shape].bn, (M + kWide[shape].bm - 1) / kWide[shape].bm)
+                    : way == kVMid ? dim3(N / kMidN, (M + kMidM - 1) / kMidM) : dim3(N / 64, (M + 191) / 192);
+#define DLLMC_V(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), 0, st, a, lda, M, w, N, K, ep)
+  if (shape == 0) DLLMC_V(k_gemm_wide_vverify<2, 2, 8, 8>);
+  else if (shape == 1) DLLMC_V(k_gemm_wide_vverify<2, 2, 6, 8>);
+  else if (shape == 3) DLLMC_V(k_gemm_wide_vverify<2, 2, 4, 8>);
+  else if (way == kVR192) DLLMC_V(k_gemm_wide_vverify<4, 1, 3, 4>);
+  else DLLMC_V(k_gemm_mid_vverify);
+#undef DLLMC_V
 }
 
 bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, int M, const void* wq,

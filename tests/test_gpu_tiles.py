@@ -205,3 +205,21 @@ def test_shapes_between_the_two_widths(H, m, L_p, L_r, paged):
         assert float(((a - c).abs() - 0.03 * c.abs()).max()) <= 0.12 * float(c.pow(2).mean().sqrt())
     tiles.close()
     plain.close()
+
+
+@pytest.mark.parametrize("rows,d,d_kv", [(2500, 512, 4096), (2048, 512, 4096), (4609, 256, 4096), (1921, 1024, 4096)])
+def test_vverify_wide_shapes(rows, d, d_kv):
+    """V-verify of thousands of rows, whole and ragged tiles of 192 and 128 rows: bars of the paths' test."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    h = torch.randn((rows, d), generator=g, device="cuda").bfloat16()
+    wv = (0.02 * torch.randn((d_kv, d), generator=g, device="cuda")).bfloat16()
+    v = h.double() @ wv.double().t()
+    cache = (v + 0.1 * torch.randn((rows, d_kv), generator=g, device="cuda").double()).bfloat16()
+    old = cache.double()
+    scores = binding.op_vverify("bf16", h, wv, cache)
+    vb = v.bfloat16()
+    assert float((cache != vb).double().mean()) < 0.01
+    new = cache.double()
+    want = (new * old).sum(1) / (new.norm(dim=1) * old.norm(dim=1)).clamp(min=1e-8)
+    assert float((scores.double() - want).abs().max()) < 2.0 ** -24 * d_kv ** 0.5 * 4
