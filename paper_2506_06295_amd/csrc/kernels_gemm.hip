@@ -6,12 +6,10 @@
 //                      models: kernels_gemm_f32.hip).
 //  * k_gemm_ring    -- bf16 MFMA kernel for few activation rows against a weight matrix that is read
 //                      exactly once from HBM, and for any column count: kernels_gemm_ring.hip.
-//  * k_gemm_fat / k_gemm_mid -- bf16 MFMA kernels with 256 x 256 / 128 x 128 tiles whose
-//                      operands both go through LDS by direct global->LDS loads, for
-//                      launches with hundreds of activation rows; the same body with paired
-//                      gate/up column blocks and SwiGLU in the epilogue (k_gemm_*_swiglu,
-//                      k_gemm_tall_swiglu: 256 x 96 for up to 256 rows), with the head's reduction
-//                      (k_gemm_mid_head), and with 192-row tiles (k_gemm_r192_*).
+//  * k_gemm_wide / k_gemm_mid -- bf16 MFMA kernels for launches with hundreds of activation rows whose operands both go
+//                      through LDS by direct global->LDS loads: tiles of 128 x 128 to 256 x 256 in one workgroup per
+//                      CU (gemm_wide.hpp), also with SwiGLU, V-verify and Q | K epilogues, and 128 x 128 tiles in two per CU, also
+//                      with V-verify's epilogue and the head's reduction (k_gemm_mid_vverify, k_gemm_mid_head).
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
