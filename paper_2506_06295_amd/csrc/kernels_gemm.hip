@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, in
 constexpr int kFatM = 256, kFatN = 256, kFatK = 64;
 constexpr int kMidM = 128, kMidN = 128;
 
-//   PAIR = 1 (fused gate/up + SwiGLU, single slice): the tile's weight rows are BN/2 rows of W0
+//   PAIR = 1 (gemm_wide_body; fused gate/up + SwiGLU, single slice): the tile's weight rows are BN/2 rows of W0
 //        (gate) followed by the same BN/2 rows of W1 (up), so every lane ends up with the gate
 //        and the up sum of the same output element and stores bf16(silu(gate) * up) to U[M, N]
 //        (N = FFN width; the grid has N / (BN/2) column tiles).
@@ -114,7 +114,7 @@ constexpr int kMidM = 128, kMidN = 128;
 //           (position first + i % per_seq of sequence i / per_seq); the sums are rounded to bf16,
 //           scored against the cached row they replace (per row and 64-column block the three
 //           sums go to `part`, laid out as for k_vverify_tile) and written to the cache.
-//        2: Q | K with RoPE.  A tile column block of 128 is one head, two column wavefronts; the
+//        2: (gemm_wide_body) Q | K with RoPE.  A tile column block of 128 is one head, two column wavefronts; the
 //           weight rows are dealt so that a lane's accumulators j and j + 2 hold the rotation pair
 //           (t, t + 64): rotated in registers, query heads go to the compact q_out[i] and the
 //           other heads to cache row rows[i].
@@ -189,13 +189,12 @@ __device__ __forceinline__ void head_tile_reduce(const float* tile, int m0, int 
     part[static_cast<size_t>(m0 + r) * tiles + col_tile] = HeadPart{mx, sum, col_tile * 128 + first, 0};
 }
 
-template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0, bool FINE = false, bool NT = false>
+template <int WM, int WN, int MI, int NJ, int EPI = 0, bool FINE = false, bool NT = false>
 __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int lda,
                                               const int* __restrict__ rows, int M,
                                               const bf16_t* __restrict__ W0,
                                               const bf16_t* __restrict__ W1, int N0, int N, int K,
                                               int k_per_slice, float* __restrict__ C,
-                                              bf16_t* __restrict__ U = nullptr,
                                               const TileEpilogue* ep = nullptr) {
   constexpr int NWV = WM * WN;
   constexpr int BM = WM * MI * 16, BN = WN * NJ * 16;
@@ -212,7 +211,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // Two workgroups per CU (128 x 128, four wavefronts), two stages of both operands: the loads of step kt+1 go out before
   // the wait for step kt and a second barrier at the end of the step protects the stage they overwrite (a five-slot loop
   // with 16 KB slots measured 3-8 % slower).
-  constexpr int kLdsTotal = 2 * kStage + (EPI == 1 || EPI == 2 ? 2 * BM / 4 : 0);
+  constexpr int kLdsTotal = 2 * kStage + (EPI == 1 ? 2 * BM / 4 : 0);
   __shared__ __attribute__((aligned(1024))) uint4 lds_all[kLdsTotal];
   uint4 (*lds)[kStage] = reinterpret_cast<uint4 (*)[kStage]>(lds_all);
   int (*meta)[BM] = reinterpret_cast<int (*)[BM]>(lds_all + 2 * kStage);
@@ -223,8 +222,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   const int wm = wave / WN, wn = wave % WN;
   int col_tile, row_tile;
   xcd_tile_map_blocked(col_tile, row_tile);
-  static_assert(!PAIR || NJ % 2 == 0, "gate and up column blocks come in pairs");
-  const int m0 = row_tile * BM, n0 = col_tile * (PAIR ? BN / 2 : BN);
+  const int m0 = row_tile * BM, n0 = col_tile * BN;
   const int kbeg = blockIdx.z * k_per_slice;
   const int klen = min(K, kbeg + k_per_slice) - kbeg;  // multiple of kFatK
   const int nkt = klen / kFatK;
@@ -248,36 +246,20 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   for (int j = 0; j < LB; ++j) {
     const int r = 8 * (LB * wave + j) + lane / 8;
     const int chunk = (lane % 8) ^ (r % 8);
-    if (PAIR) {
-      // LDS weight rows [0, BN/2): gate rows n0 + r; [BN/2, BN): up rows n0 + r - BN/2
-      const int nn = n0 + (r % (BN / 2));  // < N: N % (BN/2) == 0
-      bsrc[j] = (r < BN / 2 ? W0 : W1) + static_cast<size_t>(nn) * K + kbeg + chunk * 8;
-    } else {
-      // EPI 2: LDS weight row wn*64 + j*16 + c is column (j/2)*64 + (wn%2)*32 + (j%2)*16 + c of head
-      // wn/2 of the tile, so that a lane's accumulators j and j + 2 are a rotation pair
-      const int rp = EPI == 2 ? (r / 128) * 128 + ((r % 64) / 32) * 64 + ((r / 64) % 2) * 32 + r % 32 : r;
-      const int nn = n0 + rp;  // < N: N % BN == 0
-      bsrc[j] = (nn < N0 ? W0 + static_cast<size_t>(nn) * K
-                         : W1 + static_cast<size_t>(nn - N0) * K) + kbeg + chunk * 8;
-    }
+    const int nn = n0 + r;  // < N: N % BN == 0
+    bsrc[j] = (nn < N0 ? W0 + static_cast<size_t>(nn) * K
+                       : W1 + static_cast<size_t>(nn - N0) * K) + kbeg + chunk * 8;
   }
-  // EPI: what the epilogue needs to know about the tile's rows, looked up here so that the trips
-  // to memory pass under the main loop.  EPI 1: cache row, index of the row's score (-1: not
-  // scored); EPI 2: position in the sequence, cache row.
-  if ((EPI == 1 || EPI == 2) && threadIdx.x < BM) {
+  // EPI 1: what the epilogue needs to know about the tile's rows -- cache row, index of the row's score (-1: not
+  // scored) -- looked up here so that the trips to memory pass under the main loop.
+  if (EPI == 1 && threadIdx.x < BM) {
     const int r = threadIdx.x;
     const int m = min(m0 + r, M - 1);
-    if (EPI == 1) {
-      const int seq = m / ep->per_seq, pos = ep->first + m % ep->per_seq;
-      const int row = seq * ep->n + pos;
-      meta[0][r] = ep->rmap ? ep->rmap[row] : row;
-      meta[1][r] = (m0 + r < M && ep->part != nullptr && pos >= ep->L_p)
-                                 ? seq * (ep->n - ep->L_p) + (pos - ep->L_p) : -1;
-    } else {
-      const int row = rows ? rows[m] : m;
-      meta[0][r] = row % ep->n;
-      meta[1][r] = ep->rmap ? ep->rmap[row] : row;
-    }
+    const int seq = m / ep->per_seq, pos = ep->first + m % ep->per_seq;
+    const int row = seq * ep->n + pos;
+    meta[0][r] = ep->rmap ? ep->rmap[row] : row;
+    meta[1][r] = (m0 + r < M && ep->part != nullptr && pos >= ep->L_p)
+                     ? seq * (ep->n - ep->L_p) + (pos - ep->L_p) : -1;
   }
 #define DLLMC_LDS_ISSUE(stage, kt)                                                              \
   {                                                                                             \
@@ -330,9 +312,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
       }
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        // PAIR: column blocks j < NJ/2 are gate, j >= NJ/2 the same columns of up
-        const int r = PAIR ? (j / (NJ / 2)) * (BN / 2) + wn * (NJ / 2 * 16) + (j % (NJ / 2)) * 16 + ln
-                           : wn * (NJ * 16) + j * 16 + ln;
+        const int r = wn * (NJ * 16) + j * 16 + ln;
         bf[j] = __builtin_bit_cast(bf16x8, lb[r * 8 + (c ^ (r % 8))]);
       }
 #pragma unroll
@@ -384,13 +364,12 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     head_tile_reduce<NWV * 64 / BM>(tile, m0, M, col_tile, gridDim.x, reinterpret_cast<HeadPart*>(C));
     return;
   }
-  if (EPI == 1 || EPI == 2) {
-    // Epilogues that finish the step's work on the tile.  A wavefront's 16-row x 64-column block of
+  if (EPI == 1) {
+    // V-verify, finished on the tile.  A wavefront's 16-row x 64-column block of
     // results (rounded to bf16) is staged through a private piece of LDS so that it leaves, and
     // the cached rows it is compared with arrive, as 16-byte pieces of contiguous row segments:
     // lane l then holds columns 8*(l%8) .. +8 of block rows l/8 and l/8 + 8.
-    static_assert((EPI != 1 && EPI != 2) || NJ == 4, "a wavefront's block is 64 columns wide");
-    static_assert(EPI != 2 || WN % 2 == 0, "a head is two column wavefronts");
+    static_assert(EPI != 1 || NJ == 4, "a wavefront's block is 64 columns wide");
     constexpr int kStg = 72;  // staging row stride in elements: 64 columns + 16 bytes
     static_assert(NWV * 16 * kStg * sizeof(bf16_t) <= kStage * sizeof(uint4), "staging fits a stage");
     __syncthreads();  // everybody has finished the fragment reads of the last step
@@ -398,31 +377,10 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
     const bf16_t* stg = reinterpret_cast<const bf16_t*>(stg32);
     const int rr = lane / 8, ch = lane % 8;
     const int odd = ln & 1;
-    // EPI 2: the wavefront's columns are pairs (t, t + 64) of one head, t = tb .. tb + 31 (see the
-    // weight loader), staged as two runs of 32
-    const int tb = (wn % 2) * 32;
-    const int head0 = n0 + (wn / 2) * 128;  // first column of the head in [W0; W1]
-    const bool is_q = head0 < N0;
-    const bool rot = is_q || ep->rope_second != 0;
-    const int run = (ch / 4) * 64 + tb + (ch % 4) * 8;  // column inside the head of this lane's piece
     const int n_ct = N / 64, ct = col_tile * WN + wn;
-    // rotation factors of block i for this lane's rows lg*4 + e and pairs tb + j*16 + ln, or the old
-    // rows of block i (EPI 1): requested one block ahead
-    float2 cs[2][4];
-    uint4 old[2];
+    uint4 old[2];  // the old rows of block i, requested one block ahead
     auto request = [&](int i) {
       const int rb = wm * (MI * 16) + i * 16;  // first row of the block inside the tile
-      if (EPI == 2) {
-        if (rot) {
-          const int4 pos = *reinterpret_cast<const int4*>(&meta[0][rb + lg * 4]);
-          const int p4[4] = {pos.x, pos.y, pos.z, pos.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              cs[j][e] = ep->tab[static_cast<size_t>(p4[e]) * 64 + tb + j * 16 + ln];
-        }
-      } else {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           old[h] = make_uint4(0u, 0u, 0u, 0u);
@@ -431,12 +389,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
             old[h] = *reinterpret_cast<const uint4*>(ep->cache + static_cast<size_t>(meta[0][r]) * N + n0 +
                                                      wn * 64 + ch * 8);
         }
-      }
     };
-    if (!rot) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) cs[0][e] = cs[1][e] = make_float2(1.f, 0.f);
-    }
     request(0);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -444,21 +397,10 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
       // final values of the lane's accumulator elements
       float val[NJ][4];
       uint4 old_i[2] = {old[0], old[1]};
-      if (EPI == 2) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const float x0 = acc[i][j][e], x1 = acc[i][j + 2][e];
-            val[j][e] = x0 * cs[j][e].x - x1 * cs[j][e].y;
-            val[j + 2][e] = x1 * cs[j][e].x + x0 * cs[j][e].y;
-          }
-      } else {
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
           for (int e = 0; e < 4; ++e) val[j][e] = acc[i][j][e];
-      }
       if (i + 1 < MI) request(i + 1);
       // Neighbouring lanes hold neighbouring columns of the same four rows: they trade one value
       // of each row pair, after which the even lane owns columns (ln, ln + 1) of row e and the odd
@@ -481,8 +423,8 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
       for (int h = 0; h < 2; ++h) {
         const int r = rb + rr + 8 * h;  // row inside the tile
         const uint4 nv = *reinterpret_cast<const uint4*>(stg + (rr + 8 * h) * kStg + ch * 8);
-        const int crow = meta[EPI == 1 ? 0 : 1][r];
-        if (EPI == 1) {
+        const int crow = meta[0][r];
+        {
           const int sidx = meta[1][r];
           if (ep->part != nullptr) {  // uniform
             const uint32_t nw4[4] = {nv.x, nv.y, nv.z, nv.w};
@@ -513,10 +455,6 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
           }
           if (m0 + r < M)
             *reinterpret_cast<uint4*>(ep->cache + static_cast<size_t>(crow) * N + n0 + wn * 64 + ch * 8) = nv;
-        } else if (m0 + r < M) {
-          bf16_t* dst = is_q ? ep->q_out + static_cast<size_t>(m0 + r) * N0 + head0 + run
-                             : ep->cache + static_cast<size_t>(crow) * ep->d_kv + (head0 - N0) + run;
-          *reinterpret_cast<uint4*>(dst) = nv;
         }
       }
       // ... and the loads before the next block's stores
@@ -524,23 +462,6 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
       __builtin_amdgcn_s_waitcnt(0xC07F);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    return;
-  }
-  if (PAIR) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int m = m0 + wm * (MI * 16) + i * 16 + lg * 4 + e;
-        if (m < M) {
-#pragma unroll
-          for (int j = 0; j < NJ / 2; ++j) {
-            const float g = acc[i][j][e], up = acc[i][j + NJ / 2][e];
-            U[static_cast<size_t>(m) * N + n0 + wn * (NJ / 2 * 16) + j * 16 + ln] =
-                f32_to_bf16(g / (1.0f + expf(-g)) * up);
-          }
-        }
-      }
     return;
   }
   float* Cs = C + static_cast<size_t>(blockIdx.z) * M * N;
@@ -597,20 +518,20 @@ __global__ __launch_bounds__(256) void k_gemm_mid_fine(const bf16_t* __restrict_
                                                        const bf16_t* __restrict__ W0,
                                                        const bf16_t* __restrict__ W1, int N0, int N,
                                                        int K, int k_per_slice, float* __restrict__ C) {
-  gemm_lds_body<2, 2, 4, 4, 0, 0, true>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
+  gemm_lds_body<2, 2, 4, 4, 0, true>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
 }
 
 __global__ __launch_bounds__(256) void k_gemm_mid_vverify(const bf16_t* __restrict__ A, int lda, int M,
                                                           const bf16_t* __restrict__ W, int N, int K,
                                                           TileEpilogue ep) {
-  gemm_lds_body<2, 2, 4, 4, 0, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, nullptr, &ep);
+  gemm_lds_body<2, 2, 4, 4, 1>(A, lda, nullptr, M, W, nullptr, N, N, K, K, nullptr, &ep);
 }
 
 template <bool NT>
 __global__ __launch_bounds__(256) void k_gemm_mid_head(const bf16_t* __restrict__ A, int lda, int M,
                                                        const bf16_t* __restrict__ W, int N, int K,
                                                        float* __restrict__ C) {
-  gemm_lds_body<2, 2, 4, 4, 0, 3, false, NT>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C);
+  gemm_lds_body<2, 2, 4, 4, 3, false, NT>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C);
 }
 
 // 256 rows x (48 gate + 48 up) columns, four wavefronts of 64 x 96 each: for up to 256 rows and
@@ -964,6 +885,7 @@ int vverify_shape(int way, int M, int N, int K, double& t) {
     const WideShape& w = kWide[i];
     if (w.bm != (way == kVMid ? 128 : 192) || N % w.bn) continue;
     const double rounds = static_cast<double>((static_cast<long long>((M + w.bm - 1) / w.bm) * (N / w.bn) + 255) / 256);
+    if (w.bm == 192 && rounds < 2) continue;  // a single round leaves CUs idle: split sums or smaller tiles
     const double e = w.start + rounds * (w.round + 3.0 + w.step * (K / kFatK)) + 2e-6 * N * K / w.w + 2e-6 * M * N / 2.8;
     if (e < t) { t = e; shape = i; }
   }
