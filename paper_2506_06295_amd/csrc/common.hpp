@@ -205,9 +205,11 @@ bool gemm_last_was_stream();
 void gemm_clear_last_stream();  // a matrix product launched by another launcher follows
 // summed: what follows is launch_reduce_slices, unless there is a single slice and it went to whole (may be null);
 // otherwise a row kernel that reads every slice.
+// logits: equal weight rows have to give equal results (the lowest token wins): the streaming kernel's walk starts at the
+// same step in every column tile, without the non-temporal loads and their rotated starts.
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
-                hipStream_t st, bool summed = false, float* whole = nullptr);
+                hipStream_t st, bool summed = false, float* whole = nullptr, bool logits = false);
 // Estimated us of what reads S slices of mb MB each: a pass of k_reduce_slices with its launch (summed; a single slice is
 // the result already), or their share of a row kernel (5 TB/s, with many rows 8; at 8 throughout a response refresh of 256
 // rows took eight slices of the down projection instead of four, 217 us per layer instead of 213).

@@ -1029,7 +1029,7 @@ int dllmc_gen_step(dllmc_gen* g, int32_t* tokens, int32_t step_idx, int32_t* sel
                                static_cast<size_t>(M) * g->g.vocab / 4, st);
       if (tiles > 0) tm.bytes = (V * d + static_cast<double>(M) * d) * esz + M * tiles * 16.0;
       else if (launch_gemm(dt, z, d, nullptr, M, g->g.lm_head, nullptr, g->g.vocab, g->g.vocab, d, logits,
-                           static_cast<size_t>(M) * g->g.vocab, st) != 1)
+                           static_cast<size_t>(M) * g->g.vocab, st, false, nullptr, true) != 1)
         return DLLMC_ENOMEM;
     }
     {
@@ -1105,7 +1105,7 @@ int dllmc_op_head(int32_t dtype, const void* hidden, const int32_t* rows, int32_
     launch_head_merge(part, tiles, M, nullptr, 0, 0, 1.0f, x0, conf, st);
   } else {
     const int S = launch_gemm(dtype, z, d, nullptr, M, lm_head, nullptr, vocab, vocab, d, logits,
-                              static_cast<size_t>(M) * vocab, st);
+                              static_cast<size_t>(M) * vocab, st, false, nullptr, true);
     if (S != 1) return DLLMC_ENOMEM;
     launch_head_finalize(logits, M, vocab, static_cast<float*>(z), static_cast<size_t>(M) * d * esz / 4, nullptr, 0, 0,
                          1.0f, x0, conf, st);

@@ -737,7 +737,7 @@ int gemm_plan_slices(int dtype, int M, int N, int N0, int K, size_t c_capacity) 
 
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
-                hipStream_t st, bool summed, float* whole) {
+                hipStream_t st, bool summed, float* whole, bool logits) {
   t_last_stream = false;
   if (M <= 0 || N <= 0) return 1;
   const bool al = aligned16(A) && aligned16(W0) && (W1 == nullptr || aligned16(W1));
@@ -761,7 +761,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
                            c_part);
       break;
     case 2:
-      launch_gemm_ring(p.ring, a, lda, rows, M, w0, w1, N0, N, K, c_part, summed, g_tune.weights_once, st);
+      launch_gemm_ring(p.ring, a, lda, rows, M, w0, w1, N0, N, K, c_part, summed, g_tune.weights_once && !logits, st);
       break;
     case 7:
       launch_gemm_f32(p.f32, static_cast<const float*>(A), lda, rows, M, static_cast<const float*>(W0),

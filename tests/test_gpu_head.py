@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2506_06295_amd import binding
+from paper_2506_06295_amd import binding, inputs as I
 from tests.test_gpu_generate import head_case
 
 pytestmark = pytest.mark.gpu
@@ -39,6 +39,29 @@ def test_equal_logits_go_to_the_lower_token(dtype, M, vocab, d):
     assert np.all(x0 < vocab // 2) and np.mean(x0 == want_x0) > 0.95
     x0, conf, _, _, _ = head_case(dtype, M, vocab, d, False, flat=True)
     assert np.all(x0 == 0) and np.allclose(conf, 1.0 / vocab, rtol=2e-5)
+
+
+@pytest.mark.parametrize("L_r,vocab", [(60, 4100), (150, 4100), (192, 12300)])
+def test_equal_logits_of_a_wide_model(L_r, vocab):
+    """The closed loop of a model whose weights no cache holds, a vocabulary in no whole tiles: a hundred
+    tokens over and over, the first of the equal ones wins in every row."""
+    cfg = I.CONFIGS["llada8b"].replace(T=1, L_p=32, L_r=L_r, steps=4, vocab=vocab)
+    den = binding.CachedDenoiser(
+        n_layers=1, d_model=cfg.d, n_q_heads=cfg.H_q, n_kv_heads=cfg.H_kv, head_dim=cfg.d_h, d_ffn=cfg.m, batch=1,
+        dtype=cfg.dtype, weights=I.device_weights(cfg), L_p=cfg.L_p, L_r=L_r, rho=cfg.rho, K_p=cfg.K_p, K_r=cfg.K_r,
+        rms_eps=cfg.rms_eps, rope_theta=cfg.rope_theta)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(vocab + L_r)
+    normal = lambda *shape: torch.randn(shape, generator=g, device="cuda").bfloat16()
+    gen = binding.Generator(den, normal(vocab + 1, cfg.d), torch.ones(cfg.d, device="cuda").bfloat16(),
+                            (0.02 * normal(100, cfg.d)).repeat(vocab // 100, 1).contiguous(), cfg.steps)
+    tokens = torch.randint(0, vocab, (1, cfg.n), generator=g, device="cuda").to(torch.int32)
+    tokens[:, cfg.L_p:] = vocab
+    gen.step(tokens, 0)
+    x0 = gen.read()[0]
+    assert bool(((x0 >= 0) & (x0 < 100)).all())
+    gen.close()
+    den.close()
 
 
 @pytest.mark.parametrize("dtype,vocab", [("bf16", 512), ("bf16", 12000), ("f32", 12000)])
