@@ -205,8 +205,8 @@ bool gemm_last_was_stream();
 void gemm_clear_last_stream();  // a matrix product launched by another launcher follows
 // summed: what follows is launch_reduce_slices, unless there is a single slice and it went to whole (may be null);
 // otherwise a row kernel that reads every slice.
-// logits: equal weight rows have to give equal results (the lowest token wins): the streaming kernel's walk starts at the
-// same step in every column tile, without the non-temporal loads and their rotated starts.
+// logits: equal weight rows have to give equal results (the lowest token wins): the walk over the contraction starts at the
+// same step in every tile; the streaming kernel goes without its non-temporal loads, whose starts are rotated.
 int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const void* W0,
                 const void* W1, int N0, int N, int K, float* c_part, size_t c_capacity,
                 hipStream_t st, bool summed = false, float* whole = nullptr, bool logits = false);

@@ -45,7 +45,7 @@ template <int WM, int WN, int MI, int NJ, int PAIR = 0, int EPI = 0, bool NT = f
 __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
                                                const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0, int N,
                                                int K, int k_per_slice, float* __restrict__ C, bf16_t* __restrict__ U = nullptr,
-                                               const TileEpilogue* ep = nullptr) {
+                                               const TileEpilogue* ep = nullptr, int starts = 8) {
   constexpr int BM = WM * MI * 16, BN = WN * NJ * 16;
   constexpr int LA = BM / 32, LB = BN / 32;  // load instructions per wavefront and step
   static_assert(WM * WN == 4 && BM % 32 == 0 && BN % 32 == 0, "four wavefronts, whole load instructions");
@@ -104,7 +104,7 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
   }
   const uint32_t boff = static_cast<uint32_t>((lane / 8) * K + ((lane % 8) ^ (lane / 8)) * 8) * sizeof(bf16_t);
   // the walk starts at a step that depends on the XCD, see gemm_lds_body
-  const int rot = (((blockIdx.x + gridDim.x * blockIdx.y) & 7) * nkt) >> 3;
+  const int rot = (((blockIdx.x + gridDim.x * blockIdx.y) & (starts - 1)) * nkt) >> 3;
   auto kof = [&](int kt) { const int k = kt + rot; return (k < nkt ? k : k - nkt) * kFatK; };
   auto issue_a = [&](int slot, int ko, int j) {
     __builtin_amdgcn_global_load_lds(asrc[j] + ko, &lds[slot * kSlotA + (LA * wave + j) * 64], 16, 0, 0);

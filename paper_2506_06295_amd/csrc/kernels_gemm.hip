@@ -195,7 +195,7 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
                                               const bf16_t* __restrict__ W0,
                                               const bf16_t* __restrict__ W1, int N0, int N, int K,
                                               int k_per_slice, float* __restrict__ C,
-                                              const TileEpilogue* ep = nullptr) {
+                                              const TileEpilogue* ep = nullptr, int starts = 8) {
   constexpr int NWV = WM * WN;
   constexpr int BM = WM * MI * 16, BN = WN * NJ * 16;
   constexpr int LA = BM / 8 / NWV, LB = BN / 8 / NWV;  // load instructions per wavefront and step
@@ -280,9 +280,9 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
   // apart, so unrotated every load in flight on the chip has the same address bits below the row
   // pitch and the memory channels are loaded unevenly (4096 x 4096 x 16384: 959 -> 1097 TFLOP/s).
   // The workgroups of one XCD keep a common start, they share operand blocks through its L2.
-  // (EPI 3: no such start -- equal rows of the vocabulary projection have to give equal logits whatever tile
-  // they are in, so that the lowest token wins, and a sum's bits depend on where its walk begins)
-  const int rot = EPI == 3 ? 0 : (((blockIdx.x + gridDim.x * blockIdx.y) & 7) * nkt) >> 3;
+  // starts: 8, or 1 where every tile has to begin at the same step -- equal rows of the vocabulary projection have to give
+  // equal logits whatever tile they are in, so that the lowest token wins, and a sum's bits depend on where its walk begins
+  const int rot = (((blockIdx.x + gridDim.x * blockIdx.y) & (starts - 1)) * nkt) >> 3;
   DLLMC_LDS_ISSUE(0, rot)
   // (FINE, see k_gemm_ring: the first and the second half of the steps in sums of their own.  Halves, because even and odd
   // steps apart, two copies of the loop body in turn, took a third longer.)
@@ -482,8 +482,8 @@ __device__ __forceinline__ void gemm_lds_body(const bf16_t* __restrict__ A, int 
 template <int MI, int NJ>
 __global__ __launch_bounds__(256) void k_gemm_wide(const bf16_t* __restrict__ A, int lda, const int* __restrict__ rows, int M,
                                                    const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N0, int N,
-                                                   int K, int k_per_slice, float* __restrict__ C) {
-  gemm_wide_body<2, 2, MI, NJ>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
+                                                   int K, int k_per_slice, float* __restrict__ C, int starts) {
+  gemm_wide_body<2, 2, MI, NJ>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C, nullptr, nullptr, starts);
 }
 // gate/up + SwiGLU: N is the FFN width, a tile has 16 NJ columns of each
 template <int MI, int NJ>
@@ -509,8 +509,8 @@ __global__ __launch_bounds__(256) void k_gemm_mid(const bf16_t* __restrict__ A, 
                                                   const int* __restrict__ rows, int M,
                                                   const bf16_t* __restrict__ W0,
                                                   const bf16_t* __restrict__ W1, int N0, int N,
-                                                  int K, int k_per_slice, float* __restrict__ C) {
-  gemm_lds_body<2, 2, 4, 4>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C);
+                                                  int K, int k_per_slice, float* __restrict__ C, int starts) {
+  gemm_lds_body<2, 2, 4, 4>(A, lda, rows, M, W0, W1, N0, N, K, k_per_slice, C, nullptr, starts);
 }
 
 __global__ __launch_bounds__(256) void k_gemm_mid_fine(const bf16_t* __restrict__ A, int lda,
@@ -531,7 +531,7 @@ template <bool NT>
 __global__ __launch_bounds__(256) void k_gemm_mid_head(const bf16_t* __restrict__ A, int lda, int M,
                                                        const bf16_t* __restrict__ W, int N, int K,
                                                        float* __restrict__ C) {
-  gemm_lds_body<2, 2, 4, 4, 3, false, NT>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C);
+  gemm_lds_body<2, 2, 4, 4, 3, false, NT>(A, lda, nullptr, M, W, nullptr, N, N, K, K, C, nullptr, 1);
 }
 
 // 256 rows x (48 gate + 48 up) columns, four wavefronts of 64 x 96 each: for up to 256 rows and
@@ -749,6 +749,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
   const bf16_t* w0 = static_cast<const bf16_t*>(W0);
   const bf16_t* w1 = static_cast<const bf16_t*>(W1);
   const dim3 grid(p.nt, p.mt, p.S);
+  const int starts = logits ? 1 : 8;
   switch (p.kind) {
     case 1:
       if (dtype == 1)
@@ -769,7 +770,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
       break;
     case 3:
 #define DLLMC_W(MI, NJ) \
-  hipLaunchKernelGGL((k_gemm_wide<MI, NJ>), grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part)
+  hipLaunchKernelGGL((k_gemm_wide<MI, NJ>), grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part, starts)
       switch (p.wide) {
         case 0: DLLMC_W(8, 8); break;
         case 1: DLLMC_W(6, 8); break;
@@ -784,7 +785,7 @@ int launch_gemm(int dtype, const void* A, int lda, const int* rows, int M, const
       if (summed)
         hipLaunchKernelGGL(k_gemm_mid_fine, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part);
       else
-        hipLaunchKernelGGL(k_gemm_mid, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part);
+        hipLaunchKernelGGL(k_gemm_mid, grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, N0, N, K, p.kps, c_part, starts);
       break;
   }
   return p.S;

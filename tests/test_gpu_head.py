@@ -41,6 +41,17 @@ def test_equal_logits_go_to_the_lower_token(dtype, M, vocab, d):
     assert np.all(x0 == 0) and np.allclose(conf, 1.0 / vocab, rtol=2e-5)
 
 
+@pytest.mark.parametrize("M,vocab,d", [(700, 6400, 1024), (1030, 12800, 512), (2000, 3200, 4096)])
+def test_equal_logits_of_many_rows(M, vocab, d):
+    """Rows beyond those that the projection reduces itself: a hundred tokens over and over."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + vocab)
+    normal = lambda *shape: torch.randn(shape, generator=g, device="cuda").bfloat16()
+    x0, _ = binding.op_head("bf16", normal(M, d), torch.ones(d, device="cuda").bfloat16(),
+                            (0.05 * normal(100, d)).repeat(vocab // 100, 1).contiguous(), 1e-5)
+    assert bool(((x0 >= 0) & (x0 < 100)).all())
+
+
 @pytest.mark.parametrize("L_r,vocab", [(60, 4100), (150, 4100), (192, 12300)])
 def test_equal_logits_of_a_wide_model(L_r, vocab):
     """The closed loop of a model whose weights no cache holds, a vocabulary in no whole tiles: a hundred
