@@ -11,12 +11,18 @@
 //   * 128 x 128 per wavefront reads 128 KB of fragments per step from LDS, 128 x 64 192 KB;
 //   * with one wavefront per SIMD nothing else fills the matrix pipe, so the reads of the next 32 contraction values and the
 //     loads go out singly between MFMAs (2.5 MFMAs apart; in groups of four reads and four loads 1.43 and 1.69, loads every second
-//     MFMA 1.01 and 1.37), without branches: the last two steps load the last block again;
+//     MFMA 1.01 and 1.37).  The last steps, which have nothing to load, are copies of the loop's body; while they loaded
+//     the last block again a launch was 1 to 3 us longer;
+//   * what the V-verify and Q | K epilogues look up comes in one trip in front of the first loads (with a branch for the row
+//     list and the row map around each it was up to sixteen, one after the other), what they compare or rotate with under the
+//     last MFMAs, and results leave 16 bytes at a time.  Q | K (us; with trips one by one, so, with eight wavefronts): 8192 rows x 8192 x 4096
+//     452, 434, 430; 8192 x 4096 x 2048 138, 120, 118; 8192 x 2048 x 1024 49, 41, 40.  V-verify: 12288 x 4096 x 4096 344, 336, 340;
+//     4608 x 4096 x 4096 165, 157, 175; 4096 x 4096 x 512 44, 40, 39.6;
 //   * gate/up's epilogue, see silu_mul.  In the step (us, before: eight wavefronts): gate/up of 4608 rows x 12288 x 4096 735 -> 672, of
 //     1024 185 -> 158, of 768 156 -> 138, of 256 64 -> 57; down projection of 1024 rows 92 -> 81, of 4608 401 -> 377;
 //   * the accumulators are held in the accumulation registers by the constraint of an asm statement: left to the
 //     compiler, which has 256 of them and 130 other live registers, 48 to 540 moves enter the loop (none now; a move inside
-//     the loop would have to keep 11 wait states from the asm statement whose result it reads).
+//     the loop would have to keep 8 wait states from the asm statement whose result it reads).
 #pragma once
 
 namespace dllmc {
@@ -62,7 +68,7 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
   constexpr bool XB = DA >= DB;  // X is B
   constexpr int DX = XB ? DB : DA, DY = XB ? DA : DB, LX = XB ? LB : LA, LY = XB ? LA : LB;
   constexpr int kSlotA = BM * 8, kSlotB = BN * 8;
-  static_assert((DA * kSlotA + DB * kSlotB) * sizeof(uint4) <= 160 * 1024 && DX >= 2, "LDS of one CU");
+  static_assert((DA * kSlotA + DB * kSlotB) * sizeof(uint4) <= 160 * 1024 && DX >= 2 && DX <= 5, "LDS of one CU");
   __shared__ __attribute__((aligned(1024))) uint4 lds[DA * kSlotA + DB * kSlotB];  // A's slots, then B's
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int ln = lane % 16, lg = lane / 16;
@@ -121,15 +127,53 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
   auto issue_x = [&](int slot, int ko, int j) { if (XB) issue_b(slot, ko, j); else issue_a(slot, ko, j); };
   auto issue_y = [&](int slot, int ko, int j) { if (XB) issue_a(slot, ko, j); else issue_b(slot, ko, j); };
   auto block_x = [&](int t) {
-    const int ko = kof(min(t, nkt - 1));
+    const int ko = kof(t);
+    if (t >= nkt) return;
 #pragma unroll
     for (int j = 0; j < LX; ++j) issue_x(t, ko, j);
   };
   auto block_y = [&](int t) {
-    const int ko = kof(min(t, nkt - 1));
+    const int ko = kof(t);
+    if (t >= nkt) return;
 #pragma unroll
     for (int j = 0; j < LY; ++j) issue_y(t, ko, j);
   };
+  // row of this lane's elements of block i; their columns are 16 j + 4 lg .. + 3 of the wavefront's
+  auto row_of = [&](int i) { return m0 + wm * (MI * 16) + i * 16 + ln; };
+  // EPI: cache row of every block's row, and its position (EPI 2), looked up in front of the first blocks -- a register that is
+  // waited for behind them waits for all of them -- and all at once
+  int crow[MI], meta[MI];
+  if (EPI != 0) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int m = min(row_of(i), M - 1);
+      crow[i] = EPI == 1 ? (m / ep->per_seq) * ep->n + ep->first + m % ep->per_seq : m;
+    }
+    if (EPI == 2 && rows != nullptr) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) crow[i] = rows[crow[i]];
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+      if (EPI == 2) meta[i] = crow[i] % ep->n;
+    if (ep->rmap != nullptr) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) crow[i] = ep->rmap[crow[i]];
+    }
+    if (EPI == 1) {  // rows that are not scored: the complement
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int m = row_of(i);
+        if (m >= M || ep->part == nullptr || ep->first + m % ep->per_seq < ep->L_p) crow[i] = ~crow[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      asm volatile("" : "+v"(crow[i]));
+      if (EPI == 2) asm volatile("" : "+v"(meta[i]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
   // in the order of the main loop: X(t), Y(t + DY - DX); Y(DY - 1) goes out in step 0
 #pragma unroll
   for (int t = 0; t < DY - DX; ++t) block_y(t);
@@ -158,9 +202,10 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
     }
   };
   // The MFMAs of 32 contraction values; `between` gets the number of those before it.  The compiler does not know how long the
-  // results of an asm statement take (8 wait states) and may read accumulators as soon as the loop ends: the last
-  // statement of a step waits itself.  Inside the loop nothing but these statements may touch them (no moves; with the last four
-  // MFMAs left to the compiler it moved their results right in front of a statement that reads them).
+  // results of an asm statement take (8 wait states: it puts s_nop 7 between the builtin and a store of its result) and may read
+  // accumulators as soon as the loop ends: the last statement of a step waits itself.  Inside the loop nothing but these statements
+  // may touch them (no moves; with the last four MFMAs left to the compiler it moved their results right in front of a statement that
+  // reads them).
   auto half = [&](auto kk_, auto&& between) {
     constexpr int kk = decltype(kk_)::value;
 #pragma unroll
@@ -180,41 +225,48 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
   // 1 to 2 % slower; the others up to 4 % faster)
   constexpr int kSpan = MI * NJ >= 64 ? MI * NJ * 5 / 8 : MI * NJ * 3 / 4;
 
-  // row of this lane's elements of block i; their columns are 16 j + 4 lg .. + 3 of the wavefront's
-  auto row_of = [&](int i) { return m0 + wm * (MI * 16) + i * 16 + ln; };
-  // EPI: cache row of every block's row, and the index of its score (-1: not scored; EPI 1) or its position (EPI 2), looked up
-  // while the first blocks are on their way
-  int crow[MI], meta[MI];
-  if (EPI != 0) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int m = min(row_of(i), M - 1);
-      int row;
-      if (EPI == 1) {
-        const int seq = m / ep->per_seq, pos = ep->first + m % ep->per_seq;
-        row = seq * ep->n + pos;
-        meta[i] = row_of(i) < M && ep->part != nullptr && pos >= ep->L_p ? seq * (ep->n - ep->L_p) + (pos - ep->L_p) : -1;
-      } else {
-        row = rows ? rows[m] : m;
-        meta[i] = row % ep->n;
-      }
-      crow[i] = ep->rmap ? ep->rmap[row] : row;
-    }
-#pragma unroll
-    for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(crow[i]), "+v"(meta[i]));  // (here, not behind the loop)
-  }
-  wait_vmcnt_lds<(DX - 1) * LX + (DY > DX ? DX - 1 : DX - 2) * LY>();  // X(0) and Y(0) have landed
+  // X(0) and Y(0) have landed
+  if (nkt >= DY) wait_vmcnt_lds<(DX - 1) * LX + (DY > DX ? DX - 1 : DX - 2) * LY>();
+  else wait_vmcnt_lds<0>();
   __builtin_amdgcn_s_barrier();
 #pragma unroll
   for (int q = 0; q < MI + NJ; ++q) read(0, 0, 0, q);
-  // loads that may be in flight across a barrier: what a wavefront issued last, from the end Y, X, Y, ..., as far as none of
-  // them belongs to the next step
-  constexpr int kFly = DY == 2 ? 0 : (DX - 2) * (LX + LY) + (DY > DX ? LY : 0);
+  // What the epilogue compares or rotates with comes in units, requested one ahead of their use, the first under the last MFMAs:
+  // old values of a 64-column block (EPI 1), rotation factors of a 64-column block for half of the rows (EPI 2).
+  constexpr int HI = EPI == 2 ? MI / 2 : MI;
+  constexpr int kReq = EPI == 1 ? MI * 2 : HI * 4, kUnits = EPI == 1 ? NJ / 4 : NJ / 4 * (MI / HI);
+  static_assert(EPI != 2 || MI % 2 == 0, "halves");
+  // a lane's 16-byte pieces of a row (see `piece`) start here in a block of 32 columns
+  const int pc = (lg & 1) * 16 + (lg >> 1) * 8;
+  uint4 old[2][EPI == 1 ? MI : 1][2];
+  float4 cs[2][EPI == 2 ? HI : 1][4];
+  auto request = [&](int u, int q) {
+    if constexpr (EPI == 1) {
+      const int i = q / 2, c = crow[i] < 0 ? 0 : crow[i];  // (rows that are not scored: all the same one)
+      old[u % 2][i][q % 2] = *reinterpret_cast<const uint4*>(ep->cache + static_cast<size_t>(c) * N + n0 +
+                                                             (wn * (NJ / 4) + u) * 64 + q % 2 * 32 + pc);
+    } else if constexpr (EPI == 2) {
+      const int i = u % 2 * HI + q / 4, t0 = (wn * (NJ / 4) + u / 2) % 2 * 32 + lg * 4;
+      cs[u % 2][q / 4][q % 4] =
+          *reinterpret_cast<const float4*>(ep->tab + static_cast<size_t>(meta[i]) * 64 + t0 + q % 4 / 2 * 16 + q % 2 * 2);
+    }
+  };
+  // Four columns each of blocks j (a) and j + 1 (b): lanes 16 apart trade, so that the even 16 lanes hold eight neighbouring columns of
+  // j, the odd ones of j + 1.
+  auto piece = [](uint2 a, uint2 b) {
+    const auto x = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+    return make_uint4(x[0], y[0], x[1], y[1]);
+  };
   int sa = 0, sb = 0;          // slots of A(kt) and B(kt)
   int sy = DY - 1;             // slot of Y(kt - 1)
-  for (int kt = 0; kt < nkt; ++kt) {
+  // Step kt with `left` steps to come (DX: that many or more): what would lie beyond the last block is not loaded, and of what a
+  // wavefront issued last, from the end Y, X, Y, ..., only the blocks after kt + 1 may be in flight across the barrier.
+  auto step = [&](int kt, auto left_) {
+    constexpr int left = decltype(left_)::value;
+    constexpr int kFly = left == 0 ? 0 : (DX - 2 < left - 1 ? DX - 2 : left - 1) * LX + (DY - 2 < left - 1 ? DY - 2 : left - 1) * LY;
     const int sa1 = sa + 1 < DA ? sa + 1 : 0, sb1 = sb + 1 < DB ? sb + 1 : 0;
-    const int ky = kof(min(kt + DY - 1, nkt - 1)), kx = kof(min(kt + DX, nkt - 1));
+    const int ky = left >= DY - 1 ? kof(kt + DY - 1) : 0, kx = left >= DX ? kof(kt + DX) : 0;
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     __builtin_amdgcn_sched_barrier(0);
     half(std::integral_constant<int, 0>{}, [&](int t) {
@@ -223,52 +275,60 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
         if (1 + q * kSpan / (MI + NJ) == t) read(sa, sb, 1, q);
 #pragma unroll
       for (int l = 0; l < LY; ++l)
-        if (l * kSpan / LY == t) issue_y(sy, ky, l);
+        if (left >= DY - 1 && l * kSpan / LY == t) issue_y(sy, ky, l);
     });
     wait_vmcnt_lds<kFly>();
-    __builtin_amdgcn_s_barrier();
+    if (left > 0) __builtin_amdgcn_s_barrier();
     half(std::integral_constant<int, 1>{}, [&](int t) {
 #pragma unroll
       for (int q = 0; q < MI + NJ; ++q)
-        if (1 + q * kSpan / (MI + NJ) == t) read(sa1, sb1, 0, q);
+        if (left > 0 && 1 + q * kSpan / (MI + NJ) == t) read(sa1, sb1, 0, q);
 #pragma unroll
       for (int l = 0; l < LX; ++l)
-        if (l * kSpan / LX == t) issue_x(XB ? sb : sa, kx, l);
+        if (left >= DX && l * kSpan / LX == t) issue_x(XB ? sb : sa, kx, l);
+      if constexpr (EPI != 0 && left == 0) {
+#pragma unroll
+        for (int q = 0; q < kReq; ++q)
+          if (q * kSpan / kReq == t) request(0, q);
+      }
     });
     sy = XB ? sa : sb;
     sa = sa1;
     sb = sb1;
-  }
-  // the loads of the last steps have landed before the workgroup's LDS is given back
-  wait_vmcnt_lds<0>();
+  };
+  int kt = 0;
+  for (; kt < nkt - DX; ++kt) step(kt, std::integral_constant<int, DX>{});
+  if constexpr (DX > 4) { if (nkt - kt > 4) step(kt++, std::integral_constant<int, 4>{}); }
+  if constexpr (DX > 3) { if (nkt - kt > 3) step(kt++, std::integral_constant<int, 3>{}); }
+  if constexpr (DX > 2) { if (nkt - kt > 2) step(kt++, std::integral_constant<int, 2>{}); }
+  if (nkt - kt > 1) step(kt++, std::integral_constant<int, 1>{});
+  step(kt, std::integral_constant<int, 0>{});
+  // (results leave the accumulation registers behind the last wait: without this some did between the last MFMAs)
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
   __builtin_amdgcn_sched_barrier(0);
 
   if constexpr (EPI == 1) {
     const int n_ct = N / 64;
-    // the old values of a 64-column block are requested at once: one trip to memory per block
 #pragma unroll
-    for (int jh = 0; jh < NJ / 4; ++jh) {
-      const int wv = wn * (NJ / 4) + jh, ct = col_tile * (BN / 64) + wv;
-      bf16_t* base = ep->cache + n0 + wv * 64 + lg * 4;
-      uint2 old[MI][4];
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          old[i][j] = make_uint2(0u, 0u);
-          if (meta[i] >= 0) old[i][j] = *reinterpret_cast<const uint2*>(base + static_cast<size_t>(crow[i]) * N + j * 16);
-        }
+    for (int u = 0; u < kUnits; ++u) {
+      const int wv = wn * (NJ / 4) + u, ct = col_tile * (BN / 64) + wv;
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
+        bf16_t* dst = ep->cache + static_cast<size_t>(crow[i] < 0 ? ~crow[i] : crow[i]) * N + n0 + wv * 64 + pc;
         float dot = 0.f, nn = 0.f, no = 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x4 v = acc[i][4 * jh + j];
-          const uint2 nv = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        for (int j = 0; j < 2; ++j) {
+          const f32x4 v0 = acc[i][4 * u + 2 * j], v1 = acc[i][4 * u + 2 * j + 1];
+          const uint4 nv = piece(make_uint2(pack_bf16x2(v0[0], v0[1]), pack_bf16x2(v0[2], v0[3])),
+                                 make_uint2(pack_bf16x2(v1[0], v1[1]), pack_bf16x2(v1[2], v1[3])));
           if (ep->part != nullptr) {  // uniform
-            const uint32_t nw[2] = {nv.x, nv.y}, ow[2] = {old[i][j].x, old[i][j].y};
+            const uint4 ov = old[u % 2][i][j];
+            const uint32_t nw[4] = {nv.x, nv.y, nv.z, nv.w}, ow[4] = {ov.x, ov.y, ov.z, ov.w};
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < 4; ++t) {
               const float a0 = __uint_as_float(nw[t] << 16), a1 = __uint_as_float(nw[t] & 0xffff0000u);
               const float b0 = __uint_as_float(ow[t] << 16), b1 = __uint_as_float(ow[t] & 0xffff0000u);
               if (ep->metric == 0) {
@@ -281,57 +341,59 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
               }
             }
           }
-          if (row_of(i) < M) *reinterpret_cast<uint2*>(base + static_cast<size_t>(crow[i]) * N + j * 16) = nv;
+          if (row_of(i) < M) *reinterpret_cast<uint4*>(dst + j * 32) = nv;
+          if (u + 1 < kUnits) request(u + 1, 2 * i + j);
         }
         if (ep->part != nullptr) {
 #pragma unroll
           for (int o = 16; o < 64; o <<= 1) {
             dot += __shfl_xor(dot, o, 64); nn += __shfl_xor(nn, o, 64); no += __shfl_xor(no, o, 64);
           }
-          if (meta[i] >= 0 && lg == 0) {
-            ep->part[(static_cast<size_t>(0) * n_ct + ct) * ep->part_stride + meta[i]] = dot;
-            ep->part[(static_cast<size_t>(1) * n_ct + ct) * ep->part_stride + meta[i]] = nn;
-            ep->part[(static_cast<size_t>(2) * n_ct + ct) * ep->part_stride + meta[i]] = no;
+          if (crow[i] >= 0 && lg == 0) {
+            const int m = row_of(i), at = m / ep->per_seq * (ep->n - ep->L_p) + ep->first + m % ep->per_seq - ep->L_p;
+            ep->part[(static_cast<size_t>(0) * n_ct + ct) * ep->part_stride + at] = dot;
+            ep->part[(static_cast<size_t>(1) * n_ct + ct) * ep->part_stride + at] = nn;
+            ep->part[(static_cast<size_t>(2) * n_ct + ct) * ep->part_stride + at] = no;
           }
         }
       }
     }
   } else if constexpr (EPI == 2) {
 #pragma unroll
-    for (int jh = 0; jh < NJ / 4; ++jh) {
-      const int wv = wn * (NJ / 4) + jh;
+    for (int u = 0; u < kUnits; ++u) {
+      if (u + 1 < kUnits) {
+#pragma unroll
+        for (int q = 0; q < kReq; ++q) request(u + 1, q);
+      }
+      const int jh = u / 2, wv = wn * (NJ / 4) + jh;
       const int head0 = n0 + (wv / 2) * 128;  // first column of the head in [W0; W1]
-      const int t0 = (wv % 2) * 32 + lg * 4;  // first pair of this lane's (j = 0; + 16 for j = 1)
       const bool is_q = head0 < N0, rotate = is_q || ep->rope_second != 0;
-      // rotation factors of all rows at once: one trip to memory
-      float4 cs[MI][4];
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          cs[i][u] = make_float4(1.f, 0.f, 1.f, 0.f);
-          if (rotate)
-            cs[i][u] = *reinterpret_cast<const float4*>(ep->tab + static_cast<size_t>(meta[i]) * 64 + t0 + u / 2 * 16 + u % 2 * 2);
-        }
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
+      for (int q = 0; q < HI; ++q) {
+        const int i = u % 2 * HI + q;
         bf16_t* dst = (is_q ? ep->q_out + static_cast<size_t>(row_of(i)) * N0 + head0
-                            : ep->cache + static_cast<size_t>(crow[i]) * ep->d_kv + (head0 - N0)) + t0;
+                            : ep->cache + static_cast<size_t>(crow[i]) * ep->d_kv + (head0 - N0)) + (wv % 2) * 32 + pc;
+        uint2 lo[2], hi[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          const f32x4 x0 = acc[i][4 * jh + j], x1 = acc[i][4 * jh + j + 2];
-          const float c[4] = {cs[i][2 * j].x, cs[i][2 * j].z, cs[i][2 * j + 1].x, cs[i][2 * j + 1].z};
-          const float s[4] = {cs[i][2 * j].y, cs[i][2 * j].w, cs[i][2 * j + 1].y, cs[i][2 * j + 1].w};
-          float lo[4], hi[4];
+          f32x4 x0 = acc[i][4 * jh + j], x1 = acc[i][4 * jh + j + 2];
+          if (rotate) {
+            const float4 f0 = cs[u % 2][q][2 * j], f1 = cs[u % 2][q][2 * j + 1];
+            const float c[4] = {f0.x, f0.z, f1.x, f1.z}, sn[4] = {f0.y, f0.w, f1.y, f1.w};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            lo[e] = x0[e] * c[e] - x1[e] * s[e];
-            hi[e] = x1[e] * c[e] + x0[e] * s[e];
+            for (int e = 0; e < 4; ++e) {
+              const float a = x0[e], b = x1[e];
+              x0[e] = a * c[e] - b * sn[e];
+              x1[e] = b * c[e] + a * sn[e];
+            }
           }
-          if (row_of(i) < M) {
-            *reinterpret_cast<uint2*>(dst + j * 16) = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
-            *reinterpret_cast<uint2*>(dst + j * 16 + 64) = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
-          }
+          lo[j] = make_uint2(pack_bf16x2(x0[0], x0[1]), pack_bf16x2(x0[2], x0[3]));
+          hi[j] = make_uint2(pack_bf16x2(x1[0], x1[1]), pack_bf16x2(x1[2], x1[3]));
+        }
+        const uint4 l4 = piece(lo[0], lo[1]), h4 = piece(hi[0], hi[1]);
+        if (row_of(i) < M) {
+          *reinterpret_cast<uint4*>(dst) = l4;
+          *reinterpret_cast<uint4*>(dst + 64) = h4;
         }
       }
     }
