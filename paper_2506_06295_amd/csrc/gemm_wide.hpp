@@ -1,8 +1,9 @@
 // Body of the LDS-direct tile kernels with one workgroup per CU (tiles of 192 and 256 rows), included by kernels_gemm.hip.
 //
 // Four wavefronts, one per SIMD, of 16 MI rows x 16 NJ columns each.  Operands, LDS layout and the meaning of PAIR, EPI and
-// NT are those of gemm_lds_body; the products are taken as W A^T, so that a lane holds four neighbouring columns of one row and
-// every result leaves as 8- or 16-byte pieces.
+// NT are those of gemm_lds_body; where results are bf16 the products are taken as W A^T, so that a lane holds four neighbouring
+// columns of one row and every result leaves as 8- or 16-byte pieces.  Float32 sums are taken as A W^T: of 16-byte pieces in rows of
+// their own no two share a request, and a 256 x 256 tile took 5.4 us to store (a launch of 64 tiles, one step: 15.4 us, so 12.0).
 //
 // Bound by the matrix cores and the power they may draw: a 256 x 256 x 64 step of nothing but MFMAs takes 0.89 us on zeros and
 // 1.03 on random data (8 wavefronts; 32 x 32 x 16 MFMAs 1.10), with the fragment reads, the barrier and loads that
@@ -58,6 +59,7 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
   static_assert(!PAIR || NJ % 2 == 0, "gate and up column blocks come in pairs");
   static_assert(EPI == 0 || (NJ % 4 == 0 && (EPI == 1 || WN * NJ % 8 == 0)), "blocks of 64 columns; a head is two");
   constexpr int kAux = NT ? 2 : 0;
+  constexpr bool kPlain = EPI == 0 && !PAIR;
   // A ring of LDS slots for each operand's blocks of 64 contraction values, as deep as 160 KB allow.  The barrier of step
   // kt -- everybody has read all of A(kt) and B(kt), everybody's loads of step kt + 1 have landed -- stands between the two
   // halves of the step and makes room for the next block of operand X, loaded during the second half, and of operand
@@ -212,10 +214,11 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
+        const bf16x8 &x = kPlain ? af[kk][i] : bf[kk][j], &y = kPlain ? bf[kk][j] : af[kk][i];
         if (kk == 1 && i * NJ + j == MI * NJ - 1)
-          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(acc[i][j]) : "v"(bf[kk][j]), "v"(af[kk][i]));
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(acc[i][j]) : "v"(x), "v"(y));
         else
-          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(bf[kk][j]), "v"(af[kk][i]));
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(x), "v"(y));
         __builtin_amdgcn_sched_barrier(0);
         between(i * NJ + j);
         __builtin_amdgcn_sched_barrier(0);
@@ -411,15 +414,17 @@ __device__ __forceinline__ void gemm_wide_body(const bf16_t* __restrict__ A, int
       }
     }
   } else {
-    typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));  // (the caller's result may lie anywhere)
-    float* Cs = C + static_cast<size_t>(blockIdx.z) * M * N + n0 + wn * (NJ * 16) + lg * 4;
+    // A W^T: a lane holds four rows of one column, 16 neighbouring lanes store 64 contiguous bytes
+    float* Cs = C + static_cast<size_t>(blockIdx.z) * M * N + n0 + wn * (NJ * 16) + ln;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const f32x4 v = acc[i][j];
-        if (row_of(i) < M)
-          *reinterpret_cast<float4_any*>(Cs + static_cast<size_t>(row_of(i)) * N + j * 16) = float4_any{v[0], v[1], v[2], v[3]};
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + wm * (MI * 16) + i * 16 + lg * 4 + e;
+        if (m < M) {
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) Cs[static_cast<size_t>(m) * N + j * 16] = acc[i][j][e];
+        }
       }
   }
 }
