@@ -315,8 +315,8 @@ int32_t dllmc_plan_gemm_slices(int32_t dtype, int32_t M, int32_t N, int32_t N0, 
 int32_t dllmc_plan_gate_up(int32_t M, int32_t d_ffn, int32_t d, int32_t* cols);
 
 /* Host-only: how dllmc_op_vverify takes `rows` rows (16-byte aligned operands, cache apart from both): 0 split
- * contraction and a row kernel, else one launch that overwrites the cache, of 128 x 128 (1), 256 x 256 (2), 192 x
- * 64 (3) or 64 x 64 (4) tiles. */
+ * contraction and a row kernel, else one launch that overwrites the cache, of tiles of 128 (1), 256 (2), 192 (3) or 64
+ * (4) rows. */
 int32_t dllmc_plan_vverify(int32_t dtype, int32_t rows, int32_t d, int32_t d_kv);
 
 /* Host-only: the number of key ranges of a bf16 attention of Mq < 128 queries per sequence with head width 128

@@ -365,19 +365,20 @@ void launch_select(float* scores, int B, int L, int k, int* sel_out, int sel_str
 // old|^2, 0, 0)) over the tile's columns go to part[(c * n_ct + t) * part_stride + seq * (n -
 // L_p) + pos - L_p]; then v_cache[row] = v.  plan_vverify says whether the shape is handled.
 // Ways through V-verify of M rows: split contraction (launch_gemm with c_capacity floats) and row kernel, the tile kernels'
-// epilogue (128 x 128, 256 x 256, 192 x 64), or the 64 x 64 tiles of launch_vverify_fused.
+// epilogue (tiles of 128, 256 and 192 rows), or the 64 x 64 tiles of launch_vverify_fused.
 enum VWay { kVSplit = 0, kVMid = 1, kVFat = 2, kVR192 = 3, kVFused = 4 };
-int plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K, size_t c_capacity, bool in_step);
+struct VPlan { int way, bm, bn; double us; };  // (rows and columns of a tile; 0 for kVSplit)
+VPlan plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K, size_t c_capacity, bool in_step);
 size_t vverify_part_floats(int N, size_t scored_rows);
 int vverify_col_tiles(int N);
 void launch_vverify_fused(const void* A, int lda, int M, int first, int per_seq, int n, int L_p,
                           const void* W, int N, int K, void* v_cache, float* part, int part_stride,
                           int metric, hipStream_t st, const int* rmap = nullptr);
-// The same V-verify (way: kVMid, kVFat or kVR192), and the Q | K projection with RoPE and the cache
+// The same V-verify (a plan of kVMid, kVFat or kVR192), and the Q | K projection with RoPE and the cache
 // scatter, finished in the epilogue of the tile kernels (one slice, no float32 partial sums, no row
 // kernel).  Arguments as for launch_vverify_fused / launch_gemm + launch_qk_finalize.
 // launch_gemm_qk_tiles returns false (nothing launched) when the shape is not handled or would not fill the chip.
-void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first, int per_seq, int n,
+void launch_gemm_vverify_tiles(const VPlan& plan, const void* A, int lda, int M, int first, int per_seq, int n,
                                int L_p, const void* W, int N, int K, void* v_cache, float* part,
                                int part_stride, int metric, const int* rmap, hipStream_t st);
 bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, int M, const void* wq,

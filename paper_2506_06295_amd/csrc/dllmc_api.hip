@@ -473,17 +473,16 @@ int dllmc_step(dllmc_ctx* c, const void* hidden_in, int32_t step_idx, void* hidd
     {
       Timed t(c, DLLMC_KC_GEMM_V, gemm_bytes(Mc, d_kv, d), gemm_flops(Mc, d_kv, d));
       if (!ksrc && !defer_v) {
-        const int way = plan_vverify(dt, aligned16(h) && aligned16(w.wv) && aligned16(Vc), d, Mc, d_kv, d, cws_cap,
-                                     true);
-        if (way == kVFused) {
+        const VPlan plan = plan_vverify(dt, aligned16(h) && aligned16(w.wv) && aligned16(Vc), d, Mc, d_kv, d, cws_cap, true);
+        if (plan.way == kVFused) {
           gemm_clear_last_stream();
           launch_vverify_fused(h, d, Mc, P ? 0 : L_p, carried_per_seq, n, L_p, w.wv, d_kv, d, Vc,
                                want_scores ? part : nullptr, B * L_r, c->metric, st, rmap);
-        } else if (way != kVSplit) {
-          launch_gemm_vverify_tiles(way, h, d, Mc, P ? 0 : L_p, carried_per_seq, n, L_p, w.wv, d_kv, d, Vc,
+        } else if (plan.way != kVSplit) {
+          launch_gemm_vverify_tiles(plan, h, d, Mc, P ? 0 : L_p, carried_per_seq, n, L_p, w.wv, d_kv, d, Vc,
                                     want_scores ? part : nullptr, B * L_r, c->metric, rmap, st);
         }
-        fused_v = way != kVSplit;
+        fused_v = plan.way != kVSplit;
       }
       if (fused_v) {
         t.bytes = (static_cast<double>(d_kv) * d + static_cast<double>(Mc) * d) * esz +
@@ -701,7 +700,7 @@ int32_t dllmc_plan_gate_up(int32_t M, int32_t d_ffn, int32_t d, int32_t* cols) {
 
 int32_t dllmc_plan_vverify(int32_t dtype, int32_t rows, int32_t d, int32_t d_kv) {
   if ((dtype != DLLMC_F32 && dtype != DLLMC_BF16) || rows < 1 || d < 1 || d_kv < 1) return DLLMC_EINVAL;
-  return plan_vverify(dtype, true, d, rows, d_kv, d, static_cast<size_t>(rows) * d_kv * 8, false);
+  return plan_vverify(dtype, true, d, rows, d_kv, d, static_cast<size_t>(rows) * d_kv * 8, false).way;
 }
 
 int32_t dllmc_plan_attention(int32_t B, int32_t Mq, int32_t n, int32_t H_q, int32_t H_kv, int32_t split_keys,
@@ -783,14 +782,14 @@ int dllmc_op_vverify(int32_t dtype, const void* h, const void* wv, void* v_cache
                           apart(v_cache, cache_bytes, h, static_cast<size_t>(rows) * d * esz) &&
                           apart(v_cache, cache_bytes, wv, static_cast<size_t>(d_kv) * d * esz);
   const size_t capacity = static_cast<size_t>(rows) * d_kv * 8;
-  const int way = !one_launch ? kVSplit
-                              : plan_vverify(dtype, aligned16(h) && aligned16(wv) && aligned16(v_cache), d, rows, d_kv, d,
-                                             capacity, false);
-  if (way != kVSplit) {
-    if (way == kVFused)
+  const VPlan plan = !one_launch ? VPlan{kVSplit, 0, 0, 0.0}
+                                 : plan_vverify(dtype, aligned16(h) && aligned16(wv) && aligned16(v_cache), d, rows, d_kv, d,
+                                                capacity, false);
+  if (plan.way != kVSplit) {
+    if (plan.way == kVFused)
       launch_vverify_fused(h, d, rows, 0, 0, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, st);
     else  // one sequence of `rows` response rows
-      launch_gemm_vverify_tiles(way, h, d, rows, 0, rows, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, nullptr, st);
+      launch_gemm_vverify_tiles(plan, h, d, rows, 0, rows, rows, 0, wv, d_kv, d, v_cache, scratch, rows, 0, nullptr, st);
     launch_scores_from_part(scratch, vverify_col_tiles(d_kv), rows, 0, scores, st);
     HIP_TRY(hipGetLastError());
     return DLLMC_OK;

@@ -633,12 +633,13 @@ void gemm_set_tuning(int force_s, int target_wg) {
 #define g_tune (tune())
 
 // Shapes of k_gemm_wide and their estimates: us = start + rounds over the 256 CUs x (round + step x 64-wide steps) + MB of
-// weights / w + MB of float32 results / out.  Fitted to 2480 launches (256 to 4608 rows, maps of 1024 x 1024 to 3584 x 18944,
-// one to eight slices; 3 to 5 % rms).
-struct WideShape { int bm, bn; double start, round, step, w, out; };
-constexpr WideShape kWide[6] = {{256, 256, 3.85, 5.6, 1.182, 26, 6.8}, {192, 256, 4.23, 3.42, 0.987, 27, 6.2},
-                                {256, 128, 3.18, 2.59, 0.717, 23, 4.7}, {128, 256, 3.27, 2.86, 0.767, 22, 5.4},
-                                {192, 128, 2.49, 2.32, 0.615, 24, 4.4}, {128, 128, 2.07, 1.35, 0.477, 12, 3.7}};
+// weights / kWideW + MB of float32 results / out.  Fitted to 6048 launches (200 to 12288 rows, maps of 896 x 2432 to 3584 x 18944 and
+// 4096 x 12288, one to eight slices, cold weights; 6 to 7 % rms).
+struct WideShape { int bm, bn; double start, round, step, out; };
+constexpr double kWideW = 23;
+constexpr WideShape kWide[6] = {{256, 256, 1.37, 3.46, 1.179, 6.8}, {192, 256, 1.88, 2.4, 0.931, 6.8},
+                                {256, 128, 2.53, 0.72, 0.712, 4.8}, {128, 256, 2.94, 0.3, 0.757, 5.3},
+                                {192, 128, 2.46, 0.3, 0.605, 4.6}, {128, 128, 2.13, 0.3, 0.478, 4.6}};
 
 // Which kernel, how many slices of the contraction index and how long a slice: pure host logic.
 struct GemmPlan {
@@ -673,13 +674,12 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
   const bool fat_ok = M >= g_tune.fat_min_m && N % kFatN == 0 && N0 % kFatN == 0;
   const bool mid_ok = M >= g_tune.tile_min_m && N % kMidN == 0 && N0 % kMidN == 0;  // (and the other shapes of k_gemm_wide)
   if (fat_ok || mid_ok) {
-    // The estimate of plan_ring for the tile kernels (256 x 256: one workgroup per CU; 128 x 128: two, a round of up to 256
-    // has each CU to itself), at every slice count; 5 % rms.  Over the 432 shapes it was fitted to, op_linear takes 1.2 %
-    // longer than with the best choice of all, where an estimate with different prices for the partial sums of the two
-    // kinds of kernel, no time per launch and no difference between one slice and a slice sum took 19 %, and 47 shapes
-    // more than 5 % longer than a plain rule on rows alone (none of 340 now): 192 rows x 4096 x 4096 20.6 us, now
-    // 18.2; 333 x 3072 x 1024 19.2 -> 9.9; 400 x 2432 x 896 15.2 -> 9.5; 1536 x 896 x 2432 25.2 -> 17.8; 576 x 4096 x 4096
-    // 35.0 -> 33.2; 64 x 12288 x 4096 31.7 -> 26.1; at worst 191 x 8192 x 4096 27.5 -> 29.5.
+    // The estimate of plan_ring for the tile kernels (kWide; 128 x 128 with two workgroups per CU: a round of up to 256 has each
+    // CU to itself), at every slice count.  In a step (198 maps of 200 to 12288 rows, with what reads the sums) the choice among
+    // them is 0.6 % from the quickest (with prices fitted to tiles whose last blocks came twice and whose sums left in rows of 16
+    // bytes 3.5 %).  op_linear: a price for the launch that adds slices, in place of a plain rule on rows alone: 192 rows x 4096 x 4096 20.6 us, so 18.2;
+    // 333 x 3072 x 1024 19.2 -> 9.9; 400 x 2432 x 896 15.2 -> 9.5; 1536 x 896 x 2432 25.2 -> 17.8; 64 x 12288 x 4096 31.7 -> 26.1.  Over 208
+    // shapes (16 to 2048 rows, eleven maps) it takes 0.7 % less with kWide's present prices than with those, nowhere more than 1.5 % more.
     const bool literal = g_tune.force_s > 0 || g_tune.fat_min_m != defaults.fat_min_m ||
                          g_tune.tile_min_m != defaults.tile_min_m || g_tune.target_wg != defaults.target_wg;
     double best = 1e30;
@@ -691,7 +691,7 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
       const long long wg = static_cast<long long>(mt) * nt * used;
       const double steps = kps / kFatK, mb_w = 2.0 * N * K / 1e6, mb_out = 4.0 * M * N / 1e6, rem = wg % 512;
       double t = kind == 3 ? kWide[wide].start + static_cast<double>((wg + 255) / 256) * (kWide[wide].round + kWide[wide].step * steps) +
-                                 mb_w / kWide[wide].w + used * mb_out / kWide[wide].out
+                                 mb_w / kWideW + used * mb_out / kWide[wide].out
                            : 3.05 + (wg / 512 * 0.89 + (rem == 0 ? 0.0 : rem <= 256 ? 0.58 : 0.89)) * steps + mb_w / 20 +
                                  used * mb_out / 6.3;
       t += slices_us(used, mb_out, summed);
@@ -717,9 +717,8 @@ GemmPlan plan_gemm(int dtype, bool operands_aligned, int lda, int M, int N, int 
         if (S == s_lo || K / S >= 8 * kFatK) offer(3, i, S);
     if (!literal) {
       const RingPlan r = plan_ring(M, N, K, s_cap, 0, summed);
-      // (in a step the streaming kernel and the row kernel behind it take up to 4 us longer than by themselves: output
-      // projection of 256 rows x 4096 x 4096 in two slices 21.6 + 8.1 us there, 128 x 128 tiles in four 18.5 + 8.4)
-      if (r.t < best * (summed ? 0.98 : 0.90)) {
+      // (168 maps of 192 to 1024 rows, cold, with what reads their sums: the choice is 0.7 % from the quicker of both on average)
+      if (r.t < best * (summed ? 0.98 : 1.0)) {
         p.kind = 2; p.ring = r; p.S = r.S; p.kps = r.kps; p.nt = r.nt; p.mt = r.mt; p.t = r.t;
       }
     }
@@ -810,6 +809,31 @@ int launch_gemm_head(int dtype, const void* A, int lda, int M, const void* W, in
   return N / kMidN;
 }
 
+// Gate/up of many rows: the LDS-direct tile kernels with paired gate/up column blocks, one slice; the tile shape with the lowest
+// estimate, of the form of kWide's (rows and columns of each matrix).  The weights' term (w) differs between shapes by more than any
+// rate could: it is what the fit leaves to it, and none of it counts for the choice (one price for all, 0.40 % from the
+// quickest shape; this table 0.38).  Over 872 launches of 200 to 12288 rows and FFN widths 1536 to 18944 it is 5 to 7 % rms
+// and 0.4 % from the quickest shape on average, 8 at worst.
+struct PairTile { int rows, cols; double start, round, step, w, out; };
+constexpr PairTile kPairTiles[10] = {
+    {256, 128, 1.9, 3.27, 1.349, 318, 2.1}, {256, 96, 0.5, 3.3, 1.038, 30, 2.3}, {192, 96, 1.1, 2.0, 0.866, 20, 2.0},
+    {192, 128, 2.7, 0.65, 1.045, 35, 1.6}, {256, 64, 1.5, 1.54, 0.761, 30, 1.6}, {128, 128, 1.2, 2.16, 0.797, 37, 2.1},
+    {192, 64, 1.9, 1.13, 0.654, 54, 1.8}, {128, 96, 0.6, 2.0, 0.614, 13, 1.9}, {128, 64, 1.1, 0.88, 0.503, 25, 1.8},
+    {256, 48, 1.9, 1.3, 0.72, 50, 2.0}};
+int swiglu_shape(int M, int m, int K) {
+  int pick = -1;
+  double best = 1e30;
+  for (int i = 0; i < 10; ++i) {
+    const PairTile& p = kPairTiles[i];
+    if (m % p.cols || (i == 0 && M < g_tune.fat_min_m) || (i == 9 && M > 256)) continue;
+    const long long n = static_cast<long long>((M + p.rows - 1) / p.rows) * (m / p.cols);
+    const double t = p.start + static_cast<double>((n + 255) / 256) * (p.round + p.step * (K / kFatK)) +
+                     4e-6 * m * K / p.w + 2e-6 * M * m / p.out;
+    if (t < best) { best = t; pick = i; }
+  }
+  return pick;
+}
+
 bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int M,
                         const void* w_gate, const void* w_up, int m, int K, void* u,
                         hipStream_t st) {
@@ -823,32 +847,14 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   }
   if (!gemm_ring_ok(dtype, aligned16(A) && aligned16(w_gate) && aligned16(w_up), lda, K)) return false;
   if (M >= g_tune.tile_min_m) {
-    // Many rows: the LDS-direct tile kernels with paired gate/up column blocks, one slice; the tile shape with the lowest
-    // estimate, of the form of kWide's (rows and columns of each matrix; 310 launches of 256 to 4608 rows, FFN
-    // widths 3072, 12288 and 18944; 2 to 5 % rms).  us at FFN width 12288: 256 rows 57 (256 x 48), 384 rows 72 (192 x 96), 576
-    // rows 121 (128 x 128), 768 rows 134 (192 x 96), 1024 157 (256 x 96), 4608 692 (256 x 128); width 3072, 256 rows 11.5 (128 x
-    // 64; before 22); width 18944, 333 rows 103 (128 x 128).
-    struct Tile { int rows, cols; double start, round, step, w, out; };
-    const Tile tiles[10] = {{256, 128, 1.9, 3.27, 1.349, 318, 2.1}, {256, 96, 0.5, 3.3, 1.038, 30, 2.3}, {192, 96, 1.1, 2.0, 0.866, 20, 2.0},
-                            {192, 128, 2.7, 0.65, 1.045, 35, 1.6}, {256, 64, 1.5, 1.54, 0.761, 30, 1.6}, {128, 128, 1.2, 2.16, 0.797, 37, 2.1},
-                            {192, 64, 1.9, 1.13, 0.654, 54, 1.8}, {128, 96, 0.6, 2.0, 0.614, 13, 1.9}, {128, 64, 1.1, 0.88, 0.503, 25, 1.8},
-                            {256, 48, 1.9, 1.3, 0.72, 50, 2.0}};
-    int pick = -1;
-    double best = 1e30;
-    for (int i = 0; i < 10; ++i) {
-      if (m % tiles[i].cols || (i == 0 && M < g_tune.fat_min_m) || (i == 9 && M > 256)) continue;
-      const long long n = static_cast<long long>((M + tiles[i].rows - 1) / tiles[i].rows) * (m / tiles[i].cols);
-      const double t = tiles[i].start + static_cast<double>((n + 255) / 256) * (tiles[i].round + tiles[i].step * (K / kFatK)) +
-                       4e-6 * m * K / tiles[i].w + 2e-6 * M * m / tiles[i].out;
-      if (t < best) { best = t; pick = i; }
-    }
+    const int pick = swiglu_shape(M, m, K);
     if (pick >= 0) {
       t_last_stream = false;
       const bf16_t* a = static_cast<const bf16_t*>(A);
       const bf16_t* w0 = static_cast<const bf16_t*>(w_gate);
       const bf16_t* w1 = static_cast<const bf16_t*>(w_up);
       bf16_t* uo = static_cast<bf16_t*>(u);
-      const dim3 grid(m / tiles[pick].cols, (M + tiles[pick].rows - 1) / tiles[pick].rows, 1);
+      const dim3 grid(m / kPairTiles[pick].cols, (M + kPairTiles[pick].rows - 1) / kPairTiles[pick].rows, 1);
 #define DLLMC_SW(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), 0, st, a, lda, rows, M, w0, w1, m, K, uo)
       switch (pick) {
         case 0: DLLMC_SW(k_gemm_wide_swiglu<8, 8>); break;
@@ -876,68 +882,47 @@ bool launch_gemm_swiglu(int dtype, const void* A, int lda, const int* rows, int 
   return true;
 }
 
-// Shape of kWide that takes a V-verify of `way` (rows per tile) instead of the 128 x 128 tiles with two workgroups per CU or the
-// 192 x 64 ones, if its estimate (that of the plain map without float32 results; 3 us per round and the cached
-// rows at 2.8 MB / us for the epilogue) is below t; -1: none is.  4608 rows x 4096 x 4096: 192 x 256 tiles 148
-// us, 128 x 128 162 to 168.
-int vverify_shape(int way, int M, int N, int K, double& t) {
-  int shape = -1;
-  for (int i : {1, 3}) {
-    const WideShape& w = kWide[i];
-    if (w.bm != (way == kVMid ? 128 : 192) || N % w.bn) continue;
-    const double rounds = static_cast<double>((static_cast<long long>((M + w.bm - 1) / w.bm) * (N / w.bn) + 255) / 256);
-    if (w.bm == 192 && rounds < 2) continue;  // a single round leaves CUs idle: split sums or smaller tiles
-    const double e = w.start + rounds * (w.round + 3.0 + w.step * (K / kFatK)) + 2e-6 * N * K / w.w + 2e-6 * M * N / 2.8;
-    if (e < t) { t = e; shape = i; }
-  }
-  return shape;
-}
-double vverify_mid_us(int M, int N, int K) {  // 128 x 128, two workgroups per CU
-  const long long t = static_cast<long long>((M + kMidM - 1) / kMidM) * (N / kMidN), rem = t % 512;
-  const double steps = K / kFatK;
-  return 3.7 + t / 512 * (6.0 + 0.849 * steps) + (rem == 0 ? 0.0 : 6.0 + (rem <= 256 ? 0.583 : 0.849) * steps) +
-         2e-6 * N * K / 17 + 2e-6 * M * N / 3.2;
-}
-double vverify_192_us(int M, int N, int K) {  // 192 x 64
-  const double rounds = static_cast<double>((static_cast<long long>((M + 191) / 192) * (N / 64) + 255) / 256);
-  return 3.5 + rounds * (5.0 + 0.47 * (K / kFatK)) + 2e-6 * N * K / 6 + 2e-6 * M * N / 2.8;
-}
-
-// The way through V-verify that takes least, by estimates in us of the form of plan_ring's, with what follows the launch
-// (launch_scores_from_part, or the row kernel; in a step the selection adds the sums, which spares the former's launch).  Fitted to 270 shapes (1 to 4096 rows, 128 to 8192 columns, contraction of 896
-// to 8192) timed each way: rms 4.7 % (64 x 64 tiles), 2.5 (128 x 128), 2.7 (256 x 256), 4.1 (192 x 64), 8.2 (split).  The
-// choice is 0.3 % from the best way on average there, and 0.1 % in steps of four widths (64 to 4096 carried rows), where
-// bands of tile counts read off two widths, and a fixed 900 rows for the single operation, were 0.5 %: LLaDA-8B width, us per
-// adaptive layer, 448 rows 201 -> 194, 576 227 -> 217, 768 241 -> 233; 1280 rows as a single operation 69 -> 60.
-int plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K, size_t c_capacity, bool in_step) {
-  if (dtype != 1 || M < 1 || !operands_aligned || lda % 8 || K % kFatK || N % 64) return kVSplit;
+// The way through V-verify that takes least, by estimates in us with what follows the launch (launch_scores_from_part, or the row
+// kernel; in a step the selection adds the sums, which spares the former's launch).  One launch: start + rounds over the 256
+// CUs x (round + step x 64-wide steps) + MB of weights / w + MB of V / out.  489 shapes (32 to 12288 rows, 64 to 8192 columns,
+// contraction of 512 to 8192, cold weights) were timed each way: rms 13 % (64 x 64; priced low where it and the split are
+// level, 200 and 256 rows x 4096 x 4096 22.5 and 24.7 us against 23.8 and 23.4), 3 (128 x 128 with two workgroups per CU), 6 (192 x 64), 4 (the
+// others), 8 (split).  The single operation takes 0.8 % longer than the quickest way on average, 5 % or more in 19 shapes; with prices fitted to
+// tiles of eight wavefronts and V-verify's epilogue as a surcharge on kWide's it was 2.5 % (4608 rows x 2048 x 2048 58.7
+// us, so 46.2; 3300 x 2560 x 2560 73.2, 57.8; 12288 x 1024 x 1024 42.5, 34.6).
+VPlan plan_vverify(int dtype, bool operands_aligned, int lda, int M, int N, int K, size_t c_capacity, bool in_step) {
+  VPlan best{kVSplit, 0, 0, 0.0};
+  if (dtype != 1 || M < 1 || !operands_aligned || lda % 8 || K % kFatK || N % 64) return best;
+  struct Tile { int way, bm, bn; double start, round, step, w, out; };
+  constexpr Tile tiles[6] = {{kVFused, 64, 64, 4.7, 2.2, 0.184, 23, 1.24}, {kVMid, kMidM, kMidN, 7.5, 2.15, 0.817, 12, 2.92},
+                             {kVMid, 128, 256, 4.8, 6.59, 0.672, 9.6, 2.91}, {kVR192, 192, 64, 4.9, 1.9, 0.412, 8.6, 1.83},
+                             {kVR192, 192, 256, 3.9, 8.43, 0.988, 14, 4.79}, {kVFat, 256, 256, 4.7, 13.86, 1.157, 11, 4.64}};
   const double steps = K / kFatK, mb_w = 2.0 * N * K / 1e6, mb_v = 2.0 * M * N / 1e6;
-  auto tiles = [&](int bm, int bn) { return static_cast<long long>((M + bm - 1) / bm) * (N / bn); };
-  auto rounds = [&](int bm, int bn) { return static_cast<double>((tiles(bm, bn) + 255) / 256); };
-  int way = kVFused;
-  double best = 3.9 + rounds(64, 64) * (1.7 + 0.21 * steps) + mb_w / 12.9 + mb_v / 1.2;
-  auto offer = [&](int w, double t) { if (t < best) { best = t; way = w; } };
-  if (M >= g_tune.tile_min_m) {
-    if (N % kMidN == 0) {
-      double t = vverify_mid_us(M, N, K);
-      vverify_shape(kVMid, M, N, K, t);
-      offer(kVMid, t);
+  best.us = 1e30;
+  for (const Tile& t : tiles) {
+    if (N % t.bn || (t.bm > 64 && M < g_tune.tile_min_m) || (t.way == kVFat && M < g_tune.fat_min_m)) continue;
+    const long long n = static_cast<long long>((M + t.bm - 1) / t.bm) * (N / t.bn);
+    double rounds = static_cast<double>((n + 255) / 256), walks = rounds;
+    if (t.bm == kMidM && t.bn == kMidN) {  // two workgroups per CU; up to 256 in the last round have each CU to themselves
+      rounds = static_cast<double>((n + 511) / 512);
+      walks = rounds - (n % 512 != 0 && n % 512 <= 256 ? 0.31 : 0.0);
     }
-    double t192 = vverify_192_us(M, N, K);
-    vverify_shape(kVR192, M, N, K, t192);
-    offer(kVR192, t192);
-    if (M >= g_tune.fat_min_m && N % kFatN == 0)
-      offer(kVFat, rounds(kFatM, kFatN) * (16.6 + 1.13 * steps) + mb_w / 15 + mb_v / 2.7);
+    const double us = t.start + rounds * t.round + walks * t.step * steps + mb_w / t.w + mb_v / t.out;
+    if (us < best.us) best = VPlan{t.way, t.bm, t.bn, us};
   }
   const GemmPlan p = plan_gemm(dtype, true, lda, M, N, N, K, c_capacity, false);
-  if (p.kind != 0 && 3.8 + p.t + mb_v / 10.2 + M / 358.0 < best - (in_step ? 2.0 : 0.0)) way = kVSplit;
-  return way;
+  const double split = 3.7 + p.t + mb_v / 7.3 + M / 300.0;
+  // (against 64 x 64 tiles of 192 to 511 rows the split has to be 6 % ahead: its price is that much low there, 192 rows x 2048 x 2048
+  // 14.6 us, the tiles 13.4; 333 x 128 x 896 9.4 and 8.6)
+  const double bar = best.us * (best.way == kVFused && M >= g_tune.tile_min_m && M < g_tune.fat_min_m ? 0.94 : 1.0);
+  if (p.kind != 0 && split < bar - (in_step ? 2.0 : 0.0)) best = VPlan{kVSplit, 0, 0, split};
+  return best;
 }
 
 // Shape of kWide whose tiles finish Q | K of M rows x N columns in one slice, -1: none (every shape that divides the
-// columns would leave more than a quarter of the CUs without a workgroup).  By the estimates of the plain maps without their
-// float32 results; 2 us per round more for the epilogue (1024 rows x 8192 columns: 256 x 128 63 us, 128 x 128 with two
-// workgroups per CU 76; 4608 rows: 192 x 256 250, 256 x 256 297; 768 rows: 192 x 128 48).
+// columns would leave more than a quarter of the CUs without a workgroup).  By the estimates of the plain maps, with 4 us per
+// round and the bf16 results at 5 MB / us for the epilogue: 7 % rms over 756 launches (200 to 12288 rows, seven widths), the choice 0.04 %
+// from the quickest shape on average (at worst 1.6).
 int qk_tile_shape(int M, int N, int N0, int K) {
   if (K % kFatK || M < g_tune.tile_min_m) return -1;
   const int cus = 256, least = 3 * cus / 4;
@@ -948,13 +933,14 @@ int qk_tile_shape(int M, int N, int N0, int K) {
     if (N % w.bn || N0 % 128 || (i == 0 && M < g_tune.fat_min_m)) continue;
     const long long tiles = static_cast<long long>((M + w.bm - 1) / w.bm) * (N / w.bn);
     if (tiles < least) continue;
-    const double t = w.start + static_cast<double>((tiles + cus - 1) / cus) * (w.round + 2.0 + w.step * (K / kFatK)) + 2e-6 * N * K / w.w;
+    const double t = w.start + static_cast<double>((tiles + cus - 1) / cus) * (w.round + 4.0 + w.step * (K / kFatK)) +
+                     2e-6 * N * K / kWideW + 2e-6 * M * N / 5.0;
     if (t < best) { best = t; shape = i; }
   }
   return shape;
 }
 
-void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first, int per_seq, int n,
+void launch_gemm_vverify_tiles(const VPlan& plan, const void* A, int lda, int M, int first, int per_seq, int n,
                                int L_p, const void* W, int N, int K, void* v_cache, float* part,
                                int part_stride, int metric, const int* rmap, hipStream_t st) {
   TileEpilogue ep{};
@@ -964,16 +950,15 @@ void launch_gemm_vverify_tiles(int way, const void* A, int lda, int M, int first
   t_last_stream = false;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  double t = way == kVMid ? vverify_mid_us(M, N, K) : way == kVR192 ? vverify_192_us(M, N, K) : 0.0;
-  const int shape = way == kVFat ? 0 : vverify_shape(way, M, N, K, t);
-  const dim3 grid = shape >= 0 ? dim3(N / kWide[shape].bn, (M + kWide[shape].bm - 1) / kWide[shape].bm)
-                    : way == kVMid ? dim3(N / kMidN, (M + kMidM - 1) / kMidM) : dim3(N / 64, (M + 191) / 192);
+  const dim3 grid(N / plan.bn, (M + plan.bm - 1) / plan.bm);
 #define DLLMC_V(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), 0, st, a, lda, M, w, N, K, ep)
-  if (shape == 0) DLLMC_V(k_gemm_wide_vverify<2, 2, 8, 8>);
-  else if (shape == 1) DLLMC_V(k_gemm_wide_vverify<2, 2, 6, 8>);
-  else if (shape == 3) DLLMC_V(k_gemm_wide_vverify<2, 2, 4, 8>);
-  else if (way == kVR192) DLLMC_V(k_gemm_wide_vverify<4, 1, 3, 4>);
-  else DLLMC_V(k_gemm_mid_vverify);
+  switch (plan.bm * 1000 + plan.bn) {
+    case 256256: DLLMC_V(k_gemm_wide_vverify<2, 2, 8, 8>); break;
+    case 192256: DLLMC_V(k_gemm_wide_vverify<2, 2, 6, 8>); break;
+    case 128256: DLLMC_V(k_gemm_wide_vverify<2, 2, 4, 8>); break;
+    case 192064: DLLMC_V(k_gemm_wide_vverify<4, 1, 3, 4>); break;
+    default: DLLMC_V(k_gemm_mid_vverify); break;
+  }
 #undef DLLMC_V
 }
 

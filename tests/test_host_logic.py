@@ -112,3 +112,12 @@ def test_vverify_plan():
     assert plan(1, 256, 4096, 4100) == 0            # columns that 64 does not divide
     assert plan(1, 256, 4100, 4096) == 0            # nor the contraction
     assert plan(1, 0, 64, 64) < 0 and plan(2, 1, 64, 64) < 0
+
+
+def test_vverify_plan_takes_the_quicker_way():
+    """Sizes at which the way taken once was not the quicker of those timed (us): 58.7 in 256 x 256 tiles against 46.2 in 192 x
+    256, 73.2 against 57.8, 42.5 against 34.6, 42.2 in 64 x 64 against 30.6 in 192 x 64; and two that estimates of another form lost (64 x 64 tiles 13.4 against 14.6, 8.6 against 9.4)."""
+    plan = binding.lib().dllmc_plan_vverify
+    for rows, d, d_kv, way in [(4608, 2048, 2048, 3), (3300, 2560, 2560, 3), (12288, 1024, 1024, 3), (4096, 3584, 512, 3),
+                               (192, 2048, 2048, 4), (333, 896, 128, 4)]:
+        assert plan(1, rows, d, d_kv) == way, (rows, d, d_kv)
