@@ -319,6 +319,12 @@ int32_t dllmc_plan_gate_up(int32_t M, int32_t d_ffn, int32_t d, int32_t* cols);
  * (4) rows. */
 int32_t dllmc_plan_vverify(int32_t dtype, int32_t rows, int32_t d, int32_t d_kv);
 
+/* Host-only: rows of the tiles with which one workgroup per CU takes a launch of M rows and contraction length K of a bf16
+ * step (16-byte aligned operands, slices for eight times the result); 0: another kernel takes it.  launch 0: gathered linear map
+ * to N columns (the first N0 from one matrix), 1: gate/up projection of FFN width N, 2: Q | K of N = d_q + d_kv columns, N0 =
+ * d_q, heads of 128, 3: V-verify of N = d_kv columns.  *cols (may be NULL): the tile's columns (gate/up: of each matrix). */
+int32_t dllmc_plan_tile(int32_t launch, int32_t M, int32_t N, int32_t N0, int32_t K, int32_t* cols);
+
 /* Host-only: the number of key ranges of a bf16 attention of Mq < 128 queries per sequence with head width 128
  * (split_keys: with a scratch buffer).  *queries (may be NULL): queries per workgroup of the kernel whose
  * wavefronts split the keys, 16, 32 or 64; 0: 64 queries whose wavefronts walk all keys together; -1: the

@@ -25,7 +25,7 @@ EXPORTS = (
     "dllmc_read_cache", "dllmc_read_scores", "dllmc_destroy", "dllmc_strerror",
     "dllmc_last_hip_error", "dllmc_op_select", "dllmc_op_vverify", "dllmc_op_linear",
     "dllmc_op_attention", "dllmc_profile_enable", "dllmc_profile_read", "dllmc_kernel_class_name",
-    "dllmc_set_gemm_tuning", "dllmc_op_attention_scratch_bytes", "dllmc_plan_gemm_slices", "dllmc_plan_attention", "dllmc_plan_vverify", "dllmc_plan_gate_up",
+    "dllmc_set_gemm_tuning", "dllmc_op_attention_scratch_bytes", "dllmc_plan_gemm_slices", "dllmc_plan_attention", "dllmc_plan_vverify", "dllmc_plan_gate_up", "dllmc_plan_tile",
     "dllmc_gen_workspace_bytes", "dllmc_gen_create", "dllmc_gen_step", "dllmc_gen_read",
     "dllmc_gen_destroy", "dllmc_op_head_scratch_bytes", "dllmc_op_head", "dllmc_set_policy",
     "dllmc_set_layer_rho", "dllmc_layer_num_selected", "dllmc_probe_copy", "dllmc_probe_read", "dllmc_probe_mfma",
@@ -171,6 +171,8 @@ def lib() -> C.CDLL:
         L.dllmc_plan_gemm_slices.argtypes = [C.c_int32] * 5 + [C.c_size_t]
         L.dllmc_plan_gate_up.restype = C.c_int32
         L.dllmc_plan_gate_up.argtypes = [C.c_int32] * 3 + [C.POINTER(C.c_int32)]
+        L.dllmc_plan_tile.restype = C.c_int32
+        L.dllmc_plan_tile.argtypes = [C.c_int32] * 5 + [C.POINTER(C.c_int32)]
         L.dllmc_plan_vverify.restype = C.c_int32
         L.dllmc_plan_vverify.argtypes = [C.c_int32] * 4
         L.dllmc_plan_attention.restype = C.c_int32

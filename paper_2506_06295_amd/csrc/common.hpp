@@ -385,6 +385,8 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
                           const void* w2, int d_q, int d_kv, int d_h, int K, const float2* rope_tab,
                           int n, void* q_out, void* cache, bool rope_second, const int* rmap,
                           hipStream_t st);
+// Tile of the one-workgroup-per-CU kernels that takes a launch of a bf16 step, see dllmc_plan_tile
+int plan_tile(int launch, int M, int N, int N0, int K, int* cols);
 // score[i] = cosine (metric 0) or minus distance (metric 1) from the tile sums, i < count
 void launch_scores_from_part(const float* part, int n_ct, int count, int metric, float* score,
                              hipStream_t st);

@@ -703,6 +703,11 @@ int32_t dllmc_plan_vverify(int32_t dtype, int32_t rows, int32_t d, int32_t d_kv)
   return plan_vverify(dtype, true, d, rows, d_kv, d, static_cast<size_t>(rows) * d_kv * 8, false).way;
 }
 
+int32_t dllmc_plan_tile(int32_t launch, int32_t M, int32_t N, int32_t N0, int32_t K, int32_t* cols) {
+  if (launch < 0 || launch > 3 || M < 1 || N < 1 || N0 < 1 || N0 > N || K < 1) return DLLMC_EINVAL;
+  return plan_tile(launch, M, N, N0, K, cols);
+}
+
 int32_t dllmc_plan_attention(int32_t B, int32_t Mq, int32_t n, int32_t H_q, int32_t H_kv, int32_t split_keys,
                              int32_t* queries) {
   if (B < 1 || Mq < 1 || Mq > 127 || n < 1 || H_kv < 1 || H_q < H_kv || H_q % H_kv) return DLLMC_EINVAL;

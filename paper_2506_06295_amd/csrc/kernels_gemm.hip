@@ -992,6 +992,27 @@ bool launch_gemm_qk_tiles(int dtype, const void* A, int lda, const int* rows, in
   return true;
 }
 
+int plan_tile(int launch, int M, int N, int N0, int K, int* cols) {
+  int rows = 0, c = 0;
+  if (launch == 1) {
+    const int i = M >= g_tune.tile_min_m && gemm_ring_ok(1, true, K, K) ? swiglu_shape(M, N, K) : -1;
+    if (i >= 0) { rows = kPairTiles[i].rows; c = kPairTiles[i].cols; }
+  } else if (launch == 2) {
+    const int i = qk_tile_shape(M, N, N0, K);
+    if (i >= 0) { rows = kWide[i].bm; c = kWide[i].bn; }
+  } else {
+    const size_t slices = static_cast<size_t>(M) * N * kMaxSlices;
+    const GemmPlan p = plan_gemm(1, true, K, M, N, N0, K, slices, false);
+    if (launch == 0 && p.kind == 3) { rows = kWide[p.wide].bm; c = kWide[p.wide].bn; }
+    if (launch == 3) {
+      const VPlan v = plan_vverify(1, true, K, M, N, K, slices, true);
+      if (v.way != kVFused && !(v.bm == kMidM && v.bn == kMidN)) { rows = v.bm; c = v.bn; }
+    }
+  }
+  if (cols) *cols = c;
+  return rows;
+}
+
 #undef g_tune
 
 }  // namespace dllmc

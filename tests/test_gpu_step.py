@@ -119,9 +119,8 @@ def test_degenerate_shapes(cfg):
                          ids=lambda c: c.name)
 def test_fused_gate_up_in_tile_kernels(cfg, fat_min_m):
     """Refresh steps (hundreds of rows) run gate/up + SwiGLU fused inside the LDS-direct tile
-    kernels (128 x 128 by default, 256-row tiles when forced: 96 paired columns where the FFN width
-    is a multiple of 96 and that makes fewer rounds -- MINI_LLADA's 3072 --, 128 otherwise --
-    2048, and MINI_DREAM's 2432 = 19 x 128)."""
+    kernels, FFN widths of whole 96s (3072) and of none (2048, 2432 = 19 x 128), with and without tiles of 256 rows x
+    128 paired columns among those considered."""
     binding.set_gemm_tuning(fat_min_m=fat_min_m)
     try:
         gpu, ora, st = run_schedule(cfg.replace(steps=4), stress=True, K_r=1)   # every step refreshes the response
@@ -145,7 +144,8 @@ def test_fused_gate_up_with_uneven_column_blocks():
 
 
 def test_fused_gate_up_in_the_tall_tile_kernel():
-    """224 rows per response refresh and an FFN width of 64 x 48: the 256 x 96 tile kernel."""
+    """224 rows per response refresh and an FFN width of 64 x 48 (the choice is 128 rows x 64 paired columns now; the 256 x 96 kernel has a
+    case in test_gpu_tile_shapes)."""
     cfg = MINI_LLADA.replace(L_r=112, steps=4)
     gpu, ora, st = run_schedule(cfg, stress=True, K_r=1)
     assert st.failed == 0, st.failures

@@ -1,5 +1,5 @@
-"""Every tile shape of the refresh steps' launches (128, 192 and 256 rows; gate/up, V-verify and Q|K finished in their
-epilogues) at row counts around whole tiles and rounds, against a context whose maps of fewer than 2^20 rows all go through
+"""Refresh steps of the models' widths (gate/up, V-verify and Q|K finished in the tile kernels' epilogues) at row counts
+around whole tiles and rounds, against a context whose maps of fewer than 2^20 rows all go through
 the weight-streaming kernel.
 
 Same inputs, other orders of summation: elements may round to neighbouring bf16 values (2^-7 of the value), and
@@ -17,14 +17,15 @@ BASES = {name: I.CONFIGS[name] for name in ("llada8b", "dream7b")}
 BASES["2560_wide"] = BASES["llada8b"].replace(d=2560, H_q=20, H_kv=20, m=1536)
 
 
-# (V-verify: 0 split contraction, 1 / 2 / 3 tiles of 128, 256 and 192 rows, 4 64 x 64 tiles)
+# (V-verify: 0 split contraction, 1 / 2 / 3 tiles of 128, 256 and 192 rows, 4 64 x 64 tiles.  Which tiles the other launches take
+# follows from estimates; the cases of test_gpu_tile_shapes name theirs.)
 @pytest.mark.parametrize("base,L_p,L_r,v_way", [
-    ("llada8b", 20, 180, 4),     # 200 rows: 256 x 96 gate/up
-    ("llada8b", 129, 255, 0),    # 384 rows: two whole 192-row tiles for gate/up
+    ("llada8b", 20, 180, 4),     # 200 rows
+    ("llada8b", 129, 255, 0),    # 384 rows: two whole 192-row tiles
     ("llada8b", 129, 256, 0),    # 385
-    ("llada8b", 320, 256, 0),    # 576 rows: three 192-row tiles
+    ("llada8b", 320, 256, 0),    # 576: three
     ("llada8b", 513, 256, 0),    # 769: a fifth tile of one row
-    ("llada8b", 900, 130, 0),    # 1030: 256 x 192 gate/up
+    ("llada8b", 900, 130, 0),    # 1030: six rows past whole tiles of 256
     ("llada8b", 1900, 147, 1),   # 2047: a ragged sixteenth tile
     ("llada8b", 2800, 273, 2),   # 3073: a thirteenth 256-row tile of one row
     ("dream7b", 700, 67, 0),     # 767 rows, grouped KV heads, an FFN width that 96 does not divide
@@ -145,7 +146,8 @@ def test_fewer_steps_than_the_ring_holds(M, K):
 
 @pytest.mark.parametrize("H,rows", [(1, 256), (1, 700), (2, 1100), (3, 640)])
 def test_narrow_models(H, rows):
-    """Two to six steps in gate/up, Q|K, V-verify: every shape of tile against the streaming kernel, bars as above."""
+    """Two to six steps in gate/up, Q|K, V-verify: 128 x 128 tiles at most, 64 + 64 columns in gate/up, against the streaming
+    kernel, bars as above."""
     cfg = BASES["llada8b"].replace(T=1, K_p=1, K_r=1, L_p=rows - 90, L_r=90, d=128 * H, H_q=H, H_kv=H, m=1536)
     ws = I.device_weights(cfg)
     make = lambda: binding.CachedDenoiser(
@@ -170,14 +172,14 @@ def test_narrow_models(H, rows):
 
 @pytest.mark.parametrize("H,m,L_p,L_r", [
     (8, 3072, 300, 90),     # 390 rows: 128-row tiles throughout
-    (16, 3072, 900, 124),   # 1024: Q|K of 256 x 128
+    (16, 3072, 900, 124),   # 1024: whole tiles of 128 and 256
     (32, 6144, 1100, 180),  # 1280: a seventh 192-row tile of 128 rows
-    (16, 2432, 1400, 137),  # 1537: rows past whole tiles of 128, 192 and 256; gate/up of 64 columns
+    (16, 2432, 1400, 137),  # 1537: rows past whole tiles of 128, 192 and 256
     (24, 1536, 2700, 200),  # 2900
 ])
 @pytest.mark.parametrize("paged", [False, True])
 def test_shapes_between_the_two_widths(H, m, L_p, L_r, paged):
-    """Steps that take the 128 x 128, 192 x 128, 256 x 128, 128 x 256 and 192 x 256 tiles somewhere, bars as above; paged
+    """Steps that take the shapes between 128 x 128 and 256 x 256 somewhere, bars as above; paged
     caches reach the epilogues' rows through the row map."""
     cfg = BASES["llada8b"].replace(T=1, K_p=1, K_r=1, L_p=L_p, L_r=L_r, d=128 * H, H_q=H, H_kv=H, m=m)
     ws = I.device_weights(cfg)
@@ -209,7 +211,7 @@ def test_shapes_between_the_two_widths(H, m, L_p, L_r, paged):
 
 @pytest.mark.parametrize("rows,d,d_kv", [(2500, 512, 4096), (2048, 512, 4096), (4609, 256, 4096), (1921, 1024, 4096)])
 def test_vverify_wide_shapes(rows, d, d_kv):
-    """V-verify of thousands of rows, whole and ragged tiles of 192 and 128 rows: bars of the paths' test."""
+    """V-verify of thousands of rows, whole and ragged tiles: bars of the paths' test."""
     g = torch.Generator(device="cuda")
     g.manual_seed(rows)
     h = torch.randn((rows, d), generator=g, device="cuda").bfloat16()
