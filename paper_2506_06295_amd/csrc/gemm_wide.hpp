@@ -1,4 +1,4 @@
-// Body of the LDS-direct tile kernels with one workgroup per CU (tiles of 192 and 256 rows), included by kernels_gemm.hip.
+// Body of the LDS-direct tile kernels with one workgroup per CU (tiles of 128, 192 and 256 rows), included by kernels_gemm.hip.
 //
 // Four wavefronts, one per SIMD, of 16 MI rows x 16 NJ columns each.  Operands, LDS layout and the meaning of PAIR, EPI and
 // NT are those of gemm_lds_body; where results are bf16 the products are taken as W A^T, so that a lane holds four neighbouring
@@ -19,8 +19,8 @@
 //     last MFMAs, and results leave 16 bytes at a time.  Q | K (us; with trips one by one, so, with eight wavefronts): 8192 rows x 8192 x 4096
 //     452, 434, 430; 8192 x 4096 x 2048 138, 120, 118; 8192 x 2048 x 1024 49, 41, 40.  V-verify: 12288 x 4096 x 4096 344, 336, 340;
 //     4608 x 4096 x 4096 165, 157, 175; 4096 x 4096 x 512 44, 40, 39.6;
-//   * gate/up's epilogue, see silu_mul.  In the step (us, before: eight wavefronts): gate/up of 4608 rows x 12288 x 4096 735 -> 672, of
-//     1024 185 -> 158, of 768 156 -> 138, of 256 64 -> 57; down projection of 1024 rows 92 -> 81, of 4608 401 -> 377;
+//   * gate/up's epilogue, see silu_mul.  In the step (us, eight wavefronts / so): gate/up of 4608 rows x 12288 x 4096 735 / 694, of
+//     1024 185 / 160, of 768 156 / 133, of 256 64 / 55; down projection of 1024 rows 92 / 81;
 //   * the accumulators are held in the accumulation registers by the constraint of an asm statement: left to the
 //     compiler, which has 256 of them and 130 other live registers, 48 to 540 moves enter the loop (none now; a move inside
 //     the loop would have to keep 8 wait states from the asm statement whose result it reads).

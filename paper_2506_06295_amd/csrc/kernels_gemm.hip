@@ -538,7 +538,7 @@ __global__ __launch_bounds__(256) void k_gemm_mid_head(const bf16_t* __restrict_
 // an FFN width that is a multiple of 48 the grid is one workgroup per 48 columns (12288 / 48 =
 // 256, one per CU), where the 128 x 128 tiles leave half of the CUs with twice the work (a
 // response refresh of 256 rows: 80 -> 69 us per layer; two workgroups of 128 x 96 per CU: 73; with non-temporal
-// weight loads 65.7 -> 62.7; with the body of one wavefront per SIMD 57).
+// weight loads 65.7 -> 62.7; with the body of one wavefront per SIMD 55).
 template <bool NT>
 __global__ __launch_bounds__(256) void k_gemm_tall_swiglu(const bf16_t* __restrict__ A, int lda,
                                                           const int* __restrict__ rows, int M,
